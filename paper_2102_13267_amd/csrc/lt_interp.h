@@ -107,6 +107,21 @@ __device__ __forceinline__ float op_gelu_grad(float dy, float x) {
   return dy * fmaf(x, 0.39894228040143268f * e, cdf);
 }
 
+// tanh without branches (the library's takes divergent paths, element by element): below 0.625 an
+// odd polynomial x + x^3 P(x^2), P fitted to the least largest relative error (4.4e-9), above it
+// 1 - 2 / (e^(2|x|) + 1) with the sign of x.  Both are within 2 ulp; infinities give +-1, NaN stays NaN.
+__device__ __forceinline__ float op_tanh(float x) {
+  const float z = fabsf(x), s = x * x;
+  float p = fmaf(-5.704985412e-03f, s, 2.063908586e-02f);
+  p = fmaf(p, s, -5.373971467e-02f);
+  p = fmaf(p, s, 1.333144219e-01f);
+  p = fmaf(p, s, -3.333328194e-01f);
+  const float small = fmaf(p * s, x, x);
+  const float e = __builtin_amdgcn_exp2f(z * 2.8853900817779268f);   // e^(2|x|)
+  const float large = copysignf(fmaf(-2.0f, __builtin_amdgcn_rcpf(e + 1.0f), 1.0f), x);
+  return z < 0.625f ? small : x != x ? x : large;
+}
+
 struct ProgRegs {
   uint32_t code;   // lane j: code[j]  (j < kMaxCode <= 64)
   float scal;      // lane j: scal[j]  (j < kMaxScal)
@@ -218,7 +233,7 @@ __device__ __forceinline__ RF<NS> interp(RF<NS> f, const ProgRegs pr, const uint
       case kRecip: LT_MAP(__builtin_amdgcn_rcpf(xa)) break;    // 1 ulp
       case kExp: LT_MAP_SERIAL(expf(xa)) break;
       case kLog: LT_MAP_SERIAL(logf(xa)) break;
-      case kTanh: LT_MAP_SERIAL(tanhf(xa)) break;
+      case kTanh: LT_MAP_SERIAL(op_tanh(xa)) break;
       case kGelu: LT_MAP_SERIAL(op_gelu(xa)) break;
       case kSigmoid: LT_MAP_SERIAL(fast_div(1.0f, 1.0f + expf(-xa))) break;
       case kRoundBf16: LT_MAP(bf16_to_f32(f32_to_bf16(xa))) break;

@@ -51,9 +51,15 @@ struct EwStreamArgs {
   uint32_t vrow[4];   // bf16 kernel: 1 = vector input j is a row vector (indexed by column), 0 = a full tensor
 };
 
+// RAG: the element count is no multiple of four.  The lane with the last elements fetches the last
+// four of the tensor (every load stays whole, in bounds and unconditional) and stores, one by one,
+// only those that are its own; another lane may already have overwritten the others in place, but
+// what is computed from them goes nowhere.  (669,706 parameters through the general kernel: 18.2 us.)
 // NT: non-temporal loads and stores, for regions larger than the last-level cache (what they read
 // is not there and what they write will not be when it is needed): 5.6 -> 6.0 TB/s on 1 GiB operands.
-template <int NV, bool NT>
+typedef float RawVec4 __attribute__((ext_vector_type(4), aligned(4)));
+
+template <int NV, bool NT, bool RAG>
 __global__ __launch_bounds__(kBlock) void lt_ew_stream_kernel(const EwStreamArgs a) {
   const EwProg& p = a.prog;
   const uint64_t n = p.n;
@@ -81,8 +87,17 @@ __global__ __launch_bounds__(kBlock) void lt_ew_stream_kernel(const EwStreamArgs
     const uint64_t base0 = t0 * kTile, base1 = t1 * kTile;
     if ((uint64_t)lane >= n - base0) continue;   // (only in the last tile, which is its own partner)
     RawVec v0[NV], v1[NV];
+    const bool cut = RAG && base0 + lane + kVec > n;   // (one lane of the last tile)
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
+      if (RAG) {
+        const uint64_t e0 = cut ? n - kVec : base0 + lane, e1 = cut ? n - kVec : base1 + lane;
+        const RawVec4* s0 = (const RawVec4*)(vp[j] + e0 * 4u);
+        const RawVec4* s1 = (const RawVec4*)(vp[j] + e1 * 4u);
+        v0[j] = NT ? __builtin_nontemporal_load(s0) : *s0;
+        v1[j] = NT ? __builtin_nontemporal_load(s1) : *s1;
+        continue;
+      }
       const RawVec* s0 = (const RawVec*)(vp[j] + (base0 + lane) * 4u);
       const RawVec* s1 = (const RawVec*)(vp[j] + (base1 + lane) * 4u);
       v0[j] = NT ? __builtin_nontemporal_load(s0) : *s0;
@@ -103,6 +118,16 @@ __global__ __launch_bounds__(kBlock) void lt_ew_stream_kernel(const EwStreamArgs
       f = rf_set<16>(f, a.sin[j] + 8u, q);
     }
     f = interp<16, 2>(f, pr, n_code);
+    if (cut) {
+      for (uint32_t o = 0; o < p.n_out; ++o) {
+        const EwOut& out = p.out[o];
+        const Quad q = rf_get<16>(f, out.slot);
+#pragma unroll
+        for (int e = 0; e < kVec; ++e)
+          if (!out.scalar && n - kVec + (uint64_t)e >= base0 + lane) ((float*)out.ptr)[n - kVec + (uint64_t)e] = q.v[e];
+      }
+      continue;
+    }
     store_outputs<16, true, true, 0, NT>(f, p, base0, lane, kVec);
     store_outputs<16, true, true, 8, NT>(f, p, base1, lane, kVec);
   }
@@ -212,8 +237,11 @@ __global__ __launch_bounds__(kBlock, 4) void lt_ew_stream_bf16_kernel(const EwSt
 // Host side: fill in EwStreamArgs if the program qualifies.
 // vec_dtype: element type the vector inputs must have (kF32: everything fp32; kBF16: bf16 vector
 // inputs, fp32 device scalars, outputs of any type, n a multiple of 8).
+// fp32 programs may have any element count from 16 on (fewer than four would leave the lane with the
+// last elements nothing to fetch; the first element, which carries rank-0 results, is a whole lane's).
 static bool make_stream_args(const EwProg& p, uint32_t vec_dtype, EwStreamArgs* out) {
-  if (!p.fast || p.n_slots > 8u || p.n_in == 0u) return false;
+  if (p.n_slots > 8u || p.n_in == 0u) return false;
+  if (!p.fast && (vec_dtype != kF32 || !p.full_vec_ok || p.n < 16u)) return false;
   if (vec_dtype == kF32 ? !p.all_f32 : (p.n % 8u) != 0u) return false;
   uint32_t nv = 0, ns = 0;
   for (uint32_t k = 0; k < p.n_in; ++k) {
@@ -449,10 +477,15 @@ hipError_t launch_ew(const EwArgs& a, uint32_t grid, hipStream_t s) {
     // walking the same tiles with a grid stride (the loop stays for spaces beyond 2^31 trips)
     const dim3 g2((uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((tiles + 1) / 2, 0x7fffffffull)));
     const bool nt = p.n * 4u * (uint64_t)(p.n_in + p.n_out) > (256ull << 20);   // beyond the 256 MiB last-level cache
-    if (sa.pad <= 2u && nt) LT_LAUNCH((lt_ew_stream_kernel<2, true>), g2, b, s, sa);
-    else if (sa.pad <= 2u) LT_LAUNCH((lt_ew_stream_kernel<2, false>), g2, b, s, sa);
-    else if (nt) LT_LAUNCH((lt_ew_stream_kernel<4, true>), g2, b, s, sa);
-    else LT_LAUNCH((lt_ew_stream_kernel<4, false>), g2, b, s, sa);
+    const bool rag = (p.n % 4u) != 0u;
+    if (sa.pad <= 2u && nt && rag) LT_LAUNCH((lt_ew_stream_kernel<2, true, true>), g2, b, s, sa);
+    else if (sa.pad <= 2u && rag) LT_LAUNCH((lt_ew_stream_kernel<2, false, true>), g2, b, s, sa);
+    else if (nt && rag) LT_LAUNCH((lt_ew_stream_kernel<4, true, true>), g2, b, s, sa);
+    else if (rag) LT_LAUNCH((lt_ew_stream_kernel<4, false, true>), g2, b, s, sa);
+    else if (sa.pad <= 2u && nt) LT_LAUNCH((lt_ew_stream_kernel<2, true, false>), g2, b, s, sa);
+    else if (sa.pad <= 2u) LT_LAUNCH((lt_ew_stream_kernel<2, false, false>), g2, b, s, sa);
+    else if (nt) LT_LAUNCH((lt_ew_stream_kernel<4, true, false>), g2, b, s, sa);
+    else LT_LAUNCH((lt_ew_stream_kernel<4, false, false>), g2, b, s, sa);
     return hipGetLastError();
   }
   if (f16 && p.all_f32 && p.n_in <= 4u) LT_LAUNCH((lt_ew_kernel<16, 4, true, true>), g, b, s, a);

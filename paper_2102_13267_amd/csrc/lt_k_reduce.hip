@@ -2,6 +2,8 @@
 // elementwise prologue and an interpreted post program (epilogue / finaliser).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "lt_launch.h"
 #include "lt_reduce.h"
 
@@ -18,13 +20,21 @@ __device__ __forceinline__ void run_post(const EwProg& post, const ProgRegs post
 }
 
 // Streamed row reduction: fp32 programs of at most eight slots whose inputs are one or two whole
-// tensors and at most one vector broadcast along rows, rows of a multiple of 16 x threads_per_row
-// columns.  A lane takes four 4-vectors of its row per trip (threads_per_row x 4 columns apart):
-// their loads go out together and the interpreter runs once for the four (8 slots x 4 vectors) --
-// what bounds a cache-resident row reduction with a long prologue is the interpreter's dispatch,
-// not memory.  NV, NR: whole inputs, row-vector inputs (the host sorts out which is which).
-template <int NV, int NR>
+// tensors and at most one vector broadcast along rows.  A lane takes Q 4-vectors of its row per trip
+// (threads_per_row x 4 columns apart): their loads go out together and the interpreter runs once
+// for all of them (8 slots x Q vectors) -- what bounds a cache-resident row reduction with a long
+// prologue is the interpreter's dispatch, not memory.  NV, NR: whole inputs, row-vector inputs (the
+// host sorts out which is which).
+// RAG: the row length is no multiple of a trip's columns.  Every vector is still fetched whole and
+// unconditionally: one that would pass the row's end is fetched from the row's last four columns
+// instead, and the elements that another lane (or an earlier vector) owns are left out of the fold.
+// Rows of a length that is no multiple of four start on any 4-byte boundary, which the hardware's
+// 16-byte loads accept.
+typedef float RawVec4 __attribute__((ext_vector_type(4), aligned(4)));
+
+template <int NV, int NR, int Q, bool RAG>
 __global__ __launch_bounds__(kBlock) void lt_row_reduce_stream_kernel(const RowArgs a) {
+  constexpr int NS = 8 * Q;
   __shared__ float lds[kBlock / 64];
   const EwProg& pro = a.pro;
   const ProgRegs pro_regs = load_prog_regs(a.pro), post_regs = load_prog_regs(a.post);
@@ -47,37 +57,70 @@ __global__ __launch_bounds__(kBlock) void lt_row_reduce_stream_kernel(const RowA
     const uint32_t row = blk * rows_per_block + sub;
     float acc = red_identity(a.red);
     if (row < a.rows) {
-      for (uint32_t c = lane * kVec; c < a.cols; c += 4u * step) {   // (cols is a multiple of 4 * step)
-        RawVec v[NV][4], rv[NR ? 4 : 1];
+      const uint64_t rb = (uint64_t)row * a.cols;
+      for (uint32_t c0 = 0; c0 < a.cols; c0 += (uint32_t)Q * step) {   // (wave-uniform)
+        const uint32_t c = c0 + lane * kVec;
+        RawVec v[NV][Q], rv[NR ? Q : 1];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const uint64_t e = (uint64_t)row * a.cols + c + (uint32_t)j * step;
+        for (int j = 0; j < Q; ++j) {
+          const uint32_t cj = c + (uint32_t)j * step, at = RAG ? min(cj, a.cols - (uint32_t)kVec) : cj;
+          if (RAG) {
 #pragma unroll
-          for (int k = 0; k < NV; ++k) v[k][j] = *(const RawVec*)(vp[k] + e * 4u);
-          if (NR) rv[j] = *(const RawVec*)(rp + (size_t)(c + (uint32_t)j * step) * 4u);
+            for (int k = 0; k < NV; ++k) v[k][j] = *(const RawVec4*)(vp[k] + (rb + at) * 4u);
+            if (NR) rv[j] = *(const RawVec4*)(rp + (size_t)at * 4u);
+          } else {
+#pragma unroll
+            for (int k = 0; k < NV; ++k) v[k][j] = *(const RawVec*)(vp[k] + (rb + at) * 4u);
+            if (NR) rv[j] = *(const RawVec*)(rp + (size_t)at * 4u);
+          }
         }
-        RF<32> f = rf_zero<32>();
+        RF<NS> f = rf_zero<NS>();
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        for (int j = 0; j < Q; ++j) {
           Quad q;
 #pragma unroll
           for (int k = 0; k < NV; ++k) {
             q.v[0] = v[k][j].x; q.v[1] = v[k][j].y; q.v[2] = v[k][j].z; q.v[3] = v[k][j].w;
-            f = rf_set<32>(f, vslot[k] + (uint32_t)(8 * j), q);
+            f = rf_set<NS>(f, vslot[k] + (uint32_t)(8 * j), q);
           }
           if (NR) {
             q.v[0] = rv[j].x; q.v[1] = rv[j].y; q.v[2] = rv[j].z; q.v[3] = rv[j].w;
-            f = rf_set<32>(f, a.rin + (uint32_t)(8 * j), q);
+            f = rf_set<NS>(f, a.rin + (uint32_t)(8 * j), q);
           }
         }
-        f = interp<32, 4>(f, pro_regs, pro_n);
+        f = interp<NS, Q>(f, pro_regs, pro_n);
+        if (!RAG || c0 + (uint32_t)Q * step <= a.cols) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc = fold_vec(a.red, acc, rf_get<32>(f, pro.anchor_slot + (uint32_t)(8 * j)), kVec);
+          for (int j = 0; j < Q; ++j) acc = fold_vec(a.red, acc, rf_get<NS>(f, pro.anchor_slot + (uint32_t)(8 * j)), kVec);
+        } else {
+#pragma unroll
+          for (int j = 0; j < Q; ++j) {
+            const uint32_t cj = c + (uint32_t)j * step, at = min(cj, a.cols - (uint32_t)kVec);
+            const Quad q = rf_get<NS>(f, pro.anchor_slot + (uint32_t)(8 * j));
+#pragma unroll
+            for (int e = 0; e < kVec; ++e) {
+              const float t = red_combine(a.red, acc, q.v[e]);
+              acc = at + (uint32_t)e >= cj ? t : acc;
+            }
+          }
+        }
       }
     }
     float r;
-    if (tpr == 64u) r = wave_reduce(a.red, acc);
-    else r = block_reduce(a.red, acc, lds);
+    if (tpr == 64u) {
+      r = wave_reduce(a.red, acc);
+    } else if (tpr < 64u) {   // short rows: two or four to a wave
+      r = row16_reduce(a.red, acc);
+      if (tpr == 32u) r = red_combine(a.red, r, __shfl_xor(r, 16));
+    } else {   // (two or four waves to a row: every wave of the workgroup is here, live or not)
+      r = wave_reduce(a.red, acc);
+      __syncthreads();
+      if ((threadIdx.x & 63u) == 0u) lds[threadIdx.x >> 6] = r;
+      __syncthreads();
+      const uint32_t w0 = sub * (tpr >> 6);
+      r = lds[w0];
+      for (uint32_t w = 1; w < (tpr >> 6); ++w) r = red_combine(a.red, r, lds[w0 + w]);
+    }
     if (a.red == kRedMean) r = r / (float)a.cols;
     if (lane == 0 && row < a.rows) run_post(a.post, post_regs, splat(r), row, 1u);
   }
@@ -119,6 +162,11 @@ __global__ __launch_bounds__(kBlock) void lt_row_reduce_kernel(const RowArgs a) 
 // Global reduction in one launch.  NIN > 0: streamed (U 4-vectors per lane and trip fetched
 // together, a workgroup reading U consecutive tiles); NIN == 0: general path.
 // Q = 2, 4: so many 4-vectors per interpreter dispatch (programs of at most NS/Q slots).
+// What is left after the whole trips -- everything, for a small operand -- is dealt out over the
+// workgroups tile by tile, four tiles' loads in flight at a time, so that a few thousand elements are
+// one round trip to memory instead of a chain of them.  A vector that would pass the end is
+// fetched from the last four elements instead, and what it does not own is left out of the
+// sum, so fp32 operands of any length are streamed (bf16: whole 4-vectors).
 template <int NS, int NIN, int U, bool BF, int Q>
 __global__ __launch_bounds__(kBlock) void lt_all_reduce_kernel(const AllArgs a) {
   __shared__ float lds[kBlock / 64];
@@ -129,13 +177,12 @@ __global__ __launch_bounds__(kBlock) void lt_all_reduce_kernel(const AllArgs a) 
   const uint64_t n = pro.n;
   const uint64_t nvec = (n + kVec - 1) / kVec;
   float acc = red_identity(a.red);
-  uint64_t tail_from = 0;   // first 4-vector the general loop below has to cover
   if (NIN > 0) {
     // a trip of the grid covers gridDim.x * U tiles of kBlock vectors; workgroup b takes tiles
     // b*U .. b*U+U-1 of each trip, i.e. U * 4 KiB (fp32) of consecutive memory
     constexpr int UU = NIN > 0 ? U : 1, NN = NIN > 0 ? NIN : 1;
     const uint64_t per_trip = (uint64_t)gridDim.x * UU * kBlock;
-    const uint64_t trips = nvec / per_trip;
+    const uint64_t trips = (n / kVec) / per_trip;   // (whole 4-vectors)
     // A prologue of one instruction, square or abs of the operand, is applied in place (same
     // values, same order of additions as the interpreter's): the interpreter's dispatch is what
     // keeps such a reduction from the memory system's rate, and these two are every norm.
@@ -175,14 +222,53 @@ __global__ __launch_bounds__(kBlock) void lt_all_reduce_kernel(const AllArgs a) 
         }
       }
     }
-    tail_from = trips * per_trip;
-  }
-  for (uint64_t v = tail_from + (uint64_t)blockIdx.x * kBlock + threadIdx.x; v < nvec; v += (uint64_t)gridDim.x * kBlock) {
-    const uint64_t i = v * kVec;
-    const uint32_t nvalid = (n - i >= (uint64_t)kVec) ? (uint32_t)kVec : (uint32_t)(n - i);
-    RF<NS> f = load_inputs<NS, kMaxIn, false, false>(rf_zero<NS>(), pro, 0, (uint32_t)i, nvalid);
-    f = interp<NS>(f, pro_regs, pro_n);
-    acc = fold_vec(a.red, acc, rf_get(f, pro.anchor_slot), nvalid);
+    // The rest, kTail tiles per workgroup and round.
+    constexpr int kTail = 4;
+    const uint32_t last = (uint32_t)(n - kVec);   // (n >= 4, and every index fits 32 bits)
+    for (uint32_t t0 = (uint32_t)(trips * per_trip) + blockIdx.x * kBlock; t0 < (uint32_t)nvec; t0 += (uint32_t)kTail * gridDim.x * kBlock) {
+      Stream<NN, kTail, BF> st;
+#pragma unroll
+      for (int u = 0; u < kTail; ++u) {
+        const uint32_t tile = t0 + (uint32_t)u * gridDim.x * kBlock;   // first 4-vector of tile u (workgroup-uniform)
+        if (tile >= (uint32_t)nvec) continue;
+        const uint32_t e = min((tile + threadIdx.x) * kVec, last);
+#pragma unroll
+        for (int k = 0; k < NN; ++k) {
+          const char* src = (const char*)pro.in[k].ptr;
+          if (BF) {
+            typedef uint32_t U32x2 __attribute__((ext_vector_type(2)));
+            const U32x2 w = *(const U32x2*)(src + (size_t)e * 2u);
+            st.s[k][2 * u] = __uint_as_float(w.x);
+            st.s[k][2 * u + 1] = __uint_as_float(w.y);
+          } else {
+            const RawVec w = *(const RawVec4*)(src + (size_t)e * 4u);
+            st.s[k][4 * u] = w.x; st.s[k][4 * u + 1] = w.y; st.s[k][4 * u + 2] = w.z; st.s[k][4 * u + 3] = w.w;
+          }
+        }
+      }
+#pragma unroll 1
+      for (uint32_t u = 0; u < (uint32_t)kTail; ++u) {
+        const uint32_t tile = t0 + u * gridDim.x * kBlock;
+        if (tile >= (uint32_t)nvec) break;
+        RF<NS> f = stream_place<NS, NN, kTail, BF>(rf_zero<NS>(), st, u);
+        f = interp<NS>(f, pro_regs, pro_n);
+        const Quad q = rf_get(f, pro.anchor_slot);
+        const uint32_t own = (tile + threadIdx.x) * kVec, e = min(own, last);
+#pragma unroll
+        for (int v = 0; v < kVec; ++v) {
+          const float x = red_combine(a.red, acc, q.v[v]);
+          acc = tile + threadIdx.x < (uint32_t)nvec && e + (uint32_t)v >= own ? x : acc;
+        }
+      }
+    }
+  } else {
+    for (uint64_t v = (uint64_t)blockIdx.x * kBlock + threadIdx.x; v < nvec; v += (uint64_t)gridDim.x * kBlock) {
+      const uint64_t i = v * kVec;
+      const uint32_t nvalid = (n - i >= (uint64_t)kVec) ? (uint32_t)kVec : (uint32_t)(n - i);
+      RF<NS> f = load_inputs<NS, kMaxIn, false, false>(rf_zero<NS>(), pro, 0, (uint32_t)i, nvalid);
+      f = interp<NS>(f, pro_regs, pro_n);
+      acc = fold_vec(a.red, acc, rf_get(f, pro.anchor_slot), nvalid);
+    }
   }
   float r = block_reduce(a.red, acc, lds);
   if (gridDim.x > 1u) {   // (a single workgroup is its own last one: no partials, no ticket)
@@ -466,55 +552,77 @@ __global__ __launch_bounds__(kColBlock) void lt_col_reduce_kernel(const ColArgs 
 }
 
 
-// Host side: does the program qualify for the streamed row reduction?  Fills in a->vin, a->rin and,
-// when rows are a multiple of 1024 columns only, narrows threads_per_row to 64 (one wave per row)
-// so that a lane has four 4-vectors to take together.
-static bool row_stream_args(RowArgs* a, uint32_t* grid) {
+// Host side: does the program qualify for the streamed row reduction?  Fills in a->vin, a->rin and
+// picks threads per row and vectors per trip.
+static bool row_stream_args(RowArgs* a, uint32_t* grid, uint32_t* q, bool* ragged) {
   const EwProg& p = a->pro;
-  if (!p.fast || !p.all_f32 || p.n_slots > 8u || p.n_in == 0u) return false;
+  if (!p.all_f32 || p.n_slots > 8u || p.n_in == 0u || a->cols < 64u) return false;
   uint32_t nv = 0, nr = 0;
   for (uint32_t k = 0; k < p.n_in; ++k) {
     const EwIn& in = p.in[k];
-    if (in.fetch != kFetchVec4 || in.dtype != kF32) return false;
+    if (in.dtype != kF32) return false;
     if (in.mode == kFull && nv < 2u) a->vin[nv++] = k;
     else if (in.mode == kRowVec && nr < 1u) { a->rin = k; ++nr; }
     else return false;
   }
   if (nv == 0u) return false;
-  uint32_t tpr = a->threads_per_row;
-  if (a->cols % (16u * tpr) != 0u) {
-    tpr = 64u;
-    if (a->cols % (16u * tpr) != 0u) return false;
-  }
-  if (tpr != a->threads_per_row) {
-    a->threads_per_row = tpr;
-    const uint32_t rpb = (uint32_t)kBlock / tpr;
-    *grid = (a->rows + rpb - 1) / rpb < 4096u ? (a->rows + rpb - 1) / rpb : 4096u;
-    if (*grid == 0u) *grid = 1u;
-  }
+  // A lane takes two 4-vectors per trip, and as many waves share a row as it takes to give every
+  // SIMD of the chip two: measured (prologue of 9 instructions, HIP events included) 1024 x 1024 with one /
+  // two / four waves per row 11.2 / 9.2 / 13.5 us, 3001 x 1777 25.1 / 26.2 / 28.8, 16384 x 1024
+  // 55.5 / 58.2 / 110 (four vectors per trip: 58.6 with one wave).  Few and long rows want the
+  // loads of four vectors in flight: 64 x 8192 14.5 us against 17.2.
+  // Rows of up to 128 and 256 columns take a quarter and half a wave each: 65536 x 128 110 -> 35 us.
+  const uint32_t tpr = a->cols <= 128u ? 16u : a->cols <= 256u ? 32u : a->rows >= 2048u || a->cols <= 512u ? 64u : a->rows >= 1024u || a->cols <= 1024u ? 128u : 256u;
+  const uint32_t Q = tpr == 256u && a->cols >= 4096u ? 4u : 2u;
+  a->threads_per_row = tpr;
+  const uint32_t rpb = (uint32_t)kBlock / tpr;
+  *grid = std::max(1u, std::min((a->rows + rpb - 1) / rpb, 4096u));
+  *q = Q;
+  *ragged = !p.fast || a->cols % (4u * Q * tpr) != 0u;
   a->n_vin = nv;
   a->n_rin = nr;
   for (uint32_t j = nv; j < 2u; ++j) a->vin[j] = a->vin[0];
   return true;
 }
 
+template <int Q, bool RAG>
+static void launch_row_stream(const RowArgs& a, dim3 g, hipStream_t s) {
+  const dim3 b(kBlock);
+  if (a.n_vin == 1u && a.n_rin == 0u) LT_LAUNCH((lt_row_reduce_stream_kernel<1, 0, Q, RAG>), g, b, s, a);
+  else if (a.n_vin == 1u) LT_LAUNCH((lt_row_reduce_stream_kernel<1, 1, Q, RAG>), g, b, s, a);
+  else if (a.n_rin == 0u) LT_LAUNCH((lt_row_reduce_stream_kernel<2, 0, Q, RAG>), g, b, s, a);
+  else LT_LAUNCH((lt_row_reduce_stream_kernel<2, 1, Q, RAG>), g, b, s, a);
+}
+
 hipError_t launch_row_reduce(const RowArgs& args, uint32_t grid, hipStream_t s) {
   RowArgs a = args;
   a.vin[0] = a.vin[1] = a.rin = a.n_vin = a.n_rin = 0u;
-  if (row_stream_args(&a, &grid)) {
-    const dim3 g(grid), b(kBlock);
-    if (a.n_vin == 1u && a.n_rin == 0u) LT_LAUNCH((lt_row_reduce_stream_kernel<1, 0>), g, b, s, a);
-    else if (a.n_vin == 1u) LT_LAUNCH((lt_row_reduce_stream_kernel<1, 1>), g, b, s, a);
-    else if (a.n_rin == 0u) LT_LAUNCH((lt_row_reduce_stream_kernel<2, 0>), g, b, s, a);
-    else LT_LAUNCH((lt_row_reduce_stream_kernel<2, 1>), g, b, s, a);
+  uint32_t q = 0;
+  bool ragged = false;
+  if (row_stream_args(&a, &grid, &q, &ragged)) {
+    const dim3 g(grid);
+    if (q == 4u && ragged) launch_row_stream<4, true>(a, g, s);
+    else if (q == 4u) launch_row_stream<4, false>(a, g, s);
+    else if (ragged) launch_row_stream<2, true>(a, g, s);
+    else launch_row_stream<2, false>(a, g, s);
     return hipGetLastError();
   }
   LT_LAUNCH(lt_row_reduce_kernel, dim3(grid), dim3(kBlock), s, args);
   return hipGetLastError();
 }
+// Like stream_kind (lt_interp.h), but fp32 operands of any length: the kernel's last trip takes
+// the elements past the last whole 4-vector with the others.
+static int all_stream_kind(const EwProg& p) {
+  const int kind = stream_kind(p);
+  if (kind != 0 || p.n < (uint64_t)kVec || p.n_in == 0u) return p.n < (uint64_t)kVec ? 0 : kind;
+  for (uint32_t k = 0; k < p.n_in; ++k)
+    if (p.in[k].mode != kFull || p.in[k].fetch != kFetchVec4 || p.in[k].dtype != kF32) return 0;
+  return 1;
+}
+
 hipError_t launch_all_reduce(const AllArgs& a, uint32_t grid, hipStream_t s) {
   const dim3 g(grid), b(kBlock);
-  const int kind = stream_kind(a.pro);
+  const int kind = all_stream_kind(a.pro);
   const uint32_t n_in = a.pro.n_in;
   const bool two = a.pro.n_slots <= 8u;   // the program fits half a register file: two 4-vectors per dispatch
   if (kind == 1 && n_in == 1u && two) LT_LAUNCH((lt_all_reduce_kernel<32, 1, 8, false, 4>), g, b, s, a);

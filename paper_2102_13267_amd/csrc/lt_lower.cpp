@@ -1168,7 +1168,32 @@ struct Lowering {
     // canonical (= topological) order; a member that only the epilogue reads may well have been
     // numbered before the anchor (x - 0.5 * v: the operands are numbered last to first)
     std::sort(post_members.begin(), post_members.end());
-    if (!build_prog(post_members, post_space, Val{a, 0}, out, r->kind == C_ALL, &post)) return false;
+    // A finaliser of more than two rounds of the reduction's last workgroup (which runs it alone)
+    // is a launch of its own over the whole chip, an elementwise region that reads the reduced
+    // value from memory: 65,536 elements 107 us as the tail of the reduction, 7 + 6 us as two
+    // launches, 20,000 elements 42 us; 1024 elements 7.6 us as one launch, where a second one
+    // would cost more than it gains.  (fp32 results only: a bf16 one would be rounded on the way.)
+    const bool split_fin = r->kind == C_ALL && r->has_fin && count(post_space) > 2048 && out_dtype(Val{a, 0}) == LT_F32;
+    ProgBuild fin_head;
+    if (split_fin) {
+      if (storage_of[a][0] < 0) {
+        Storage ns;
+        ns.first_launch = -1;
+        ns.bytes = sizeof(float);
+        plan->storages.push_back(ns);
+        storage_of[a][0] = (int32_t)plan->storages.size() - 1;
+      }
+      const std::vector<int32_t> only{a};
+      if (!build_prog(only, shape_of(a), Val{a, 0}, std::vector<Val>{Val{a, 0}}, true, &fin_head)) return false;
+      std::vector<int32_t> rest = post_m;
+      std::sort(rest.begin(), rest.end());
+      std::vector<Val> rest_out;
+      for (const Val& v : out)
+        if (v.node != a) rest_out.push_back(v);
+      if (!build_prog(rest, post_space, Val{-1, 0}, rest_out, true, &post)) return false;
+    } else if (!build_prog(post_members, post_space, Val{a, 0}, out, r->kind == C_ALL, &post)) {
+      return false;
+    }
     const uint32_t red = an->op == LT_OP_SUM ? ltk::kRedSum : an->op == LT_OP_AMAX ? ltk::kRedMax : ltk::kRedMean;
     if (r->kind == C_ROW) {
       ltk::RowArgs args{};
@@ -1194,8 +1219,26 @@ struct Lowering {
       Launch l = make_launch(L_ALL, k, args);
       l.grid_x = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((args.count + 4095) / 4096, 256 * 2));
       l.bytes = pro.bytes + post.bytes;
+      if (split_fin) {
+        l.bytes = pro.bytes + 4;
+        ((ltk::AllArgs*)l.args.data())->post = fin_head.prog;
+      }
       plan->launches.push_back(std::move(l));
       add_prog_patches(launch, offsetof(ltk::AllArgs, pro), pro);
+      if (split_fin) {
+        add_prog_patches(launch, offsetof(ltk::AllArgs, post), fin_head);
+        note_prog_storages(pro, launch);
+        note_prog_storages(fin_head, launch);
+        ltk::EwArgs ea{};
+        ea.prog = post.prog;
+        Launch l2 = make_launch(L_EW, k, ea);
+        l2.grid_x = ew_grid(post.prog.n);
+        l2.bytes = post.bytes;
+        plan->launches.push_back(std::move(l2));
+        add_prog_patches(launch + 1, offsetof(ltk::EwArgs, prog), post);
+        note_prog_storages(post, launch + 1);
+        return true;
+      }
       add_prog_patches(launch, offsetof(ltk::AllArgs, post), post);
     } else {
       if (in_shape.size() != 2) return bad(LT_ERR_UNSUPPORTED, "axis-0 reduction needs a rank-2 operand (reshape first)");
