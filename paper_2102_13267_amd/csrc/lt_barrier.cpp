@@ -279,7 +279,14 @@ static lt_status execute(lt_ctx* ctx, Plan* plan, const std::vector<BufRef>& par
   // Several streams: only when the schedule found independent work, no per-launch timing is
   // asked for, and the workspace holds every temporary at once (memory given back while the step
   // is still being enqueued could be handed to a launch that runs next to its last reader).
-  const bool multi = real && !prof && !use_static && ctx->max_streams > 1 && plan->n_streams > 1 && upfront;
+  // And only for plans long enough to gain by it.  An edge between streams is an event recorded and
+  // an event waited for, about 10 us of the host's time, in which it would have enqueued three
+  // launches; in a short plan little runs next to anything and the host falls behind the device.
+  // One stream against four: 48 launches (a transformer layer's step) 1719 / 1497, 811 / 654 and
+  // 606 / 521 us, one of them 537 / 618; 4 to 14 launches (norm, attention, feed-forward block, head,
+  // small classifier) 64 / 80, 102 / 155, 343 / 373, 390 / 396, 196 / 206, 115 / 134, never better.
+  constexpr size_t kSpreadLaunches = 24;
+  const bool multi = real && !prof && !use_static && ctx->max_streams > 1 && plan->n_streams > 1 && upfront && plan->launches.size() >= kSpreadLaunches;
   ctx->last_launches.clear();
   if (prof) {
     while (ctx->events.size() < 2 * plan->launches.size()) {
