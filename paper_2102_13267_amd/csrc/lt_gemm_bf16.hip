@@ -20,8 +20,12 @@
 //    transpose happens in the LDS read: ds_read_b64_tr_b16 hands each lane of a 16-lane group one
 //    column of a 4 x 16 sub-tile (lane i gets element i of each of the four rows that lanes
 //    4j .. 4j+3 point at), so two such reads give the 8 k values of one x.
-// Nothing is transposed by scalar code.  Ragged or unaligned tiles take a second path: every
-// access checked, global -> registers -> padded LDS tiles, one slice at a time.
+// Nothing is transposed by scalar code.  A tile that hangs over the edge of its operand takes the same
+// path (rows and chunks past the edge are copies of the last one, never stored); what is left of k
+// behind the last whole slice is fetched element by element, one slice.  Rows that are not 16-byte
+// aligned (odd lengths) go through registers into padded LDS tiles, 16 bytes at a time, one slice
+// ahead.  128 heads of 200 x 64: q k^T 10.7 us, p v 10.3 us (with every access checked element by element: 14.4
+// and 14.9).
 //
 // Epilogue (lt_gemm_epilogue.h): the accumulators leave the MFMA layout through LDS, the whole tile
 // at once, and are then walked in row-major 4-element quads by the interpreter (bias, activation,
@@ -78,36 +82,50 @@ __device__ __forceinline__ void chunk_pos(uint32_t it, uint32_t* outer, uint32_t
   }
 }
 
-// Guarded fetch of 8 elements at (outer, inner .. inner+7); out-of-range elements read as zero.
-__device__ __noinline__ uint4 fetch_guarded(const uint16_t* base, int64_t s_outer, uint32_t outer, uint32_t inner,
-                                            uint32_t n_outer, uint32_t n_inner, bool aligned) {
-  uint4 v = make_uint4(0, 0, 0, 0);
-  if (outer >= n_outer || inner >= n_inner) return v;
-  const uint16_t* src = base + (int64_t)outer * s_outer + inner;
-  if (aligned && inner + 8u <= n_inner) return *(const uint4*)src;
-  uint32_t w0 = 0, w1 = 0, w2 = 0, w3 = 0;
-  if (inner + 0 < n_inner) w0 |= (uint32_t)src[0];
-  if (inner + 1 < n_inner) w0 |= (uint32_t)src[1] << 16;
-  if (inner + 2 < n_inner) w1 |= (uint32_t)src[2];
-  if (inner + 3 < n_inner) w1 |= (uint32_t)src[3] << 16;
-  if (inner + 4 < n_inner) w2 |= (uint32_t)src[4];
-  if (inner + 5 < n_inner) w2 |= (uint32_t)src[5] << 16;
-  if (inner + 6 < n_inner) w3 |= (uint32_t)src[6];
-  if (inner + 7 < n_inner) w3 |= (uint32_t)src[7] << 16;
-  return make_uint4(w0, w1, w2, w3);
-}
-
-// Global -> registers for the slice starting at k0, every access checked.
+// Global -> registers for a slice that may run over the end of k (or touch the operand's last row, see
+// the kernel): element by element at addresses clamped into the operand, branch-free so that all of
+// a lane's loads are in flight together.  k past the end reads as zero; rows or columns past the
+// edge are copies of the last one and are never stored.
 template <int BX, bool KC>
 __device__ __forceinline__ Chunks<Geo<BX>::kChunks> fetch_checked(const uint16_t* base, int64_t s_x, int64_t s_k, uint32_t x0,
-                                                                  uint32_t k0, uint32_t nx, uint32_t nk, bool aligned) {
+                                                                  uint32_t k0, uint32_t nx, uint32_t nk) {
   Chunks<Geo<BX>::kChunks> c;
 #pragma unroll
   for (int it = 0; it < Geo<BX>::kChunks; ++it) {
     uint32_t o, i;
     chunk_pos<BX, KC>(it, &o, &i);
-    c.g[it] = KC ? fetch_guarded(base, s_x, x0 + o, k0 + i, nx, nk, aligned)
-                 : fetch_guarded(base, s_k, k0 + o, x0 + i, nk, nx, aligned);
+    uint32_t e[8];
+#pragma unroll
+    for (uint32_t j = 0; j < 8u; ++j) {
+      const uint32_t x = KC ? x0 + o : x0 + i + j, k = KC ? k0 + i + j : k0 + o;
+      e[j] = (uint32_t)base[(int64_t)min(x, nx - 1u) * s_x + (int64_t)min(k, nk - 1u) * s_k];
+    }
+#pragma unroll
+    for (uint32_t j = 0; j < 8u; ++j)
+      if ((KC ? k0 + i + j : k0 + o) >= nk) e[j] = 0u;
+    c.g[it] = make_uint4(e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6] | e[7] << 16);
+  }
+  return c;
+}
+
+// This lane's element offset of its chunk at (outer, inner) from the (wave-uniform) start of the panel at x0, k0 = 0: the
+// same for every slice.  Rows (KC) or chunks of eight columns past the operand's edge become copies
+// of the last one.
+template <int BX, bool KC>
+__device__ __forceinline__ int64_t chunk_offset(uint32_t outer, uint32_t inner, int64_t s_x, int64_t s_k, uint32_t left) {
+  return KC ? (int64_t)min(outer, left - 1u) * s_x + inner : (int64_t)outer * s_k + min(inner, (left - 1u) & ~7u);
+}
+
+// Global -> registers for a whole slice of an operand whose rows start at any element: 16-byte
+// loads at 2-byte boundaries (the hardware takes them; half the rate of aligned ones at worst).
+typedef uint32_t U32x4u __attribute__((ext_vector_type(4), aligned(2)));
+template <int BX, bool KC>
+__device__ __forceinline__ Chunks<Geo<BX>::kChunks> fetch_unaligned(const uint16_t* panel, const int64_t (&off)[Geo<BX>::kChunks]) {
+  Chunks<Geo<BX>::kChunks> c;
+#pragma unroll
+  for (int it = 0; it < Geo<BX>::kChunks; ++it) {
+    const U32x4u v = *(const U32x4u*)(panel + off[it]);
+    c.g[it] = make_uint4(v.x, v.y, v.z, v.w);
   }
   return c;
 }
@@ -163,18 +181,18 @@ template <int BX, bool KC> struct Dense {
   __device__ static __forceinline__ uint32_t swz_x(uint32_t x) { return (x >> 2) & 3u; }
 };
 
-// This lane's byte offset from the (wave-uniform) origin of an instruction's 64 rows (KC) or
-// 256 / kPerRow k rows (otherwise): the same for every instruction and every slice.
+// This lane's byte offset, for wave instruction `it` of a slice, from the (wave-uniform) start of the
+// panel at x0: the same for every slice.  `left`: rows or columns from x0 to the operand's edge.
 template <int BX, bool KC>
-__device__ __forceinline__ uint32_t dma_lane_offset(int64_t s_x, int64_t s_k) {
+__device__ __forceinline__ uint32_t dma_lane_offset(uint32_t it, int64_t s_x, int64_t s_k, uint32_t left) {
   typedef Dense<BX, KC> D;
   const uint32_t t = threadIdx.x;
   if (KC) {
-    const uint32_t row = t >> 2, c = (t & 3u) ^ D::swz_x(row);
-    return (uint32_t)((row * s_x + c * 8u) * 2);
+    const uint32_t row = it * 64u + (t >> 2), c = (t & 3u) ^ D::swz_x(row);
+    return (uint32_t)(2 * chunk_offset<BX, KC>(row, c * 8u, s_x, s_k, left));
   }
   const uint32_t k = t / D::kPerRow, xc = (t % D::kPerRow) ^ D::swz_k(k);
-  return (uint32_t)((k * s_k + xc * 8u) * 2);
+  return (uint32_t)(2 * chunk_offset<BX, KC>(it * ((uint32_t)kGemmThreads / D::kPerRow) + k, xc * 8u, s_x, s_k, left));
 }
 
 // One wave instruction of such a copy.  Written in assembly on purpose: the compiler orders every
@@ -184,8 +202,8 @@ __device__ __forceinline__ uint32_t dma_lane_offset(int64_t s_x, int64_t s_k) {
 // nothing else in the loop uses it, and the interpreter's register indexing sets it afresh.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
-__device__ __forceinline__ void copy_1k(const void* gptr, uint32_t lds_base) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_base), "v"(gptr) : "memory", "m0");
+__device__ __forceinline__ void copy_1k(const void* base, uint32_t lane_off, uint32_t lds_base) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_base), "v"(lane_off), "s"(base) : "memory", "m0");
 }
 #pragma clang diagnostic pop
 
@@ -197,18 +215,13 @@ __device__ __forceinline__ void landed() {
   __builtin_amdgcn_s_waitcnt((int)((outstanding & 15u) | ((outstanding >> 4) << 14) | 0x0f70u));
 }
 
-// Start the copy of the slice at k0 of the BX-wide panel at x0 into the tile at LDS address `tile`.
+// Start the copy of a slice (`src`: the panel's start at the slice's first k) into the tile at LDS
+// address `tile`.
 template <int BX, bool KC>
-__device__ __forceinline__ void dma_tile(const uint16_t* base, int64_t s_x, int64_t s_k, uint32_t x0, uint32_t k0, uint32_t lane_off,
-                                         uint32_t tile, uint32_t wave) {
-  typedef Dense<BX, KC> D;
-  constexpr uint32_t rows_per_instr = KC ? 64u : (uint32_t)kGemmThreads / D::kPerRow;
+__device__ __forceinline__ void dma_tile(const uint16_t* src, const uint32_t (&off)[Dense<BX, KC>::kInstr], uint32_t tile, uint32_t wave) {
 #pragma unroll
-  for (uint32_t it = 0; it < D::kInstr; ++it) {
-    const uint16_t* u = KC ? base + (int64_t)(x0 + it * rows_per_instr) * s_x + k0
-                           : base + (int64_t)(k0 + it * rows_per_instr) * s_k + x0;
-    copy_1k((const char*)u + lane_off, tile + (it * (uint32_t)kGemmThreads + wave * 64u) * 16u);
-  }
+  for (uint32_t it = 0; it < Dense<BX, KC>::kInstr; ++it)
+    copy_1k(src, off[it], tile + (it * (uint32_t)kGemmThreads + wave * 64u) * 16u);
 }
 
 // Two consecutive slices (ka, kb = ka + 32 unless clamped) at once, instruction by instruction.
@@ -217,19 +230,13 @@ __device__ __forceinline__ void dma_tile(const uint16_t* base, int64_t s_x, int6
 // request to L2 (measured: 1.8 times the L2 requests, the address unit stalled by the cache for
 // 40 % of the kernel).  Back to back, the second access finds the line already on its way.
 template <int BX, bool KC>
-__device__ __forceinline__ void dma_tile2(const uint16_t* base, int64_t s_x, int64_t s_k, uint32_t x0, uint32_t ka, uint32_t kb,
-                                          uint32_t lane_off, uint32_t tile_a, uint32_t tile_b, uint32_t wave) {
-  typedef Dense<BX, KC> D;
-  constexpr uint32_t rows_per_instr = KC ? 64u : (uint32_t)kGemmThreads / D::kPerRow;
+__device__ __forceinline__ void dma_tile2(const uint16_t* src_a, const uint16_t* src_b, const uint32_t (&off)[Dense<BX, KC>::kInstr],
+                                          uint32_t tile_a, uint32_t tile_b, uint32_t wave) {
 #pragma unroll
-  for (uint32_t it = 0; it < D::kInstr; ++it) {
-    const uint16_t* ua = KC ? base + (int64_t)(x0 + it * rows_per_instr) * s_x + ka
-                            : base + (int64_t)(ka + it * rows_per_instr) * s_k + x0;
-    const uint16_t* ub = KC ? base + (int64_t)(x0 + it * rows_per_instr) * s_x + kb
-                            : base + (int64_t)(kb + it * rows_per_instr) * s_k + x0;
+  for (uint32_t it = 0; it < Dense<BX, KC>::kInstr; ++it) {
     const uint32_t dst = (it * (uint32_t)kGemmThreads + wave * 64u) * 16u;
-    copy_1k((const char*)ua + lane_off, tile_a + dst);
-    copy_1k((const char*)ub + lane_off, tile_b + dst);
+    copy_1k(src_a, off[it], tile_a + dst);
+    copy_1k(src_b, off[it], tile_b + dst);
   }
 }
 
@@ -266,11 +273,13 @@ template <int BM, int BN> struct Smem {
   static constexpr size_t kStage = Geo<BM>::kBytes + Geo<BN>::kBytes;
   static constexpr size_t kStripBytes = (size_t)BM * (BN + kCPad) * sizeof(float);   // the whole tile
   static constexpr size_t kDense = 4 * (size_t)(BM + BN) * 64;                        // four dense stages
-  static constexpr size_t kMax2 = kStage > kStripBytes ? kStage : kStripBytes;   // (ragged tiles: one padded stage)
+  static constexpr size_t kMax2 = 2 * kStage > kStripBytes ? 2 * kStage : kStripBytes;   // (unaligned rows: two padded stages)
   static constexpr size_t kBytes = kMax2 > kDense ? kMax2 : kDense;
 };
 
-template <int BM, int BN, bool AKC, bool BKC>
+// AL: both operands' rows are 16-byte aligned (the launcher looks).  Two instances, because the path
+// that the other one takes costs registers in the main loop.
+template <int BM, int BN, bool AKC, bool BKC, bool AL>
 __global__ __launch_bounds__(kGemmThreads, 2) void lt_gemm_bf16_kernel(const GemmArgs a) {
   constexpr int MB = BM / 64, NB = BN / 64;   // 32 x 32 blocks per wave: rows, columns
   __shared__ __attribute__((aligned(16))) char smem[Smem<BM, BN>::kBytes];
@@ -290,11 +299,8 @@ __global__ __launch_bounds__(kGemmThreads, 2) void lt_gemm_bf16_kernel(const Gem
   const uint32_t per = (slices + a.splits - 1) / a.splits;
   const uint32_t k_begin = min(a.k, split * per * BK), k_end = min(a.k, (split + 1) * per * BK);
   const int64_t a_outer = AKC ? a.a.s_row : a.a.s_col, b_outer = BKC ? a.b.s_col : a.b.s_row;
-  const bool a_al = (((uintptr_t)A) & 15u) == 0 && (a_outer % 8) == 0;
-  const bool b_al = (((uintptr_t)B) & 15u) == 0 && (b_outer % 8) == 0;
-  const bool a_in = a_al && tile_m + BM <= a.m, b_in = b_al && tile_n + BN <= a.n;
 
-    constexpr uint32_t kStage = (uint32_t)Smem<BM, BN>::kStage;   // padded layout (ragged tiles): A tile then B tile
+  constexpr uint32_t kStage = (uint32_t)Smem<BM, BN>::kStage;   // padded layout (ragged tiles): A tile then B tile
   v16f acc[MB][NB];
 #pragma unroll
   for (int i = 0; i < MB; ++i)
@@ -328,8 +334,20 @@ __global__ __launch_bounds__(kGemmThreads, 2) void lt_gemm_bf16_kernel(const Gem
 #pragma unroll
         for (int j = 0; j < NB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[kk][i], f.b[kk][j], acc[i][j], 0, 0, 0);
   };
-  const bool whole = a_in && b_in && ((k_end - k_begin) % BK) == 0u;
-  if (k_begin < k_end && whole) {
+  // Whole slices of k are fetched in 16-byte chunks with no checks; what is left of k goes through
+  // fetch_checked as one last slice.  A tile that hangs over the operand's edge is filled with copies
+  // of the last row (k contiguous), or of the last chunk of eight columns.  That chunk may reach up
+  // to seven elements past its row, into the next one (in bounds if rows are at least that far
+  // apart): then the slice with the operand's last row has to be the checked one.
+  const uint32_t left_m = a.m - tile_m, left_n = a.n - tile_n;
+  const bool a_over = !AKC && left_m < (uint32_t)BM && (a.m & 7u) != 0u, b_over = !BKC && left_n < (uint32_t)BN && (a.n & 7u) != 0u;
+  uint32_t n = (k_end - k_begin) / BK;   // whole slices
+  if ((a_over && a_outer < 8) || (b_over && b_outer < 8)) n = 0u;
+  else if ((a_over || b_over) && n > 0u && k_begin + n * BK == a.k) --n;
+  const uint16_t* const pa = A + (int64_t)tile_m * a.a.s_row + (int64_t)k_begin * a.a.s_col;
+  const uint16_t* const pb = B + (int64_t)tile_n * a.b.s_col + (int64_t)k_begin * a.b.s_row;
+  const int64_t step_a = BK * a.a.s_col, step_b = BK * a.b.s_row;   // elements per slice of k
+  if (AL && n > 0u) {
     // Software pipeline over slices j = 0 .. n-1, four LDS stages: the MFMAs of slice j run from
     // fragment registers, the fragments of slice j+1 are read from the stage that holds it, and
     // later slices are on their way from global memory straight into their stages -- no
@@ -338,23 +356,25 @@ __global__ __launch_bounds__(kGemmThreads, 2) void lt_gemm_bf16_kernel(const Gem
     constexpr uint32_t kDenseStage = Dense<BM, AKC>::kBytes + Dense<BN, BKC>::kBytes;
     constexpr uint32_t kPer = Dense<BM, AKC>::kInstr + Dense<BN, BKC>::kInstr;   // copy instructions per wave and slice
     static_assert(4 * kDenseStage <= Smem<BM, BN>::kBytes, "four dense stages fit the tile's LDS");
-    const uint32_t n = (k_end - k_begin) / BK;
     const uint32_t wave_u = __builtin_amdgcn_readfirstlane(wave);
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
-    const uint32_t a_off = dma_lane_offset<BM, AKC>(a.a.s_row, a.a.s_col), b_off = dma_lane_offset<BN, BKC>(a.b.s_col, a.b.s_row);
-#define LT_COPY(I, STAGE)                                                                                          \
-  {                                                                                                               \
-    const uint32_t kf = k_begin + min((uint32_t)(I), n - 1u) * BK;                                                \
-    dma_tile<BM, AKC>(A, a.a.s_row, a.a.s_col, tile_m, kf, a_off, lds0 + (STAGE) * kDenseStage, wave_u);          \
-    dma_tile<BN, BKC>(B, a.b.s_col, a.b.s_row, tile_n, kf, b_off, lds0 + (STAGE) * kDenseStage + Dense<BM, AKC>::kBytes, wave_u); \
+    uint32_t a_off[Dense<BM, AKC>::kInstr], b_off[Dense<BN, BKC>::kInstr];
+#pragma unroll
+    for (uint32_t it = 0; it < Dense<BM, AKC>::kInstr; ++it) a_off[it] = dma_lane_offset<BM, AKC>(it, a.a.s_row, a.a.s_col, left_m);
+#pragma unroll
+    for (uint32_t it = 0; it < Dense<BN, BKC>::kInstr; ++it) b_off[it] = dma_lane_offset<BN, BKC>(it, a.b.s_col, a.b.s_row, left_n);
+#define LT_COPY(I, STAGE)                                                                                  \
+  {                                                                                                       \
+    const int64_t sl = min((uint32_t)(I), n - 1u);                                                        \
+    dma_tile<BM, AKC>(pa + sl * step_a, a_off, lds0 + (STAGE) * kDenseStage, wave_u);                     \
+    dma_tile<BN, BKC>(pb + sl * step_b, b_off, lds0 + (STAGE) * kDenseStage + Dense<BM, AKC>::kBytes, wave_u); \
   }
-#define LT_COPY2(I0, S0, I1, S1)                                                                                   \
-  {                                                                                                               \
-    const uint32_t ka = k_begin + min((uint32_t)(I0), n - 1u) * BK, kb = k_begin + min((uint32_t)(I1), n - 1u) * BK; \
-    dma_tile2<BM, AKC>(A, a.a.s_row, a.a.s_col, tile_m, ka, kb, a_off, lds0 + (S0) * kDenseStage,                  \
-                       lds0 + (S1) * kDenseStage, wave_u);                                                        \
-    dma_tile2<BN, BKC>(B, a.b.s_col, a.b.s_row, tile_n, ka, kb, b_off, lds0 + (S0) * kDenseStage + Dense<BM, AKC>::kBytes, \
-                       lds0 + (S1) * kDenseStage + Dense<BM, AKC>::kBytes, wave_u);                               \
+#define LT_COPY2(I0, S0, I1, S1)                                                                           \
+  {                                                                                                       \
+    const int64_t sa = min((uint32_t)(I0), n - 1u), sb = min((uint32_t)(I1), n - 1u);                     \
+    dma_tile2<BM, AKC>(pa + sa * step_a, pa + sb * step_a, a_off, lds0 + (S0) * kDenseStage, lds0 + (S1) * kDenseStage, wave_u); \
+    dma_tile2<BN, BKC>(pb + sa * step_b, pb + sb * step_b, b_off, lds0 + (S0) * kDenseStage + Dense<BM, AKC>::kBytes, \
+                       lds0 + (S1) * kDenseStage + Dense<BM, AKC>::kBytes, wave_u);                       \
   }
     auto dense_frags = [&](uint32_t stage) {
       const char* As = smem + stage * kDenseStage;
@@ -437,23 +457,53 @@ __global__ __launch_bounds__(kGemmThreads, 2) void lt_gemm_bf16_kernel(const Gem
       LT_SLICE(1, f1, f0, true);
       LT_SLICE(2, f0, f1, true);
     }
-    landed<0>();   // nothing may still be on its way into LDS when the epilogue reuses it
+    landed<0>();   // nothing may still be on its way into LDS when it is used again
     }
 #undef LT_SLICE
 #undef LT_COPY2
 #undef LT_COPY
-  } else if (k_begin < k_end) {
-    // ragged or unaligned tile: every access checked, one slice at a time
+  }
+  if (!AL && n > 0u) {
+    // an operand whose rows are not 16-byte aligned: through registers into padded LDS tiles, the
+    // loads of slice j+1 under the MFMAs of slice j, two buffers and one barrier per slice
+    int64_t a_off[Geo<BM>::kChunks], b_off[Geo<BN>::kChunks];
+#pragma unroll
+    for (int it = 0; it < Geo<BM>::kChunks; ++it) {
+      uint32_t o, i;
+      chunk_pos<BM, AKC>(it, &o, &i);
+      a_off[it] = chunk_offset<BM, AKC>(o, i, a.a.s_row, a.a.s_col, left_m);
+    }
+#pragma unroll
+    for (int it = 0; it < Geo<BN>::kChunks; ++it) {
+      uint32_t o, i;
+      chunk_pos<BN, BKC>(it, &o, &i);
+      b_off[it] = chunk_offset<BN, BKC>(o, i, a.b.s_col, a.b.s_row, left_n);
+    }
+    Chunks<Geo<BM>::kChunks> ca = fetch_unaligned<BM, AKC>(pa, a_off);
+    Chunks<Geo<BN>::kChunks> cb = fetch_unaligned<BN, BKC>(pb, b_off);
 #pragma unroll 1
-    for (uint32_t k0 = k_begin; k0 < k_end; k0 += BK) {
-      const Chunks<Geo<BM>::kChunks> ca = fetch_checked<BM, AKC>(A, a.a.s_row, a.a.s_col, tile_m, k0, a.m, k_end, a_al);
-      const Chunks<Geo<BN>::kChunks> cb = fetch_checked<BN, BKC>(B, a.b.s_col, a.b.s_row, tile_n, k0, a.n, k_end, b_al);
+    for (uint32_t j = 0; j < n; ++j) {
+      char* const st = smem + (j & 1u) * kStage;
+      stash<BM, AKC>(ca, st);
+      stash<BN, BKC>(cb, st + Geo<BM>::kBytes);
+      const int64_t nx = min(j + 1u, n - 1u);   // (past the end: the last slice again, unused)
+      ca = fetch_unaligned<BM, AKC>(pa + nx * step_a, a_off);
+      cb = fetch_unaligned<BN, BKC>(pb + nx * step_b, b_off);
+      __syncthreads();
+      mma(load_frags(j & 1u));
+    }
+  }
+  if (k_begin + n * BK < k_end) {
+    // the rest of k: every address checked, one slice at a time
+#pragma unroll 1
+    for (uint32_t k0 = k_begin + n * BK; k0 < k_end; k0 += BK) {
+      const Chunks<Geo<BM>::kChunks> ca = fetch_checked<BM, AKC>(A, a.a.s_row, a.a.s_col, tile_m, k0, a.m, k_end);
+      const Chunks<Geo<BN>::kChunks> cb = fetch_checked<BN, BKC>(B, a.b.s_col, a.b.s_row, tile_n, k0, a.n, k_end);
       __syncthreads();
       stash<BM, AKC>(ca, smem);
       stash<BN, BKC>(cb, smem + Geo<BM>::kBytes);
       __syncthreads();
-      const Frags f = load_frags(0);
-      mma(f);
+      mma(load_frags(0));
     }
   }
 
@@ -462,17 +512,27 @@ __global__ __launch_bounds__(kGemmThreads, 2) void lt_gemm_bf16_kernel(const Gem
   epilogue<BM, BN, MB, NB>(a, acc, (float*)smem, tile_m, tile_n, wave_m, wave_n, lane, batch, raw);
 }
 
-template <int BM, int BN>
-static void launch_tile(const GemmArgs& a, dim3 grid, hipStream_t s) {
+template <int BM, int BN, bool AL>
+static void launch_layout(const GemmArgs& a, dim3 grid, hipStream_t s) {
   const dim3 block(kGemmThreads);
   const bool akc = a.a.s_col == 1, bkc = a.b.s_row == 1;
-  if (akc && bkc) LT_LAUNCH((lt_gemm_bf16_kernel<BM, BN, true, true>), grid, block, s, a);
-  else if (akc) LT_LAUNCH((lt_gemm_bf16_kernel<BM, BN, true, false>), grid, block, s, a);
-  else if (bkc) LT_LAUNCH((lt_gemm_bf16_kernel<BM, BN, false, true>), grid, block, s, a);
-  else LT_LAUNCH((lt_gemm_bf16_kernel<BM, BN, false, false>), grid, block, s, a);
-  char name[48];
-  snprintf(name, sizeof(name), "lt_gemm_bf16_kernel<%d, %d, %s, %s>", BM, BN, akc ? "true" : "false", bkc ? "true" : "false");
+  if (akc && bkc) LT_LAUNCH((lt_gemm_bf16_kernel<BM, BN, true, true, AL>), grid, block, s, a);
+  else if (akc) LT_LAUNCH((lt_gemm_bf16_kernel<BM, BN, true, false, AL>), grid, block, s, a);
+  else if (bkc) LT_LAUNCH((lt_gemm_bf16_kernel<BM, BN, false, true, AL>), grid, block, s, a);
+  else LT_LAUNCH((lt_gemm_bf16_kernel<BM, BN, false, false, AL>), grid, block, s, a);
+  char name[64];
+  snprintf(name, sizeof(name), "lt_gemm_bf16_kernel<%d, %d, %s, %s, %s>", BM, BN, akc ? "true" : "false", bkc ? "true" : "false", AL ? "true" : "false");
   note_kernel(name);
+}
+
+template <int BM, int BN>
+static void launch_tile(const GemmArgs& a, dim3 grid, hipStream_t s) {
+  // (a lane's offset into a panel is a 32-bit number of bytes: 128 rows of less than 2^24 elements)
+  auto aligned = [](const GemmOperand& o, int64_t outer) {
+    return ((uintptr_t)o.ptr & 15u) == 0 && outer % 8 == 0 && outer < (1 << 24) && o.s_b0 % 8 == 0 && o.s_b1 % 8 == 0;
+  };
+  if (aligned(a.a, a.a.s_col == 1 ? a.a.s_row : a.a.s_col) && aligned(a.b, a.b.s_row == 1 ? a.b.s_col : a.b.s_row)) launch_layout<BM, BN, true>(a, grid, s);
+  else launch_layout<BM, BN, false>(a, grid, s);
 }
 
 }  // namespace bf

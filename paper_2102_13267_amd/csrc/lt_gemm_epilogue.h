@@ -38,14 +38,16 @@ __device__ __forceinline__ void post_wide(const GemmArgs& a, const ProgRegs pr, 
   const char* ptr0 = (const char*)p.in[0].ptr;
   const char* ptr1 = (const char*)p.in[k1].ptr;
   const bool full0 = p.in[0].mode == kFull, full1 = p.in[k1].mode == kFull;
-  const uint32_t col = tile_n + c;
+  // (a tile over the edge: rows and columns past it read the last ones' inputs and store nothing)
+  const uint32_t col = min(tile_n + c, a.n - (uint32_t)kVec);
+  const bool edge = tile_m + BM > a.m || tile_n + BN > a.n;   // (wave-uniform)
 #pragma unroll 1
   for (uint32_t pass = 0; pass < kTrips / (uint32_t)Q; ++pass) {
     uint32_t idx[Q];   // flat output index of quad j of this trip
 #pragma unroll
     for (int j = 0; j < Q; ++j) {
       const uint32_t r = r0 + (pass * (uint32_t)Q + (uint32_t)j) * kRowStep;
-      idx[j] = (uint32_t)(base + (int64_t)(tile_m + r) * a.o_row + col);
+      idx[j] = (uint32_t)(base + (int64_t)min(tile_m + r, a.m - 1u) * a.o_row + col);
     }
     RF<NS> f = rf_zero<NS>();
     if (bf) {
@@ -94,7 +96,10 @@ __device__ __forceinline__ void post_wide(const GemmArgs& a, const ProgRegs pr, 
       if ((uint32_t)o < p.n_out) {
         const EwOut& out = p.out[o];
 #pragma unroll
-        for (int j = 0; j < Q; ++j) store_vec4<false>(out.ptr, out.dtype, 0, idx[j], rf_get<NS>(f, out.slot + (uint32_t)(j * SL)));
+        for (int j = 0; j < Q; ++j) {
+          if (edge && (tile_n + c >= a.n || tile_m + r0 + (pass * (uint32_t)Q + (uint32_t)j) * kRowStep >= a.m)) continue;
+          store_vec4<false>(out.ptr, out.dtype, 0, idx[j], rf_get<NS>(f, out.slot + (uint32_t)(j * SL)));
+        }
       }
     }
   }
@@ -161,21 +166,41 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, const v16f (&acc)[MB
     }
     return;
   }
-  // Whole tile, whole aligned 4-vectors, at most four inputs (none of them strided) and eight
-  // slots: no bounds checks, no divisions (row and column are known).
-  const bool fast = p.fast && p.full_vec_ok && p.n_in <= 4u && p.n_slots <= 8u && tile_m + BM <= a.m && tile_n + BN <= a.n;
+  // Whole aligned 4-vectors, at most four inputs (none of them strided) and eight slots: no bounds
+  // checks on inputs, no divisions (row and column are known).
+  const bool fast = p.fast && p.full_vec_ok && (a.n & 3u) == 0u && p.n_in <= 4u && p.n_slots <= 8u;
   const uint32_t row_flat0 = (b0 * a.batch1 + b1) * a.m + tile_m;   // row number in the flattened [rows, n] output
-  if (fast && n_code == 0u && p.n_in == 0u && p.n_out == 1u && !p.out[0].scalar && p.out[0].slot == p.anchor_slot) {
+  if (n_code == 0u && p.n_in == 0u && p.n_out == 1u && !p.out[0].scalar && p.out[0].slot == p.anchor_slot) {
     // the product itself is the only output: convert and store, nothing to interpret
     const EwOut& o = p.out[0];
+    if (fast && tile_m + BM <= a.m && tile_n + BN <= a.n) {
 #pragma unroll 4
+      for (uint32_t q = threadIdx.x; q < (uint32_t)(BM * BN / kVec); q += kGemmThreads) {
+        const uint32_t r = q / (BN / kVec), c = (q % (BN / kVec)) * kVec;
+        const uint32_t i = (uint32_t)(base + (int64_t)(tile_m + r) * a.o_row + tile_n + c);
+        const float4 t = *(const float4*)&Cs[r * kCStride + c];
+        Quad v;
+        v.v[0] = t.x; v.v[1] = t.y; v.v[2] = t.z; v.v[3] = t.w;
+        store_vec4<false>(o.ptr, o.dtype, 0, i, v);
+      }
+      return;
+    }
+    // a tile over the edge, or rows that start at any element (an odd n)
+#pragma unroll 2
     for (uint32_t q = threadIdx.x; q < (uint32_t)(BM * BN / kVec); q += kGemmThreads) {
       const uint32_t r = q / (BN / kVec), c = (q % (BN / kVec)) * kVec;
+      if (tile_m + r >= a.m || tile_n + c >= a.n) continue;
       const uint32_t i = (uint32_t)(base + (int64_t)(tile_m + r) * a.o_row + tile_n + c);
       const float4 t = *(const float4*)&Cs[r * kCStride + c];
       Quad v;
       v.v[0] = t.x; v.v[1] = t.y; v.v[2] = t.z; v.v[3] = t.w;
-      store_vec4<false>(o.ptr, o.dtype, 0, i, v);
+      if (tile_n + c + (uint32_t)kVec <= a.n) {
+        store_vec4_any(o.ptr, o.dtype, i, v);
+      } else {
+#pragma unroll
+        for (int e = 0; e < kVec - 1; ++e)
+          if (tile_n + c + (uint32_t)e < a.n) store_elem<false>(o.ptr, o.dtype, i + (uint32_t)e, v.v[e]);
+      }
     }
     return;
   }
@@ -192,7 +217,7 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, const v16f (&acc)[MB
       return;
     }
   }
-  if (fast) {
+  if (fast && tile_m + BM <= a.m && tile_n + BN <= a.n) {
     // two quads per trip (same columns, kGemmThreads quads apart): the interpreter is fetched,
     // decoded and dispatched once for both (register file = 8 slots x 2)
     constexpr uint32_t kRowStep = (uint32_t)kGemmThreads / (BN / kVec);

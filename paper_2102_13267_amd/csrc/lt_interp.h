@@ -541,6 +541,17 @@ __device__ __forceinline__ void store_vec4(void* ptr, uint32_t dtype, uint64_t b
   }
 }
 
+// The same at any element boundary (rows of odd length).
+__device__ __forceinline__ void store_vec4_any(void* ptr, uint32_t dtype, uint64_t idx, const Quad& q) {
+  if (dtype == kBF16) {
+    typedef uint32_t U32x2u __attribute__((ext_vector_type(2), aligned(2)));
+    *(U32x2u*)((uint16_t*)ptr + idx) = U32x2u{f32_to_bf16_pair(q.v[0], q.v[1]), f32_to_bf16_pair(q.v[2], q.v[3])};
+  } else {
+    typedef float F32x4u __attribute__((ext_vector_type(4), aligned(4)));
+    *(F32x4u*)((float*)ptr + idx) = F32x4u{q.v[0], q.v[1], q.v[2], q.v[3]};
+  }
+}
+
 // Store the outputs of the program for elements i .. i+nvalid-1, i = base + lane (flat,
 // contiguous outputs).
 template <int NS, bool FAST = false, bool F32 = false, int OFF = 0, bool NT = false>

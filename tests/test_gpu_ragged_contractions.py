@@ -1,0 +1,60 @@
+"""GPU parity (-m gpu) of contractions whose rows, columns and depth are no multiple of a tile, a slice
+or a 16-byte chunk, against the CPU oracle; operands are the middle part of larger buffers whose other
+elements are NaN, so that a value from past an edge shows."""
+import numpy as np
+import pytest
+
+from oracle.numeric import Eager, round_to_bf16
+from test_gpu_parity import check, ctx, rng  # noqa: F401  (ctx is a fixture)
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(1, 1, 1), (3, 5, 7), (9, 65, 33), (127, 129, 31), (129, 63, 32), (130, 200, 64), (200, 64, 200), (201, 203, 97), (64, 72, 136), (136, 257, 264),
+          (300, 10, 160), (256, 130, 1000), (77, 128, 4101)]
+
+
+def window(B, full, rows):
+    return B.narrow(full, 0, 1, rows)
+
+
+@pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, False), (True, True)])
+@pytest.mark.parametrize("m,n,k", SHAPES)
+def test_ragged_bf16(ctx, m, n, k, ta, tb):  # noqa: F811
+    """Bar: 2e-2 of the result's largest value (one bf16 rounding of it, and of the inputs of the sum
+    with a bias): the products themselves are exact in fp32."""
+    E, g = Eager(), rng(m * 7 + n * 11 + k)
+
+    def operand(rows, cols):
+        t = np.full((rows + 2, cols), np.nan, np.float32)
+        t[1:-1] = round_to_bf16(g.standard_normal((rows, cols), dtype=np.float32))
+        return t
+    a, b = operand(*((k, m) if ta else (m, k))), operand(*((n, k) if tb else (k, n)))
+    bias, res = (round_to_bf16(g.standard_normal(s, dtype=np.float32)) for s in ((n,), (m, n)))
+
+    def prog(B, a, b, bias, res):
+        p = B.matmul(window(B, a, a.shape[0] - 2), window(B, b, b.shape[0] - 2), trans_a=ta, trans_b=tb)
+        q = B.matmul(window(B, a, a.shape[0] - 2), window(B, b, b.shape[0] - 2), trans_a=ta, trans_b=tb)
+        return p, B.add(B.relu(B.add(q, bias)), res)
+    got = prog(ctx, *(ctx.tensor(t, dtype="bf16") for t in (a, b, bias, res)))
+    ref = prog(E, *(E.tensor(t, dtype="bf16") for t in (a, b, bias, res)))
+    for i, (x, y) in enumerate(zip(got, ref)):
+        check(ctx, E, x, y, 2e-2, i)
+
+
+@pytest.mark.parametrize("s,h,d", [(200, 3, 64), (201, 2, 32), (33, 4, 128), (259, 2, 64), (16, 5, 32)])
+def test_ragged_attention_products(ctx, s, h, d):  # noqa: F811
+    """The five products of an attention layer over heads that are split and merged by views."""
+    E, g = Eager(), rng(s * 100 + h * 10 + d)
+    q, k, v, dc = (round_to_bf16(g.standard_normal((2 * s, h * d), dtype=np.float32)) for _ in range(4))
+
+    def prog(B, q, k, v, dc):
+        split = lambda t: B.permute(B.reshape(t, (2, s, h, d)), (0, 2, 1, 3))                  # noqa: E731
+        merge = lambda t: B.reshape(B.permute(t, (0, 2, 1, 3)), (2 * s, h * d))                # noqa: E731
+        qh, kh, vh, dh = (split(t) for t in (q, k, v, dc))
+        p = B.softmax(B.mul(B.matmul(qh, kh, trans_b=True), 0.125))
+        ds = B.softmax_grad(B.matmul(dh, vh, trans_b=True), p)
+        return merge(B.matmul(p, vh)), merge(B.matmul(ds, kh)), merge(B.matmul(ds, qh, trans_a=True)), merge(B.matmul(p, dh, trans_a=True))
+    got = prog(ctx, *(ctx.tensor(t, dtype="bf16") for t in (q, k, v, dc)))
+    ref = prog(E, *(E.tensor(t, dtype="bf16") for t in (q, k, v, dc)))
+    for i, (x, y) in enumerate(zip(got, ref)):
+        check(ctx, E, x, y, 2e-2, i)
