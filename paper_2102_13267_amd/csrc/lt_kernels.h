@@ -199,6 +199,20 @@ struct SplitPostArgs {
   uint64_t stride;           // floats between consecutive splits (= elements of the output)
 };
 
+// ---- attention core ------------------------------------------------------------------------
+// o = softmax(q k^T) v over batch0 x batch1 heads, q and o [sq, d], k and v [sk, d], and its gradients
+// for dy [sq, d].  Rows contiguous (s_col = 1), any row and head strides.
+enum : uint32_t { kAttnForward = 0, kAttnDq, kAttnDkv };
+
+struct AttnArgs {
+  uint32_t pass, dtype, d, sq, sk, batch0, batch1, pad;
+  GemmOperand q, k, v, o, dy;
+  GemmOperand dq, dk, dv;
+  // [3][batch0 * batch1 * sq]: row maxima and reciprocal row sums (written by the forward pass unless
+  // null), row sums of p * (dy v^T) (written by kAttnDq, read by kAttnDkv)
+  float* stats;
+};
+
 // ---- window update -------------------------------------------------------------------------
 // out = base with the window [start, start + len) along one axis replaced by upd.  The tensors are
 // seen as [outer, dim, inner] (base, out) and [outer, len, inner] (upd), dense.  window_only: out
@@ -215,7 +229,8 @@ struct SliceArgs {
 
 // Argument blocks travel by value in the kernel argument segment, which holds 4 KiB.
 static_assert(sizeof(EwArgs) <= 4096 && sizeof(RowArgs) <= 4096 && sizeof(AllArgs) <= 4096 && sizeof(ColArgs) <= 4096 &&
-                  sizeof(GemmArgs) <= 4096 && sizeof(SplitPostArgs) <= 4096 && sizeof(SliceArgs) <= 4096,
+                  sizeof(GemmArgs) <= 4096 && sizeof(SplitPostArgs) <= 4096 && sizeof(SliceArgs) <= 4096 &&
+                  sizeof(AttnArgs) <= 4096,
               "a kernel's argument block must fit the kernel argument segment");
 
 }  // namespace ltk

@@ -1092,8 +1092,10 @@ struct Lowering {
       plan->roots.push_back(rb);
     }
     // launches
-    for (size_t k = 0; k < ordered.size(); ++k) {
-      if (!emit_region((int)k, ordered[k])) return false;
+    for (int k : emission_order()) {
+      bool in_core = false;
+      emit_attention(k, &in_core);
+      if (!in_core && !emit_region(k, ordered[k])) return false;
     }
     for (Storage& s : plan->storages)
       if (s.first_launch < 0) s.first_launch = s.last_launch = 0;
@@ -1494,6 +1496,271 @@ struct Lowering {
     return true;
   }
 
+  // Where element (b0, b1, row, col) of a contraction's result goes: contiguous [batch0, batch1, m, n]
+  // unless the region ends in a layout permute.
+  bool output_layout(const Region* r, const std::vector<int64_t>& lead, uint32_t batch1, int64_t m, int64_t n, int64_t* o_row, int64_t* o_b0,
+                     int64_t* o_b1) {
+    *o_row = n;
+    *o_b1 = m * n;
+    *o_b0 = (int64_t)batch1 * m * n;
+    if (!r->sealed) return true;
+    const int32_t a = r->anchor, pm = r->members[0] == a ? r->members[1] : r->members[0];   // the permute member
+    const std::vector<int64_t> os = shape_of(a);
+    // stride of anchor dimension d in the permuted, dense result
+    const std::vector<int64_t> pshape = shape_of(pm), pcs = contiguous(pshape);
+    std::vector<int64_t> sd(os.size(), 0);
+    for (size_t j = 0; j < pshape.size(); ++j) sd[nd[pm]->attrs[j].v.i] = pcs[j];
+    const size_t rr = os.size();
+    if (sd[rr - 1] != 1) return bad(LT_ERR_UNSUPPORTED, "permuted matmul result must keep its last axis last");
+    std::vector<int64_t> ol;
+    for (size_t d = 0; d + 2 < rr; ++d)
+      if (os[d] != 1) ol.push_back(sd[d]);
+    if (ol.size() != lead.size()) return bad(LT_ERR_UNSUPPORTED, "permuted matmul result: batch axes do not match");
+    *o_row = sd[rr - 2];
+    *o_b0 = ol.size() >= 1 ? ol[0] : 0;
+    *o_b1 = ol.size() == 2 ? ol[1] : 0;
+    return true;
+  }
+
+  // ---- the attention core -----------------------------------------------------------------------------
+  // p = softmax(q k^T), o = p v and, when the trace has it, its backward half ds = softmax_grad(dy v^T, p),
+  // dq = ds k, dk = ds^T q, dv = p^T dy: three regions and five more whose intermediate results nobody else
+  // reads.  They stay regions of their own (the partition does not change) but get one launch (forward)
+  // and two (dq; dk and dv) instead of one each.  Taken when every contraction is bare (or ends in a
+  // layout permute), heads are 32, 64 or 128 columns wide and contiguous, all of one element type, and the
+  // backward half names the same q, k, v and dy as the forward half.  Anything else keeps its parts.
+  struct Attn {
+    int qk = -1, sm = -1, pv = -1;                             // regions, by position in `ordered`
+    int dp = -1, sg = -1, dq = -1, dk = -1, dv = -1;           // -1: forward only
+    ltk::AttnArgs args{};
+    int32_t st[9] = {-1, -1, -1, -1, -1, -1, -1, -1, -1};      // storages of q, k, v, o, dy, dq, dk, dv, stats
+    int64_t off[9] = {0};                                      // byte offsets (inputs)
+    int group[2] = {-1, -1};
+  };
+  std::vector<Attn> attns;
+
+  bool quiet(bool ok) {   // a probe that does not fit is no error
+    if (!ok) {
+      status = LT_OK;
+      err.clear();
+    }
+    return ok;
+  }
+  bool matmul_flag(int32_t a, uint16_t key) const {
+    for (int i = 0; i < nd[a]->n_attr; ++i)
+      if (nd[a]->attrs[i].key == key) return nd[a]->attrs[i].v.i != 0;
+    return false;
+  }
+  // region number of a bare (or, with `sealed_ok`, layout-permuted) contraction, or -1
+  int bare_mm(int32_t node, bool sealed_ok) const {
+    const Region* r = region_of[node];
+    if (cls[node] != C_MM || !r || r->anchor != node) return -1;
+    if (!(r->members.size() == 1 || (sealed_ok && r->sealed && r->members.size() == 2))) return -1;
+    return (int)(std::find(ordered.begin(), ordered.end(), r) - ordered.begin());
+  }
+
+  bool match_attention(int sm_pos, Attn* t) {
+    const Region* rs = ordered[sm_pos];
+    const int32_t sm = rs->anchor;
+    if (rs->members.size() != 1 || is_root[sm]) return false;
+    const uint8_t dt = out_dtype(Val{sm, 0});
+    if (dt != LT_BF16 && dt != LT_F32) return false;
+    // scores: a bare contraction that only the softmax reads
+    const Val sc = rins[sm][0];
+    if (is_root[sc.node] || users[sc.node].size() != 1 || (t->qk = bare_mm(sc.node, false)) < 0 || out_dtype(sc) != dt) return false;
+    t->sm = sm_pos;
+    int32_t sg = -1, dvn = -1, pvn = -1;
+    for (int32_t u : users[sm]) {
+      if (nd[u]->op == LT_OP_SOFTMAX_GRAD && sg < 0 && rins[u][1].node == sm && rins[u][0].node != sm) {
+        sg = u;
+        continue;
+      }
+      if (bare_mm(u, true) < 0 || rins[u][0].node != sm || base(rins[u][1]).node == sm) return false;
+      int32_t& slot = matmul_flag(u, LT_ATTR_TRANS_A) ? dvn : pvn;
+      if (slot >= 0) return false;
+      slot = u;
+    }
+    if (pvn < 0 || (sg >= 0) != (dvn >= 0)) return false;
+    t->pv = bare_mm(pvn, true);
+    MatView q, k, v, p;
+    auto view = [&](int32_t mm, int operand, MatView* m) {
+      return quiet(operand_gemm(rins[mm][operand], matmul_flag(mm, operand == 0 ? LT_ATTR_TRANS_A : LT_ATTR_TRANS_B), m)) && m->dtype == dt;
+    };
+    if (!view(sc.node, 0, &q) || !view(sc.node, 1, &k) || !view(pvn, 1, &v) || !view(pvn, 0, &p)) return false;
+    const int64_t d = q.cols, sq = q.rows, sk = k.cols;
+    if ((d != 32 && d != 64 && d != 128) || v.cols != d || v.rows != sk || p.rows != sq || p.cols != sk) return false;
+    if (q.s_col != 1 || k.s_row != 1 || v.s_col != 1 || q.lead.size() > 2 || k.lead != q.lead || v.lead != q.lead || p.lead != q.lead) return false;
+    if (out_dtype(Val{pvn, 0}) != dt) return false;
+    ltk::AttnArgs& a = t->args;
+    a.dtype = dt;
+    a.d = (uint32_t)d;
+    a.sq = (uint32_t)sq;
+    a.sk = (uint32_t)sk;
+    a.batch0 = q.lead.size() >= 1 ? (uint32_t)q.lead[0] : 1u;
+    a.batch1 = q.lead.size() == 2 ? (uint32_t)q.lead[1] : 1u;
+    auto input = [&](int i, ltk::GemmOperand* g, const MatView& m, int64_t s_row) {
+      g->s_row = s_row;
+      g->s_col = 1;
+      g->s_b0 = m.s_lead.size() >= 1 ? m.s_lead[0] : 0;
+      g->s_b1 = m.s_lead.size() == 2 ? m.s_lead[1] : 0;
+      t->st[i] = m.storage;
+      t->off[i] = m.byte_offset;
+    };
+    auto output = [&](int i, ltk::GemmOperand* g, int32_t mm, int64_t rows) {
+      const Region* r = region_of[mm];
+      g->s_col = 1;
+      if (out_dtype(Val{mm, 0}) != dt || !quiet(output_layout(r, q.lead, a.batch1, rows, d, &g->s_row, &g->s_b0, &g->s_b1))) return false;
+      t->st[i] = storage_of[r->sealed ? (r->members[0] == mm ? r->members[1] : r->members[0]) : mm][0];
+      return t->st[i] >= 0;
+    };
+    input(0, &a.q, q, q.s_row);
+    input(1, &a.k, k, k.s_col);
+    input(2, &a.v, v, v.s_row);
+    if (!output(3, &a.o, pvn, sq)) return false;
+    if (sg >= 0) {
+      const Region* rg = region_of[sg];
+      if (rg->members.size() != 1 || is_root[sg] || out_dtype(Val{sg, 0}) != dt) return false;
+      t->sg = (int)(std::find(ordered.begin(), ordered.end(), rg) - ordered.begin());
+      const Val dpv = rins[sg][0];
+      if (is_root[dpv.node] || users[dpv.node].size() != 1 || (t->dp = bare_mm(dpv.node, false)) < 0 || out_dtype(dpv) != dt) return false;
+      int32_t dqn = -1, dkn = -1;
+      for (int32_t u : users[sg]) {
+        if (bare_mm(u, true) < 0 || rins[u][0].node != sg || base(rins[u][1]).node == sg) return false;
+        int32_t& slot = matmul_flag(u, LT_ATTR_TRANS_A) ? dkn : dqn;
+        if (slot >= 0) return false;
+        slot = u;
+      }
+      if (dqn < 0 || dkn < 0) return false;
+      t->dq = bare_mm(dqn, true);
+      t->dk = bare_mm(dkn, true);
+      t->dv = bare_mm(dvn, true);
+      MatView dy, v2, k2, q2, dy2;
+      if (!view(dpv.node, 0, &dy) || !view(dpv.node, 1, &v2) || !view(dqn, 1, &k2) || !view(dkn, 1, &q2) || !view(dvn, 1, &dy2)) return false;
+      if (dy.rows != sq || dy.cols != d || dy.s_col != 1 || dy.lead != q.lead) return false;
+      auto same = [](const MatView& x, int64_t x_row, const MatView& y, int64_t y_row) {
+        return x.storage == y.storage && x.byte_offset == y.byte_offset && x_row == y_row && x.lead == y.lead && x.s_lead == y.s_lead;
+      };
+      if (v2.s_row != 1 || v2.cols != sk || v2.rows != d || !same(v2, v2.s_col, v, v.s_row)) return false;
+      if (k2.s_col != 1 || k2.rows != sk || k2.cols != d || !same(k2, k2.s_row, k, k.s_col)) return false;
+      if (q2.s_col != 1 || q2.rows != sq || q2.cols != d || !same(q2, q2.s_row, q, q.s_row)) return false;
+      if (dy2.s_col != 1 || dy2.rows != sq || dy2.cols != d || !same(dy2, dy2.s_row, dy, dy.s_row)) return false;
+      input(4, &a.dy, dy, dy.s_row);
+      if (!output(5, &a.dq, dqn, sq) || !output(6, &a.dk, dkn, sk) || !output(7, &a.dv, dvn, sk)) return false;
+    }
+    // nothing a launch writes may be what another of them (or another workgroup) reads
+    auto buffer_of = [&](int i) -> int64_t {
+      const int32_t st = t->st[i];
+      return plan->storages[st].param >= 0 ? -(int64_t)plan->storages[st].param - 1 : (int64_t)st;
+    };
+    for (int w : {3, 5, 6, 7})
+      for (int r = 0; r < 8; ++r)
+        if (w != r && t->st[w] >= 0 && t->st[r] >= 0 && buffer_of(w) == buffer_of(r)) return false;
+    return true;
+  }
+
+  // The order in which regions are lowered: that of `ordered`, with the regions of an attention core's
+  // forward half, and of its backward half, taken together (at the place of the group's last one
+  // whose inputs are there).  A core whose grouping would make the order cyclic keeps its parts.
+  std::vector<int> emission_order() {
+    const int n = (int)ordered.size();
+    std::vector<int> order;
+    for (int k = 0; k < n; ++k) order.push_back(k);
+    if (!ctx->fusion) return order;
+    for (int k = 0; k < n; ++k) {
+      Attn t;
+      if (ordered[k]->kind == C_ROW && nd[ordered[k]->anchor]->op == LT_OP_SOFTMAX && match_attention(k, &t)) attns.push_back(t);
+    }
+    while (!attns.empty()) {
+      std::vector<int> group(n), first;   // group of a region; a group's first region
+      for (int k = 0; k < n; ++k) group[k] = k;
+      for (Attn& t : attns) {
+        for (int k : {t.qk, t.sm}) group[k] = t.pv;
+        if (t.dq >= 0)
+          for (int k : {t.dp, t.sg, t.dk, t.dv}) group[k] = t.dq;
+      }
+      std::vector<std::vector<int>> succ(n);
+      std::vector<int> indeg(n, 0);
+      for (int k = 0; k < n; ++k)
+        for (Region* s : successors(ordered[k])) {
+          const int j = (int)(std::find(ordered.begin(), ordered.end(), s) - ordered.begin());
+          if (group[j] == group[k]) continue;
+          succ[group[k]].push_back(group[j]);
+          indeg[group[j]]++;
+        }
+      order.clear();
+      std::vector<char> done(n, 0);
+      for (;;) {
+        int pick = -1;
+        for (int k = 0; k < n && pick < 0; ++k)
+          if (!done[group[k]] && indeg[group[k]] == 0) pick = group[k];
+        if (pick < 0) break;
+        done[pick] = 1;
+        for (int k = 0; k < n; ++k)
+          if (group[k] == pick) order.push_back(k);
+        for (int j : succ[pick]) indeg[j]--;
+      }
+      if ((int)order.size() == n) return order;
+      attns.pop_back();
+      order.clear();
+      for (int k = 0; k < n; ++k) order.push_back(k);
+    }
+    return order;
+  }
+
+  // Emits the launches of the attention core that region k belongs to, when k is the one they are
+  // emitted for; *mine says whether k belongs to one.
+  void emit_attention(int k, bool* mine) {
+    *mine = false;
+    for (Attn& t : attns) {
+      const bool fwd = k == t.qk || k == t.sm || k == t.pv;
+      const bool bwd = t.dq >= 0 && (k == t.dp || k == t.sg || k == t.dq || k == t.dk || k == t.dv);
+      if (!fwd && !bwd) continue;
+      *mine = true;
+      const uint64_t rows = (uint64_t)t.args.batch0 * t.args.batch1 * t.args.sq, keys = (uint64_t)t.args.batch0 * t.args.batch1 * t.args.sk;
+      const uint64_t es = dtype_size(t.args.dtype), qb = rows * t.args.d * es, kb = keys * t.args.d * es, mm = 2ull * rows * t.args.sk * t.args.d;
+      static const size_t at[9] = {offsetof(ltk::AttnArgs, q),  offsetof(ltk::AttnArgs, k),  offsetof(ltk::AttnArgs, v),
+                                   offsetof(ltk::AttnArgs, o),  offsetof(ltk::AttnArgs, dy), offsetof(ltk::AttnArgs, dq),
+                                   offsetof(ltk::AttnArgs, dk), offsetof(ltk::AttnArgs, dv), offsetof(ltk::AttnArgs, stats)};
+      auto push = [&](uint32_t pass, std::initializer_list<int> reads, std::initializer_list<int> writes, uint64_t bytes, uint64_t flops) {
+        const int launch = (int)plan->launches.size();
+        ltk::AttnArgs a = t.args;
+        a.pass = pass;
+        Launch l = make_launch(L_ATTN, k, a);
+        l.bytes = bytes;
+        l.flops = flops;
+        plan->launches.push_back(std::move(l));
+        for (int i : reads) {
+          plan->ptr_patches.push_back(PtrPatch{(uint32_t)launch, (uint32_t)(at[i] + (i < 8 ? offsetof(ltk::GemmOperand, ptr) : 0)), t.st[i], t.off[i]});
+          touch(t.st[i], launch);
+        }
+        for (int i : writes) {
+          plan->ptr_patches.push_back(PtrPatch{(uint32_t)launch, (uint32_t)(at[i] + (i < 8 ? offsetof(ltk::GemmOperand, ptr) : 0)), t.st[i], t.off[i], 1});
+          touch(t.st[i], launch);
+        }
+      };
+      if (fwd && t.group[0] < 0) {
+        t.group[0] = k;
+        for (int e : {t.qk, t.sm}) plan->storages[storage_of[ordered[e]->anchor][0]].bytes = 0;   // (never in memory)
+        if (t.dq >= 0) {
+          Storage ns;
+          ns.first_launch = -1;
+          ns.bytes = (size_t)(3 * rows * sizeof(float));
+          plan->storages.push_back(ns);
+          t.st[8] = (int32_t)plan->storages.size() - 1;
+          push(ltk::kAttnForward, {0, 1, 2}, {3, 8}, 2 * qb + 2 * kb, 2 * mm);
+        } else {
+          push(ltk::kAttnForward, {0, 1, 2}, {3}, 2 * qb + 2 * kb, 2 * mm);
+        }
+      } else if (bwd && t.group[1] < 0) {
+        t.group[1] = k;
+        for (int e : {t.dp, t.sg}) plan->storages[storage_of[ordered[e]->anchor][0]].bytes = 0;
+        push(ltk::kAttnDq, {0, 1, 2, 4}, {5, 8}, 3 * qb + 2 * kb, 2 * mm);
+        push(ltk::kAttnDkv, {0, 1, 2, 4, 8}, {6, 7}, 2 * qb + 4 * kb, 2 * mm);
+      }
+      return;
+    }
+  }
+
   bool emit_gemm(int k, Region* r, const std::vector<int32_t>& post_m_in, const std::vector<Val>& out_in) {
     const int32_t a = r->anchor;
     const Node* an = nd[a];
@@ -1545,29 +1812,13 @@ struct Lowering {
     fill(&args.b, B);
     args.in_dtype = A.dtype;
     const int64_t batch = (int64_t)args.batch0 * args.batch1;
-    // output layout: contiguous [batch0, batch1, m, n] unless the region ends in a layout permute
-    args.o_row = n;
-    args.o_b1 = m * n;
-    args.o_b0 = (int64_t)args.batch1 * m * n;
     std::vector<int32_t> post_m = post_m_in;
     std::vector<Val> out = out_in;
+    if (!output_layout(r, lead, args.batch1, m, n, &args.o_row, &args.o_b0, &args.o_b1)) return false;
     if (r->sealed) {
-      const int32_t pm = post_m.back();   // the permute member
-      if (post_m.size() != 1 || nd[pm]->op != LT_OP_PERMUTE) return bad(LT_ERR_UNSUPPORTED, "internal: sealed region shape");
-      // stride of anchor dimension d in the permuted, dense result
-      const std::vector<int64_t> pshape = shape_of(pm), pcs = contiguous(pshape);
-      std::vector<int64_t> sd(os.size(), 0);
-      for (size_t j = 0; j < pshape.size(); ++j) sd[nd[pm]->attrs[j].v.i] = pcs[j];
-      const size_t rr = os.size();
-      if (sd[rr - 1] != 1) return bad(LT_ERR_UNSUPPORTED, "permuted matmul result must keep its last axis last");
-      std::vector<int64_t> ol;
-      for (size_t d = 0; d + 2 < rr; ++d)
-        if (os[d] != 1) ol.push_back(sd[d]);
-      if (ol.size() != lead.size()) return bad(LT_ERR_UNSUPPORTED, "permuted matmul result: batch axes do not match");
-      args.o_row = sd[rr - 2];
-      args.o_b0 = ol.size() >= 1 ? ol[0] : 0;
-      args.o_b1 = ol.size() == 2 ? ol[1] : 0;
       // the region's output is the permute's value; the program only stores the accumulator
+      const int32_t pm = post_m.back();
+      if (post_m.size() != 1 || nd[pm]->op != LT_OP_PERMUTE) return bad(LT_ERR_UNSUPPORTED, "internal: sealed region shape");
       storage_of[a][0] = storage_of[pm][0];
       post_m.clear();
       out.assign(1, Val{a, 0});
