@@ -7,17 +7,22 @@
 //
 // Structure: workgroup tile 128 x 128 (or 64 x 64 for small problems so that more compute units
 // get a tile), four wavefronts in a 2 x 2 arrangement, each owning a quarter as MFMA 32x32x2
-// blocks.  K is walked in slices of 32 with register prefetch: the global loads of slice k+1 are
-// issued before the MFMAs of slice k and written to the other LDS buffer afterwards.  Global
-// loads are 16 bytes per lane along whichever dimension of the operand is contiguous; an operand
-// whose contiguous dimension is k is transposed on its way into LDS.  A long k over few tiles is
-// split over workgroups (partial products to a workspace, summed by a second launch).
+// blocks.  K is walked in slices of 32 that travel from global memory straight into LDS (lt_dma.h), four
+// stages, so that the loop holds nothing but LDS reads, MFMAs and one barrier per slice: the matrix
+// cores bound it (fp32 MFMA 157 TFLOP/s; the vendor library reaches 141 to 154).  Measured against
+// staging the same tiles through registers (transposing stores, the same four slices ahead):
+// [1024, 2048] x [2048, 2048] with bias and GELU 90.5 -> 70 us (122 TFLOP/s), a head's three products of
+// 2048 x 1024 x 1000, ragged, 67 / 62 / 75 -> 44 / 42 / 45.  A tile over the operand's edge takes the same
+// path; what is left of k behind the last whole slice is one checked slice; rows that are not
+// 16-byte aligned go through registers.  A long k over few tiles is split over workgroups (partial
+// products to a workspace, summed by a second launch).
 // Small products take another kernel further down (lt_gemm_small_kernel: no LDS staging, k split
 // inside the workgroup and, for a long k, over a few workgroups that meet inside the launch).
 #include <hip/hip_runtime.h>
 
 #include <cstdio>
 
+#include "lt_dma.h"
 #include "lt_gemm_epilogue.h"
 #include "lt_launch.h"
 #include "lt_reduce.h"
@@ -30,23 +35,6 @@ namespace ltk {
 // as uint4.
 template <typename T> struct Elem;
 template <> struct Elem<float> { static constexpr int G = 4; static constexpr int BK = 32; };
-
-// Guarded fetch of G elements at (outer, inner .. inner+G-1); element (o, i) lives at
-// base + o*s_outer + i (unit stride inside the group).  Out-of-range elements read as zero.
-template <typename T>
-__device__ __forceinline__ uint4 fetch_group(const T* base, int64_t s_outer, uint32_t outer, uint32_t inner, uint32_t n_outer,
-                                             uint32_t n_inner, bool aligned) {
-  constexpr int G = Elem<T>::G;
-  uint4 v = make_uint4(0, 0, 0, 0);
-  if (outer >= n_outer || inner >= n_inner) return v;
-  const T* src = base + (int64_t)outer * s_outer + inner;
-  if (aligned && inner + G <= n_inner) return *(const uint4*)src;
-  T t[G];
-#pragma unroll
-  for (int j = 0; j < G; ++j) t[j] = (inner + j < n_inner) ? src[j] : (T)0;
-  v = make_uint4(((const uint32_t*)t)[0], ((const uint32_t*)t)[1], ((const uint32_t*)t)[2], ((const uint32_t*)t)[3]);
-  return v;
-}
 
 // LDS layout: tile[k][x] (x = m or n contiguous); an MFMA 32x32x2 lane reads one float.  Row stride:
 // BX + 4 for an operand that arrives x-contiguous (16-byte row writes stay aligned).  An operand
@@ -71,24 +59,22 @@ template <int N> struct GroupRegs {
   U32x4 g[N];
 };
 
-// Fetch this lane's groups of the slice starting at k0.  KC: the contraction dimension is the
-// operand's contiguous one.  x0: first row (A) / column (B) of the tile.
+// Fetch this lane's groups of the slice starting at k0, element by element at addresses clamped into the
+// operand (branch-free: all of a lane's loads are in flight together).  k past the end reads as zero;
+// rows or columns past the edge are copies of the last one and are never stored.  KC: the contraction
+// dimension is the operand's contiguous one.  x0: first row (A) / column (B) of the tile.
 template <typename T, int BX, bool KC>
 __device__ __forceinline__ void fetch_tile(GroupRegs<Groups<T, BX>::N>& gr, const T* base, int64_t s_x, int64_t s_k, uint32_t x0,
-                                           uint32_t k0, uint32_t nx, uint32_t nk, bool aligned) {
-  constexpr int G = Elem<T>::G, BK = Elem<T>::BK, NG = Groups<T, BX>::N;
-  const uint32_t t = threadIdx.x;
+                                           uint32_t k0, uint32_t nx, uint32_t nk) {
+  constexpr uint32_t G = Elem<T>::G, per_row = (KC ? Elem<T>::BK : BX) / G;
 #pragma unroll
-  for (int it = 0; it < NG; ++it) {
-    const uint32_t e = it * kGemmThreads + t;
-    if (KC) {
-      const uint32_t x = e / (BK / G), kq = e % (BK / G);
-      const uint4 v = fetch_group<T>(base, s_x, x0 + x, k0 + kq * G, nx, nk, aligned);
-      gr.g[it] = U32x4{v.x, v.y, v.z, v.w};
-    } else {
-      const uint32_t k = e / (BX / G), xq = e % (BX / G);
-      const uint4 v = fetch_group<T>(base, s_k, k0 + k, x0 + xq * G, nk, nx, aligned);
-      gr.g[it] = U32x4{v.x, v.y, v.z, v.w};
+  for (int it = 0; it < Groups<T, BX>::N; ++it) {
+    const uint32_t e = it * kGemmThreads + threadIdx.x, o = e / per_row, i = (e % per_row) * G;
+#pragma unroll
+    for (uint32_t j = 0; j < G; ++j) {
+      const uint32_t x = x0 + (KC ? o : i + j), k = k0 + (KC ? i + j : o);
+      const T v = base[(int64_t)min(x, nx - 1u) * s_x + (int64_t)min(k, nk - 1u) * s_k];
+      gr.g[it][j] = k < nk ? __float_as_uint(v) : 0u;
     }
   }
 }
@@ -113,24 +99,66 @@ __device__ __forceinline__ void stash_tile(const GroupRegs<Groups<float, BX>::N>
   }
 }
 
-// Interior tiles of aligned operands: the slice at k0, 16 bytes per lane and load, no checks and
-// no branches, so that all of a slice's loads are in flight together.
-// x_last: the operand's last row (KC only): rows of a tile that hangs over the edge are read as
-// copies of it -- in bounds, and their products are never stored -- so that a tile of a few rows
-// (a small batch) still takes this path.
+// ---- whole slices ---------------------------------------------------------------------------------
+// Element offset, from the panel's start, of the 16-byte chunk at (outer, inner) of a slice: the same for
+// every slice.  Rows (KC) or chunks of four columns past the operand's edge (`left` rows or columns from
+// the panel's start) become copies of the last one: in bounds, and their products are never stored.
+template <bool KC>
+__device__ __forceinline__ int64_t chunk_offset(uint32_t outer, uint32_t inner, int64_t s_x, int64_t s_k, uint32_t left) {
+  return KC ? (int64_t)min(outer, left - 1u) * s_x + inner : (int64_t)outer * s_k + min(inner, (left - 1u) & ~3u);
+}
+
+// Rows that start at any element: through registers into the padded tiles above, 16-byte loads at
+// 4-byte boundaries.
+template <int BX> struct Offsets {
+  int64_t o[Groups<float, BX>::N];
+};
 template <int BX, bool KC>
-__device__ __forceinline__ void fetch_tile_whole(GroupRegs<Groups<float, BX>::N>& gr, const float* base, int64_t s_x, int64_t s_k,
-                                                 uint32_t x0, uint32_t k0, uint32_t x_last) {
-  constexpr int G = 4, BK = Elem<float>::BK, NG = Groups<float, BX>::N;
-  const uint32_t t = threadIdx.x;
+__device__ __forceinline__ Offsets<BX> unaligned_offsets(int64_t s_x, int64_t s_k, uint32_t left) {
+  constexpr uint32_t per_row = (KC ? Elem<float>::BK : BX) / 4;
+  Offsets<BX> off;
 #pragma unroll
-  for (int it = 0; it < NG; ++it) {
-    const uint32_t e = it * kGemmThreads + t;
-    const float* src = KC ? base + (int64_t)min(x0 + e / (BK / G), x_last) * s_x + (k0 + (e % (BK / G)) * G)
-                          : base + (int64_t)(k0 + e / (BX / G)) * s_k + (x0 + (e % (BX / G)) * G);
-    gr.g[it] = *(const U32x4*)src;
+  for (int it = 0; it < Groups<float, BX>::N; ++it) {
+    const uint32_t e = it * kGemmThreads + threadIdx.x;
+    off.o[it] = chunk_offset<KC>(e / per_row, (e % per_row) * 4u, s_x, s_k, left);
+  }
+  return off;
+}
+template <int BX>
+__device__ __forceinline__ void fetch_unaligned(GroupRegs<Groups<float, BX>::N>& gr, const float* panel, const Offsets<BX>& off) {
+  typedef uint32_t V __attribute__((ext_vector_type(4), aligned(4)));
+#pragma unroll
+  for (int it = 0; it < Groups<float, BX>::N; ++it) {
+    const V v = *(const V*)(panel + off.o[it]);
+    gr.g[it] = U32x4{v.x, v.y, v.z, v.w};
   }
 }
+
+// 16-byte aligned rows: straight into LDS (lt_dma.h), dense tiles whose bank conflicts a swizzle avoids.
+//   [x][k] tile (k contiguous): rows of 128 bytes, the chunk c of row x at position c ^ ((x >> 1) & 7) --
+//     sixteen rows of a ds_read_b128 then cover all 64 banks;
+//   [k][x] tile: rows of BX floats; an MFMA lane reads single floats, 32 consecutive ones per half wave,
+//     and the half waves read rows four apart: those are exchanged by 32 columns.
+template <int BX, bool KC> struct Dense {
+  static constexpr uint32_t kBytes = BX * 128, kInstr = BX / 32, kPerRow = KC ? 8 : BX / 4;
+  __device__ static __forceinline__ uint32_t swz(uint32_t row) { return KC ? (row >> 1) & 7u : ((row >> 2) & 1u) << 3; }
+  // this lane's byte offset for wave instruction `it` of a slice
+  __device__ static __forceinline__ uint32_t lane_offset(uint32_t it, int64_t s_x, int64_t s_k, uint32_t left) {
+    const uint32_t e = it * (uint32_t)kGemmThreads + threadIdx.x, row = e / kPerRow, c = (e % kPerRow) ^ swz(row);
+    return (uint32_t)(4 * chunk_offset<KC>(row, c * 4u, s_x, s_k, left));
+  }
+  __device__ static __forceinline__ void copy(const float* src, const uint32_t (&off)[kInstr], uint32_t tile, uint32_t wave) {
+#pragma unroll
+    for (uint32_t it = 0; it < kInstr; ++it) copy_1k(src, off[it], tile + (it * (uint32_t)kGemmThreads + wave * 64u) * 16u);
+  }
+  // This lane's values of row / column x for the k of group g (eight k: four for each half wave).  Which
+  // k goes into which of a group's four MFMAs is free as long as both operands agree.
+  __device__ static __forceinline__ RawVec group(const char* tile, uint32_t x, uint32_t g, uint32_t h) {
+    if (KC) return *(const RawVec*)(tile + x * 128u + (((2u * g + h) ^ swz(x)) << 4));
+    const char* p = tile + (8u * g + 4u * h) * (BX * 4u) + (x ^ (h << 5)) * 4u;
+    return RawVec{*(const float*)p, *(const float*)(p + BX * 4), *(const float*)(p + BX * 8), *(const float*)(p + BX * 12)};
+  }
+};
 
 // MFMAs of one k-slice, in groups of four k-steps: the fragments of the next group are read from
 // LDS BEFORE the MFMAs of the current one are issued (two register sets; scheduling barriers keep
@@ -175,11 +203,14 @@ __device__ __forceinline__ void mma_slice(v16f (&acc)[NCH][MB][NB], const float*
 template <typename T, int BM, int BN> struct Smem {
   static constexpr size_t kOperands = 2 * (Tile<T, BM>::ELEMS + Tile<T, BN>::ELEMS) * sizeof(T);   // double buffered
   static constexpr size_t kC = (size_t)BM * (BN + kCPad) * sizeof(float);
-  static constexpr size_t kBytes = kOperands > kC ? kOperands : kC;
+  static constexpr size_t kDense = 4 * (size_t)(BM + BN) * 128;   // four dense stages
+  static constexpr size_t kMax2 = kOperands > kC ? kOperands : kC;
+  static constexpr size_t kBytes = kMax2 > kDense ? kMax2 : kDense;
 };
 
-// T: float.  AKC / BKC: the operand's contiguous dimension is k.
-template <typename T, int BM, int BN, bool AKC, bool BKC>
+// T: float.  AKC / BKC: the operand's contiguous dimension is k.  AL: both operands' rows are 16-byte
+// aligned (the launcher looks).
+template <typename T, int BM, int BN, bool AKC, bool BKC, bool AL>
 __global__ __launch_bounds__(kGemmThreads, BM == 64 ? 2 : 1) void lt_gemm_kernel(const GemmArgs a) {
   constexpr int MB = BM / 64, NB = BN / 64, BK = Elem<T>::BK;
   __shared__ __attribute__((aligned(16))) char smem[Smem<T, BM, BN>::kBytes];
@@ -197,11 +228,7 @@ __global__ __launch_bounds__(kGemmThreads, BM == 64 ? 2 : 1) void lt_gemm_kernel
   const uint32_t b0 = batch / a.batch1, b1 = batch % a.batch1;
   const T* A = (const T*)a.a.ptr + (int64_t)b0 * a.a.s_b0 + (int64_t)b1 * a.a.s_b1;
   const T* B = (const T*)a.b.ptr + (int64_t)b0 * a.b.s_b0 + (int64_t)b1 * a.b.s_b1;
-  // 16-byte loads need 16-byte aligned groups: base, and the stride between groups' rows
-  constexpr int G = Elem<T>::G;
   const int64_t a_outer = AKC ? a.a.s_row : a.a.s_col, b_outer = BKC ? a.b.s_col : a.b.s_row;
-  const bool a_al = (((uintptr_t)A) & 15u) == 0 && (a_outer % G) == 0;
-  const bool b_al = (((uintptr_t)B) & 15u) == 0 && (b_outer % G) == 0;
   constexpr int NCH = MB * NB == 1 ? 2 : 1;   // independent accumulator chains per block
   v16f accs[NCH][MB][NB];
 #pragma unroll
@@ -215,83 +242,124 @@ __global__ __launch_bounds__(kGemmThreads, BM == 64 ? 2 : 1) void lt_gemm_kernel
 
   GroupRegs<Groups<T, BM>::N> ga;
   GroupRegs<Groups<T, BN>::N> gb;
-  const bool whole = a_al && b_al && (AKC || tile_m + BM <= a.m) && (BKC || tile_n + BN <= a.n) && ((k_end - k_begin) % BK) == 0u;
-  if (k_begin < k_end && whole) {
-    // Interior tile: unchecked 16-byte loads, D slices ahead in registers (a slice's MFMAs are over
-    // in 1000 to 4000 cycles, a load under traffic takes longer: counters showed a wave of the
-    // one-slice-ahead loop waiting two thirds of its life), two LDS buffers.  Slice i: start the
-    // loads of slice i + D into the register set that slice i left when it was written to LDS;
-    // multiply slice i from its LDS buffer; write slice i + 1 to the other buffer; barrier.  The
-    // body is unrolled D times so that set and buffer numbers are compile-time; loads past the
-    // end are clamped to the last slice (in bounds, unused).
-    // (Four named register sets, not an array: an array of sets indexed by the unrolled loop
-    // counter is left in scratch memory by the compiler, and every load then waits to be spilled.)
-    const uint32_t n = (k_end - k_begin) / BK;
-    typedef GroupRegs<Groups<T, BM>::N> RA;
-    typedef GroupRegs<Groups<T, BN>::N> RB;
-    RA ra0, ra1, ra2, ra3;
-    RB rb0, rb1, rb2, rb3;
-    constexpr uint32_t D = BM == 64 ? 4u : 2u;   // slices in flight (a 128 x 128 tile's sets are twice as large)
-#define LT_FETCH(RA_, RB_, I)                                                                 \
-  {                                                                                           \
-    const uint32_t kf = k_begin + min((uint32_t)(I), n - 1u) * BK;                            \
-    fetch_tile_whole<BM, AKC>(RA_, A, a.a.s_row, a.a.s_col, tile_m, kf, a.m - 1u);            \
-    fetch_tile_whole<BN, BKC>(RB_, B, a.b.s_col, a.b.s_row, tile_n, kf, a.n - 1u);            \
+  // Whole slices of k are fetched in 16-byte chunks with no checks; what is left of k goes through the
+  // checked path below.  The last chunk of a tile over the edge may reach up to three elements past its
+  // row, into the next one (in bounds if rows are at least that far apart): then the slice with the
+  // operand's last row has to be a checked one.
+  const uint32_t left_m = a.m - tile_m, left_n = a.n - tile_n;
+  const bool a_over = !AKC && left_m < (uint32_t)BM && (a.m & 3u) != 0u, b_over = !BKC && left_n < (uint32_t)BN && (a.n & 3u) != 0u;
+  uint32_t n = (k_end - k_begin) / BK;   // whole slices
+  if ((a_over && a_outer < 4) || (b_over && b_outer < 4)) n = 0u;
+  else if ((a_over || b_over) && n > 0u && k_begin + n * BK == a.k) --n;
+  const T* const pa = A + (int64_t)tile_m * a.a.s_row + (int64_t)k_begin * a.a.s_col;
+  const T* const pb = B + (int64_t)tile_n * a.b.s_col + (int64_t)k_begin * a.b.s_row;
+  const int64_t step_a = BK * a.a.s_col, step_b = BK * a.b.s_row;   // elements per slice of k
+  if (AL && n > 0u) {
+    // Four LDS stages: the MFMAs of slice j run from registers, the fragments of slice j + 1 are read from
+    // its stage, slices j + 2 .. j + 4 are on their way from global memory into theirs.  Behind the
+    // barrier of slice j slice j + 1 has landed for every wave, and every wave's reads of slice j's stage,
+    // which is copied into next, have returned.  (Copies past the end: the last slice again, unused.)
+    typedef Dense<BM, AKC> DA;
+    typedef Dense<BN, BKC> DB;
+    constexpr uint32_t kStage = DA::kBytes + DB::kBytes, kPer = DA::kInstr + DB::kInstr;
+    const uint32_t wave_u = __builtin_amdgcn_readfirstlane(wave), h = lane >> 5;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
+    uint32_t a_off[DA::kInstr], b_off[DB::kInstr];
+#pragma unroll
+    for (uint32_t it = 0; it < DA::kInstr; ++it) a_off[it] = DA::lane_offset(it, a.a.s_row, a.a.s_col, left_m);
+#pragma unroll
+    for (uint32_t it = 0; it < DB::kInstr; ++it) b_off[it] = DB::lane_offset(it, a.b.s_col, a.b.s_row, left_n);
+    struct Frags {
+      RawVec a[BK / 8][MB], b[BK / 8][NB];
+    };
+    auto frags = [&](uint32_t stage) {
+      const char* At = smem + stage * kStage;
+      const char* Bt = At + DA::kBytes;
+      Frags f;
+#pragma unroll
+      for (uint32_t g = 0; g < BK / 8; ++g) {
+#pragma unroll
+        for (int i = 0; i < MB; ++i) f.a[g][i] = DA::group(At, wave_m * (BM / 2) + i * 32u + (lane & 31u), g, h);
+#pragma unroll
+        for (int j = 0; j < NB; ++j) f.b[g][j] = DB::group(Bt, wave_n * (BN / 2) + j * 32u + (lane & 31u), g, h);
+      }
+      return f;
+    };
+    auto mma = [&](const Frags& f) {
+#pragma unroll
+      for (int g = 0; g < BK / 8; ++g)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int i = 0; i < MB; ++i)
+#pragma unroll
+            for (int j = 0; j < NB; ++j)
+              accs[e % NCH][i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(f.a[g][i][e], f.b[g][j][e], accs[e % NCH][i][j], 0, 0, 0);
+    };
+#define LT_COPY(I, STAGE)                                                                  \
+  {                                                                                       \
+    const int64_t sl = min((uint32_t)(I), n - 1u);                                        \
+    DA::copy(pa + sl * step_a, a_off, lds0 + (STAGE) * kStage, wave_u);                   \
+    DB::copy(pb + sl * step_b, b_off, lds0 + (STAGE) * kStage + DA::kBytes, wave_u);      \
   }
-#define LT_STEP(J, RA_CUR, RB_CUR, RA_NEXT, RB_NEXT)                                          \
-  {                                                                                           \
-    const uint32_t i = i0 + (J);                                                              \
-    LT_FETCH(RA_CUR, RB_CUR, i + D);                                                          \
-    if (i < n) mma_slice<BM, BN, MB, NB, AKC, BKC, NCH>(accs, As((J) & 1), Bs((J) & 1), wave_m, wave_n, lane); \
-    stash_tile<BM, AKC>(RA_NEXT, As(((J) + 1) & 1));                                          \
-    stash_tile<BN, BKC>(RB_NEXT, Bs(((J) + 1) & 1));                                          \
-    __syncthreads();                                                                          \
+#define LT_SLICE(J, CUR, NEXT, GUARD)             \
+  {                                               \
+    landed_and_read<2 * kPer>();                  \
+    __syncthreads();                              \
+    LT_COPY(i + (J) + 4u, (J) & 3);               \
+    NEXT = frags(((J) + 1) & 3);                  \
+    if (!(GUARD) || i + (J) < n) mma(CUR);        \
   }
-    LT_FETCH(ra0, rb0, 0);
-    LT_FETCH(ra1, rb1, 1);
-    if (D == 4u) {
-      LT_FETCH(ra2, rb2, 2);
-      LT_FETCH(ra3, rb3, 3);
-    }
-    stash_tile<BM, AKC>(ra0, As(0));
-    stash_tile<BN, BKC>(rb0, Bs(0));
+    LT_COPY(0, 0);
+    LT_COPY(1, 1);
+    LT_COPY(2, 2);
+    LT_COPY(3, 3);
+    landed<3 * kPer>();
     __syncthreads();
-    if (D == 4u) {
-      for (uint32_t i0 = 0; i0 < n; i0 += 4u) {
-        LT_STEP(0u, ra0, rb0, ra1, rb1);
-        LT_STEP(1u, ra1, rb1, ra2, rb2);
-        LT_STEP(2u, ra2, rb2, ra3, rb3);
-        LT_STEP(3u, ra3, rb3, ra0, rb0);
-      }
-    } else {
-      for (uint32_t i0 = 0; i0 < n; i0 += 2u) {
-        LT_STEP(0u, ra0, rb0, ra1, rb1);
-        LT_STEP(1u, ra1, rb1, ra0, rb0);
-      }
+    Frags f0 = frags(0), f1;
+    uint32_t i = 0;
+    for (; i + 4u <= n; i += 4u) {
+      LT_SLICE(0, f0, f1, false);
+      LT_SLICE(1, f1, f0, false);
+      LT_SLICE(2, f0, f1, false);
+      LT_SLICE(3, f1, f0, false);
     }
-#undef LT_STEP
-#undef LT_FETCH
-  } else if (k_begin < k_end) {
-    fetch_tile<T, BM, AKC>(ga, A, a.a.s_row, a.a.s_col, tile_m, k_begin, a.m, k_end, a_al);
-    fetch_tile<T, BN, BKC>(gb, B, a.b.s_col, a.b.s_row, tile_n, k_begin, a.n, k_end, b_al);
+    if (i < n) {
+      LT_SLICE(0, f0, f1, true);
+      LT_SLICE(1, f1, f0, true);
+      LT_SLICE(2, f0, f1, true);
+    }
+    landed<0>();   // nothing may still be on its way into LDS when it is used again
+#undef LT_SLICE
+#undef LT_COPY
+  }
+  if (!AL && n > 0u) {
+    // the loads of slice j + 1 under the MFMAs of slice j, two padded buffers, one barrier per slice
+    const Offsets<BM> a_off = unaligned_offsets<BM, AKC>(a.a.s_row, a.a.s_col, left_m);
+    const Offsets<BN> b_off = unaligned_offsets<BN, BKC>(a.b.s_col, a.b.s_row, left_n);
+    fetch_unaligned<BM>(ga, pa, a_off);
+    fetch_unaligned<BN>(gb, pb, b_off);
+#pragma unroll 1
+    for (uint32_t j = 0; j < n; ++j) {
+      stash_tile<BM, AKC>(ga, As(j & 1u));
+      stash_tile<BN, BKC>(gb, Bs(j & 1u));
+      const int64_t nx = min(j + 1u, n - 1u);
+      fetch_unaligned<BM>(ga, pa + nx * step_a, a_off);
+      fetch_unaligned<BN>(gb, pb + nx * step_b, b_off);
+      __syncthreads();
+      mma_slice<BM, BN, MB, NB, AKC, BKC, NCH>(accs, As(j & 1u), Bs(j & 1u), wave_m, wave_n, lane);
+    }
+  }
+  // the rest of k: every access checked, one slice at a time
+#pragma unroll 1
+  for (uint32_t k0 = k_begin + n * BK; k0 < k_end; k0 += BK) {
+    fetch_tile<T, BM, AKC>(ga, A, a.a.s_row, a.a.s_col, tile_m, k0, a.m, k_end);
+    fetch_tile<T, BN, BKC>(gb, B, a.b.s_col, a.b.s_row, tile_n, k0, a.n, k_end);
+    __syncthreads();
     stash_tile<BM, AKC>(ga, As(0));
     stash_tile<BN, BKC>(gb, Bs(0));
     __syncthreads();
-    uint32_t cur = 0;
-    for (uint32_t k0 = k_begin; k0 < k_end; k0 += BK) {
-      const bool more = k0 + BK < k_end;
-      if (more) {
-        fetch_tile<T, BM, AKC>(ga, A, a.a.s_row, a.a.s_col, tile_m, k0 + BK, a.m, k_end, a_al);
-        fetch_tile<T, BN, BKC>(gb, B, a.b.s_col, a.b.s_row, tile_n, k0 + BK, a.n, k_end, b_al);
-      }
-      mma_slice<BM, BN, MB, NB, AKC, BKC, NCH>(accs, As(cur), Bs(cur), wave_m, wave_n, lane);
-      if (more) {
-        stash_tile<BM, AKC>(ga, As(cur ^ 1));
-        stash_tile<BN, BKC>(gb, Bs(cur ^ 1));
-      }
-      __syncthreads();
-      cur ^= 1;
-    }
+    mma_slice<BM, BN, MB, NB, AKC, BKC, NCH>(accs, As(0), Bs(0), wave_m, wave_n, lane);
   }
   v16f (&acc)[MB][NB] = accs[0];
   if (NCH > 1) {
@@ -587,15 +655,15 @@ static hipError_t launch_small(const GemmArgs& args, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <typename T, int BM, int BN>
+template <typename T, int BM, int BN, bool AL>
 static void launch_variant(const GemmArgs& a, const dim3 grid, hipStream_t s) {
   const bool akc = a.a.s_col == 1, bkc = a.b.s_row == 1;
-  if (akc && bkc) LT_LAUNCH((lt_gemm_kernel<T, BM, BN, true, true>), grid, dim3(kGemmThreads), s, a);
-  else if (akc) LT_LAUNCH((lt_gemm_kernel<T, BM, BN, true, false>), grid, dim3(kGemmThreads), s, a);
-  else if (bkc) LT_LAUNCH((lt_gemm_kernel<T, BM, BN, false, true>), grid, dim3(kGemmThreads), s, a);
-  else LT_LAUNCH((lt_gemm_kernel<T, BM, BN, false, false>), grid, dim3(kGemmThreads), s, a);
-  char name[48];
-  snprintf(name, sizeof(name), "lt_gemm_kernel<float, %d, %d, %s, %s>", BM, BN, akc ? "true" : "false", bkc ? "true" : "false");
+  if (akc && bkc) LT_LAUNCH((lt_gemm_kernel<T, BM, BN, true, true, AL>), grid, dim3(kGemmThreads), s, a);
+  else if (akc) LT_LAUNCH((lt_gemm_kernel<T, BM, BN, true, false, AL>), grid, dim3(kGemmThreads), s, a);
+  else if (bkc) LT_LAUNCH((lt_gemm_kernel<T, BM, BN, false, true, AL>), grid, dim3(kGemmThreads), s, a);
+  else LT_LAUNCH((lt_gemm_kernel<T, BM, BN, false, false, AL>), grid, dim3(kGemmThreads), s, a);
+  char name[64];
+  snprintf(name, sizeof(name), "lt_gemm_kernel<float, %d, %d, %s, %s, %s>", BM, BN, akc ? "true" : "false", bkc ? "true" : "false", AL ? "true" : "false");
   note_kernel(name);
 }
 
@@ -611,8 +679,15 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
   if (a.splits == 0u) return hipErrorInvalidValue;
   const dim3 grid((a.n + bm - 1) / bm, (a.m + bm - 1) / bm, batch * a.splits);
   if (grid.y > 65535u || grid.z > 65535u) return hipErrorInvalidValue;
-  if (big) launch_variant<float, 128, 128>(a, grid, s);
-  else launch_variant<float, 64, 64>(a, grid, s);
+  // (a lane's offset into a panel is a 32-bit number of bytes: 128 rows of less than 2^23 elements)
+  auto aligned = [](const GemmOperand& o, int64_t outer) {
+    return ((uintptr_t)o.ptr & 15u) == 0 && outer % 4 == 0 && outer < (1 << 23) && o.s_b0 % 4 == 0 && o.s_b1 % 4 == 0;
+  };
+  const bool al = aligned(a.a, a.a.s_col == 1 ? a.a.s_row : a.a.s_col) && aligned(a.b, a.b.s_row == 1 ? a.b.s_col : a.b.s_row);
+  if (big && al) launch_variant<float, 128, 128, true>(a, grid, s);
+  else if (big) launch_variant<float, 128, 128, false>(a, grid, s);
+  else if (al) launch_variant<float, 64, 64, true>(a, grid, s);
+  else launch_variant<float, 64, 64, false>(a, grid, s);
   return hipGetLastError();
 }
 

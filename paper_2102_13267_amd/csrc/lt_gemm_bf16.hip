@@ -44,6 +44,7 @@
 
 #include <cstdio>
 
+#include "lt_dma.h"
 #include "lt_gemm_epilogue.h"
 #include "lt_launch.h"
 
@@ -195,26 +196,6 @@ __device__ __forceinline__ uint32_t dma_lane_offset(uint32_t it, int64_t s_x, in
   return (uint32_t)(2 * chunk_offset<BX, KC>(it * ((uint32_t)kGemmThreads / D::kPerRow) + k, xc * 8u, s_x, s_k, left));
 }
 
-// One wave instruction of such a copy.  Written in assembly on purpose: the compiler orders every
-// later LDS read behind every copy it knows to be in flight (and loses track of them around a
-// loop's back edge), so a pipeline deeper than one slice needs copies it does not know about and
-// waits that the code spells out (landed(), below).  M0 holds the LDS base of the instruction;
-// nothing else in the loop uses it, and the interpreter's register indexing sets it afresh.
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-__device__ __forceinline__ void copy_1k(const void* base, uint32_t lane_off, uint32_t lds_base) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_base), "v"(lane_off), "s"(base) : "memory", "m0");
-}
-#pragma clang diagnostic pop
-
-// Wait until at most `outstanding` of this wave's copies are still in flight (they complete in
-// order).  s_waitcnt immediate: vmcnt in bits 3:0 and 15:14, the other counters left alone.
-template <uint32_t outstanding>
-__device__ __forceinline__ void landed() {
-  static_assert(outstanding < 64u, "vmcnt is a 6-bit counter");
-  __builtin_amdgcn_s_waitcnt((int)((outstanding & 15u) | ((outstanding >> 4) << 14) | 0x0f70u));
-}
-
 // Start the copy of a slice (`src`: the panel's start at the slice's first k) into the tile at LDS
 // address `tile`.
 template <int BX, bool KC>
@@ -260,13 +241,6 @@ __device__ __forceinline__ v8bf fragment_dense(const char* tile, uint32_t x_blk,
     r[4] = hi[0]; r[5] = hi[1]; r[6] = hi[2]; r[7] = hi[3];
     return __builtin_bit_cast(v8bf, r);
   }
-}
-
-// The same, and every LDS read of this wave has returned as well (lgkmcnt = 0).
-template <uint32_t outstanding>
-__device__ __forceinline__ void landed_and_read() {
-  static_assert(outstanding < 64u, "vmcnt is a 6-bit counter");
-  __builtin_amdgcn_s_waitcnt((int)((outstanding & 15u) | ((outstanding >> 4) << 14) | 0x0070u));
 }
 
 template <int BM, int BN> struct Smem {

@@ -10,35 +10,39 @@ from test_gpu_parity import check, ctx, rng  # noqa: F401  (ctx is a fixture)
 pytestmark = pytest.mark.gpu
 
 SHAPES = [(1, 1, 1), (3, 5, 7), (9, 65, 33), (127, 129, 31), (129, 63, 32), (130, 200, 64), (200, 64, 200), (201, 203, 97), (64, 72, 136), (136, 257, 264),
-          (300, 10, 160), (256, 130, 1000), (77, 128, 4101)]
+          (300, 10, 160), (256, 130, 1000), (77, 128, 4101), (700, 1030, 70)]
 
 
 def window(B, full, rows):
     return B.narrow(full, 0, 1, rows)
 
 
+@pytest.mark.parametrize("dt", ["bf16", "f32"])
 @pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, False), (True, True)])
 @pytest.mark.parametrize("m,n,k", SHAPES)
-def test_ragged_bf16(ctx, m, n, k, ta, tb):  # noqa: F811
-    """Bar: 2e-2 of the result's largest value (one bf16 rounding of it, and of the inputs of the sum
-    with a bias): the products themselves are exact in fp32."""
+def test_ragged(ctx, m, n, k, ta, tb, dt):  # noqa: F811
+    """Bar: bf16 2e-2 of the result's largest value (one bf16 rounding of it, and of the inputs of the sum
+    with a bias; the products themselves are exact in fp32); fp32 1e-5, and 6e-8 of the terms'
+    magnitudes adding up like a random walk where k is long."""
     E, g = Eager(), rng(m * 7 + n * 11 + k)
+    rnd = round_to_bf16 if dt == "bf16" else (lambda t: t)
+    tol = 2e-2 if dt == "bf16" else max(1e-5, 1e-6 * k ** 0.5)
 
     def operand(rows, cols):
         t = np.full((rows + 2, cols), np.nan, np.float32)
-        t[1:-1] = round_to_bf16(g.standard_normal((rows, cols), dtype=np.float32))
+        t[1:-1] = rnd(g.standard_normal((rows, cols), dtype=np.float32))
         return t
     a, b = operand(*((k, m) if ta else (m, k))), operand(*((n, k) if tb else (k, n)))
-    bias, res = (round_to_bf16(g.standard_normal(s, dtype=np.float32)) for s in ((n,), (m, n)))
+    bias, res = (rnd(g.standard_normal(s, dtype=np.float32)) for s in ((n,), (m, n)))
 
     def prog(B, a, b, bias, res):
         p = B.matmul(window(B, a, a.shape[0] - 2), window(B, b, b.shape[0] - 2), trans_a=ta, trans_b=tb)
         q = B.matmul(window(B, a, a.shape[0] - 2), window(B, b, b.shape[0] - 2), trans_a=ta, trans_b=tb)
         return p, B.add(B.relu(B.add(q, bias)), res)
-    got = prog(ctx, *(ctx.tensor(t, dtype="bf16") for t in (a, b, bias, res)))
-    ref = prog(E, *(E.tensor(t, dtype="bf16") for t in (a, b, bias, res)))
+    got = prog(ctx, *(ctx.tensor(t, dtype=dt) for t in (a, b, bias, res)))
+    ref = prog(E, *(E.tensor(t, dtype=dt) for t in (a, b, bias, res)))
     for i, (x, y) in enumerate(zip(got, ref)):
-        check(ctx, E, x, y, 2e-2, i)
+        check(ctx, E, x, y, tol, i)
 
 
 @pytest.mark.parametrize("s,h,d", [(200, 3, 64), (201, 2, 32), (33, 4, 128), (259, 2, 64), (16, 5, 32)])
