@@ -95,3 +95,26 @@ def test_attention_core_same_as_its_parts(ctx):  # noqa: F811
     other.close()
     for x, y in zip(*res):
         assert np.max(np.abs(x - y)) <= 2e-5 * np.max(np.abs(y))
+
+
+def test_results_that_are_other_shapes_of_a_computed_value(ctx):  # noqa: F811
+    """A reshaped result takes the memory of the value it reshapes when it can: a value with other
+    readers, two reshapes of one value, a value that is a result too, a permuted one; and updating one
+    of them in place afterwards changes none of the others."""
+    E, g = Eager(), rng(77)
+    a, b = (g.standard_normal((24, 24), dtype=np.float32) for _ in range(2))
+
+    def prog(B, a, b):
+        y = B.matmul(a, b)
+        e = B.mul(a, 2.0)
+        p = B.matmul(B.reshape(a, (2, 12, 24)), B.reshape(b, (2, 12, 24)), trans_b=True)
+        r = [B.reshape(y, (12, 48)), B.reshape(y, (576,)), B.sum(B.relu(y), axis=1), e, B.reshape(e, (4, 144)), B.reshape(B.permute(p, (1, 0, 2)), (12, 24)),
+             B.reshape(B.softmax(b), (8, 72))]
+        if B is ctx:
+            ctx.barrier()
+        B.assign(r[0], B.mul(r[0], -1.0))
+        B.assign(r[4], B.add(r[4], 1.0))
+        return r
+    got, ref = prog(ctx, ctx.tensor(a), ctx.tensor(b)), prog(E, E.tensor(a), E.tensor(b))
+    for i, (x, y) in enumerate(zip(got, ref)):
+        check(ctx, E, x, y, 1e-5, i)
