@@ -575,7 +575,7 @@ __global__ __launch_bounds__(kSmallThreads) void lt_gemm_small_kernel(const Gemm
 #pragma unroll
       for (uint32_t j = 0; j < QT; ++j)
         publish4(parts + (size_t)split * (NB * 1024u) + (size_t)((threadIdx.x + j * kSmallThreads) % kQuads) * 4u, sum[j]);
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");   // (this wave's stores have been performed before the ticket is taken)
+      all_published();
     }
     __syncthreads();
     if (threadIdx.x == 0u) {

@@ -274,7 +274,7 @@ __global__ __launch_bounds__(kBlock) void lt_all_reduce_kernel(const AllArgs a) 
   if (gridDim.x > 1u) {   // (a single workgroup is its own last one: no partials, no ticket)
     if (threadIdx.x == 0) {
       publish(&a.partials[blockIdx.x], r);
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");   // (the store has been performed before the ticket is taken)
+      all_published();
       uint32_t t = atomicAdd(a.ticket, 1u);
       is_last = (t == gridDim.x - 1) ? 1u : 0u;
     }
@@ -489,7 +489,7 @@ __global__ __launch_bounds__(kColBlock) void lt_col_reduce_kernel(const ColArgs 
       if (nvalid > 1u) publish(dst + 1, acc.y);
       if (nvalid > 2u) publish(dst + 2, acc.z);
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");   // (this wave's stores have been performed before its ticket is taken)
+    all_published();
     if (lane == 0) {
       uint32_t t = atomicAdd(&a.tickets[blockIdx.x], 1u);
       is_last = (t == gridDim.y - 1) ? 1u : 0u;

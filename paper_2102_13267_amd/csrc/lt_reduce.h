@@ -15,9 +15,11 @@ __device__ __forceinline__ float red_combine(uint32_t red, float x, float y) {
 // different L2 caches.  They are written and read with relaxed device-scope atomic accesses --
 // stores and loads that go through to the memory side -- so that no cache has to be written back
 // or invalidated as a whole, which is what a device-scope fence does (microseconds per fence, and
-// every other workgroup of the die loses what it had cached).  Order: the writer waits for its
-// stores (a workgroup-scope release: a wait, no cache operation) before it takes the ticket; the
-// reader starts only after it has seen the last ticket.
+// every other workgroup of the die loses what it had cached).  Order: every wave waits for its own
+// stores (all_published) before the barrier behind which its workgroup takes the ticket; the reader
+// starts only after it has seen the last ticket.  The wait is spelled out: a workgroup-scope release
+// fence waits for LDS only (one workgroup shares an L1, so its own waves need no more), and a ticket
+// taken on the strength of it has overtaken the stores of another wave.
 __device__ __forceinline__ void publish(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ float published(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void publish4(float* p, const float4& v) {   // p 16-byte aligned
@@ -32,6 +34,8 @@ __device__ __forceinline__ float4 published4(const float* p) {
   return make_float4(__uint_as_float((uint32_t)lo), __uint_as_float((uint32_t)(lo >> 32)), __uint_as_float((uint32_t)hi),
                      __uint_as_float((uint32_t)(hi >> 32)));
 }
+
+__device__ __forceinline__ void all_published() { asm volatile("s_waitcnt vmcnt(0)" : : : "memory"); }
 
 // One butterfly step inside a row of 16 lanes through the data-parallel-primitive lane crossbar
 // (no LDS traffic).  CTRL: 0xB1 swaps neighbours, 0x4E swaps pairs, 0x141 mirrors each half row
