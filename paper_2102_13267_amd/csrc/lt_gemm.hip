@@ -20,6 +20,7 @@
 // inside the workgroup and, for a long k, over a few workgroups that meet inside the launch).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdio>
 
 #include "lt_dma.h"
@@ -441,7 +442,7 @@ __device__ __forceinline__ float small_colsum(const float (&bv)[kSmallG][4]) {
 // strides and k % 4).  CS: the column sums of B ride along (GemmArgs::col_sum); a variant of its own, because the
 // second program costs 40 registers that the plain product does not have to carry.
 template <int TM, int TN, bool AV, bool BV, bool CS>
-__global__ __launch_bounds__(kSmallThreads) void lt_gemm_small_kernel(const GemmArgs a) {
+__device__ __forceinline__ void small_tile32(const GemmArgs& a) {
   constexpr uint32_t NB = TM * TN, KW = kSmallWaves / NB;      // blocks, k shares inside the workgroup
   constexpr uint32_t kQuads = NB * 256u, QT = (kQuads + kSmallThreads - 1u) / kSmallThreads;   // quads of the tile, per thread
   __shared__ __attribute__((aligned(16))) float Cs[kSmallWaves * 32 * kSmallStride];
@@ -617,41 +618,218 @@ __global__ __launch_bounds__(kSmallThreads) void lt_gemm_small_kernel(const Gemm
   }
 }
 
+// ---- tiny contractions --------------------------------------------------------------------------
+// The same for products whose 32 x 32 tiles would number a few dozen (a layer of a small classifier, a few
+// rows against a wide weight): tiles of 16 rows by 16 (or 64) columns on MFMA 16x16x4, so that four times as
+// many compute units get one and a wave's share of k is a handful of loads that are all in flight at once.  What
+// bounds it is launch and memory latency and the number of instructions a wave walks through: counters on
+// 128 x 512 x 784 in 32 x 32 tiles (64 workgroups) gave 1350 instructions per wave, a fifth of its cycles, and as
+// long again waiting for the matrix cores of a quarter of the chip.  Lane (x, q) supplies A[x][k] and B[k][x] for the four
+// consecutive k at 16 g + 4 q of group g.
+// BMODE: 0 = B element by element, 1 = four k at once (k contiguous), 2 = four columns at once (columns
+// contiguous; the tile is then 64 columns wide, column 4 x + j in accumulator j).
+template <bool AV, int BMODE>
+__device__ __forceinline__ void small_tile16(const GemmArgs& a) {
+  constexpr uint32_t NB = BMODE == 2 ? 4 : 1, kCols = 16u * NB, kStride = kCols + 4u, kQuads = 64u * NB;
+  constexpr uint32_t G = BMODE == 2 ? 2 : 4;   // groups of 16 k in flight (and as many being multiplied)
+  __shared__ __attribute__((aligned(16))) float Cs[kSmallWaves * 16 * kStride];
+  __shared__ uint32_t is_last;
+  const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), kw = blockDim.x >> 6;
+  const uint32_t per_batch = a.tiles_m * a.tiles_n, tile = blockIdx.x / a.splits, split = blockIdx.x % a.splits;
+  const uint32_t batch = tile / per_batch, rem = tile % per_batch, tile_m = (rem / a.tiles_n) * 16u, tile_n = (rem % a.tiles_n) * kCols;
+  const uint32_t b0 = batch / a.batch1, b1 = batch % a.batch1, x = lane & 15u, q = lane >> 4;
+  const float* A = (const float*)a.a.ptr + (int64_t)b0 * a.a.s_b0 + (int64_t)b1 * a.a.s_b1;
+  const float* B = (const float*)a.b.ptr + (int64_t)b0 * a.b.s_b0 + (int64_t)b1 * a.b.s_b1;
+  // rows and columns over the edge are read as copies of the last one (in bounds; never stored)
+  const float* ap = A + (int64_t)min(tile_m + x, a.m - 1u) * a.a.s_row;
+  const float* bp = BMODE == 2 ? B + min(tile_n + 4u * x, a.n - 4u) : B + (int64_t)min(tile_n + x, a.n - 1u) * a.b.s_col;
+  // this workgroup's slice of k and this wave's share of it: whole groups of 16
+  const uint32_t per_wg = ((a.k + 15u) / 16u + a.splits - 1u) / a.splits;
+  const uint32_t wg_begin = min(a.k, split * per_wg * 16u), wg_end = min(a.k, (split + 1u) * per_wg * 16u);
+  const uint32_t per = ((wg_end - wg_begin + 15u) / 16u + kw - 1u) / kw;
+  const uint32_t k_begin = min(wg_end, wg_begin + wave * per * 16u), k_end = min(wg_end, wg_begin + (wave + 1u) * per * 16u);
+  float av[2][G][4], bv[2][G][4][NB];
+  auto fetch = [&](int set, uint32_t k0) {
+#pragma unroll
+    for (uint32_t g = 0; g < G; ++g) {
+      const uint32_t kg = k0 + g * 16u + 4u * q;
+      if (AV) {   // (k is a multiple of 4: the four are valid together)
+        const RawVec t = *(const RawVec*)(ap + (kg < k_end ? kg : 0u));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) av[set][g][e] = t[e];
+      } else {
+#pragma unroll
+        for (uint32_t e = 0; e < 4u; ++e) av[set][g][e] = ap[(int64_t)(kg + e < k_end ? kg + e : 0u) * a.a.s_col];
+      }
+      if (BMODE == 1) {
+        const RawVec t = *(const RawVec*)(bp + (kg < k_end ? kg : 0u));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) bv[set][g][e][0] = t[e];
+      } else {
+#pragma unroll
+        for (uint32_t e = 0; e < 4u; ++e) {
+          const float* src = bp + (int64_t)(kg + e < k_end ? kg + e : 0u) * a.b.s_row;
+          if (BMODE == 2) {
+            typedef float V __attribute__((ext_vector_type(4), aligned(4)));   // (rows may start at any element)
+            const V t = *(const V*)src;
+#pragma unroll
+            for (uint32_t j = 0; j < NB; ++j) bv[set][g][e][j] = t[j];
+          } else {
+            bv[set][g][e][0] = *src;
+          }
+        }
+      }
+    }
+  };
+  // The post program (its registers live in all lanes of a wave) and its inputs travel under the contraction.
+  const EwProg& p = a.post;
+  const ProgRegs pr = load_prog_regs(p);
+  const uint32_t qrow = tile_m + (threadIdx.x % kQuads) / (4u * NB), qcol = tile_n + (threadIdx.x % (4u * NB)) * (uint32_t)kVec;
+  const uint32_t qi = (uint32_t)((int64_t)b0 * a.o_b0 + (int64_t)b1 * a.o_b1 + (int64_t)qrow * a.o_row + qcol);
+  const bool has_quad = threadIdx.x < kQuads;   // (wave-uniform)
+  const bool fast = p.fast && p.full_vec_ok && p.n_in <= 4u && p.n_slots <= 8u && tile_m + 16u <= a.m && tile_n + kCols <= a.n;
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Wuninitialized"
+#pragma clang diagnostic ignored "-Wsometimes-uninitialized"
+  Staged<4> staged;
+  if (k_begin < k_end) fetch(0, k_begin);
+  if (fast && has_quad) staged = fetch_inputs_at<4, false, false>(p, qi, (b0 * a.batch1 + b1) * a.m + qrow, qcol);
+#pragma clang diagnostic pop
+  typedef float v4f __attribute__((ext_vector_type(4)));
+  v4f acc[2][NB];
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (uint32_t j = 0; j < NB; ++j) acc[c][j] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+  auto mma = [&](int set, uint32_t k0) {
+#pragma unroll
+    for (uint32_t g = 0; g < G; ++g)
+#pragma unroll
+      for (uint32_t e = 0; e < 4u; ++e) {
+        const bool ok = k0 + g * 16u + 4u * q + e < k_end;   // k past this wave's share: zero on both sides
+        const float av_ = ok ? av[set][g][e] : 0.0f;
+#pragma unroll
+        for (uint32_t j = 0; j < NB; ++j)
+          acc[e & 1u][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av_, ok ? bv[set][g][e][j] : 0.0f, acc[e & 1u][j], 0, 0, 0);
+      }
+  };
+  constexpr uint32_t kStep = G * 16u;
+  for (uint32_t k0 = k_begin; k0 < k_end; k0 += 2u * kStep) {
+    if (k0 + kStep < k_end) fetch(1, k0 + kStep);
+    mma(0, k0);
+    if (k0 + 2u * kStep < k_end) fetch(0, k0 + 2u * kStep);
+    if (k0 + kStep < k_end) mma(1, k0 + kStep);
+  }
+  float* mine = Cs + wave * (16u * kStride);
+#pragma unroll
+  for (uint32_t r = 0; r < 4u; ++r)
+#pragma unroll
+    for (uint32_t j = 0; j < NB; ++j) mine[(4u * q + r) * kStride + NB * x + j] = acc[0][j][r] + acc[1][j][r];
+  __syncthreads();
+  float4 sum = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  if (has_quad) {
+    const float* src = Cs + (qrow - tile_m) * kStride + (qcol - tile_n);
+    sum = *(const float4*)src;
+    for (uint32_t w = 1; w < kw; ++w) {   // share order: deterministic
+      const float4 t = *(const float4*)(src + w * (16u * kStride));
+      sum.x += t.x; sum.y += t.y; sum.z += t.z; sum.w += t.w;
+    }
+  }
+  if (a.splits > 1u) {
+    // leave this workgroup's partial tile, take a ticket; whoever draws the last one goes on
+    float* const parts = a.split_ws + (size_t)tile * a.splits * (kQuads * 4u);
+    if (has_quad) {
+      publish4(parts + (size_t)split * (kQuads * 4u) + threadIdx.x * 4u, sum);
+      all_published();
+    }
+    __syncthreads();
+    if (threadIdx.x == 0u) {
+      const uint32_t t = atomicAdd(&a.tickets[tile], 1u);
+      is_last = (t == a.splits - 1u) ? 1u : 0u;
+      if (t == a.splits - 1u) a.tickets[tile] = 0u;   // (every workgroup of the tile has been here)
+    }
+    __syncthreads();
+    if (!is_last) return;
+    if (has_quad) {
+      sum = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      for (uint32_t sp = 0; sp < a.splits; ++sp) {   // split order: deterministic
+        const float4 t = published4(parts + (size_t)sp * (kQuads * 4u) + threadIdx.x * 4u);
+        sum.x += t.x; sum.y += t.y; sum.z += t.z; sum.w += t.w;
+      }
+    }
+  }
+  if (!has_quad) return;
+  Quad anchor;
+  anchor.v[0] = sum.x; anchor.v[1] = sum.y; anchor.v[2] = sum.z; anchor.v[3] = sum.w;
+  const uint32_t n_code = p.n_code;
+  if (fast) {
+    RF<16> f = place_inputs<16, 4, true, false, 0>(rf_zero<16>(), p, staged, kVec);
+    f = rf_set<16>(f, p.anchor_slot, anchor);
+    f = interp<16>(f, pr, n_code);
+    store_outputs<16, true, false, 0>(f, p, 0, qi, kVec);
+  } else if (qrow < a.m && qcol < a.n) {
+    const uint32_t nvalid = a.n - qcol >= (uint32_t)kVec ? (uint32_t)kVec : a.n - qcol;
+    RF<16> f = load_inputs<16, kMaxIn, false, false>(rf_zero<16>(), p, 0, qi, nvalid);
+    f = rf_set<16>(f, p.anchor_slot, anchor);
+    f = interp<16>(f, pr, n_code);
+    store_outputs<16, false, false>(f, p, 0, qi, nvalid);
+  }
+}
+
+// TM x TN: the workgroup's tile in units of 16 (2 x 2, 4 x 2, 1 x 1, 1 x 4).
+template <int TM, int TN, bool AV, bool BV, bool CS>
+__global__ __launch_bounds__(kSmallThreads) void lt_gemm_small_kernel(const GemmArgs a) {
+  if constexpr (TM == 1) small_tile16<AV, TN == 4 ? 2 : BV ? 1 : 0>(a);
+  else small_tile32<TM / 2, TN / 2, AV, BV, CS>(a);
+}
+
 template <int TM, int TN, bool CS>
-static void launch_small_tile(const GemmArgs& a, bool av, bool bv, dim3 grid, hipStream_t s) {
-  const dim3 block(kSmallThreads);
-  if (av && bv) LT_LAUNCH((lt_gemm_small_kernel<TM, TN, true, true, CS>), grid, block, s, a);
+static void launch_small_tile(const GemmArgs& a, bool av, bool bv, dim3 grid, uint32_t threads, hipStream_t s) {
+  const dim3 block(threads);
+  if (TN == 4) bv = false;   // (columns contiguous, four at a time)
+  if (av && bv) LT_LAUNCH((lt_gemm_small_kernel<TM, TN, true, true && TN != 4, CS>), grid, block, s, a);
   else if (av) LT_LAUNCH((lt_gemm_small_kernel<TM, TN, true, false, CS>), grid, block, s, a);
-  else if (bv) LT_LAUNCH((lt_gemm_small_kernel<TM, TN, false, true, CS>), grid, block, s, a);
+  else if (bv) LT_LAUNCH((lt_gemm_small_kernel<TM, TN, false, true && TN != 4, CS>), grid, block, s, a);
   else LT_LAUNCH((lt_gemm_small_kernel<TM, TN, false, false, CS>), grid, block, s, a);
+  char name[64];
+  snprintf(name, sizeof(name), "lt_gemm_small_kernel<%d, %d, %s, %s, %s>", TM, TN, av ? "true" : "false", bv ? "true" : "false", CS ? "true" : "false");
+  note_kernel(name);
 }
 
 static hipError_t launch_small(const GemmArgs& args, hipStream_t s) {
   GemmArgs a = args;
-  // (the kernel is written for 1 x 1, 2 x 1 and 2 x 2 blocks; 2 x 2 lost to the split pair on every
-  // shape measured and is not built)
-  const bool t11 = a.tile_m == 32u && a.tile_n == 32u, t21 = a.tile_m == 64u && a.tile_n == 32u;
-  if (!t11 && !t21) return hipErrorInvalidValue;
+  // (64 x 64 tiles lost to the split pair on every shape measured and are not built)
+  const bool t22 = a.tile_m == 32u && a.tile_n == 32u, t42 = a.tile_m == 64u && a.tile_n == 32u;
+  const bool t11 = a.tile_m == 16u && a.tile_n == 16u, t14 = a.tile_m == 16u && a.tile_n == 64u;
+  if (!t22 && !t42 && !t11 && !t14) return hipErrorInvalidValue;
   a.tiles_m = (a.m + a.tile_m - 1u) / a.tile_m;
   a.tiles_n = (a.n + a.tile_n - 1u) / a.tile_n;
   const uint64_t wgs = (uint64_t)a.tiles_m * a.tiles_n * a.batch0 * a.batch1;
   if (a.splits == 0u || wgs * a.splits > 0x7fffffffull) return hipErrorInvalidValue;
   if (a.splits > 1u && (!a.split_ws || !a.tickets)) return hipErrorInvalidValue;
   // column sums ride along only with an unshared, unbatched product whose B is [k, n] with rows contiguous
-  if (a.col_sum && (!t11 || a.splits != 1u || a.batch0 * a.batch1 != 1u || a.b.s_col != 1 || a.col_post.n_slots > 16u)) return hipErrorInvalidValue;
+  if (a.col_sum && (!t22 || a.splits != 1u || a.batch0 * a.batch1 != 1u || a.b.s_col != 1 || a.col_post.n_slots > 16u)) return hipErrorInvalidValue;
   if (wgs == 0u) return hipSuccess;
-  auto whole = [&](const GemmOperand& o, bool k_contiguous, int64_t s_outer) {
-    return k_contiguous && (a.k % 4u) == 0u && (((uintptr_t)o.ptr) & 15u) == 0u && (s_outer % 4) == 0 && (o.s_b0 % 4) == 0 && (o.s_b1 % 4) == 0;
+  auto aligned = [&](const GemmOperand& o, int64_t s_outer) {
+    return (((uintptr_t)o.ptr) & 15u) == 0u && (s_outer % 4) == 0 && (o.s_b0 % 4) == 0 && (o.s_b1 % 4) == 0;
   };
-  const bool av = whole(a.a, a.a.s_col == 1, a.a.s_row), bv = whole(a.b, a.b.s_row == 1, a.b.s_col);
+  const bool av = a.a.s_col == 1 && (a.k % 4u) == 0u && aligned(a.a, a.a.s_row), bv = a.b.s_row == 1 && (a.k % 4u) == 0u && aligned(a.b, a.b.s_col);
   const dim3 grid((uint32_t)(wgs * a.splits));
-  if (t11 && a.col_sum) launch_small_tile<1, 1, true>(a, av, bv, grid, s);
-  else if (t11) launch_small_tile<1, 1, false>(a, av, bv, grid, s);
-  else launch_small_tile<2, 1, false>(a, av, bv, grid, s);
-  char name[64];
-  snprintf(name, sizeof(name), "lt_gemm_small_kernel<%u, %u, %s, %s, %s>", a.tile_m / 32u, a.tile_n / 32u, av ? "true" : "false", bv ? "true" : "false",
-           a.col_sum ? "true" : "false");
-  note_kernel(name);
+  if (t22 && a.col_sum) launch_small_tile<2, 2, true>(a, av, bv, grid, kSmallThreads, s);
+  else if (t22) launch_small_tile<2, 2, false>(a, av, bv, grid, kSmallThreads, s);
+  else if (t42) launch_small_tile<4, 2, false>(a, av, bv, grid, kSmallThreads, s);
+  else {
+    // a wave per group of 16 k that a workgroup has to do: at most eight, and the four that a tile of 64
+    // columns needs for its epilogue
+    const uint32_t groups = ((a.k + 15u) / 16u + a.splits - 1u) / a.splits;
+    const uint32_t waves = std::max(std::min(groups, (uint32_t)kSmallWaves), t14 ? 4u : 1u);
+    if (t14) {
+      if (a.b.s_col != 1 || a.n < 4u || a.n % 4u != 0u) return hipErrorInvalidValue;   // (four columns at a time)
+      launch_small_tile<1, 4, false>(a, av, false, grid, 64u * waves, s);
+    } else {
+      launch_small_tile<1, 1, false>(a, av, bv, grid, 64u * waves, s);
+    }
+  }
   return hipGetLastError();
 }
 

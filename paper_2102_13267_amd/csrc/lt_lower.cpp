@@ -1915,9 +1915,31 @@ struct Lowering {
       // 26.2 -> 17.6 (two per tile); from B = 256 on the split pair is faster.
       {
         const uint64_t tiles32 = (uint64_t)((m + 31) / 32) * ((n + 31) / 32) * (uint64_t)batch;
-        if (tiles32 <= 512 && 2.0 * (double)batch * m * n * kk <= 2.5e8 && kk >= 32 && kk <= 1024) {
+        // Tiles of 16 x 16 where those of 32 x 32 leave most compute units idle and a wave with a long walk.
+        // Times with HIP events around the launch (which cost 2 us), 32 x 32 or split pair against 16 x 16:
+        // 128 x 512 x 784 14.8 -> 9.2 us, 128 x 512 x 512 11.2 -> 8.0, 8 x 1024 x 1024 14.3 -> 10.0, 128 x 10 x 512
+        // 11.7 -> 9.4, 128 x 512 x 10 8.7 -> 7.1, 512 x 512 x 512 21.0 -> 16.5; even at 256 x 1024 x 1024 and 300 x 1000 x 512,
+        // hence tiles times k.  A product with both operands across k (a weight gradient) keeps
+        // the larger tile, which the bias gradient can ride in.  [B, 2048] x [2048, 2048] in tiles of 16 x 64: B = 8
+        // 13.8 -> 13.5 us, 32 14.0 -> 13.2, 64 17.8 -> 16.1, 128 26.9 -> 21.8 (tiles of 16 x 16 unshared 14.4, 14.4, 23.3, -).
+        const uint64_t tiles16 = (uint64_t)((m + 15) / 16) * ((n + 15) / 16) * (uint64_t)batch;
+        const uint64_t tiles64 = (uint64_t)((m + 15) / 16) * (n / 64) * (uint64_t)batch;
+        const bool across = A.s_col != 1 && B.s_row != 1;
+        if (!across && tiles16 >= 1 && kk <= 1024 && tiles16 * (uint64_t)kk <= 512 * 1024) {
+          args.tile_m = args.tile_n = 16u;
+          args.direct = 1u;
+          splits = 1;
+        } else if (tiles32 <= 512 && 2.0 * (double)batch * m * n * kk <= 2.5e8 && kk >= 32 && kk <= 1024) {
           args.tile_m = args.tile_n = 32u;
           args.direct = 1u;
+          splits = 1;
+        } else if (!r->sealed && B.s_col == 1 && n % 64 == 0 && kk > 1024 && tiles64 >= 1 && tiles64 <= 256) {
+          // (the same for a long k against a whole, wide weight matrix: tiles of 16 x 64, four columns per load,
+          // workgroups that share a tile of at least 128 of k each)
+          args.tile_m = 16u;
+          args.tile_n = 64u;
+          args.direct = 1u;
+          args.splits = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>({8, 256 / tiles64, (uint64_t)kk / 128}));
           splits = 1;
         } else if (!r->sealed && tiles32 >= 1 && tiles32 <= 256 && kk > 1024) {
           // (above 128 tiles of 32 x 32: tiles of 64 x 32, two blocks times four shares of k per

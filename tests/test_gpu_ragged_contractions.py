@@ -10,7 +10,7 @@ from test_gpu_parity import check, ctx, rng  # noqa: F401  (ctx is a fixture)
 pytestmark = pytest.mark.gpu
 
 SHAPES = [(1, 1, 1), (3, 5, 7), (9, 65, 33), (127, 129, 31), (129, 63, 32), (130, 200, 64), (200, 64, 200), (201, 203, 97), (64, 72, 136), (136, 257, 264),
-          (300, 10, 160), (256, 130, 1000), (77, 128, 4101), (700, 1030, 70)]
+          (300, 10, 160), (256, 130, 1000), (77, 128, 4101), (5, 64, 1100), (40, 192, 2052), (16, 64, 1025), (700, 1030, 70)]
 
 
 def window(B, full, rows):
