@@ -399,6 +399,36 @@ __global__ __launch_bounds__(kGemmThreads, BM == 64 ? 2 : 1) void lt_gemm_kernel
 // launch.
 constexpr int kSmallThreads = 512, kSmallWaves = 8, kSmallG = 4, kSmallStride = 32 + kCPad;
 
+// Which tile a workgroup works on: grid = (column tiles x workgroups per tile, row tiles, batch), so that
+// nothing is divided in the usual case (an integer division costs some 250 cycles at a kernel's start,
+// and one flat index took five of them).  The workgroups of a tile are neighbours.
+struct SmallTile {
+  uint32_t number, row, col, split, b0, b1;
+};
+__device__ __forceinline__ SmallTile small_tile(const GemmArgs& a) {
+  // everything the operands' addresses need, read in one go (field by field, each behind the use of the one
+  // before, it is one wait per field)
+  asm volatile("" : : "s"(a.splits), "s"(a.batch1), "s"(a.tiles_n), "s"(a.m), "s"(a.n), "s"(a.k), "s"(a.a.ptr), "s"(a.a.s_row), "s"(a.a.s_col),
+               "s"(a.a.s_b0), "s"(a.b.ptr), "s"(a.b.s_row), "s"(a.b.s_col), "s"(a.b.s_b0), "s"(a.o_row), "s"(a.post.fast), "s"(a.post.n_in),
+               "s"(a.post.n_slots), "s"(a.post.full_vec_ok), "s"(a.post.in[0].ptr), "s"(a.post.in[0].mode), "s"(a.post.in[0].dtype), "s"(a.post.in[0].fetch));
+  SmallTile t;
+  t.row = blockIdx.y;
+  t.col = blockIdx.x;
+  t.split = 0u;
+  if (a.splits > 1u) {
+    t.col = blockIdx.x / a.splits;
+    t.split = blockIdx.x - t.col * a.splits;
+  }
+  t.b0 = blockIdx.z;
+  t.b1 = 0u;
+  if (a.batch1 > 1u) {
+    t.b0 = blockIdx.z / a.batch1;
+    t.b1 = blockIdx.z - t.b0 * a.batch1;
+  }
+  t.number = (blockIdx.z * gridDim.y + t.row) * a.tiles_n + t.col;
+  return t;
+}
+
 template <bool V>
 __device__ __forceinline__ void small_fetch(float (&v)[kSmallG][4], const float* base, int64_t s_k, uint32_t k0, uint32_t k_end) {
 #pragma unroll
@@ -450,11 +480,8 @@ __device__ __forceinline__ void small_tile32(const GemmArgs& a) {
   __shared__ float colp[CS ? kSmallThreads : 1], coltot[CS ? 32 * TN : 1];
   const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t block = wave % NB, kway = wave / NB, bm = block / TN, bn = block % TN;
-  const uint32_t per_batch = a.tiles_m * a.tiles_n;
-  const uint32_t tile = blockIdx.x / a.splits, split = blockIdx.x % a.splits;   // (the workgroups of a tile are neighbours)
-  const uint32_t batch = tile / per_batch, rem = tile % per_batch;
-  const uint32_t tile_m = (rem / a.tiles_n) * (32u * TM), tile_n = (rem % a.tiles_n) * (32u * TN);
-  const uint32_t b0 = batch / a.batch1, b1 = batch % a.batch1;
+  const SmallTile st = small_tile(a);
+  const uint32_t tile = st.number, split = st.split, tile_m = st.row * (32u * TM), tile_n = st.col * (32u * TN), b0 = st.b0, b1 = st.b1;
   const float* A = (const float*)a.a.ptr + (int64_t)b0 * a.a.s_b0 + (int64_t)b1 * a.a.s_b1;
   const float* B = (const float*)a.b.ptr + (int64_t)b0 * a.b.s_b0 + (int64_t)b1 * a.b.s_b1;
   // this workgroup's slice of k, and this wave's share of it: whole groups of 8
@@ -635,9 +662,8 @@ __device__ __forceinline__ void small_tile16(const GemmArgs& a) {
   __shared__ __attribute__((aligned(16))) float Cs[kSmallWaves * 16 * kStride];
   __shared__ uint32_t is_last;
   const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), kw = blockDim.x >> 6;
-  const uint32_t per_batch = a.tiles_m * a.tiles_n, tile = blockIdx.x / a.splits, split = blockIdx.x % a.splits;
-  const uint32_t batch = tile / per_batch, rem = tile % per_batch, tile_m = (rem / a.tiles_n) * 16u, tile_n = (rem % a.tiles_n) * kCols;
-  const uint32_t b0 = batch / a.batch1, b1 = batch % a.batch1, x = lane & 15u, q = lane >> 4;
+  const SmallTile st = small_tile(a);
+  const uint32_t split = st.split, tile_m = st.row * 16u, tile_n = st.col * kCols, b0 = st.b0, b1 = st.b1, x = lane & 15u, q = lane >> 4;
   const float* A = (const float*)a.a.ptr + (int64_t)b0 * a.a.s_b0 + (int64_t)b1 * a.a.s_b1;
   const float* B = (const float*)a.b.ptr + (int64_t)b0 * a.b.s_b0 + (int64_t)b1 * a.b.s_b1;
   // rows and columns over the edge are read as copies of the last one (in bounds; never stored)
@@ -649,29 +675,34 @@ __device__ __forceinline__ void small_tile16(const GemmArgs& a) {
   const uint32_t per = ((wg_end - wg_begin + 15u) / 16u + kw - 1u) / kw;
   const uint32_t k_begin = min(wg_end, wg_begin + wave * per * 16u), k_end = min(wg_end, wg_begin + (wave + 1u) * per * 16u);
   float av[2][G][4], bv[2][G][4][NB];
+  // (whole steps: a lane's own pointer plus a wave-uniform offset; the last step checks every k)
+  const float *al = ap + (int64_t)(4u * q) * a.a.s_col, *bl = bp + (int64_t)(4u * q) * a.b.s_row;
+  constexpr uint32_t kStep = G * 16u;
+  typedef float V4 __attribute__((ext_vector_type(4), aligned(4)));   // (rows may start at any element)
   auto fetch = [&](int set, uint32_t k0) {
+    const bool whole = k0 + kStep <= k_end;
 #pragma unroll
     for (uint32_t g = 0; g < G; ++g) {
       const uint32_t kg = k0 + g * 16u + 4u * q;
+      const bool in = kg < k_end;
       if (AV) {   // (k is a multiple of 4: the four are valid together)
-        const RawVec t = *(const RawVec*)(ap + (kg < k_end ? kg : 0u));
+        const RawVec t = *(const RawVec*)(in ? al + (k0 + g * 16u) : ap);
 #pragma unroll
         for (int e = 0; e < 4; ++e) av[set][g][e] = t[e];
       } else {
 #pragma unroll
-        for (uint32_t e = 0; e < 4u; ++e) av[set][g][e] = ap[(int64_t)(kg + e < k_end ? kg + e : 0u) * a.a.s_col];
+        for (uint32_t e = 0; e < 4u; ++e) av[set][g][e] = *(whole || kg + e < k_end ? al + (int64_t)(k0 + g * 16u + e) * a.a.s_col : ap);
       }
       if (BMODE == 1) {
-        const RawVec t = *(const RawVec*)(bp + (kg < k_end ? kg : 0u));
+        const RawVec t = *(const RawVec*)(in ? bl + (k0 + g * 16u) : bp);
 #pragma unroll
         for (int e = 0; e < 4; ++e) bv[set][g][e][0] = t[e];
       } else {
 #pragma unroll
         for (uint32_t e = 0; e < 4u; ++e) {
-          const float* src = bp + (int64_t)(kg + e < k_end ? kg + e : 0u) * a.b.s_row;
+          const float* src = whole || kg + e < k_end ? bl + (int64_t)(k0 + g * 16u + e) * a.b.s_row : bp;
           if (BMODE == 2) {
-            typedef float V __attribute__((ext_vector_type(4), aligned(4)));   // (rows may start at any element)
-            const V t = *(const V*)src;
+            const V4 t = *(const V4*)src;
 #pragma unroll
             for (uint32_t j = 0; j < NB; ++j) bv[set][g][e][j] = t[j];
           } else {
@@ -702,18 +733,25 @@ __device__ __forceinline__ void small_tile16(const GemmArgs& a) {
 #pragma unroll
     for (uint32_t j = 0; j < NB; ++j) acc[c][j] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
   auto mma = [&](int set, uint32_t k0) {
+    if (k0 + kStep > k_end) {   // k past this wave's share: zero on both sides
+#pragma unroll
+      for (uint32_t g = 0; g < G; ++g)
+#pragma unroll
+        for (uint32_t e = 0; e < 4u; ++e) {
+          const bool ok = k0 + g * 16u + 4u * q + e < k_end;
+          av[set][g][e] = ok ? av[set][g][e] : 0.0f;
+#pragma unroll
+          for (uint32_t j = 0; j < NB; ++j) bv[set][g][e][j] = ok ? bv[set][g][e][j] : 0.0f;
+        }
+    }
 #pragma unroll
     for (uint32_t g = 0; g < G; ++g)
 #pragma unroll
-      for (uint32_t e = 0; e < 4u; ++e) {
-        const bool ok = k0 + g * 16u + 4u * q + e < k_end;   // k past this wave's share: zero on both sides
-        const float av_ = ok ? av[set][g][e] : 0.0f;
+      for (uint32_t e = 0; e < 4u; ++e)
 #pragma unroll
         for (uint32_t j = 0; j < NB; ++j)
-          acc[e & 1u][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av_, ok ? bv[set][g][e][j] : 0.0f, acc[e & 1u][j], 0, 0, 0);
-      }
+          acc[e & 1u][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[set][g][e], bv[set][g][e][j], acc[e & 1u][j], 0, 0, 0);
   };
-  constexpr uint32_t kStep = G * 16u;
   for (uint32_t k0 = k_begin; k0 < k_end; k0 += 2u * kStep) {
     if (k0 + kStep < k_end) fetch(1, k0 + kStep);
     mma(0, k0);
@@ -730,23 +768,33 @@ __device__ __forceinline__ void small_tile16(const GemmArgs& a) {
   if (has_quad) {
     const float* src = Cs + (qrow - tile_m) * kStride + (qcol - tile_n);
     sum = *(const float4*)src;
-    for (uint32_t w = 1; w < kw; ++w) {   // share order: deterministic
-      const float4 t = *(const float4*)(src + w * (16u * kStride));
-      sum.x += t.x; sum.y += t.y; sum.z += t.z; sum.w += t.w;
+    if (kw == (uint32_t)kSmallWaves) {   // (all at once: a read behind the other costs an LDS latency each)
+      float4 t[kSmallWaves];
+#pragma unroll
+      for (uint32_t w = 1; w < (uint32_t)kSmallWaves; ++w) t[w] = *(const float4*)(src + w * (16u * kStride));
+#pragma unroll
+      for (uint32_t w = 1; w < (uint32_t)kSmallWaves; ++w) {   // share order: deterministic
+        sum.x += t[w].x; sum.y += t[w].y; sum.z += t[w].z; sum.w += t[w].w;
+      }
+    } else {
+      for (uint32_t w = 1; w < kw; ++w) {
+        const float4 t = *(const float4*)(src + w * (16u * kStride));
+        sum.x += t.x; sum.y += t.y; sum.z += t.z; sum.w += t.w;
+      }
     }
   }
   if (a.splits > 1u) {
     // leave this workgroup's partial tile, take a ticket; whoever draws the last one goes on
-    float* const parts = a.split_ws + (size_t)tile * a.splits * (kQuads * 4u);
+    float* const parts = a.split_ws + (size_t)st.number * a.splits * (kQuads * 4u);
     if (has_quad) {
       publish4(parts + (size_t)split * (kQuads * 4u) + threadIdx.x * 4u, sum);
       all_published();
     }
     __syncthreads();
     if (threadIdx.x == 0u) {
-      const uint32_t t = atomicAdd(&a.tickets[tile], 1u);
+      const uint32_t t = atomicAdd(&a.tickets[st.number], 1u);
       is_last = (t == a.splits - 1u) ? 1u : 0u;
-      if (t == a.splits - 1u) a.tickets[tile] = 0u;   // (every workgroup of the tile has been here)
+      if (t == a.splits - 1u) a.tickets[st.number] = 0u;   // (every workgroup of the tile has been here)
     }
     __syncthreads();
     if (!is_last) return;
@@ -779,8 +827,10 @@ __device__ __forceinline__ void small_tile16(const GemmArgs& a) {
 // TM x TN: the workgroup's tile in units of 16 (2 x 2, 4 x 2, 1 x 1, 1 x 4).
 template <int TM, int TN, bool AV, bool BV, bool CS>
 __global__ __launch_bounds__(kSmallThreads) void lt_gemm_small_kernel(const GemmArgs a) {
+  const uint32_t t = touch_args<GemmArgs>();
   if constexpr (TM == 1) small_tile16<AV, TN == 4 ? 2 : BV ? 1 : 0>(a);
   else small_tile32<TM / 2, TN / 2, AV, BV, CS>(a);
+  args_touched(t);
 }
 
 template <int TM, int TN, bool CS>
@@ -805,7 +855,7 @@ static hipError_t launch_small(const GemmArgs& args, hipStream_t s) {
   a.tiles_m = (a.m + a.tile_m - 1u) / a.tile_m;
   a.tiles_n = (a.n + a.tile_n - 1u) / a.tile_n;
   const uint64_t wgs = (uint64_t)a.tiles_m * a.tiles_n * a.batch0 * a.batch1;
-  if (a.splits == 0u || wgs * a.splits > 0x7fffffffull) return hipErrorInvalidValue;
+  if (a.splits == 0u || wgs * a.splits > 0x7fffffffull || a.tiles_m > 65535u || (uint64_t)a.batch0 * a.batch1 > 65535u) return hipErrorInvalidValue;
   if (a.splits > 1u && (!a.split_ws || !a.tickets)) return hipErrorInvalidValue;
   // column sums ride along only with an unshared, unbatched product whose B is [k, n] with rows contiguous
   if (a.col_sum && (!t22 || a.splits != 1u || a.batch0 * a.batch1 != 1u || a.b.s_col != 1 || a.col_post.n_slots > 16u)) return hipErrorInvalidValue;
@@ -814,7 +864,7 @@ static hipError_t launch_small(const GemmArgs& args, hipStream_t s) {
     return (((uintptr_t)o.ptr) & 15u) == 0u && (s_outer % 4) == 0 && (o.s_b0 % 4) == 0 && (o.s_b1 % 4) == 0;
   };
   const bool av = a.a.s_col == 1 && (a.k % 4u) == 0u && aligned(a.a, a.a.s_row), bv = a.b.s_row == 1 && (a.k % 4u) == 0u && aligned(a.b, a.b.s_col);
-  const dim3 grid((uint32_t)(wgs * a.splits));
+  const dim3 grid(a.tiles_n * a.splits, a.tiles_m, a.batch0 * a.batch1);
   if (t22 && a.col_sum) launch_small_tile<2, 2, true>(a, av, bv, grid, kSmallThreads, s);
   else if (t22) launch_small_tile<2, 2, false>(a, av, bv, grid, kSmallThreads, s);
   else if (t42) launch_small_tile<4, 2, false>(a, av, bv, grid, kSmallThreads, s);

@@ -122,6 +122,17 @@ __device__ __forceinline__ float op_tanh(float x) {
   return z < 0.625f ? small : x != x ? x : large;
 }
 
+// A launch's argument block (1 to 4 KiB) is new to every cache, and a kernel reads it a field here and a field
+// there, each read waiting for a line of its own.  Touched up front, one line per lane, the lines
+// are on their way together.  The value is handed to args_touched() where the kernel ends.
+template <typename Args>
+__device__ __forceinline__ uint32_t touch_args() {
+  const __attribute__((address_space(4))) uint32_t* p = (const __attribute__((address_space(4))) uint32_t*)__builtin_amdgcn_kernarg_segment_ptr();
+  const uint32_t at = (threadIdx.x & 63u) * 16u;
+  return at < sizeof(Args) / 4u ? p[at] : 0u;
+}
+__device__ __forceinline__ void args_touched(uint32_t v) { asm volatile("" : : "v"(v)); }
+
 struct ProgRegs {
   uint32_t code;   // lane j: code[j]  (j < kMaxCode <= 64)
   float scal;      // lane j: scal[j]  (j < kMaxScal)

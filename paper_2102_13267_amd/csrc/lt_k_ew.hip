@@ -14,6 +14,7 @@ constexpr int kBlock = 256;
 // tile base is wave-uniform (scalar registers); lanes differ only by a constant 32-bit offset.
 template <int NS, int MAXIN, bool FAST, bool F32>
 __global__ __launch_bounds__(kBlock) void lt_ew_kernel(const EwArgs a) {
+  const uint32_t touched = touch_args<EwArgs>();
   const EwProg& p = a.prog;
   const uint64_t n = p.n;
   constexpr uint64_t kTile = (uint64_t)kBlock * kVec;
@@ -32,6 +33,7 @@ __global__ __launch_bounds__(kBlock) void lt_ew_kernel(const EwArgs a) {
     f = interp<NS>(f, pr, n_code);
     store_outputs<NS, FAST, F32>(f, p, base, lane, nvalid);
   }
+  args_touched(touched);
 }
 
 // ---- streamed elementwise region --------------------------------------------------------------
@@ -61,6 +63,7 @@ typedef float RawVec4 __attribute__((ext_vector_type(4), aligned(4)));
 
 template <int NV, bool NT, bool RAG>
 __global__ __launch_bounds__(kBlock) void lt_ew_stream_kernel(const EwStreamArgs a) {
+  const uint32_t touched = touch_args<EwStreamArgs>();
   const EwProg& p = a.prog;
   const uint64_t n = p.n;
   constexpr uint64_t kTile = (uint64_t)kBlock * kVec;
@@ -131,6 +134,7 @@ __global__ __launch_bounds__(kBlock) void lt_ew_stream_kernel(const EwStreamArgs
     store_outputs<16, true, true, 0, NT>(f, p, base0, lane, kVec);
     store_outputs<16, true, true, 8, NT>(f, p, base1, lane, kVec);
   }
+  args_touched(touched);
 }
 
 // The same for programs whose plain inputs are all bf16 (outputs of any type): a lane takes 8
@@ -146,6 +150,7 @@ __global__ __launch_bounds__(kBlock) void lt_ew_stream_kernel(const EwStreamArgs
 // leave in one store.
 template <int NV>
 __global__ __launch_bounds__(kBlock, 4) void lt_ew_stream_bf16_kernel(const EwStreamArgs a) {
+  const uint32_t touched = touch_args<EwStreamArgs>();
   const EwProg& p = a.prog;
   const uint64_t n = p.n;   // a multiple of 8: a lane is either wholly inside or wholly outside
   constexpr uint64_t kTile = (uint64_t)kBlock * 2 * kVec;
@@ -232,6 +237,7 @@ __global__ __launch_bounds__(kBlock, 4) void lt_ew_stream_bf16_kernel(const EwSt
     }
     if (!more) break;
   }
+  args_touched(touched);
 }
 
 // Host side: fill in EwStreamArgs if the program qualifies.
@@ -278,6 +284,7 @@ static bool make_stream_args(const EwProg& p, uint32_t vec_dtype, EwStreamArgs* 
 // sum does not depend on scheduling) and run the contraction's post program on the result.
 template <int MAXIN, bool FAST>
 __global__ __launch_bounds__(kBlock) void lt_split_post_kernel(const SplitPostArgs a) {
+  const uint32_t touched = touch_args<SplitPostArgs>();
   const EwProg& p = a.prog;
   const uint64_t n = p.n;
   constexpr uint64_t kTile = (uint64_t)kBlock * kVec;
@@ -306,6 +313,7 @@ __global__ __launch_bounds__(kBlock) void lt_split_post_kernel(const SplitPostAr
     f = interp<16>(f, pr, n_code);
     store_outputs<16, FAST, false>(f, p, base, lane, nvalid);
   }
+  args_touched(touched);
 }
 
 // The same with the loads sorted out on the host, for post programs of at most eight slots whose
@@ -322,6 +330,7 @@ struct SplitStreamArgs {
 
 template <int NVF, int NVB>
 __global__ __launch_bounds__(kBlock) void lt_split_post_stream_kernel(const SplitStreamArgs sa) {
+  const uint32_t touched = touch_args<SplitStreamArgs>();
   const SplitPostArgs& a = sa.base;
   const EwProg& p = a.prog;
   const uint64_t n = p.n;
@@ -405,6 +414,7 @@ __global__ __launch_bounds__(kBlock) void lt_split_post_stream_kernel(const Spli
     store_outputs<16, true, false, 0>(f, p, t0 * kTile, lane, kVec);
     store_outputs<16, true, false, 8>(f, p, t1 * kTile, lane, kVec);
   }
+  args_touched(touched);
 }
 
 static bool make_split_stream_args(const SplitPostArgs& a, SplitStreamArgs* out) {

@@ -34,6 +34,7 @@ typedef float RawVec4 __attribute__((ext_vector_type(4), aligned(4)));
 
 template <int NV, int NR, int Q, bool RAG>
 __global__ __launch_bounds__(kBlock) void lt_row_reduce_stream_kernel(const RowArgs a) {
+  const uint32_t touched = touch_args<RowArgs>();
   constexpr int NS = 8 * Q;
   __shared__ float lds[kBlock / 64];
   const EwProg& pro = a.pro;
@@ -124,10 +125,12 @@ __global__ __launch_bounds__(kBlock) void lt_row_reduce_stream_kernel(const RowA
     if (a.red == kRedMean) r = r / (float)a.cols;
     if (lane == 0 && row < a.rows) run_post(a.post, post_regs, splat(r), row, 1u);
   }
+  args_touched(touched);
 }
 
 // Row reduction.  threads_per_row is 64 (one wave per row, four rows per workgroup) or 256.
 __global__ __launch_bounds__(kBlock) void lt_row_reduce_kernel(const RowArgs a) {
+  const uint32_t touched = touch_args<RowArgs>();
   __shared__ float lds[kBlock / 64];
   const EwProg& pro = a.pro;
   const ProgRegs pro_regs = load_prog_regs(a.pro), post_regs = load_prog_regs(a.post);
@@ -157,6 +160,7 @@ __global__ __launch_bounds__(kBlock) void lt_row_reduce_kernel(const RowArgs a) 
     if (a.red == kRedMean) r = r / (float)a.cols;
     if (lane == 0 && row < a.rows) run_post(a.post, post_regs, splat(r), row, 1u);
   }
+  args_touched(touched);
 }
 
 // Global reduction in one launch.  NIN > 0: streamed (U 4-vectors per lane and trip fetched
@@ -169,6 +173,7 @@ __global__ __launch_bounds__(kBlock) void lt_row_reduce_kernel(const RowArgs a) 
 // sum, so fp32 operands of any length are streamed (bf16: whole 4-vectors).
 template <int NS, int NIN, int U, bool BF, int Q>
 __global__ __launch_bounds__(kBlock) void lt_all_reduce_kernel(const AllArgs a) {
+  const uint32_t touched = touch_args<AllArgs>();
   __shared__ float lds[kBlock / 64];
   __shared__ uint32_t is_last;
   const EwProg& pro = a.pro;
@@ -295,6 +300,7 @@ __global__ __launch_bounds__(kBlock) void lt_all_reduce_kernel(const AllArgs a) 
     const uint32_t nvalid = (pn - i >= (uint64_t)kVec) ? (uint32_t)kVec : (uint32_t)(pn - i);
     run_post(post, post_regs, splat(r), i, nvalid);
   }
+  args_touched(touched);
 }
 
 constexpr int kColBlock = 512;
@@ -314,6 +320,7 @@ __device__ __forceinline__ void col_fold(uint32_t red, float4& acc, const Quad& 
 // (a.cin: a mean, a reciprocal deviation), which a wave reads as one broadcast element per row.
 template <int NS, int NIN, int U, bool BF, int NC = 0>
 __global__ __launch_bounds__(kColBlock) void lt_col_reduce_kernel(const ColArgs a) {
+  const uint32_t touched = touch_args<ColArgs>();
   constexpr uint32_t kWaves = kColBlock / 64;
   __shared__ float4 lds[kColBlock];
   __shared__ uint32_t is_last;
@@ -549,6 +556,7 @@ __global__ __launch_bounds__(kColBlock) void lt_col_reduce_kernel(const ColArgs 
   Quad accq;
   accq.v[0] = acc.x; accq.v[1] = acc.y; accq.v[2] = acc.z; accq.v[3] = acc.w;
   run_post(a.post, post_regs, accq, c, nvalid);
+  args_touched(touched);
 }
 
 

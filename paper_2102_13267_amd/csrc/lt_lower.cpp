@@ -1925,7 +1925,7 @@ struct Lowering {
         const uint64_t tiles16 = (uint64_t)((m + 15) / 16) * ((n + 15) / 16) * (uint64_t)batch;
         const uint64_t tiles64 = (uint64_t)((m + 15) / 16) * (n / 64) * (uint64_t)batch;
         const bool across = A.s_col != 1 && B.s_row != 1;
-        if (!across && tiles16 >= 1 && kk <= 1024 && tiles16 * (uint64_t)kk <= 512 * 1024) {
+        if (!across && tiles16 >= 1 && tiles16 <= 65535 && kk <= 1024 && tiles16 * (uint64_t)kk <= 512 * 1024) {
           args.tile_m = args.tile_n = 16u;
           args.direct = 1u;
           splits = 1;
