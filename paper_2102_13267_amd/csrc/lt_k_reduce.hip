@@ -318,7 +318,10 @@ __device__ __forceinline__ void col_fold(uint32_t red, float4& acc, const Quad& 
 
 // NC > 0: besides the NIN inputs read in full (input numbers a.vin) the program has per-row inputs
 // (a.cin: a mean, a reciprocal deviation), which a wave reads as one broadcast element per row.
-template <int NS, int NIN, int U, bool BF, int NC = 0>
+// NG: a layer norm's weight gradient (ColArgs::norm_grad), computed directly: interpreted, its three
+// instructions were most of the launch, and the bias gradient's own launch over the same dy becomes a
+// second accumulator (8192 x 1024 in bf16: 24.8 + 11.6 us -> 19.4 for both).
+template <int NS, int NIN, int U, bool BF, int NC = 0, bool NG = false>
 __global__ __launch_bounds__(kColBlock) void lt_col_reduce_kernel(const ColArgs a) {
   const uint32_t touched = touch_args<ColArgs>();
   constexpr uint32_t kWaves = kColBlock / 64;
@@ -326,6 +329,7 @@ __global__ __launch_bounds__(kColBlock) void lt_col_reduce_kernel(const ColArgs 
   __shared__ uint32_t is_last;
   const EwProg& pro = a.pro;
   const ProgRegs pro_regs = load_prog_regs(a.pro), post_regs = load_prog_regs(a.post);
+  const ProgRegs post2_regs = NG ? load_prog_regs(a.post2) : ProgRegs{0u, 0.0f};
   const uint32_t pro_n = a.pro.n_code;
   const uint32_t lane = threadIdx.x & 63;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -389,7 +393,7 @@ __global__ __launch_bounds__(kColBlock) void lt_col_reduce_kernel(const ColArgs 
     }
     return;
   }
-  float4 acc = make_float4(id, id, id, id);
+  float4 acc = make_float4(id, id, id, id), acc2 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
   if (nvalid) {
     uint32_t r = r0 + wave;
     if (NIN > 0) {   // streamed: cols is a multiple of 4, so this lane's vector is whole
@@ -419,6 +423,18 @@ __global__ __launch_bounds__(kColBlock) void lt_col_reduce_kernel(const ColArgs 
               const EwIn& in = pro.in[a.cin[j]];
               cw[j][u] = load_elem<false>(in.ptr, in.dtype, r + u * kWaves);
             }
+          }
+          if (NG) {
+#pragma unroll
+            for (int u = 0; u < UU; ++u) {
+              const Quad dy = stream_quad<NN, UU, BF>(st, 0, u), x = stream_quad<NN, UU, BF>(st, NN - 1, u);
+              Quad q;
+#pragma unroll
+              for (int e = 0; e < kVec; ++e) q.v[e] = dy.v[e] * ((x.v[e] - cw[0][u]) * cw[NC > 0 ? NC - 1 : 0][u]);
+              col_fold(a.red, acc, q);
+              col_fold(kRedSum, acc2, dy);
+            }
+            continue;
           }
           // NS = 32: four rows per interpreter dispatch (8 slots x 4 rows), programs of at most 8 slots
           constexpr int QQ = NS == 32 ? 4 : 1;
@@ -460,21 +476,38 @@ __global__ __launch_bounds__(kColBlock) void lt_col_reduce_kernel(const ColArgs 
       const uint64_t rb = (uint64_t)r * a.cols + blockIdx.x * 256u;
       RF<NS> f = (pro.fast && nvalid == (uint32_t)kVec) ? load_inputs<NS, kMaxIn, true, false>(rf_zero<NS>(), pro, rb, lane * kVec, nvalid)
                                                         : load_inputs<NS, kMaxIn, false, false>(rf_zero<NS>(), pro, rb, lane * kVec, nvalid);
+      if (NG) col_fold(kRedSum, acc2, rf_get(f, a.vin[0]));
       f = interp<NS>(f, pro_regs, pro_n);
       col_fold(a.red, acc, rf_get(f, pro.anchor_slot));
     }
   }
-  lds[threadIdx.x] = acc;
-  __syncthreads();
-  if (wave == 0) {
+  // the waves' values of every column, in wave 0
+  auto meet = [&](uint32_t red, float4& v) {
+    lds[threadIdx.x] = v;
+    __syncthreads();
+    if (wave == 0) {
 #pragma unroll
-    for (int w = 1; w < (int)kWaves; ++w) {
-      const float4 o = lds[w * 64 + lane];
-      acc.x = red_combine(a.red, acc.x, o.x);
-      acc.y = red_combine(a.red, acc.y, o.y);
-      acc.z = red_combine(a.red, acc.z, o.z);
-      acc.w = red_combine(a.red, acc.w, o.w);
+      for (int w = 1; w < (int)kWaves; ++w) {
+        const float4 o = lds[w * 64 + lane];
+        v.x = red_combine(red, v.x, o.x);
+        v.y = red_combine(red, v.y, o.y);
+        v.z = red_combine(red, v.z, o.z);
+        v.w = red_combine(red, v.w, o.w);
+      }
     }
+  };
+  auto run_second = [&]() {
+    Quad q;
+    q.v[0] = acc2.x; q.v[1] = acc2.y; q.v[2] = acc2.z; q.v[3] = acc2.w;
+    run_post(a.post2, post2_regs, q, c, nvalid);
+  };
+  const bool second = NG && a.sum2 != 0u;
+  if (second) {
+    meet(kRedSum, acc2);
+    __syncthreads();
+  }
+  meet(a.red, acc);
+  if (wave == 0) {
     if (gridDim.y == 1u) {   // one slab: this is the result, no partials, no tickets
       if (!nvalid) return;
       if (a.red == kRedMean) {
@@ -484,12 +517,14 @@ __global__ __launch_bounds__(kColBlock) void lt_col_reduce_kernel(const ColArgs 
       Quad accq;
       accq.v[0] = acc.x; accq.v[1] = acc.y; accq.v[2] = acc.z; accq.v[3] = acc.w;
       run_post(a.post, post_regs, accq, c, nvalid);
+      if (second) run_second();
       return;
     }
     // The slab stride is padded to a multiple of four floats so that whole vectors stay 16-byte
     // aligned.
     if (nvalid == (uint32_t)kVec) {
       publish4(a.partials + (uint64_t)blockIdx.y * pstride + c, acc);
+      if (second) publish4(a.partials + (uint64_t)(gridDim.y + blockIdx.y) * pstride + c, acc2);   // (whole vectors only: cols % 4 == 0)
     } else if (nvalid) {
       float* dst = a.partials + (uint64_t)blockIdx.y * pstride + c;
       publish(dst, acc.x);
@@ -509,11 +544,17 @@ __global__ __launch_bounds__(kColBlock) void lt_col_reduce_kernel(const ColArgs 
   // the last workgroup of a strip combines the slabs: each wave a contiguous share, eight loads in
   // flight, fixed order (deterministic for a given grid)
   acc = make_float4(id, id, id, id);
+  acc2 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
   if (nvalid) {
     const uint32_t per_wave = (gridDim.y + kWaves - 1) / kWaves;
     const uint32_t s0 = min(gridDim.y, wave * per_wave), s1 = min(gridDim.y, s0 + per_wave);
     for (uint32_t sb = s0; sb < s1; sb += 8) {
-      float4 t[8];
+      float4 t[8], t2[NG ? 8 : 1];
+      if (second) {
+#pragma unroll
+        for (uint32_t j = 0; j < 8; ++j)
+          t2[NG ? j : 0] = sb + j < s1 ? published4(a.partials + (uint64_t)(gridDim.y + sb + j) * pstride + c) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      }
 #pragma unroll
       for (uint32_t j = 0; j < 8; ++j) {
         t[j] = make_float4(id, id, id, id);
@@ -535,20 +576,22 @@ __global__ __launch_bounds__(kColBlock) void lt_col_reduce_kernel(const ColArgs 
         acc.z = red_combine(a.red, acc.z, t[j].z);
         acc.w = red_combine(a.red, acc.w, t[j].w);
       }
+      if (second) {
+#pragma unroll
+        for (uint32_t j = 0; j < 8; ++j) {
+          const float4 o = t2[NG ? j : 0];
+          acc2.x += o.x; acc2.y += o.y; acc2.z += o.z; acc2.w += o.w;
+        }
+      }
     }
   }
   __syncthreads();   // every wave has read its slot of the first exchange
-  lds[threadIdx.x] = acc;
-  __syncthreads();
-  if (wave != 0 || !nvalid) return;
-#pragma unroll
-  for (int w = 1; w < (int)kWaves; ++w) {
-    const float4 o = lds[w * 64 + lane];
-    acc.x = red_combine(a.red, acc.x, o.x);
-    acc.y = red_combine(a.red, acc.y, o.y);
-    acc.z = red_combine(a.red, acc.z, o.z);
-    acc.w = red_combine(a.red, acc.w, o.w);
+  if (second) {
+    meet(kRedSum, acc2);
+    __syncthreads();
   }
+  meet(a.red, acc);
+  if (wave != 0 || !nvalid) return;
   if (a.red == kRedMean) {
     const float inv = 1.0f / (float)a.rows;
     acc.x *= inv; acc.y *= inv; acc.z *= inv; acc.w *= inv;
@@ -556,6 +599,7 @@ __global__ __launch_bounds__(kColBlock) void lt_col_reduce_kernel(const ColArgs 
   Quad accq;
   accq.v[0] = acc.x; accq.v[1] = acc.y; accq.v[2] = acc.z; accq.v[3] = acc.w;
   run_post(a.post, post_regs, accq, c, nvalid);
+  if (second) run_second();
   args_touched(touched);
 }
 
@@ -671,6 +715,12 @@ static int mixed_kind(ColArgs* a) {
 hipError_t launch_col_reduce(const ColArgs& args, uint32_t grid_x, uint32_t grid_y, hipStream_t s) {
   const dim3 g(grid_x, grid_y), b(kColBlock);
   ColArgs a = args;
+  if (a.norm_grad) {   // (the lowering has looked at the program; cols % 4 == 0, whole vectors)
+    if ((a.cols % 4u) != 0u || (a.sum2 && a.red != kRedSum)) return hipErrorInvalidValue;
+    if (a.pro.in[a.vin[0]].dtype == kBF16) LT_LAUNCH((lt_col_reduce_kernel<16, 2, 8, true, 2, true>), g, b, s, a);
+    else LT_LAUNCH((lt_col_reduce_kernel<16, 2, 4, false, 2, true>), g, b, s, a);
+    return hipGetLastError();
+  }
   a.vin[0] = 0u; a.vin[1] = 1u; a.cin[0] = a.cin[1] = 0u;
   const int kind = (a.cols % 4u) == 0u ? stream_kind(a.pro) : 0;
   const uint32_t n_in = a.pro.n_in;

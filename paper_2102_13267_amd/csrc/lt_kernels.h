@@ -133,9 +133,17 @@ struct ColArgs {
   uint32_t* tickets;   // [gridDim.x], zero before launch; reset by the kernel
   uint32_t rows, cols, red;
   uint32_t narrow;     // set by launch_col_reduce: at most 64 columns and 65536 elements, one workgroup (see the kernel)
-  // filled in by launch_col_reduce for the streamed variants: input numbers of the (up to two)
-  // inputs read in full and of the (up to two) per-row inputs (kColVec), padded with the first
+  // filled in by launch_col_reduce for the streamed variants (by the lowering if norm_grad): input
+  // numbers of the (up to two) inputs read in full and of the (up to two) per-row inputs (kColVec),
+  // padded with the first
   uint32_t vin[2], cin[2];
+  // 1: the program is input vin[0] * ((input vin[1] - input cin[0]) * input cin[1]), a layer norm's
+  // weight gradient before its sum, and is not interpreted
+  uint32_t norm_grad;
+  // 1 (with norm_grad and a sum): the column sums of input vin[0] (the norm's bias gradient) ride along;
+  // their partials follow the others', post2 runs on them
+  uint32_t sum2;
+  EwProg post2;        // iteration space [cols]
 };
 
 // ---- row operators with a fixed body ---------------------------------------------------

@@ -983,8 +983,8 @@ struct Lowering {
   void touch(int32_t storage, int launch) {
     if (storage < 0) return;
     Storage& s = plan->storages[storage];
-    if (s.first_launch < 0) s.first_launch = launch;
-    s.last_launch = launch;
+    if (s.first_launch < 0 || launch < s.first_launch) s.first_launch = launch;   // (a region may ride in an earlier launch)
+    s.last_launch = std::max(s.last_launch, launch);
   }
 
   template <class T>
@@ -1271,13 +1271,14 @@ struct Lowering {
       add_prog_patches(launch, offsetof(ltk::AllArgs, post), post);
     } else {
       if (in_shape.size() != 2) return bad(LT_ERR_UNSUPPORTED, "axis-0 reduction needs a rank-2 operand (reshape first)");
-      if (ride_with_contraction(r, red, in_shape, pro, post)) return true;
+      if (ride_with_contraction(r, red, in_shape, pro, post) || ride_with_norm(r, red, in_shape, pro, post)) return true;
       ltk::ColArgs args{};
       args.pro = pro.prog;
       args.post = post.prog;
       args.rows = (uint32_t)in_shape[0];
       args.cols = (uint32_t)in_shape[1];
       args.red = red;
+      norm_grad_form(&args);
       Launch l = make_launch(L_COL, k, args);
       l.grid_x = (args.cols + 255) / 256;
       if (l.grid_x > kTickets) return bad(LT_ERR_UNSUPPORTED, "axis-0 reduction wider than 262144 columns");
@@ -1298,6 +1299,76 @@ struct Lowering {
     note_prog_storages(pro, launch);
     note_prog_storages(post, launch);
     return true;
+  }
+
+  // Is the program dy * ((x - mean) * rstd), dy and x whole tensors of one element type, mean and rstd
+  // one value per row?  Then the kernel computes it directly (ColArgs::norm_grad).
+  static void norm_grad_form(ltk::ColArgs* a) {
+    const ltk::EwProg& p = a->pro;
+    if (p.n_code != 3u || p.n_in != 4u || !p.fast || (a->cols % 4u) != 0u || p.n_slots > 16u) return;
+    struct In { uint32_t op, d, a, b; } c[3];
+    for (int i = 0; i < 3; ++i) c[i] = In{p.code[i] & 0xffu, (p.code[i] >> 8) & 31u, (p.code[i] >> 13) & 63u, (p.code[i] >> 19) & 63u};
+    uint32_t x, mean;
+    if (c[0].op == ltk::kSub) x = c[0].a, mean = c[0].b;
+    else if (c[0].op == ltk::kRsub) x = c[0].b, mean = c[0].a;
+    else return;
+    if (c[1].op != ltk::kMul || c[2].op != ltk::kMul || p.anchor_slot != c[2].d) return;
+    // (slots are reused: an operand is an input only while no instruction has written its slot)
+    auto fresh = [&](uint32_t s, int before) {
+      if (s >= p.n_in) return false;
+      for (int i = 0; i < before; ++i)
+        if (c[i].d == s) return false;
+      return true;
+    };
+    const uint32_t rstd = c[1].a == c[0].d ? c[1].b : c[1].a, dy = c[2].a == c[1].d ? c[2].b : c[2].a;
+    if (!((c[1].a == c[0].d) != (c[1].b == c[0].d)) || !((c[2].a == c[1].d) != (c[2].b == c[1].d))) return;
+    if (!fresh(x, 0) || !fresh(mean, 0) || !fresh(rstd, 1) || !fresh(dy, 2)) return;
+    auto whole = [&](uint32_t s) { return p.in[s].mode == ltk::kFull && p.in[s].fetch == ltk::kFetchVec4; };
+    auto row = [&](uint32_t s) { return p.in[s].mode == ltk::kColVec && p.in[s].dtype == ltk::kF32; };
+    if (!whole(dy) || !whole(x) || !row(mean) || !row(rstd) || p.in[dy].dtype != p.in[x].dtype) return;
+    if (p.in[dy].dtype != ltk::kF32 && p.in[dy].dtype != ltk::kBF16) return;
+    a->vin[0] = dy;
+    a->vin[1] = x;
+    a->cin[0] = mean;
+    a->cin[1] = rstd;
+    a->norm_grad = 1u;
+  }
+
+  // A layer norm's bias gradient sum(dy) next to its weight gradient sum(dy * xhat): the same dy, so the sum
+  // rides along in that launch (ColArgs::sum2), wherever it stands before this one -- if nothing from that launch
+  // on writes what this region's program reads, or touches what it writes.
+  bool ride_with_norm(const Region* r, uint32_t red, const std::vector<int64_t>& in_shape, const ProgBuild& pro, const ProgBuild& post) {
+    if (r->has_fin || red != ltk::kRedSum) return false;
+    if (pro.prog.n_code != 0u || pro.prog.n_in != 1u || pro.in_storage.size() != 1 || pro.prog.in[0].mode != ltk::kFull || !pro.scal_patch.empty() ||
+        post.prog.n_slots > 16u)
+      return false;
+    auto buffer_of = [&](int32_t st) -> int64_t {
+      if (st < 0) return INT64_MIN;
+      return plan->storages[st].param >= 0 ? -(int64_t)plan->storages[st].param - 1 : (int64_t)st;
+    };
+    for (size_t j = plan->launches.size(); j-- > 0;) {
+      Launch& l = plan->launches[j];
+      if (l.kind != L_COL) continue;
+      ltk::ColArgs* ca = (ltk::ColArgs*)l.args.data();
+      if (!ca->norm_grad || ca->sum2 || ca->red != ltk::kRedSum || ca->rows != (uint32_t)in_shape[0] || ca->cols != (uint32_t)in_shape[1]) continue;
+      if (ca->pro.in[ca->vin[0]].dtype != pro.prog.in[0].dtype || 2ull * l.grid_y * ca->cols > kPartialFloats) continue;
+      const uint32_t dy_off = (uint32_t)(offsetof(ltk::ColArgs, pro) + offsetof(ltk::EwProg, in) + ca->vin[0] * sizeof(ltk::EwIn) + offsetof(ltk::EwIn, ptr));
+      bool same = false, clear = true;
+      for (const PtrPatch& pp : plan->ptr_patches) {
+        if (pp.launch < j) continue;
+        if (pp.launch == j && pp.offset == dy_off) same = pp.storage == pro.in_storage[0].second && pp.byte_offset == pro.in_storage[0].byte_offset;
+        for (auto& is : post.in_storage) clear = clear && !(pp.write && buffer_of(pp.storage) == buffer_of(is.second));
+        for (auto& os : post.out_storage) clear = clear && buffer_of(pp.storage) != buffer_of(os.second);
+      }
+      if (!same || !clear) continue;
+      ca->sum2 = 1u;
+      ca->post2 = post.prog;
+      l.bytes += post.bytes;
+      add_prog_patches((uint32_t)j, offsetof(ltk::ColArgs, post2), post);
+      note_prog_storages(post, (int)j);
+      return true;
+    }
+    return false;
   }
 
   // A bias gradient next to its weight gradient: dW = x^T dy and db = sum over the rows of dy read

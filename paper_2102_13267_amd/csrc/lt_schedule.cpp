@@ -85,7 +85,7 @@ void schedule_streams(Plan* plan) {
     uint64_t floats = l.grid_x, tickets = 1;
     if (l.kind == L_COL) {
       const ltk::ColArgs* a = (const ltk::ColArgs*)l.args.data();
-      floats = (uint64_t)l.grid_y * ((a->cols + 3u) & ~3u);
+      floats = (uint64_t)l.grid_y * ((a->cols + 3u) & ~3u) * (a->sum2 ? 2u : 1u);
       tickets = l.grid_x;
     } else if (l.kind == L_GEMM) {
       {
