@@ -75,3 +75,19 @@ def test_bias_gradient_keeps_its_own_launch_when_it_must(ctx):  # noqa: F811
     for variant in range(6):
         for i, (p, q) in enumerate(zip(prog(ctx, variant), prog(E, variant))):
             check(ctx, E, p, q, 4e-5, (variant, i))
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("rows,cols", [(1, 8), (3, 256), (5, 504), (4097, 512), (130, 520), (4100, 1024), (33, 1032), (70, 2048), (9, 2056), (6, 4096), (5, 1028)])
+def test_norm_forward_and_backward(ctx, rows, cols, dt):  # noqa: F811
+    """One to eight chunks per lane, a last chunk that few lanes have, more rows than waves (a wave walks
+    several), columns that are no whole chunks; a row of large equal values next to a row of minus ones."""
+    E, data = Eager(), operands(rows, cols, dt)
+    data[0][-1] = 1000.0 + np.arange(cols) % 2 * 8                       # (a large mean: 8 is representable next to it in bf16)
+
+    def prog(B):
+        x, dy, w, b = (B.tensor(t, dtype=dt) for t in data)
+        y, mu, rs = B.layer_norm(x, w, b, eps=1e-5)
+        return y, mu, rs, B.layer_norm_grad(dy, x, w, mu, rs)
+    for i, (p, q) in enumerate(zip(prog(ctx), prog(E))):
+        check(ctx, E, p, q, 2e-2 if dt == "bf16" else 2e-5, i)
