@@ -243,7 +243,7 @@ static lt_status execute(lt_ctx* ctx, Plan* plan, const std::vector<BufRef>& par
     size_t top = kPartialFloats * sizeof(float) + kTickets * sizeof(uint32_t);
     for (size_t s = 0; s < ns; ++s) {
       const Storage& st = plan->storages[s];
-      if (st.param >= 0 || st.bound_to_root) continue;
+      if (st.param >= 0 || st.bound_to_root || st.optional) continue;
       const size_t need = (std::max<size_t>(st.bytes, 1) + 255) & ~(size_t)255;
       if (need > ctx->static_scratch_bytes - top)
         return fail(ctx, LT_ERR_OOM, "lt_barrier_static: the plan's temporaries need more than the " +
@@ -273,9 +273,10 @@ static lt_status execute(lt_ctx* ctx, Plan* plan, const std::vector<BufRef>& par
     std::vector<void*> tp(ns, nullptr);
     for (size_t li = 0; li < plan->launches.size(); ++li) {
       for (size_t s : born[li])
-        if (!(tp[s] = trial.alloc(plan->storages[s].bytes)))
+        if (!plan->storages[s].optional && !(tp[s] = trial.alloc(plan->storages[s].bytes)))
           return fail(ctx, LT_ERR_OOM, "workspace arena exhausted: the plan's temporaries and results do not fit");
-      for (size_t s : dies[li]) trial.release(tp[s]);
+      for (size_t s : dies[li])
+        if (tp[s]) trial.release(tp[s]);
     }
   }
   // Several streams: only when the schedule found independent work, no per-launch timing is
@@ -412,7 +413,7 @@ static lt_status execute(lt_ctx* ctx, Plan* plan, const std::vector<BufRef>& par
     const Launch& l = plan->launches[li];
     if (!upfront)
       for (size_t s : born[li])
-        if (!fresh(s)) return give_up(fail(ctx, LT_ERR_OOM, "internal: the arena differs from its trial run"));
+        if (!plan->storages[s].optional && !fresh(s)) return give_up(fail(ctx, LT_ERR_OOM, "internal: the arena differs from its trial run"));
     args = l.args;
     for (; pp < plan->ptr_patches.size() && plan->ptr_patches[pp].launch == li; ++pp) {
       const PtrPatch& p = plan->ptr_patches[pp];
@@ -425,7 +426,7 @@ static lt_status execute(lt_ctx* ctx, Plan* plan, const std::vector<BufRef>& par
       float f = (float)(p.reciprocal ? 1.0 / v : v);
       std::memcpy(args.data() + p.offset, &f, sizeof(float));
     }
-    if (real) {
+    if (real && !(l.needs >= 0 && !ptr[l.needs])) {   // (short of memory: one stream, so no event is waited for)
       // reductions that may run next to each other work in different quarters of the scratch
       if (l.kind == L_ALL) {
         ltk::AllArgs* a = (ltk::AllArgs*)args.data();

@@ -119,6 +119,7 @@ struct Storage {
   size_t bytes = 0;      // param < 0: a fresh arena allocation of this size
   int first_launch = 0, last_launch = 0;
   bool bound_to_root = false;
+  bool optional = false; // a workspace that the plan can do without (Launch::needs): not taken when memory is short
 };
 
 struct PtrPatch {
@@ -145,6 +146,8 @@ struct Launch {
   // stream waits for it, and its quarter of the reduction scratch
   uint8_t stream = 0, record = 0, scratch_slot = 0;
   std::vector<uint32_t> waits;
+  // >= 0: an optional storage; without it this launch is left out (the one before does its work)
+  int32_t needs = -1;
 };
 
 struct RootBind {

@@ -372,7 +372,7 @@ __global__ __launch_bounds__(kGemmThreads, BM == 64 ? 2 : 1) void lt_gemm_kernel
         for (int r = 0; r < 16; ++r) acc[i][j][r] += accs[NCH - 1][i][j][r];
   }
   // split-K: this workgroup's partial product goes to its own fp32 copy of the output, row major
-  float* const raw = a.splits > 1u ? a.split_ws + (size_t)split * ((size_t)a.batch0 * a.batch1 * a.m * a.n) : nullptr;
+  float* const raw = a.split_ws ? a.split_ws + (size_t)split * ((size_t)a.batch0 * a.batch1 * a.m * a.n) : nullptr;
   epilogue<BM, BN, MB, NB>(a, acc, (float*)smem, tile_m, tile_n, wave_m, wave_n, lane, batch, raw);
 }
 
@@ -904,7 +904,7 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
   if (a.tile_m != a.tile_n || (a.tile_m != 64u && a.tile_m != 128u)) return hipErrorInvalidValue;
   const bool big = a.tile_m == 128u;   // the host picks big tiles only when they still give every compute unit work
   const uint32_t bm = a.tile_m;
-  if (a.splits == 0u) return hipErrorInvalidValue;
+  if (a.splits == 0u || (a.splits > 1u && !a.split_ws)) return hipErrorInvalidValue;
   const dim3 grid((a.n + bm - 1) / bm, (a.m + bm - 1) / bm, batch * a.splits);
   if (grid.y > 65535u || grid.z > 65535u) return hipErrorInvalidValue;
   // (a lane's offset into a panel is a 32-bit number of bytes: 128 rows of less than 2^23 elements)

@@ -482,7 +482,7 @@ __global__ __launch_bounds__(kGemmThreads, 2) void lt_gemm_bf16_kernel(const Gem
   }
 
   // split-K: this workgroup's partial product goes to its own fp32 copy of the output, row major
-  float* const raw = a.splits > 1u ? a.split_ws + (size_t)split * ((size_t)a.batch0 * a.batch1 * a.m * a.n) : nullptr;
+  float* const raw = a.split_ws ? a.split_ws + (size_t)split * ((size_t)a.batch0 * a.batch1 * a.m * a.n) : nullptr;
   epilogue<BM, BN, MB, NB>(a, acc, (float*)smem, tile_m, tile_n, wave_m, wave_n, lane, batch, raw);
 }
 
@@ -522,7 +522,7 @@ static void launch_tile(const GemmArgs& a, dim3 grid, hipStream_t s) {
 hipError_t launch_gemm_bf16(const GemmArgs& a, hipStream_t s) {
   const uint32_t batch = a.batch0 * a.batch1;
   const uint32_t tiles = a.tiles_m * a.tiles_n;
-  if (a.splits == 0u || (uint64_t)batch * a.splits > 65535u) return hipErrorInvalidValue;
+  if (a.splits == 0u || (a.splits > 1u && !a.split_ws) || (uint64_t)batch * a.splits > 65535u) return hipErrorInvalidValue;
   if (a.tile_m != 128u || (a.tile_n != 128u && a.tile_n != 64u)) return hipErrorInvalidValue;
   if (a.tiles_m != (a.m + a.tile_m - 1) / a.tile_m || a.tiles_n != (a.n + a.tile_n - 1) / a.tile_n) return hipErrorInvalidValue;
   const dim3 grid(tiles, batch * a.splits);

@@ -181,6 +181,7 @@ struct GemmArgs {
   // Split-K (the LDS-staged kernels): `splits` workgroups share an output tile, each contracting a
   // slice of k and leaving its fp32 partial product, row major, in split_ws[split]; the post
   // program then runs in a second launch (SplitPostArgs) that adds the partials up in split order.
+  // With splits = 1 and split_ws set the product goes there as it is, for the second launch.
   uint32_t splits, tile_m, tile_n;   // workgroup tile: 128 rows, 128 or 64 columns
   uint32_t direct;           // 1: the one-launch kernel for small fp32 products (tiles of 32 x 32 or 64 x 32)
   float* split_ws;           // [splits][batch * m * n] floats

@@ -1860,6 +1860,18 @@ struct Lowering {
     }
   }
 
+  // A post program that the contraction's epilogue interprets two quads at a time, an input at a time (an
+  // optimiser update: three inputs of two types, thirteen instructions).  With 200 rows of 512 columns, 16 tiles, that
+  // was 65 of a weight gradient's 69 us; the product through a workspace and the program in a second launch over
+  // the whole chip take 9 together.  (Programs of one or two inputs of one type go eight quads at a time.)
+  static bool heavy_post(const ltk::EwProg& p) {
+    if (p.n_code < 6u) return false;
+    bool wide = p.n_in <= 2u && p.n_slots <= 8u;
+    for (uint32_t i = 0; i < p.n_in; ++i)
+      wide = wide && p.in[i].dtype == p.in[0].dtype && p.in[i].fetch == ltk::kFetchVec4 && (p.in[i].mode == ltk::kFull || p.in[i].mode == ltk::kRowVec);
+    return !wide;
+  }
+
   bool emit_gemm(int k, Region* r, const std::vector<int32_t>& post_m_in, const std::vector<Val>& out_in) {
     const int32_t a = r->anchor;
     const Node* an = nd[a];
@@ -1951,11 +1963,12 @@ struct Lowering {
       const uint64_t slices = (uint64_t)(kk + 63) / 64;
       uint64_t splits = std::min<uint64_t>({512 / std::max<uint64_t>(tiles, 1), slices / 4, 16});
       if (r->sealed) splits = 1;   // the second launch writes the dense layout only
-      if (splits > 1) {
-        args.splits = (uint32_t)splits;
+      if (splits > 1 || (!r->sealed && heavy_post(post.prog))) {
+        args.splits = (uint32_t)std::max<uint64_t>(splits, 1);
         Storage ws;
+        ws.optional = splits <= 1;
         ws.param = -1;
-        ws.bytes = (size_t)((uint64_t)splits * (uint64_t)batch * m * n * sizeof(float));
+        ws.bytes = (size_t)((uint64_t)args.splits * (uint64_t)batch * m * n * sizeof(float));
         ws.first_launch = launch;
         ws.last_launch = launch + 1;
         ws_storage = (int32_t)plan->storages.size();
@@ -2027,11 +2040,12 @@ struct Lowering {
           }
         }
       }
-      if (splits > 1) {
-        args.splits = (uint32_t)splits;
+      if (splits > 1 || (!r->sealed && !args.direct && heavy_post(post.prog))) {
+        args.splits = (uint32_t)std::max<uint64_t>(splits, 1);
         Storage ws;
+        ws.optional = splits <= 1;
         ws.param = -1;
-        ws.bytes = (size_t)(splits * (uint64_t)batch * m * n * sizeof(float));
+        ws.bytes = (size_t)(args.splits * (uint64_t)batch * m * n * sizeof(float));
         ws.first_launch = launch;
         ws.last_launch = launch + 1;
         ws_storage = (int32_t)plan->storages.size();
@@ -2040,7 +2054,10 @@ struct Lowering {
     }
     if (ws_storage >= 0) {
       // two launches: the contraction proper (no post program), then partial sums + post program
-      args.post = ltk::EwProg{};
+      // (a workspace that the plan can do without: the contraction carries the post program as well, and runs
+      // it when it is given no workspace)
+      const bool optional = plan->storages[ws_storage].optional;
+      if (!optional) args.post = ltk::EwProg{};
       Launch l = make_launch(L_GEMM, k, args);
       l.flops = 2ull * (uint64_t)batch * m * n * kk;
       l.bytes = (uint64_t)batch * ((uint64_t)m * kk + (uint64_t)kk * n) * dtype_size(A.dtype);
@@ -2054,7 +2071,12 @@ struct Lowering {
       pa.prog = post.prog;
       pa.splits = args.splits;
       pa.stride = (uint64_t)batch * m * n;
+      if (optional) {
+        add_prog_patches(launch, offsetof(ltk::GemmArgs, post), post);
+        note_prog_storages(post, launch);
+      }
       Launch l2 = make_launch(L_SPLITPOST, k, pa);
+      if (optional) l2.needs = ws_storage;
       l2.grid_x = ew_grid(post.prog.n);
       l2.bytes = post.bytes;
       plan->launches.push_back(std::move(l2));
