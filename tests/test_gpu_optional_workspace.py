@@ -1,0 +1,54 @@
+"""GPU parity (-m gpu) of a weight gradient whose optimiser update runs in a second launch over a workspace
+that the plan can do without: with it, without it because the library's static scratch is used, and
+without it because the caller's workspace is too small (8 MiB, half of them taken by the library's scratch,
+against 4.2 MiB and more of product) -- the same bits, and the oracle's values."""
+import numpy as np
+import pytest
+
+from oracle.numeric import Eager, round_to_bf16
+from test_gpu_parity import rel_err, rng
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dt,m,n,k", [("bf16", 512, 512, 200), ("bf16", 1028, 1040, 200), ("bf16", 100, 70, 130), ("bf16", 130, 1028, 33), ("f32", 1100, 1030, 70), ("f32", 1028, 1024, 64)])
+def test_update_in_a_second_launch_or_in_the_contraction(dt, m, n, k):
+    from paper_2102_13267_amd import Context
+    g, rnd = rng(m + n + k), (round_to_bf16 if dt == "bf16" else (lambda t: t))
+    x, dy, w = (rnd(g.standard_normal(s, dtype=np.float32)) for s in ((k, m), (k, n), (m, n)))
+    m0, v0 = g.standard_normal((m, n), dtype=np.float32), np.abs(g.standard_normal((m, n), dtype=np.float32)) + 0.5
+
+    def run(B, mk):
+        tx, tdy, tw = (mk(t, dt) for t in (x, dy, w))
+        tm, tv = mk(m0, "f32"), mk(v0, "f32")
+        for t in (3, 4):
+            gr = B.matmul(tx, tdy, trans_a=True)
+            m1 = B.add(B.mul(tm, 0.9), gr, alpha=0.1)
+            v1 = B.add(B.mul(tv, 0.999), B.square(gr), alpha=0.001)
+            step = B.div(B.mul(B.div(m1, 1.0 - 0.9 ** t), 0.1), B.add(B.sqrt(B.div(v1, 1.0 - 0.999 ** t)), 1e-8))
+            p1 = B.sub(tw, step)
+            B.assign(tw, B.cast(p1, "bf16") if dt == "bf16" else p1)
+            B.assign(tm, m1)
+            B.assign(tv, v1)
+            del gr, m1, v1, step, p1
+            yield B
+        yield [tw, tm, tv]
+    results = []
+    for size, static in ((256 << 20, False), (256 << 20, True), (8 << 20, False)):
+        c = Context(device=0, workspace_bytes=size)
+        it = run(c, lambda a, d, c=c: c.tensor(a.copy(), dtype=d, donatable=True))
+        for _ in range(2):
+            next(it)
+            info = c.barrier_static() if static else c.barrier()
+            assert info.n_launches == 2
+        results.append([c.fetch(t).copy() for t in next(it)])
+        c.close()
+    for other in results[1:]:
+        for a, b in zip(results[0], other):
+            assert np.array_equal(a, b)
+    E = Eager()
+    it = run(E, lambda a, d: E.tensor(a.copy(), dtype=d))
+    next(it)
+    next(it)
+    for a, r in zip(results[0], next(it)):
+        assert rel_err(a, E.fetch(r)) <= (2e-2 if dt == "bf16" else 2e-5)
