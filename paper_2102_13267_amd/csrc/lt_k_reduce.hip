@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstdio>
 
 #include "lt_launch.h"
 #include "lt_reduce.h"
@@ -644,6 +645,9 @@ static void launch_row_stream(const RowArgs& a, dim3 g, hipStream_t s) {
   else if (a.n_vin == 1u) LT_LAUNCH((lt_row_reduce_stream_kernel<1, 1, Q, RAG>), g, b, s, a);
   else if (a.n_rin == 0u) LT_LAUNCH((lt_row_reduce_stream_kernel<2, 0, Q, RAG>), g, b, s, a);
   else LT_LAUNCH((lt_row_reduce_stream_kernel<2, 1, Q, RAG>), g, b, s, a);
+  char name[64];
+  snprintf(name, sizeof(name), "lt_row_reduce_stream_kernel<%u, %u, %d, %s>", a.n_vin, a.n_rin, Q, RAG ? "true" : "false");
+  note_kernel(name);
 }
 
 hipError_t launch_row_reduce(const RowArgs& args, uint32_t grid, hipStream_t s) {
