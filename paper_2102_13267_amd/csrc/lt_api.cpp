@@ -966,7 +966,8 @@ lt_status lt_dump_schedule(lt_ctx* ctx, char* buf, size_t cap, size_t* len) {
   if (!ctx) return LT_ERR_ARG;
   std::string s;
   if (ctx->last_plan) {
-    static const char* const kinds[] = {"EW", "ROW", "ALL", "COL", "ROWOP", "MM", "SPLITPOST", "SLICE"};
+    static const char* const kinds[] = {"EW", "ROW", "ALL", "COL", "ROWOP", "MM", "SPLITPOST", "SLICE", "ATTN"};
+    static_assert(sizeof(kinds) / sizeof(kinds[0]) == kLaunchKinds, "a name per kind of launch");
     const Plan& p = *ctx->last_plan;
     for (size_t i = 0; i < p.launches.size(); ++i) {
       const Launch& l = p.launches[i];

@@ -113,6 +113,7 @@ struct Handle {
 // ---- a lowered, cached program ------------------------------------------------------------
 
 enum LaunchKind : uint8_t { L_EW, L_ROW, L_ALL, L_COL, L_ROWOP, L_GEMM, L_SPLITPOST, L_SLICE, L_ATTN };
+constexpr size_t kLaunchKinds = L_ATTN + 1;
 
 struct Storage {
   int param = -1;        // >= 0: the buffer of device parameter `param` (input, or donated output)
