@@ -957,8 +957,8 @@ class Tracer:
 
         # -- pass 3: donation.  A root whose old buffer was donated is written in place
         # when (i) inside the writing region the donor is only read index-aligned (by
-        # elementwise members, directly -- never as the anchor's operand, through a
-        # view or by a permute) and (ii) every other region that reads the donor can
+        # elementwise members of its own shape, directly -- never as the anchor's operand,
+        # through a view, broadcast or by a permute) and (ii) every other region that reads the donor can
         # be ordered before the writer.  (ii) is enforced by adding reader->writer
         # ordering edges, which is refused when the reader depends on the writer.
         param_nodes = [i for i in range(N) if nd[i].op == DEVICE_DATA]   # ordinal = position
@@ -993,7 +993,7 @@ class Tracer:
                             if (m == rw["anchor"] and nd[m].op == SLICE_UPDATE and x in pn and x == rins[m][0]
                                     and base(rins[m][1]) not in pn):
                                 continue
-                            if m == rw["anchor"] or x not in pn or nd[m].op in (PERMUTE, EXPAND, RESHAPE, NARROW):
+                            if m == rw["anchor"] or x not in pn or nd[m].shape != nd[x[0]].shape or nd[m].op in (PERMUTE, EXPAND, RESHAPE, NARROW):
                                 ok = False
                 else:
                     readers.append(r)

@@ -19,7 +19,8 @@
 //             regions of equal shape are merged; never through a view, never if the region graph
 //             would get a cycle, never beyond the caps (8 inputs, 8 outputs, inputs + members <= 32).
 //   pass 3    donation: a root may overwrite its donated input when all other readers can be
-//             ordered first (ordering edges are added) and the writer reads it index-aligned.
+//             ordered first (ordering edges are added) and the writer reads it index-aligned (directly,
+//             by members of the input's own shape).
 //   pass 4    regions run in topological order, smallest id (anchor, else first member) first.
 #include <algorithm>
 #include <cstdlib>
@@ -466,8 +467,9 @@ struct Lowering {
               if (names_donor(base(x))) {
                 // a window update may overwrite its own base (operand 0, read in place) ...
                 if (m == rw->anchor && nd[m]->op == LT_OP_SLICE_UPDATE && names_donor(x) && x == rins[m][0] && !names_donor(base(rins[m][1]))) continue;
-                // ... everything else must read the donor position by position
-                if (m == rw->anchor || !names_donor(x) || nd[m]->op == LT_OP_PERMUTE || nd[m]->op == LT_OP_EXPAND ||
+                // ... everything else must read the donor position by position (an operand of another
+                // shape is broadcast: x[64, 64] * b[64] summed over rows into b)
+                if (m == rw->anchor || !names_donor(x) || shape_of(m) != out_shape(x) || nd[m]->op == LT_OP_PERMUTE || nd[m]->op == LT_OP_EXPAND ||
                     nd[m]->op == LT_OP_RESHAPE || nd[m]->op == LT_OP_NARROW)
                   ok = false;
               }
