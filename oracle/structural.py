@@ -958,7 +958,7 @@ class Tracer:
         # -- pass 3: donation.  A root whose old buffer was donated is written in place
         # when (i) inside the writing region the donor is only read index-aligned (by
         # elementwise members of its own shape, directly -- never as the anchor's operand,
-        # through a view, broadcast or by a permute) and (ii) every other region that reads the donor can
+        # through a view, broadcast or by a permute, and no one-element donor by a larger finaliser) and (ii) every other region that reads the donor can
         # be ordered before the writer.  (ii) is enforced by adding reader->writer
         # ordering edges, which is refused when the reader depends on the writer.
         param_nodes = [i for i in range(N) if nd[i].op == DEVICE_DATA]   # ordinal = position
@@ -995,6 +995,9 @@ class Tracer:
                                 continue
                             if m == rw["anchor"] or x not in pn or nd[m].shape != nd[x[0]].shape or nd[m].op in (PERMUTE, EXPAND, RESHAPE, NARROW):
                                 ok = False
+                    # a finaliser reads its one-element operands once per element it walks
+                    if r["fin_shape"] is not None and math.prod(r["fin_shape"]) > 1 and math.prod(nd[v[0]].shape) == 1:
+                        ok = False
                 else:
                     readers.append(r)
             if ok and any(reachable(rw, r) for r in readers):

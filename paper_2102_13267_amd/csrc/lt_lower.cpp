@@ -20,7 +20,8 @@
 //             would get a cycle, never beyond the caps (8 inputs, 8 outputs, inputs + members <= 32).
 //   pass 3    donation: a root may overwrite its donated input when all other readers can be
 //             ordered first (ordering edges are added) and the writer reads it index-aligned (directly,
-//             by members of the input's own shape).
+//             by members of the input's own shape, and no one-element input that a finaliser of
+//             more elements reads).
 //   pass 4    regions run in topological order, smallest id (anchor, else first member) first.
 #include <algorithm>
 #include <cstdlib>
@@ -456,12 +457,14 @@ struct Lowering {
       for (int32_t pi : pnode) leaves += live[pi] && nd[pi]->buffer.get() == buf;
       if (leaves > 1) ok = false;
       std::vector<Region*> readers;
+      bool inside = false;   // the writing region reads the donor itself
       for (Region* r : alive_regions) {
         bool reads = false;
         for (int32_t m : r->members)
           for (Val x : rins[m]) reads |= names_donor(base(x));
         if (!reads) continue;
         if (r == rw) {
+          inside = true;
           for (int32_t m : r->members)
             for (Val x : rins[m])
               if (names_donor(base(x))) {
@@ -477,6 +480,10 @@ struct Lowering {
           readers.push_back(r);
         }
       }
+      // A finaliser computes its one-element members anew for every element it walks, by many threads
+      // and (in a launch of its own) many workgroups: what one of them reads -- a running maximum --
+      // cannot be overwritten by the first to finish.
+      if (inside && rw->has_fin && count(rw->fin_shape) > 1 && count(out_shape(v)) == 1) ok = false;
       if (ok)
         for (Region* r : readers) ok &= !reachable(rw, r);
       if (!ok) continue;

@@ -25,11 +25,14 @@ and in-place updates only where nothing can observe the old value (section 4.3):
   7. an in-place entry `v->pK` writes a region output of parameter K's dtype and shape; K is claimed
      once; no later region reads K, no other result is K itself, and inside the writing region K is
      read only position by position (a direct operand of an elementwise member, not through a view,
-     not by the anchor, not by a permutation).
+     not by the anchor, not by a permutation), and not at all when K has one element and the region
+     walks more behind its anchor (every thread would read K, and one of them overwrites it).
 """
 from __future__ import annotations
 
 import struct
+
+import numpy as np
 
 DEVICE_DATA, SCALAR_PARAM, CONSTANT = 1, 2, 3
 ADD, SUB, MUL, DIV = 32, 33, 34, 35
@@ -318,10 +321,13 @@ def check_plan(key: bytes, n_nodes: int, plan_text: str):
             for k2 in range(k + 1, len(regions)):
                 for w in regions[k2]["inputs"]:
                     need(not is_donor(base(w)), f"R{k}: parameter {p} is overwritten before R{k2} reads it")
+            size = lambda shape: int(np.prod(shape, dtype=np.int64))                          # noqa: E731
+            walks = max(size(nodes[m].shape) for m in after | {a}) if r["kind"] not in ("EW", "SLICE") else size(nodes[r["members"][0]].shape)
             for m in r["members"]:
                 for w in operands(m):
                     if w[0] in members or is_immediate(w) or not is_donor(base(w)):
                         continue
+                    need(size(nodes[leaf].shape) != 1 or walks == 1, f"R{k}: one-element parameter {p} is overwritten while {walks} elements read it (member {m})")
                     if m == a and nodes[m].op == SLICE_UPDATE and w == (leaf, 0) and w == operands(m)[0] and not is_donor(base(operands(m)[1])):
                         continue        # a window update rewrites part of its own base: the rest stays as it is
                     need(w == (leaf, 0) and m != a and nodes[m].op not in (PERMUTE, EXPAND, RESHAPE, NARROW) and nodes[m].shape == nodes[leaf].shape,

@@ -64,3 +64,27 @@ def test_broadcast_operand_values():
         B.assign(b, B.mul(B.sum(B.mul(x, b), 1), 1 / 320))
         return [b]
     values(build, [x, (b,)])
+
+
+def running_scale(B, x, s):
+    """A running maximum kept in s, and x scaled by it."""
+    r = B.add(B.mul(s, 0.9), B.mul(B.amax(B.abs(x)), 0.1))
+    out = B.div(x, r)
+    B.assign(s, r)
+    return [out, s]
+
+
+@pytest.mark.parametrize("n,in_place", [(1, True), (4, False), (1000, False), (2048, False), (2052, False), (65536, False), (65537, True)])
+def test_a_running_scalar_that_a_finaliser_reads(n, in_place):
+    """Up to 65,536 elements x / r is the finaliser of the maximum and computes r for each of its
+    elements; beyond, and for a single one, r is computed once."""
+    plan = plans(lambda B, mk: running_scale(B, mk((n,)), mk((), True)))
+    assert ("->p" in plan) == in_place, plan
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [1, 5, 1000, 1025, 2048, 2052, 65536, 65537])
+def test_running_scalar_values(n):
+    """1e-5 of the norm: a handful of fp32 roundings."""
+    x = np.random.Generator(np.random.PCG64(n)).standard_normal(n).astype(np.float32)
+    values(running_scale, [x, (np.float32(3.0).reshape(()),)])
