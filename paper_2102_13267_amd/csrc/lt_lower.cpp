@@ -1696,6 +1696,7 @@ struct Lowering {
     if (!view(sc.node, 0, &q) || !view(sc.node, 1, &k) || !view(pvn, 1, &v) || !view(pvn, 0, &p)) return false;
     const int64_t d = q.cols, sq = q.rows, sk = k.cols;
     if (sk > 4096) return false;   // (longer rows are refused, as by the row operator)
+    if (sq == 0 || sk == 0 || std::find(q.lead.begin(), q.lead.end(), 0) != q.lead.end()) return false;   // (nothing to launch: the parts know how)
     if ((d != 32 && d != 64 && d != 128) || v.cols != d || v.rows != sk || p.rows != sq || p.cols != sk) return false;
     if (q.s_col != 1 || k.s_row != 1 || v.s_col != 1 || q.lead.size() > 2 || k.lead != q.lead || v.lead != q.lead || p.lead != q.lead) return false;
     if (out_dtype(Val{pvn, 0}) != dt) return false;

@@ -30,3 +30,9 @@ def launches(dt, sq, sk, h=2, d=64, backward=True):
 def test_schedule_names_the_launches_of_the_core():
     assert launches("bf16", 128, 128) == ["ATTN"] * 3
     assert launches("f32", 70, 33, backward=False) == ["ATTN"]
+
+
+def test_empty_sides_keep_the_parts():
+    """No keys (a context of zeros), no queries: the parts' launches take them."""
+    for sq, sk in ((128, 0), (0, 128)):
+        assert "ATTN" not in launches("f32", sq, sk) and "ATTN" not in launches("bf16", sq, sk, backward=False)

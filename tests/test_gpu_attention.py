@@ -118,3 +118,9 @@ def test_results_that_are_other_shapes_of_a_computed_value(ctx):  # noqa: F811
     got, ref = prog(ctx, ctx.tensor(a), ctx.tensor(b)), prog(E, E.tensor(a), E.tensor(b))
     for i, (x, y) in enumerate(zip(got, ref)):
         check(ctx, E, x, y, 1e-5, i)
+
+
+def test_no_keys(ctx):  # noqa: F811
+    """A context over no keys at all is zero, as the parts give it."""
+    z = lambda n: ctx.tensor(np.ones((n, 64), np.float32))                                   # noqa: E731
+    assert not np.any(ctx.fetch(ctx.matmul(ctx.softmax(ctx.matmul(z(70), z(0), trans_b=True)), z(0))))
