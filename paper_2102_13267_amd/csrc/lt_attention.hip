@@ -22,8 +22,8 @@
 // very p and dp that the second walk uses: as the row sum of dy * o, with o rounded to bf16, it left the
 // rows of ds with a sum that is not zero, which a key bias's gradient (exactly zero) showed.
 //
-// Rows past the end are copies of the last one on the register side (never stored) and zero in LDS,
-// with their scores at minus infinity (forward, dq) or their reciprocal sum at zero (dk, dv).
+// Rows past the end are copies of the last one on the register side (never stored) and zero in LDS, with
+// their scores set to minus infinity (forward) or their probabilities (dq, dk, dv) and gradients (dk, dv) to zero.
 #include <hip/hip_runtime.h>
 
 #include <cstdio>
@@ -366,6 +366,11 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 1 : 2) void lt_attention_dkv_k
           s[r] = __builtin_amdgcn_exp2f((s[r] - m[e]) * kLog2e) * inv[e];
           ds[r] = s[r] * (ds[r] - delta[e]);
         }
+      }
+      if (q0 + G::TK > a.sq) {   // (zeros in LDS are not enough: 0 * inf, a key or value that is not finite)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (q0 + b * 32u + (r >> 2) * 8u + 4u * h + (r & 3) >= a.sq) s[r] = ds[r] = 0.0f;
       }
       add_rows<T, D>(dv, Ds, b, s, lane);
       add_rows<T, D>(dk, Qs, b, ds, lane);

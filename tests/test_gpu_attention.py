@@ -124,3 +124,27 @@ def test_no_keys(ctx):  # noqa: F811
     """A context over no keys at all is zero, as the parts give it."""
     z = lambda n: ctx.tensor(np.ones((n, 64), np.float32))                                   # noqa: E731
     assert not np.any(ctx.fetch(ctx.matmul(ctx.softmax(ctx.matmul(z(70), z(0), trans_b=True)), z(0))))
+
+
+@pytest.mark.parametrize("dt", ["bf16", "f32"])
+@pytest.mark.parametrize("s,d", [(64, 64), (70, 64), (33, 32), (129, 128)])
+def test_a_key_that_no_query_attends_to(ctx, s, d, dt):  # noqa: F811
+    """A key with minus infinity in a column where every query is positive has probability 0 and gets
+    gradients of 0, whether or not the last block of queries is whole; its neighbours are unaffected.  (dq is 0 * inf.)"""
+    E = Eager()
+    q, k, v, dy = operands(s + d, dt, 1, s, s, 1, d)
+    q[:, 3] = np.abs(q[:, 3]) + 0.5
+    q = round_to_bf16(q) if dt == "bf16" else q
+    k[5, 3] = -np.inf
+    out = []
+    for B in (ctx, E):
+        qt, kt, vt, dt_ = (B.tensor(t, dtype=dt) for t in (q, k, v, dy))
+        p = B.softmax(B.matmul(qt, kt, trans_b=True))
+        ds = B.softmax_grad(B.matmul(dt_, vt, trans_b=True), p)
+        out.append([B.matmul(p, vt), B.matmul(ds, kt), B.matmul(ds, qt, trans_a=True), B.matmul(p, dt_, trans_a=True)])
+    assert sum(n.startswith("lt_attention") for n in kinds(ctx)) == 3
+    for i in (0, 2, 3):
+        x, y = ctx.fetch(out[0][i]), E.fetch(out[1][i])
+        assert np.all(np.isfinite(x)), i
+        assert np.max(np.abs(x - y)) <= (2e-2 if dt == "bf16" else 2e-5) * np.max(np.abs(y)), i
+    assert not np.any(ctx.fetch(out[0][2])[5]) and not np.any(ctx.fetch(out[0][3])[5])
