@@ -196,6 +196,9 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 1 : 2) void lt_attention_kerne
   v16f acc[G::DB];
   clear<T, D>(acc);
   float m = -INFINITY, l = 0.0f;   // of this lane's query; l over this half's rows
+  // (a power of two of at most 1 / keys on every term, in l as well: unnormalised, values of the type's highest few
+  // powers of two would add up to infinity)
+  const float shrink = __builtin_amdgcn_ldexpf(1.0f, -(32 - (int)__clz((int)(a.sk - 1u))));
   U4 kr[G::N], vr[G::N];
   block_fetch<T, D>(kr, kp, a.k.s_row, 0, a.sk);
   block_fetch<T, D>(vr, vp, a.v.s_row, 0, a.sk);
@@ -233,7 +236,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 1 : 2) void lt_attention_kerne
     for (int b = 0; b < G::NB; ++b) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        s[b][r] = __builtin_amdgcn_exp2f((s[b][r] - base) * kLog2e);
+        s[b][r] = __builtin_amdgcn_exp2f((s[b][r] - base) * kLog2e) * shrink;
         l += s[b][r];
       }
       add_rows<T, D>(acc, Vs, b, s[b], lane);
@@ -247,7 +250,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 1 : 2) void lt_attention_kerne
   if (a.stats && h == 0u) {
     const uint64_t i = (uint64_t)bh * a.sq + q, n = (uint64_t)a.batch0 * a.batch1 * a.sq;
     a.stats[i] = m;
-    a.stats[n + i] = inv;
+    a.stats[n + i] = inv * shrink;
   }
 }
 

@@ -148,3 +148,18 @@ def test_a_key_that_no_query_attends_to(ctx, s, d, dt):  # noqa: F811
         assert np.all(np.isfinite(x)), i
         assert np.max(np.abs(x - y)) <= (2e-2 if dt == "bf16" else 2e-5) * np.max(np.abs(y)), i
     assert not np.any(ctx.fetch(out[0][2])[5]) and not np.any(ctx.fetch(out[0][3])[5])
+
+
+@pytest.mark.parametrize("dt", ["bf16", "f32"])
+@pytest.mark.parametrize("s", [1, 3, 200, 1025])
+def test_values_near_the_largest(ctx, s, dt):  # noqa: F811
+    """An average of values near the type's largest is finite."""
+    E, d = Eager(), 64
+    q, k, _, _ = operands(s, dt, 1, s, s, 1, d)
+    v = np.full((s, d), 2.0 ** 127, np.float32)
+    out = []
+    for B in (ctx, E):
+        qt, kt, vt = (B.tensor(t, dtype=dt) for t in (q, k, v))
+        out.append(B.matmul(B.softmax(B.matmul(qt, kt, trans_b=True)), vt))
+    assert kinds(ctx)[0].startswith("lt_attention_kernel")
+    check(ctx, E, *out, 2e-2 if dt == "bf16" else 1e-5)
