@@ -260,15 +260,20 @@ static lt_status execute(lt_ctx* ctx, Plan* plan, const std::vector<BufRef>& par
       if (plan->storages[s].param < 0 && plan->storages[s].bound_to_root && !fresh(s))
         return fail(ctx, LT_ERR_OOM, "workspace arena exhausted: the plan's results do not fit");
   } else {
-    for (size_t s = 0; s < ns && upfront; ++s)
-      if (plan->storages[s].param < 0) upfront = fresh(s);
+    // (first with the storages that the plan can do without, then without them)
+    for (int with_optional = 1; with_optional >= 0; --with_optional) {
+      upfront = true;
+      for (size_t s = 0; s < ns && upfront; ++s)
+        if (plan->storages[s].param < 0 && (with_optional || !plan->storages[s].optional)) upfront = fresh(s);
+      if (upfront) break;
+      for (size_t s = 0; s < ns; ++s)
+        if (plan->storages[s].param < 0) {
+          (*storage_bufs)[s].reset();
+          ptr[s] = nullptr;
+        }
+    }
   }
   if (!upfront) {
-    for (size_t s = 0; s < ns; ++s)
-      if (plan->storages[s].param < 0) {
-        (*storage_bufs)[s].reset();
-        ptr[s] = nullptr;
-      }
     Arena trial = ctx->arena;
     std::vector<void*> tp(ns, nullptr);
     for (size_t li = 0; li < plan->launches.size(); ++li) {
@@ -426,7 +431,7 @@ static lt_status execute(lt_ctx* ctx, Plan* plan, const std::vector<BufRef>& par
       float f = (float)(p.reciprocal ? 1.0 / v : v);
       std::memcpy(args.data() + p.offset, &f, sizeof(float));
     }
-    if (real && !(l.needs >= 0 && !ptr[l.needs])) {   // (short of memory: one stream, so no event is waited for)
+    if (real) {
       // reductions that may run next to each other work in different quarters of the scratch
       if (l.kind == L_ALL) {
         ltk::AllArgs* a = (ltk::AllArgs*)args.data();
@@ -453,7 +458,10 @@ static lt_status execute(lt_ctx* ctx, Plan* plan, const std::vector<BufRef>& par
         if (e != hipSuccess) return give_up(hip_fail(ctx, "hipStreamWaitEvent", e));
       }
       if (prof) (void)hipEventRecord(ctx->events[2 * li], ctx->stream);
-      hipError_t e = launch_one(l, args.data(), stream);
+      // (a launch whose optional workspace is not there is left out: the one before has done its work.  Its
+      // waits and its event stay, so the order of the others is the schedule's)
+      const bool left_out = l.needs >= 0 && !ptr[l.needs];
+      hipError_t e = left_out ? hipSuccess : launch_one(l, args.data(), stream);
       if (e != hipSuccess) return give_up(hip_fail(ctx, kind_name(l.kind), e));
       if (prof) {
         if (launch_names.size() <= li) launch_names.resize(plan->launches.size());

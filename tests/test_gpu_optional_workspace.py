@@ -52,3 +52,42 @@ def test_update_in_a_second_launch_or_in_the_contraction(dt, m, n, k):
     next(it)
     for a, r in zip(results[0], next(it)):
         assert rel_err(a, E.fetch(r)) <= (2e-2 if dt == "bf16" else 2e-5)
+
+
+def adam_steps(c, n_steps, data):
+    """Adam on a 1028 x 1040 weight whose gradient is a contraction in bf16; results after n_steps."""
+    x, dy, w, m0, v0 = data
+    tx, tdy, tw = (c.tensor(t, dtype="bf16", donatable=True) for t in (x, dy, w))
+    tm, tv = (c.tensor(t.copy(), donatable=True) for t in (m0, v0))
+    for _ in range(n_steps):
+        gr = c.matmul(tx, tdy, trans_a=True)
+        m1 = c.add(c.mul(tm, 0.9), gr, alpha=0.1)
+        v1 = c.add(c.mul(tv, 0.999), c.square(gr), alpha=0.001)
+        p1 = c.sub(tw, c.div(c.mul(m1, 0.1), c.add(c.sqrt(v1), 1e-8)))
+        c.assign(tw, c.cast(p1, "bf16"))
+        c.assign(tm, m1)
+        c.assign(tv, v1)
+        del gr, m1, v1, p1
+        c.barrier()
+    return [c.fetch(t).copy() for t in (tw, tm, tv)]
+
+
+def adam_data():
+    g = rng(11)
+    x, dy, w = (round_to_bf16(g.standard_normal(s, dtype=np.float32)) for s in ((200, 1028), (200, 1040), (1028, 1040)))
+    return x, dy, w, g.standard_normal((1028, 1040), dtype=np.float32), np.abs(g.standard_normal((1028, 1040), dtype=np.float32)) + 0.5
+
+
+def test_a_step_short_of_the_optional_workspace_keeps_its_graphs():
+    """8 MiB hold everything the step needs but the product's workspace: it runs without that, and as one
+    HIP graph from the third repetition on, like the step with all its memory; the same bits."""
+    from paper_2102_13267_amd import Context
+    results = []
+    for size in (256 << 20, 8 << 20):
+        c = Context(device=0, workspace_bytes=size)
+        c.set_graphs(True)
+        results.append(adam_steps(c, 6, adam_data()))
+        assert c.stats().graph_launches > 0, size
+        c.close()
+    for a, b in zip(*results):
+        assert np.array_equal(a, b)
