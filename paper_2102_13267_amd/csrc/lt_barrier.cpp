@@ -284,6 +284,13 @@ static lt_status execute(lt_ctx* ctx, Plan* plan, const std::vector<BufRef>& par
         if (tp[s]) trial.release(tp[s]);
     }
   }
+  // (a launch whose optional workspace is not there is left out: the one before does its work)
+  std::vector<char> left_out(plan->launches.size(), 0);
+  size_t n_run = 0;
+  for (size_t li = 0; li < plan->launches.size(); ++li) {
+    left_out[li] = plan->launches[li].needs >= 0 && !ptr[plan->launches[li].needs];
+    n_run += !left_out[li];
+  }
   // Several streams: only when the schedule found independent work, no per-launch timing is
   // asked for, and the workspace holds every temporary at once (memory given back while the step
   // is still being enqueued could be handed to a launch that runs next to its last reader).
@@ -331,7 +338,7 @@ static lt_status execute(lt_ctx* ctx, Plan* plan, const std::vector<BufRef>& par
       g.used = ++gs.clock;
       for (size_t li = 0; li < plan->launches.size(); ++li)
         for (size_t s : dies[li]) (*storage_bufs)[s].reset();   // behind the graph on the caller's stream
-      ctx->stats.kernels_launched += plan->launches.size();
+      ctx->stats.kernels_launched += n_run;
       ctx->stats.graph_launches++;
       return LT_OK;
     }
@@ -458,10 +465,8 @@ static lt_status execute(lt_ctx* ctx, Plan* plan, const std::vector<BufRef>& par
         if (e != hipSuccess) return give_up(hip_fail(ctx, "hipStreamWaitEvent", e));
       }
       if (prof) (void)hipEventRecord(ctx->events[2 * li], ctx->stream);
-      // (a launch whose optional workspace is not there is left out: the one before has done its work.  Its
-      // waits and its event stay, so the order of the others is the schedule's)
-      const bool left_out = l.needs >= 0 && !ptr[l.needs];
-      hipError_t e = left_out ? hipSuccess : launch_one(l, args.data(), stream);
+      // (the waits and the event of a launch that is left out stay, so the order of the others is the schedule's)
+      hipError_t e = left_out[li] ? hipSuccess : launch_one(l, args.data(), stream);
       if (e != hipSuccess) return give_up(hip_fail(ctx, kind_name(l.kind), e));
       if (prof) {
         if (launch_names.size() <= li) launch_names.resize(plan->launches.size());
@@ -482,7 +487,7 @@ static lt_status execute(lt_ctx* ctx, Plan* plan, const std::vector<BufRef>& par
       (*storage_bufs)[s].reset();
       ptr[s] = nullptr;
     }
-    ctx->stats.kernels_launched++;
+    if (!left_out[li]) ctx->stats.kernels_launched++;
   }
   if (multi) {
     hipError_t e = join_streams();
@@ -501,7 +506,7 @@ static lt_status execute(lt_ctx* ctx, Plan* plan, const std::vector<BufRef>& par
       ctx->stats.graph_launches++;
       ctx->stats.graphs_built++;
     } else {
-      ctx->stats.kernels_launched -= plan->launches.size();
+      ctx->stats.kernels_launched -= n_run;
       for (size_t s : deferred) (*storage_bufs)[s].reset();
       for (size_t s = 0; s < ns; ++s)
         if (plan->storages[s].param < 0) (*storage_bufs)[s].reset();
@@ -514,6 +519,7 @@ static lt_status execute(lt_ctx* ctx, Plan* plan, const std::vector<BufRef>& par
     hipError_t e = hipStreamSynchronize(ctx->stream);
     if (e != hipSuccess) return hip_fail(ctx, "hipStreamSynchronize", e);
     for (size_t li = 0; li < plan->launches.size(); ++li) {
+      if (left_out[li]) continue;
       lt_launch_record r{};
       std::snprintf(r.kernel, sizeof(r.kernel), "%s", li < launch_names.size() && !launch_names[li].empty() ? launch_names[li].c_str()
                                                                                                         : kind_name(plan->launches[li].kind));

@@ -91,3 +91,16 @@ def test_a_step_short_of_the_optional_workspace_keeps_its_graphs():
         c.close()
     for a, b in zip(*results):
         assert np.array_equal(a, b)
+
+
+def test_a_launch_left_out_is_not_reported():
+    """Without its workspace the step is one launch: one record with a time of its own, one launch counted."""
+    from paper_2102_13267_amd import Context
+    for size, n in ((256 << 20, 2), (8 << 20, 1)):
+        c = Context(device=0, workspace_bytes=size)
+        c.set_profiling(True)
+        adam_steps(c, 3, adam_data())
+        records = c.last_launches()
+        assert len(records) == n and c.stats().kernels_launched == 3 * n
+        assert all(r["ms"] > 0 for r in records) and "gemm" in records[0]["kernel"]
+        c.close()
