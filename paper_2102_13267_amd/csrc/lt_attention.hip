@@ -23,7 +23,9 @@
 // rows of ds with a sum that is not zero, which a key bias's gradient (exactly zero) showed.
 //
 // Rows past the end are copies of the last one on the register side (never stored) and zero in LDS, with
-// their scores set to minus infinity (forward) or their probabilities (dq, dk, dv) and gradients (dk, dv) to zero.
+// their scores at minus infinity (forward) or their probabilities at zero (dq).  The dk / dv pass has a copy of the last
+// query and its maximum there, but a reciprocal sum of zero: a probability of at most 1, times zero.  (Zeros in
+// the query's place meet a key with an infinity as 0 * inf.)
 #include <hip/hip_runtime.h>
 
 #include <cstdio>
@@ -334,7 +336,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 1 : 2) void lt_attention_dkv_k
     const uint32_t q = q0 + threadIdx.x;
     if (threadIdx.x < (uint32_t)G::TK) {
 #pragma unroll
-      for (int j = 0; j < 3; ++j) sr[j] = q < a.sq ? sp[(uint64_t)j * n + q] : 0.0f;
+      for (int j = 0; j < 3; ++j) sr[j] = j == 0 || q < a.sq ? sp[(uint64_t)j * n + min(q, a.sq - 1u)] : 0.0f;
     }
   };
   fetch(0);
@@ -346,7 +348,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 1 : 2) void lt_attention_dkv_k
   clear<T, D>(dv);
   for (uint32_t q0 = 0; q0 < a.sq; q0 += G::TK) {
     __syncthreads();
-    block_stash<T, D>(qr, Qs, q0, a.sq);
+    block_stash<T, D>(qr, Qs, q0, ~0u);   // (past the end: the last query again, see the top)
     block_stash<T, D>(dr, Ds, q0, a.sq);
     if (threadIdx.x < (uint32_t)G::TK) {
 #pragma unroll
@@ -369,11 +371,6 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 1 : 2) void lt_attention_dkv_k
           s[r] = __builtin_amdgcn_exp2f((s[r] - m[e]) * kLog2e) * inv[e];
           ds[r] = s[r] * (ds[r] - delta[e]);
         }
-      }
-      if (q0 + G::TK > a.sq) {   // (zeros in LDS are not enough: 0 * inf, a key or value that is not finite)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          if (q0 + b * 32u + (r >> 2) * 8u + 4u * h + (r & 3) >= a.sq) s[r] = ds[r] = 0.0f;
       }
       add_rows<T, D>(dv, Ds, b, s, lane);
       add_rows<T, D>(dk, Qs, b, ds, lane);
