@@ -31,6 +31,10 @@ __device__ __forceinline__ void run_post(const EwProg& post, const ProgRegs post
 // instead, and the elements that another lane (or an earlier vector) owns are left out of the fold.
 // Rows of a length that is no multiple of four start on any 4-byte boundary, which the hardware's
 // 16-byte loads accept.
+// A trip's values are added up pairwise before they join the lane's sum: few lanes to a row mean many values per
+// lane, and one after another they left a row's sum further from 64 bits than 256 lanes did.  Root mean square error of
+// rows of 1777 (8192) terms N(0, 1), in fp32 on the CPU: one by one 1.2e-7 (2.1e-7), pairwise 0.9e-7 (1.1e-7), 256 lanes
+// one by one 1.0e-7 (1.3e-7).
 typedef float RawVec4 __attribute__((ext_vector_type(4), aligned(4)));
 
 template <int NV, int NR, int Q, bool RAG>
@@ -91,21 +95,26 @@ __global__ __launch_bounds__(kBlock) void lt_row_reduce_stream_kernel(const RowA
           }
         }
         f = interp<NS, Q>(f, pro_regs, pro_n);
+        float part[Q];
         if (!RAG || c0 + (uint32_t)Q * step <= a.cols) {
 #pragma unroll
-          for (int j = 0; j < Q; ++j) acc = fold_vec(a.red, acc, rf_get<NS>(f, pro.anchor_slot + (uint32_t)(8 * j)), kVec);
+          for (int j = 0; j < Q; ++j) part[j] = fold_pairs(a.red, rf_get<NS>(f, pro.anchor_slot + (uint32_t)(8 * j)));
         } else {
+          const float id = red_identity(a.red);
 #pragma unroll
           for (int j = 0; j < Q; ++j) {
             const uint32_t cj = c + (uint32_t)j * step, at = min(cj, a.cols - (uint32_t)kVec);
-            const Quad q = rf_get<NS>(f, pro.anchor_slot + (uint32_t)(8 * j));
+            Quad q = rf_get<NS>(f, pro.anchor_slot + (uint32_t)(8 * j));
 #pragma unroll
-            for (int e = 0; e < kVec; ++e) {
-              const float t = red_combine(a.red, acc, q.v[e]);
-              acc = at + (uint32_t)e >= cj ? t : acc;
-            }
+            for (int e = 0; e < kVec; ++e) q.v[e] = at + (uint32_t)e >= cj ? q.v[e] : id;
+            part[j] = fold_pairs(a.red, q);
           }
         }
+#pragma unroll
+        for (int n = Q / 2; n > 0; n /= 2)
+#pragma unroll
+          for (int j = 0; j < n; ++j) part[j] = red_combine(a.red, part[2 * j], part[2 * j + 1]);
+        acc = red_combine(a.red, acc, part[0]);
       }
     }
     float r;

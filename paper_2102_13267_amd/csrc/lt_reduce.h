@@ -78,6 +78,11 @@ __device__ __forceinline__ float block_reduce(uint32_t red, float v, float* lds 
   return r;
 }
 
+// combine the four elements of a vector, pairwise
+__device__ __forceinline__ float fold_pairs(uint32_t red, const Quad& q) {
+  return red_combine(red, red_combine(red, q.v[0], q.v[1]), red_combine(red, q.v[2], q.v[3]));
+}
+
 // combine the (valid) element lanes of slot `slot`
 __device__ __forceinline__ float fold_vec(uint32_t red, float acc, const Quad& q, uint32_t nvalid) {
   if (nvalid > 0u) acc = red_combine(red, acc, q.v[0]);

@@ -25,3 +25,32 @@ def test_tanh_of_special_values(ctx):  # noqa: F811
     x = np.array([0.0, -0.0, 1e-40, -1e-40, 9.5, -9.5, 44.0, -100.0, 3e38, -3e38, np.inf, -np.inf, np.nan], np.float32)
     y, e = ctx.fetch(ctx.tanh(ctx.tensor(x))), np.tanh(x.astype(np.float64)).astype(np.float32)
     assert np.array_equal(y, e, equal_nan=True) and np.array_equal(np.signbit(y[:-1]), np.signbit(e[:-1]))
+
+
+def lanes_one_by_one(x, lanes):
+    """Row sums as `lanes` lanes add them up: each its groups of four columns one by one, then all of them pairwise."""
+    rows, cols = x.shape
+    steps = -(-cols // (4 * lanes))
+    t = np.zeros((rows, steps * 4 * lanes), np.float32)
+    t[:, :cols] = x
+    t = t.reshape(rows, steps, lanes, 4)
+    acc = np.zeros((rows, lanes), np.float32)
+    for s in range(steps):
+        for e in range(4):
+            acc = acc + t[:, s, :, e]
+    while acc.shape[1] > 1:
+        acc = acc[:, 0::2] + acc[:, 1::2]
+    return acc[:, 0]
+
+
+@pytest.mark.parametrize("rows,cols", [(4000, 100), (4000, 200), (3000, 513), (3001, 1777), (1500, 2000), (2100, 4097), (2100, 8192), (600, 8192), (1024, 1024)])
+def test_row_sums(ctx, rows, cols):  # noqa: F811
+    """Error of the sums of N(0, 1) terms: not above that of 256 lanes (64 below 512 columns) adding one by
+    one, the arrangement that gives a lane the fewest terms, but for what the estimate over so many rows scatters
+    (a relative 1 / sqrt(2 rows) each, 4 of them)."""
+    x = rng(rows + cols).standard_normal((rows, cols), dtype=np.float32)
+    e = x.astype(np.float64).sum(1)
+    got = ctx.fetch(ctx.sum(ctx.mul(ctx.tensor(x), ctx.tensor(np.ones(cols, np.float32))), axis=1))
+    ref = lanes_one_by_one(x, 256 if cols >= 512 else 64)
+    err = lambda s: np.linalg.norm(s - e) / np.linalg.norm(e)                                   # noqa: E731
+    assert err(got) <= err(ref) * (1 + 4 / np.sqrt(2 * rows)), (err(got), err(ref))
