@@ -294,14 +294,16 @@ static lt_status execute(lt_ctx* ctx, Plan* plan, const std::vector<BufRef>& par
   // Several streams: only when the schedule found independent work, no per-launch timing is
   // asked for, and the workspace holds every temporary at once (memory given back while the step
   // is still being enqueued could be handed to a launch that runs next to its last reader).
-  // And only for plans long enough to gain by it.  An edge between streams is an event recorded and
-  // an event waited for, about 10 us of the host's time, in which it would have enqueued three
-  // launches; in a short plan little runs next to anything and the host falls behind the device.
-  // One stream against four: 48 launches (a transformer layer's step) 1719 / 1497, 811 / 654 and
-  // 606 / 521 us, one of them 537 / 618; 4 to 14 launches (norm, attention, feed-forward block, head,
-  // small classifier) 64 / 80, 102 / 155, 343 / 373, 390 / 396, 196 / 206, 115 / 134, never better.
-  constexpr size_t kSpreadLaunches = 24;
-  const bool multi = real && !prof && !use_static && ctx->max_streams > 1 && plan->n_streams > 1 && upfront && plan->launches.size() >= kSpreadLaunches;
+  // And only for plans of many launches.  An edge between streams is an event recorded and an event waited
+  // for, about 10 us of the host's time, in which it would have enqueued three launches; in a short plan the host
+  // falls behind the device, and what runs next to each other shares a chip that each launch fills.  One stream
+  // against four, us: transformer layer steps (42 to 54 launches) of 32 x 256 x 1024 1480 / 1317, 16 x 256 x 1024
+  // 1182 / 1018, 4 x 256 x 1024 761 / 737, 32 x 256 x 256 636 / 662, 4 x 128 x 512 492 / 590; three feed-forward blocks in one
+  // plan (40 to 46) 561 / 535, 741 / 753, 320 / 367, two (26 to 30) 488 / 527, 372 / 393; 3 to 18 launches: feed-forward block
+  // 512 rows 102 / 135, 4096 374 / 383, 16384 1178 / 1288, head of 16384 rows 683 / 745, norm of 131072 rows 408 / 425, attention 8 x
+  // 1024 303 / 319, classifier 245 / 270.  Long launches are no reason either: at best, independent fp32 products and
+  // column sums of 8 x 16384 x 1024, 2400 / 2298.  (Where a plan of 30 launches and more gains is not a matter of their number alone.)
+  const bool multi = real && !prof && !use_static && ctx->max_streams > 1 && plan->n_streams > 1 && upfront && plan->launches.size() >= LT_SPREAD_LAUNCHES;
   ctx->last_launches.clear();
   if (prof) {
     while (ctx->events.size() < 2 * plan->launches.size()) {

@@ -104,3 +104,32 @@ def test_a_launch_left_out_is_not_reported():
         assert len(records) == n and c.stats().kernels_launched == 3 * n
         assert all(r["ms"] > 0 for r in records) and "gemm" in records[0]["kernel"]
         c.close()
+
+
+def test_streams_without_the_optional_workspaces():
+    """A transformer layer step on four streams, with all its memory, then 8 MiB short of that: the optimiser
+    updates' workspaces are left out, and with them launches that others are ordered behind; the same bits."""
+    from paper_2102_13267_amd import Context
+    from test_gpu_parity import spread
+    from workloads import programs
+    from workloads.inputs import c3_inputs
+    bsz, seq, d, ffn, heads = 2, 100, 1024, 4096, 16
+    inp, keys, results, counts, size = c3_inputs(bsz, seq, d, ffn), programs.C3_WEIGHTS + programs.C3_VECTORS, [], [], 1 << 30
+    for n_streams in (4, 4, 1):
+        c = Context(device=0, workspace_bytes=size)
+        c.set_streams(n_streams)
+        P = {k: c.tensor(round_to_bf16(inp[k]), dtype="bf16", donatable=True) for k in keys}
+        M, V = ({k: c.tensor(np.zeros_like(inp[k]), donatable=True) for k in keys} for _ in range(2))
+        xt, dyt = c.tensor(round_to_bf16(inp["x"]), dtype="bf16"), c.tensor(round_to_bf16(inp["dy"]), dtype="bf16")
+        for step in range(3):
+            y, dx = programs.c3_step(c, xt, dyt, P, M, V, heads, t=step + 1)
+            assert spread(c, c.barrier())
+        counts.append(c.stats().kernels_launched)
+        if size == 1 << 30:
+            size = c.stats().arena_bytes_peak - (8 << 20)
+        results.append([c.fetch(t) for t in [y, dx] + [D[k] for D in (P, M, V) for k in keys]])
+        c.close()
+    assert counts[0] > counts[1] == counts[2]
+    for other in results[1:]:
+        for a, b in zip(results[0], other):
+            assert np.array_equal(np.asarray(a).view(np.uint8), np.asarray(b).view(np.uint8))
