@@ -157,7 +157,7 @@ static hipError_t launch_one(const Launch& l, const uint8_t* args, hipStream_t s
     case L_ROWOP: return ltk::launch_row_op(*(const ltk::RowOpArgs*)args, l.grid_x, s);
     case L_GEMM: return ltk::launch_gemm(*(const ltk::GemmArgs*)args, s);
     case L_SPLITPOST: return ltk::launch_split_post(*(const ltk::SplitPostArgs*)args, l.grid_x, s);
-    case L_ATTN: return ltk::launch_attention ? ltk::launch_attention(*(const ltk::AttnArgs*)args, s) : hipErrorInvalidValue;
+    case L_ATTN: return ltk::launch_attention(*(const ltk::AttnArgs*)args, s);
     case L_SLICE: return ltk::launch_slice_update(*(const ltk::SliceArgs*)args, l.grid_x, s);
   }
   return hipErrorInvalidValue;

@@ -15,8 +15,7 @@ hipError_t launch_row_op(const RowOpArgs& a, uint32_t grid, hipStream_t s);
 hipError_t launch_split_post(const SplitPostArgs& a, uint32_t grid, hipStream_t s);
 hipError_t launch_slice_update(const SliceArgs& a, uint32_t grid, hipStream_t s);
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s);
-// (weak: the host files also link without the kernel files)
-__attribute__((weak)) hipError_t launch_attention(const AttnArgs& a, hipStream_t s);
+hipError_t launch_attention(const AttnArgs& a, hipStream_t s);
 hipError_t launch_gemm_bf16(const GemmArgs& a, hipStream_t s);   // 128 x 128 tiles, split-K (called by launch_gemm)
 
 // The library's static device scratch (lt_static_scratch.hip): its size, its address on `device`

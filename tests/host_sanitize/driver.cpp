@@ -120,6 +120,18 @@ int main() {
   CHECK(lt_op(ctx, LT_OP_LAYER_NORM, ln_in, 3, &eps, 1, ln, 3) == LT_OK);
   CHECK(lt_barrier(ctx, 1, &info) == LT_OK && info.n_regions >= 4 && info.flops_planned == 2ull * 128 * 64 * 32);
   (void)col; (void)loss;
+  // an attention core forward and backward (three launches for eight regions), and over no keys
+  for (int64_t keys : {int64_t{40}, int64_t{0}}) {
+    lt_tensor q = dev({2, 70, 64}), k = dev({2, keys, 64}), v = dev({2, keys, 64}), dy = dev({2, 70, 64});
+    const lt_attr ta = iattr(LT_ATTR_TRANS_A, 1), tb = iattr(LT_ATTR_TRANS_B, 1);
+    lt_tensor sc = op(LT_OP_MATMUL, {q, k}, {tb}), pr = op(LT_OP_SOFTMAX, {sc}), o = op(LT_OP_MATMUL, {pr, v});
+    lt_tensor dp = op(LT_OP_MATMUL, {dy, v}, {tb}), ds = op(LT_OP_SOFTMAX_GRAD, {dp, pr});
+    lt_tensor dq = op(LT_OP_MATMUL, {ds, k}), dk = op(LT_OP_MATMUL, {ds, q}, {ta}), dv = op(LT_OP_MATMUL, {pr, dy}, {ta});
+    for (lt_tensor t : {sc, pr, dp, ds}) CHECK(lt_release(ctx, t) == LT_OK);
+    CHECK(lt_barrier(ctx, 1, &info) == LT_OK && info.n_regions == 8 && info.n_launches == (keys ? 3 : 8));
+    CHECK((dump(lt_dump_schedule).find("ATTN") != std::string::npos) == (keys != 0));
+    for (lt_tensor t : {o, dq, dk, dv}) CHECK(lt_release(ctx, t) == LT_OK);
+  }
   // a weight gradient and the bias gradient next to it (the column sum rides in the contraction's
   // launch: two regions, one launch), a long k over few tiles (workgroups share tiles), and a pair
   // that must not share a launch (the column program reads what the contraction writes)

@@ -11,6 +11,7 @@ hipError_t launch_row_op(const RowOpArgs&, uint32_t, hipStream_t) { return hipEr
 hipError_t launch_split_post(const SplitPostArgs&, uint32_t, hipStream_t) { return hipErrorInvalidValue; }
 hipError_t launch_slice_update(const SliceArgs&, uint32_t, hipStream_t) { return hipErrorInvalidValue; }
 hipError_t launch_gemm(const GemmArgs&, hipStream_t) { return hipErrorInvalidValue; }
+hipError_t launch_attention(const AttnArgs&, hipStream_t) { return hipErrorInvalidValue; }
 hipError_t launch_gemm_bf16(const GemmArgs&, hipStream_t) { return hipErrorInvalidValue; }
 hipError_t static_scratch(int, void**, size_t*) { return hipErrorInvalidValue; }
 hipError_t launch_fill_u32(uint32_t*, uint32_t, uint32_t, hipStream_t) { return hipErrorInvalidValue; }
