@@ -186,6 +186,7 @@ void destroy_device_objects(Plan* plan) {
   for (GraphEntry& g : plan->graphs.entries)
     if (g.exec) (void)hipGraphExecDestroy(g.exec);
   plan->graphs.entries.clear();
+  if (plan->spare) destroy_device_objects(plan->spare.get());
 }
 
 // Bind this step's buffers and scalars into the cached plan and launch it.
@@ -626,6 +627,23 @@ static lt_status barrier_impl(lt_ctx* ctx, int blocking, lt_barrier_info* info, 
   for (size_t k = 0; k < params.size(); ++k) params[k] = ctx->nodes[cut.param_nodes[k]].buffer;
   for (size_t k = 0; k < scalars.size(); ++k) scalars[k] = ctx->nodes[cut.scalar_nodes[k]].value;
   lt_status st = execute(ctx, plan, params, scalars, &bufs, use_static);
+  if (st == LT_ERR_OOM && plan->merged) {   // (nothing has run: see Plan::spare)
+    if (!plan->spare) {
+      Cut whole;   // (a quick hit has not walked the trace)
+      collect_cut(ctx, &whole);
+      std::vector<uint8_t> same_key;
+      serialise_cut(ctx, &whole, &same_key);
+      const std::string why = ctx->err;
+      lt_status ls = LT_OK;
+      plan->spare = lower(ctx, whole, &ls, true);
+      ctx->err = why;
+      if (plan->spare) plan->spare->key = plan->key;
+    }
+    if (plan->spare) {
+      plan = plan->spare.get();
+      st = execute(ctx, plan, params, scalars, &bufs, use_static);
+    }
+  }
   if (st != LT_OK) return st;
   // what a captured step needs of this barrier (lt_step_capture)
   StepRecord& rec = ctx->last_step;

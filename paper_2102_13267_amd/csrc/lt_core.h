@@ -188,6 +188,11 @@ struct Plan {
   size_t temp_bytes = 0;             // arena bytes when no temporary is reused inside the step
   std::vector<hipEvent_t> events;    // one per launch with `record` set (created on first use)
   GraphSlots graphs;                 // lt_set_graphs
+  // Lowering regroups and merges launches where that saves time; a result may then be born earlier, or a
+  // reduced value need a place in memory.  `merged` says that it did; `spare` is the same program without any of it,
+  // lowered when a step does not fit the memory there is.
+  bool merged = false;
+  std::unique_ptr<Plan> spare;
 };
 
 // Fingerprint of the trace as it is being recorded (section 7 of the paper: hashing while the graph
@@ -317,8 +322,8 @@ void collect_cut(lt_ctx* ctx, Cut* cut);
 void serialise_cut(lt_ctx* ctx, Cut* cut, std::vector<uint8_t>* out);
 uint64_t fnv1a64(const uint8_t* p, size_t n);
 
-// lowering (lt_lower.cpp): returns nullptr and sets ctx->err / *status on failure
-std::unique_ptr<Plan> lower(lt_ctx* ctx, const Cut& cut, lt_status* status);
+// lowering (lt_lower.cpp): returns nullptr and sets ctx->err / *status on failure.  spare: see Plan
+std::unique_ptr<Plan> lower(lt_ctx* ctx, const Cut& cut, lt_status* status, bool spare = false);
 // stream schedule of a lowered plan (lt_schedule.cpp)
 void schedule_streams(Plan* plan);
 // 32 x 32 tiles of a one-launch small contraction whose workgroups share tiles (they exchange partial

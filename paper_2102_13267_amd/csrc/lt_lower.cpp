@@ -66,8 +66,9 @@ struct Lowering {
   std::vector<Region*> ordered;
   std::string err;
   lt_status status = LT_OK;
+  const bool merge;   // regroup and merge launches (not for a spare plan, nor with one region per op)
 
-  explicit Lowering(lt_ctx* c, const Cut& k) : ctx(c), cut(k), N((int32_t)k.order.size()) {}
+  Lowering(lt_ctx* c, const Cut& k, bool spare) : ctx(c), cut(k), N((int32_t)k.order.size()), merge(c->fusion && !spare) {}
 
   bool bad(lt_status s, const std::string& m) {
     if (status == LT_OK) {
@@ -1125,7 +1126,7 @@ struct Lowering {
   std::vector<char> elided;   // by position in `ordered`
   void elide_copies() {
     elided.assign(ordered.size(), 0);
-    if (!ctx->fusion) return;
+    if (!merge) return;
     for (size_t k = 0; k < ordered.size(); ++k) {
       const Region* r = ordered[k];
       if (r->kind != C_EW || r->members.size() != 1) continue;
@@ -1140,6 +1141,7 @@ struct Lowering {
       plan->storages[from].bytes = 0;
       storage_of[v.node][v.slot] = to;
       elided[k] = 1;
+      plan->merged = true;
     }
   }
 
@@ -1211,7 +1213,7 @@ struct Lowering {
     // value from memory: 65,536 elements 107 us as the tail of the reduction, 7 + 6 us as two
     // launches, 20,000 elements 42 us; 1024 elements 7.6 us as one launch, where a second one
     // would cost more than it gains.  (fp32 results only: a bf16 one would be rounded on the way.)
-    const bool split_fin = r->kind == C_ALL && r->has_fin && count(post_space) > 2048 && out_dtype(Val{a, 0}) == LT_F32;
+    const bool split_fin = merge && r->kind == C_ALL && r->has_fin && count(post_space) > 2048 && out_dtype(Val{a, 0}) == LT_F32;
     ProgBuild fin_head;
     if (split_fin) {
       if (storage_of[a][0] < 0) {
@@ -1219,6 +1221,7 @@ struct Lowering {
         ns.first_launch = -1;
         ns.bytes = sizeof(float);
         plan->storages.push_back(ns);
+        plan->merged = true;
         storage_of[a][0] = (int32_t)plan->storages.size() - 1;
       }
       const std::vector<int32_t> only{a};
@@ -1347,7 +1350,7 @@ struct Lowering {
   // rides along in that launch (ColArgs::sum2), wherever it stands before this one -- if nothing from that launch
   // on writes what this region's program reads, or touches what it writes.
   bool ride_with_norm(const Region* r, uint32_t red, const std::vector<int64_t>& in_shape, const ProgBuild& pro, const ProgBuild& post) {
-    if (r->has_fin || red != ltk::kRedSum) return false;
+    if (!merge || r->has_fin || red != ltk::kRedSum) return false;
     if (pro.prog.n_code != 0u || pro.prog.n_in != 1u || pro.in_storage.size() != 1 || pro.prog.in[0].mode != ltk::kFull || !pro.scal_patch.empty() ||
         post.prog.n_slots > 16u)
       return false;
@@ -1370,6 +1373,7 @@ struct Lowering {
         for (auto& os : post.out_storage) clear = clear && buffer_of(pp.storage) != buffer_of(os.second);
       }
       if (!same || !clear) continue;
+      plan->merged = true;
       ca->sum2 = 1u;
       ca->post2 = post.prog;
       l.bytes += post.bytes;
@@ -1774,7 +1778,7 @@ struct Lowering {
     const int n = (int)ordered.size();
     std::vector<int> order;
     for (int k = 0; k < n; ++k) order.push_back(k);
-    if (!ctx->fusion) return order;
+    if (!merge) return order;
     for (int k = 0; k < n; ++k) {
       Attn t;
       if (ordered[k]->kind == C_ROW && nd[ordered[k]->anchor]->op == LT_OP_SOFTMAX && match_attention(k, &t)) attns.push_back(t);
@@ -1808,7 +1812,10 @@ struct Lowering {
           if (group[k] == pick) order.push_back(k);
         for (int j : succ[pick]) indeg[j]--;
       }
-      if ((int)order.size() == n) return order;
+      if ((int)order.size() == n) {
+        plan->merged = true;
+        return order;
+      }
       attns.pop_back();
       order.clear();
       for (int k = 0; k < n; ++k) order.push_back(k);
@@ -2111,8 +2118,8 @@ struct Lowering {
 
 }  // namespace
 
-std::unique_ptr<Plan> lower(lt_ctx* ctx, const Cut& cut, lt_status* status) {
-  Lowering L(ctx, cut);
+std::unique_ptr<Plan> lower(lt_ctx* ctx, const Cut& cut, lt_status* status, bool spare) {
+  Lowering L(ctx, cut, spare);
   for (int32_t idx : cut.order) L.nd.push_back(&ctx->nodes[idx]);
   std::unique_ptr<Plan> plan(new Plan());
   L.plan = plan.get();
