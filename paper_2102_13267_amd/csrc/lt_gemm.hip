@@ -50,7 +50,7 @@ template <int BX> struct Tile<float, BX> {
 };
 // Number of 16-byte groups per lane and k-slice for an operand tile of BX x BK elements.
 template <typename T, int BX> struct Groups {
-  static constexpr int N = BX * Elem<T>::BK / Elem<T>::G / kGemmThreads;   // 128: 2, 64: 1
+  static constexpr int N = BX * Elem<T>::BK / Elem<T>::G / kGemmThreads;   // 128: 4, 64: 2
 };
 
 // (a native vector type, not HIP's uint4 struct: sets of the struct kind that are only ever moved

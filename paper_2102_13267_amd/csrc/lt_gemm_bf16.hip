@@ -511,8 +511,8 @@ static void launch_tile(const GemmArgs& a, dim3 grid, hipStream_t s) {
 
 }  // namespace bf
 
-// a.tile_m, a.tile_n: rows and columns per workgroup tile (128 x 128, or 128 x 64 for narrow outputs).  The kernel is written for 128 or 256; only 128 is built: the
-// 256 x 128 variant needs more than the 256 registers that two wavefronts per SIMD leave each, and
+// a.tile_m, a.tile_n: rows and columns per workgroup tile (128 x 128, or 128 x 64 for narrow outputs).  A
+// 256 x 128 tile needs more than the 256 registers that two wavefronts per SIMD leave each, and
 // measured slower both ways (two workgroups per compute unit with spills, or one with 385 registers).
 // A 256 x 256 tile (128 x 128 per wave, one workgroup per compute unit, 512 registers) runs its main
 // loop at twice the matrix-core utilisation of this one (54 % against 28 %), but the layer's shapes

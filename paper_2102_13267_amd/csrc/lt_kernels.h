@@ -182,8 +182,10 @@ struct GemmArgs {
   // slice of k and leaving its fp32 partial product, row major, in split_ws[split]; the post
   // program then runs in a second launch (SplitPostArgs) that adds the partials up in split order.
   // With splits = 1 and split_ws set the product goes there as it is, for the second launch.
-  uint32_t splits, tile_m, tile_n;   // workgroup tile: 128 rows, 128 or 64 columns
-  uint32_t direct;           // 1: the one-launch kernel for small fp32 products (tiles of 32 x 32 or 64 x 32)
+  // Workgroup tile: bf16 128 x 128 or 128 x 64; fp32 128 x 128 or 64 x 64, and for direct = 1, the one-launch
+  // kernel for small products, 16 x 16, 16 x 64, 32 x 32 or 64 x 32.
+  uint32_t splits, tile_m, tile_n;
+  uint32_t direct;
   float* split_ws;           // [splits][batch * m * n] floats
   // The one-launch small kernel (direct = 1) with splits > 1: `splits` workgroups share a tile;
   // split_ws then holds [tile][split][tile_m x tile_n] partial tiles and tickets[tile]

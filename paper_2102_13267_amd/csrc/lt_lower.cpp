@@ -1878,9 +1878,12 @@ struct Lowering {
   }
 
   // A post program that the contraction's epilogue interprets two quads at a time, an input at a time (an
-  // optimiser update: three inputs of two types, thirteen instructions).  With 200 rows of 512 columns, 16 tiles, that
-  // was 65 of a weight gradient's 69 us; the product through a workspace and the program in a second launch over
-  // the whole chip take 9 together.  (Programs of one or two inputs of one type go eight quads at a time.)
+  // optimiser update: three inputs of two types, thirteen instructions).  Any number of tiles: the epilogue is
+  // exposed in every workgroup, and the product's way through a workspace is cheaper even where it no longer fits the
+  // caches.  Weight gradient with Adam, in the contraction / in a second launch, us, bf16: 512 x 512 from 200 rows 59.6 /
+  // 17.4, 2048 x 2048 from 200 71.5 / 39.8, 4096 x 4096 from 64, 1024, 4096 136 / 103, 172 / 139, 275 / 250, 8192 x 4096 from
+  // 4096 560 / 504; fp32: 1024 x 1024 from 64 19.6 / 19.7 (the closest), 4096 x 4096 from 64, 1024, 4096 258 / 170, 486 / 405,
+  // 1260 / 1139.  (Programs of one or two inputs of one type go eight quads at a time.)
   static bool heavy_post(const ltk::EwProg& p) {
     if (p.n_code < 6u) return false;
     bool wide = p.n_in <= 2u && p.n_slots <= 8u;
@@ -1995,7 +1998,8 @@ struct Lowering {
     if (A.dtype == LT_F32) {
       // 64 x 64 tiles unless 128 x 128 ones still give every compute unit a workgroup; a long k
       // over few tiles is split until about two workgroups per compute unit exist (one hides the
-      // other's slice boundaries: loads landing, the barrier), each with >= 4 slices of 16.
+      // other's slice boundaries: loads landing, the barrier), each with at least 64 of k (two of the
+      // kernel's slices).
       // Measured on [B, 2048] x [2048, 2048]: B = 1024 as 512 unsplit tiles of 64 x 64 runs at
       // 85 TFLOP/s (128 x 128 tiles split in two: 78); B = 256 at 54 split in four, 37 unsplit.
       const uint64_t big_tiles = (uint64_t)((m + 127) / 128) * ((n + 127) / 128) * (uint64_t)batch;
