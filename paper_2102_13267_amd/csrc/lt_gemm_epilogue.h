@@ -3,12 +3,12 @@
 #define LT_GEMM_EPILOGUE_H_
 #include <hip/hip_runtime.h>
 
+#include "lt_chain.h"
 #include "lt_interp.h"
 
 namespace ltk {
 
 constexpr int kGemmThreads = 256;
-constexpr int kCPad = 4;
 
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
@@ -122,7 +122,8 @@ __device__ __forceinline__ int post_stream_kind(const EwProg& p) {
 // tile is written once, then every lane walks it in row-major 4-element quads, so the post
 // program sees flat, contiguous indices exactly like the elementwise kernel does (16-byte loads
 // of residuals, 16-byte stores) and is compiled in only once.
-template <int BM, int BN, int MB, int NB>
+// BF: the operands are bf16.
+template <bool BF, int BM, int BN, int MB, int NB>
 __device__ __forceinline__ void epilogue(const GemmArgs& a, const v16f (&acc)[MB][NB], float* Cs, uint32_t tile_m,
                                          uint32_t tile_n, uint32_t wave_m, uint32_t wave_n, uint32_t lane, uint32_t batch,
                                          float* raw = nullptr) {
@@ -164,6 +165,10 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, const v16f (&acc)[MB
         if (col + 3 < a.n) dst[3] = t.w;
       }
     }
+    return;
+  }
+  if (a.chain.n) {
+    run_chain<BF, BM, BN, kGemmThreads>(a, load_chain_regs(a), Cs, threadIdx.x, tile_m, tile_n, base);
     return;
   }
   // Whole aligned 4-vectors, at most four inputs (none of them strided) and eight slots: no bounds

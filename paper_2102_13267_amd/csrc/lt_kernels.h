@@ -168,6 +168,25 @@ struct GemmOperand {
   int64_t s_row, s_col, s_b0, s_b1;
 };
 
+//
+// A post program that is a chain -- one running value per element, each step combining it with nothing, a scalar
+// or an input, results stored on the way -- is also laid out as such.  The epilogues then evaluate it with the
+// running values in registers the compiler has numbered: no slot is looked up, copied out or copied back, and
+// 32 elements of a lane share the decoding of a step.
+constexpr int kMaxChain = 8;
+enum : uint32_t { kSrcNone = 0, kSrcScal, kSrcRow0, kSrcRow1, kSrcFull0, kSrcFull1 };
+constexpr uint32_t kNoOut = 0xff;
+// step word: op[7:0] src[11:8] scal[19:12] out[27:20].  With v the running value, s the source and c the scalar: an op's
+// first operand is v, its second s, and its reversed form takes them the other way round; kFma: v * c + s, kRfma: s * c + v.
+constexpr uint32_t kRfma = kNumOps;
+struct Chain {
+  uint32_t n;                  // steps + 1; 0: the program is no chain
+  uint32_t n_row, n_full;      // inputs addressed by column, inputs addressed like the output (up to two of each),
+  uint32_t row[2], full[2];    // their input numbers
+  uint32_t first_out;          // the output that is the product itself, or kNoOut
+  uint32_t step[kMaxChain];    // out: the output that is the running value after the step, or kNoOut
+};
+
 struct GemmArgs {
   GemmOperand a, b;
   uint32_t m, n, k;
@@ -182,7 +201,7 @@ struct GemmArgs {
   // slice of k and leaving its fp32 partial product, row major, in split_ws[split]; the post
   // program then runs in a second launch (SplitPostArgs) that adds the partials up in split order.
   // With splits = 1 and split_ws set the product goes there as it is, for the second launch.
-  // Workgroup tile: bf16 128 x 128 or 128 x 64; fp32 128 x 128 or 64 x 64, and for direct = 1, the one-launch
+  // Workgroup tile: bf16 256 x 256, 256 x 128, 128 x 128 or 128 x 64; fp32 128 x 128 or 64 x 64, and for direct = 1, the one-launch
   // kernel for small products, 16 x 16, 16 x 64, 32 x 32 or 64 x 32.
   uint32_t splits, tile_m, tile_n;
   uint32_t direct;
@@ -193,6 +212,9 @@ struct GemmArgs {
   // partials up in split order, runs the post program and resets the ticket).
   uint32_t* tickets;
   EwProg post;               // iteration space = the output
+  // post as a chain, for the LDS-staged kernels: every input and output has the operands' type, columns come in
+  // whole 16-byte chunks
+  Chain chain;
   // The one-launch small kernel can carry the column sums of its B operand ([k, n], rows
   // contiguous) along: a weight gradient x^T dy and the bias gradient sum_rows(dy) read the same
   // dy.  col_sum = 1: the workgroups of the first tile row add up the columns of B they fetch
