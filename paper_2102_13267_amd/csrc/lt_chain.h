@@ -8,8 +8,8 @@
 // values stay where they are, an operand is at most copied once, a bias is loaded once per lane (a lane's
 // columns are the same in all its rows), and loads and stores are 16 bytes wide.  8192 x 4096 x 1024 in bf16 with bias,
 // GELU and both results stored, tiles of 128 x 128: 124.8 -> 108.2 us, with bias alone 101.5 -> 89.5 (stored as it is:
-87 to 89), through GELU's gradient 117.2 -> 103.9.  With 16 elements of a lane per trip the first takes 2 us
-longer, with 8 or 4 it takes 12.
+// 87 to 89), through GELU's gradient 117.2 -> 103.9.  With 16 elements of a lane per trip the first takes 2 us
+// longer, with 8 or 4 it takes 12.
 #ifndef LT_CHAIN_H_
 #define LT_CHAIN_H_
 #include <hip/hip_runtime.h>
