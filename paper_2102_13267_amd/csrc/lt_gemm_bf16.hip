@@ -263,7 +263,17 @@ __global__ __launch_bounds__(kGemmThreads, 2) void lt_gemm_bf16_kernel(const Gem
   const uint32_t nt = gridDim.x;
   uint32_t t = blockIdx.x;
   if ((nt & 7u) == 0u) t = (blockIdx.x & 7u) * (nt >> 3) + (blockIdx.x >> 3);
-  const uint32_t tile_m = (t / a.tiles_n) * BM, tile_n = (t % a.tiles_n) * BN;
+  // and, where they number 256 or more, walks it eight rows of tiles at a time, column by column: the 64 tiles that
+  // an XCD works on at a time then share eight panels of A and eight of B (row by row, 32 columns: two and 32).
+  // 8192 x 4096 x 1024 with bias, GELU and both results 117 -> 103.5 us, 1024 x 4096 from 4096 rows 58.7 -> 50; fewer
+  // tiles run at once anyway and lose (300 x 4096 x 1024: 22.9 -> 25.9).
+  uint32_t row = t / a.tiles_n, col = t - row * a.tiles_n;
+  if (nt >= 256u) {
+    const uint32_t strip = row / 8u, rows = min(8u, a.tiles_m - strip * 8u), in_strip = t - strip * (8u * a.tiles_n);
+    col = in_strip / rows;
+    row = strip * 8u + in_strip - col * rows;
+  }
+  const uint32_t tile_m = row * BM, tile_n = col * BN;
   const uint32_t batch = blockIdx.y / a.splits, split = blockIdx.y % a.splits;
   const uint32_t b0 = batch / a.batch1, b1 = batch % a.batch1;
   const uint16_t* A = (const uint16_t*)a.a.ptr + (int64_t)b0 * a.a.s_b0 + (int64_t)b1 * a.a.s_b1;
