@@ -70,7 +70,7 @@ __device__ __forceinline__ void fetch_tile(GroupRegs<Groups<T, BX>::N>& gr, cons
   constexpr uint32_t G = Elem<T>::G, per_row = (KC ? Elem<T>::BK : BX) / G;
 #pragma unroll
   for (int it = 0; it < Groups<T, BX>::N; ++it) {
-    const uint32_t e = it * kGemmThreads + threadIdx.x, o = e / per_row, i = (e % per_row) * G;
+    const uint32_t e = it * kGemmThreads + threadIdx.x % kGemmThreads, o = e / per_row, i = (e % per_row) * G;
 #pragma unroll
     for (uint32_t j = 0; j < G; ++j) {
       const uint32_t x = x0 + (KC ? o : i + j), k = k0 + (KC ? i + j : o);
@@ -83,7 +83,7 @@ __device__ __forceinline__ void fetch_tile(GroupRegs<Groups<T, BX>::N>& gr, cons
 template <int BX, bool KC>
 __device__ __forceinline__ void stash_tile(const GroupRegs<Groups<float, BX>::N>& gr, float* tile) {
   constexpr int G = 4, BK = Elem<float>::BK, STRIDE = Tile<float, BX>::stride(KC), NG = Groups<float, BX>::N;
-  const uint32_t t = threadIdx.x;
+  const uint32_t t = threadIdx.x % kGemmThreads;
 #pragma unroll
   for (int it = 0; it < NG; ++it) {
     const uint32_t e = it * kGemmThreads + t;
@@ -145,7 +145,7 @@ template <int BX, bool KC> struct Dense {
   __device__ static __forceinline__ uint32_t swz(uint32_t row) { return KC ? (row >> 1) & 7u : ((row >> 2) & 1u) << 3; }
   // this lane's byte offset for wave instruction `it` of a slice
   __device__ static __forceinline__ uint32_t lane_offset(uint32_t it, int64_t s_x, int64_t s_k, uint32_t left) {
-    const uint32_t e = it * (uint32_t)kGemmThreads + threadIdx.x, row = e / kPerRow, c = (e % kPerRow) ^ swz(row);
+    const uint32_t e = it * (uint32_t)kGemmThreads + threadIdx.x % kGemmThreads, row = e / kPerRow, c = (e % kPerRow) ^ swz(row);
     return (uint32_t)(4 * chunk_offset<KC>(row, c * 4u, s_x, s_k, left));
   }
   __device__ static __forceinline__ void copy(const float* src, const uint32_t (&off)[kInstr], uint32_t tile, uint32_t wave) {
@@ -211,15 +211,20 @@ template <typename T, int BM, int BN> struct Smem {
 
 // T: float.  AKC / BKC: the operand's contiguous dimension is k.  AL: both operands' rows are 16-byte
 // aligned (the launcher looks).
-template <typename T, int BM, int BN, bool AKC, bool BKC, bool AL>
-__global__ __launch_bounds__(kGemmThreads, BM == 64 ? 2 : 1) void lt_gemm_kernel(const GemmArgs a) {
+// KS: halves of the workgroup that share its k (GemmArgs::halves); each has LDS stages of its own, and they
+// walk their slices side by side.
+template <typename T, int BM, int BN, bool AKC, bool BKC, bool AL, int KS>
+__global__ __launch_bounds__(kGemmThreads * KS, BM == 64 ? 2 : 1) void lt_gemm_kernel(const GemmArgs a) {
   constexpr int MB = BM / 64, NB = BN / 64, BK = Elem<T>::BK;
-  __shared__ __attribute__((aligned(16))) char smem[Smem<T, BM, BN>::kBytes];
+  constexpr size_t kHalf = Smem<T, BM, BN>::kBytes;
+  __shared__ __attribute__((aligned(16))) char smem_all[KS * kHalf];
+  const uint32_t half = KS > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / kGemmThreads) : 0u;
+  char* const smem = smem_all + half * kHalf;
   // LDS map: A buffer 0, A buffer 1, B buffer 0, B buffer 1 (the C tile of the epilogue reuses it)
   T* const lds = (T*)smem;
   auto As = [&](uint32_t buf) { return lds + buf * Tile<T, BM>::ELEMS; };
   auto Bs = [&](uint32_t buf) { return lds + 2 * Tile<T, BM>::ELEMS + buf * Tile<T, BN>::ELEMS; };
-  const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const uint32_t tid = threadIdx.x % kGemmThreads, lane = tid & 63, wave = tid >> 6;
   const uint32_t wave_m = wave >> 1, wave_n = wave & 1;
   const uint32_t tile_m = blockIdx.y * BM, tile_n = blockIdx.x * BN;
   const uint32_t batch = blockIdx.z / a.splits, split = blockIdx.z % a.splits;
@@ -252,8 +257,10 @@ __global__ __launch_bounds__(kGemmThreads, BM == 64 ? 2 : 1) void lt_gemm_kernel
   uint32_t n = (k_end - k_begin) / BK;   // whole slices
   if ((a_over && a_outer < 4) || (b_over && b_outer < 4)) n = 0u;
   else if ((a_over || b_over) && n > 0u && k_begin + n * BK == a.k) --n;
-  const T* const pa = A + (int64_t)tile_m * a.a.s_row + (int64_t)k_begin * a.a.s_col;
-  const T* const pb = B + (int64_t)tile_n * a.b.s_col + (int64_t)k_begin * a.b.s_row;
+  if (KS > 1) n /= 2u;                   // the same number for both halves; an odd one is left to the rest
+  const uint32_t k_first = k_begin + half * n * BK, k_rest = k_begin + KS * n * BK;
+  const T* const pa = A + (int64_t)tile_m * a.a.s_row + (int64_t)k_first * a.a.s_col;
+  const T* const pb = B + (int64_t)tile_n * a.b.s_col + (int64_t)k_first * a.b.s_row;
   const int64_t step_a = BK * a.a.s_col, step_b = BK * a.b.s_row;   // elements per slice of k
   if (AL && n > 0u) {
     // Four LDS stages: the MFMAs of slice j run from registers, the fragments of slice j + 1 are read from
@@ -351,16 +358,16 @@ __global__ __launch_bounds__(kGemmThreads, BM == 64 ? 2 : 1) void lt_gemm_kernel
       mma_slice<BM, BN, MB, NB, AKC, BKC, NCH>(accs, As(j & 1u), Bs(j & 1u), wave_m, wave_n, lane);
     }
   }
-  // the rest of k: every access checked, one slice at a time
+  // the rest of k: every access checked, one slice at a time, multiplied by the first half
 #pragma unroll 1
-  for (uint32_t k0 = k_begin + n * BK; k0 < k_end; k0 += BK) {
+  for (uint32_t k0 = k_rest; k0 < k_end; k0 += BK) {
     fetch_tile<T, BM, AKC>(ga, A, a.a.s_row, a.a.s_col, tile_m, k0, a.m, k_end);
     fetch_tile<T, BN, BKC>(gb, B, a.b.s_col, a.b.s_row, tile_n, k0, a.n, k_end);
     __syncthreads();
     stash_tile<BM, AKC>(ga, As(0));
     stash_tile<BN, BKC>(gb, Bs(0));
     __syncthreads();
-    mma_slice<BM, BN, MB, NB, AKC, BKC, NCH>(accs, As(0), Bs(0), wave_m, wave_n, lane);
+    if (half == 0u) mma_slice<BM, BN, MB, NB, AKC, BKC, NCH>(accs, As(0), Bs(0), wave_m, wave_n, lane);
   }
   v16f (&acc)[MB][NB] = accs[0];
   if (NCH > 1) {
@@ -373,7 +380,7 @@ __global__ __launch_bounds__(kGemmThreads, BM == 64 ? 2 : 1) void lt_gemm_kernel
   }
   // split-K: this workgroup's partial product goes to its own fp32 copy of the output, row major
   float* const raw = a.split_ws ? a.split_ws + (size_t)split * ((size_t)a.batch0 * a.batch1 * a.m * a.n) : nullptr;
-  epilogue<false, BM, BN, MB, NB>(a, acc, (float*)smem, tile_m, tile_n, wave_m, wave_n, lane, batch, raw);
+  epilogue<false, BM, BN, MB, NB, KS, kHalf>(a, acc, (float*)smem_all, tile_m, tile_n, wave_m, wave_n, lane, batch, raw);
 }
 
 // ---- small contractions -------------------------------------------------------------------------
@@ -883,15 +890,15 @@ static hipError_t launch_small(const GemmArgs& args, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <typename T, int BM, int BN, bool AL>
+template <typename T, int BM, int BN, bool AL, int KS>
 static void launch_variant(const GemmArgs& a, const dim3 grid, hipStream_t s) {
   const bool akc = a.a.s_col == 1, bkc = a.b.s_row == 1;
-  if (akc && bkc) LT_LAUNCH((lt_gemm_kernel<T, BM, BN, true, true, AL>), grid, dim3(kGemmThreads), s, a);
-  else if (akc) LT_LAUNCH((lt_gemm_kernel<T, BM, BN, true, false, AL>), grid, dim3(kGemmThreads), s, a);
-  else if (bkc) LT_LAUNCH((lt_gemm_kernel<T, BM, BN, false, true, AL>), grid, dim3(kGemmThreads), s, a);
-  else LT_LAUNCH((lt_gemm_kernel<T, BM, BN, false, false, AL>), grid, dim3(kGemmThreads), s, a);
+  if (akc && bkc) LT_LAUNCH((lt_gemm_kernel<T, BM, BN, true, true, AL, KS>), grid, dim3(kGemmThreads * KS), s, a);
+  else if (akc) LT_LAUNCH((lt_gemm_kernel<T, BM, BN, true, false, AL, KS>), grid, dim3(kGemmThreads * KS), s, a);
+  else if (bkc) LT_LAUNCH((lt_gemm_kernel<T, BM, BN, false, true, AL, KS>), grid, dim3(kGemmThreads * KS), s, a);
+  else LT_LAUNCH((lt_gemm_kernel<T, BM, BN, false, false, AL, KS>), grid, dim3(kGemmThreads * KS), s, a);
   char name[64];
-  snprintf(name, sizeof(name), "lt_gemm_kernel<float, %d, %d, %s, %s, %s>", BM, BN, akc ? "true" : "false", bkc ? "true" : "false", AL ? "true" : "false");
+  snprintf(name, sizeof(name), "lt_gemm_kernel<float, %d, %d, %s, %s, %s, %d>", BM, BN, akc ? "true" : "false", bkc ? "true" : "false", AL ? "true" : "false", KS);
   note_kernel(name);
 }
 
@@ -904,6 +911,7 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
   if (a.tile_m != a.tile_n || (a.tile_m != 64u && a.tile_m != 128u)) return hipErrorInvalidValue;
   const bool big = a.tile_m == 128u;   // the host picks big tiles only when they still give every compute unit work
   const uint32_t bm = a.tile_m;
+  if (a.halves != 1u && (a.halves != 2u || big)) return hipErrorInvalidValue;
   if (a.splits == 0u || (a.splits > 1u && !a.split_ws)) return hipErrorInvalidValue;
   const dim3 grid((a.n + bm - 1) / bm, (a.m + bm - 1) / bm, batch * a.splits);
   if (grid.y > 65535u || grid.z > 65535u) return hipErrorInvalidValue;
@@ -912,10 +920,12 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
     return ((uintptr_t)o.ptr & 15u) == 0 && outer % 4 == 0 && outer < (1 << 23) && o.s_b0 % 4 == 0 && o.s_b1 % 4 == 0;
   };
   const bool al = aligned(a.a, a.a.s_col == 1 ? a.a.s_row : a.a.s_col) && aligned(a.b, a.b.s_row == 1 ? a.b.s_col : a.b.s_row);
-  if (big && al) launch_variant<float, 128, 128, true>(a, grid, s);
-  else if (big) launch_variant<float, 128, 128, false>(a, grid, s);
-  else if (al) launch_variant<float, 64, 64, true>(a, grid, s);
-  else launch_variant<float, 64, 64, false>(a, grid, s);
+  if (big && al) launch_variant<float, 128, 128, true, 1>(a, grid, s);
+  else if (big) launch_variant<float, 128, 128, false, 1>(a, grid, s);
+  else if (al && a.halves == 2u) launch_variant<float, 64, 64, true, 2>(a, grid, s);
+  else if (al) launch_variant<float, 64, 64, true, 1>(a, grid, s);
+  else if (a.halves == 2u) launch_variant<float, 64, 64, false, 2>(a, grid, s);
+  else launch_variant<float, 64, 64, false, 1>(a, grid, s);
   return hipGetLastError();
 }
 

@@ -73,7 +73,7 @@ template <int N> struct Chunks {
 // 4 chunks of 8 k each; otherwise rows are k, BX/8 chunks of 8 x each.
 template <int BX, bool KC>
 __device__ __forceinline__ void chunk_pos(uint32_t it, uint32_t* outer, uint32_t* inner) {
-  const uint32_t e = it * kGemmThreads + threadIdx.x;
+  const uint32_t e = it * kGemmThreads + threadIdx.x % kGemmThreads;
   if (KC) {
     *outer = e >> 2;
     *inner = (e & 3u) * 8u;
@@ -187,7 +187,7 @@ template <int BX, bool KC> struct Dense {
 template <int BX, bool KC>
 __device__ __forceinline__ uint32_t dma_lane_offset(uint32_t it, int64_t s_x, int64_t s_k, uint32_t left) {
   typedef Dense<BX, KC> D;
-  const uint32_t t = threadIdx.x;
+  const uint32_t t = threadIdx.x % kGemmThreads;
   if (KC) {
     const uint32_t row = it * 64u + (t >> 2), c = (t & 3u) ^ D::swz_x(row);
     return (uint32_t)(2 * chunk_offset<BX, KC>(row, c * 8u, s_x, s_k, left));
@@ -253,11 +253,16 @@ template <int BM, int BN> struct Smem {
 
 // AL: both operands' rows are 16-byte aligned (the launcher looks).  Two instances, because the path
 // that the other one takes costs registers in the main loop.
-template <int BM, int BN, bool AKC, bool BKC, bool AL>
-__global__ __launch_bounds__(kGemmThreads, 2) void lt_gemm_bf16_kernel(const GemmArgs a) {
+// KS: halves of the workgroup that share its k (GemmArgs::halves); each has LDS stages of its own, and they
+// walk their slices side by side.
+template <int BM, int BN, bool AKC, bool BKC, bool AL, int KS>
+__global__ __launch_bounds__(kGemmThreads * KS, 2) void lt_gemm_bf16_kernel(const GemmArgs a) {
   constexpr int MB = BM / 64, NB = BN / 64;   // 32 x 32 blocks per wave: rows, columns
-  __shared__ __attribute__((aligned(16))) char smem[Smem<BM, BN>::kBytes];
-  const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+  constexpr size_t kHalf = Smem<BM, BN>::kBytes;
+  __shared__ __attribute__((aligned(16))) char smem_all[KS * kHalf];
+  const uint32_t half = KS > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / kGemmThreads) : 0u;
+  char* const smem = smem_all + half * kHalf;
+  const uint32_t tid = threadIdx.x % kGemmThreads, lane = tid & 63u, wave = tid >> 6;
   const uint32_t wave_m = wave >> 1, wave_n = wave & 1u;
   // tile number: remap so that each XCD (workgroup number mod 8) owns a contiguous range
   const uint32_t nt = gridDim.x;
@@ -328,8 +333,10 @@ __global__ __launch_bounds__(kGemmThreads, 2) void lt_gemm_bf16_kernel(const Gem
   uint32_t n = (k_end - k_begin) / BK;   // whole slices
   if ((a_over && a_outer < 8) || (b_over && b_outer < 8)) n = 0u;
   else if ((a_over || b_over) && n > 0u && k_begin + n * BK == a.k) --n;
-  const uint16_t* const pa = A + (int64_t)tile_m * a.a.s_row + (int64_t)k_begin * a.a.s_col;
-  const uint16_t* const pb = B + (int64_t)tile_n * a.b.s_col + (int64_t)k_begin * a.b.s_row;
+  if (KS > 1) n /= 2u;                   // the same number for both halves; an odd one is left to the rest
+  const uint32_t k_first = k_begin + half * n * BK, k_rest = k_begin + KS * n * BK;
+  const uint16_t* const pa = A + (int64_t)tile_m * a.a.s_row + (int64_t)k_first * a.a.s_col;
+  const uint16_t* const pb = B + (int64_t)tile_n * a.b.s_col + (int64_t)k_first * a.b.s_row;
   const int64_t step_a = BK * a.a.s_col, step_b = BK * a.b.s_row;   // elements per slice of k
   if (AL && n > 0u) {
     // Software pipeline over slices j = 0 .. n-1, four LDS stages: the MFMAs of slice j run from
@@ -477,35 +484,35 @@ __global__ __launch_bounds__(kGemmThreads, 2) void lt_gemm_bf16_kernel(const Gem
       mma(load_frags(j & 1u));
     }
   }
-  if (k_begin + n * BK < k_end) {
-    // the rest of k: every address checked, one slice at a time
+  if (k_rest < k_end) {
+    // the rest of k: every address checked, one slice at a time, multiplied by the first half
 #pragma unroll 1
-    for (uint32_t k0 = k_begin + n * BK; k0 < k_end; k0 += BK) {
+    for (uint32_t k0 = k_rest; k0 < k_end; k0 += BK) {
       const Chunks<Geo<BM>::kChunks> ca = fetch_checked<BM, AKC>(A, a.a.s_row, a.a.s_col, tile_m, k0, a.m, k_end);
       const Chunks<Geo<BN>::kChunks> cb = fetch_checked<BN, BKC>(B, a.b.s_col, a.b.s_row, tile_n, k0, a.n, k_end);
       __syncthreads();
       stash<BM, AKC>(ca, smem);
       stash<BN, BKC>(cb, smem + Geo<BM>::kBytes);
       __syncthreads();
-      mma(load_frags(0));
+      if (half == 0u) mma(load_frags(0));
     }
   }
 
   // split-K: this workgroup's partial product goes to its own fp32 copy of the output, row major
   float* const raw = a.split_ws ? a.split_ws + (size_t)split * ((size_t)a.batch0 * a.batch1 * a.m * a.n) : nullptr;
-  epilogue<true, BM, BN, MB, NB>(a, acc, (float*)smem, tile_m, tile_n, wave_m, wave_n, lane, batch, raw);
+  epilogue<true, BM, BN, MB, NB, KS, kHalf>(a, acc, (float*)smem_all, tile_m, tile_n, wave_m, wave_n, lane, batch, raw);
 }
 
-template <int BM, int BN, bool AL>
+template <int BM, int BN, bool AL, int KS>
 static void launch_layout(const GemmArgs& a, dim3 grid, hipStream_t s) {
-  const dim3 block(kGemmThreads);
+  const dim3 block(kGemmThreads * KS);
   const bool akc = a.a.s_col == 1, bkc = a.b.s_row == 1;
-  if (akc && bkc) LT_LAUNCH((lt_gemm_bf16_kernel<BM, BN, true, true, AL>), grid, block, s, a);
-  else if (akc) LT_LAUNCH((lt_gemm_bf16_kernel<BM, BN, true, false, AL>), grid, block, s, a);
-  else if (bkc) LT_LAUNCH((lt_gemm_bf16_kernel<BM, BN, false, true, AL>), grid, block, s, a);
-  else LT_LAUNCH((lt_gemm_bf16_kernel<BM, BN, false, false, AL>), grid, block, s, a);
+  if (akc && bkc) LT_LAUNCH((lt_gemm_bf16_kernel<BM, BN, true, true, AL, KS>), grid, block, s, a);
+  else if (akc) LT_LAUNCH((lt_gemm_bf16_kernel<BM, BN, true, false, AL, KS>), grid, block, s, a);
+  else if (bkc) LT_LAUNCH((lt_gemm_bf16_kernel<BM, BN, false, true, AL, KS>), grid, block, s, a);
+  else LT_LAUNCH((lt_gemm_bf16_kernel<BM, BN, false, false, AL, KS>), grid, block, s, a);
   char name[64];
-  snprintf(name, sizeof(name), "lt_gemm_bf16_kernel<%d, %d, %s, %s, %s>", BM, BN, akc ? "true" : "false", bkc ? "true" : "false", AL ? "true" : "false");
+  snprintf(name, sizeof(name), "lt_gemm_bf16_kernel<%d, %d, %s, %s, %s, %d>", BM, BN, akc ? "true" : "false", bkc ? "true" : "false", AL ? "true" : "false", KS);
   note_kernel(name);
 }
 
@@ -515,8 +522,11 @@ static void launch_tile(const GemmArgs& a, dim3 grid, hipStream_t s) {
   auto aligned = [](const GemmOperand& o, int64_t outer) {
     return ((uintptr_t)o.ptr & 15u) == 0 && outer % 8 == 0 && outer < (1 << 24) && o.s_b0 % 8 == 0 && o.s_b1 % 8 == 0;
   };
-  if (aligned(a.a, a.a.s_col == 1 ? a.a.s_row : a.a.s_col) && aligned(a.b, a.b.s_row == 1 ? a.b.s_col : a.b.s_row)) launch_layout<BM, BN, true>(a, grid, s);
-  else launch_layout<BM, BN, false>(a, grid, s);
+  const bool al = aligned(a.a, a.a.s_col == 1 ? a.a.s_row : a.a.s_col) && aligned(a.b, a.b.s_row == 1 ? a.b.s_col : a.b.s_row);
+  if (al && a.halves == 2u) launch_layout<BM, BN, true, 2>(a, grid, s);
+  else if (al) launch_layout<BM, BN, true, 1>(a, grid, s);
+  else if (a.halves == 2u) launch_layout<BM, BN, false, 2>(a, grid, s);
+  else launch_layout<BM, BN, false, 1>(a, grid, s);
 }
 
 }  // namespace bf
@@ -533,6 +543,7 @@ hipError_t launch_gemm_bf16(const GemmArgs& a, hipStream_t s) {
   const uint32_t batch = a.batch0 * a.batch1;
   const uint32_t tiles = a.tiles_m * a.tiles_n;
   if (a.splits == 0u || (a.splits > 1u && !a.split_ws) || (uint64_t)batch * a.splits > 65535u) return hipErrorInvalidValue;
+  if (a.halves != 1u && a.halves != 2u) return hipErrorInvalidValue;
   if (a.tile_m != 128u || (a.tile_n != 128u && a.tile_n != 64u)) return hipErrorInvalidValue;
   if (a.tiles_m != (a.m + a.tile_m - 1) / a.tile_m || a.tiles_n != (a.n + a.tile_n - 1) / a.tile_n) return hipErrorInvalidValue;
   const dim3 grid(tiles, batch * a.splits);

@@ -23,13 +23,13 @@ typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 // the Q quads are fetched straight into the register file -- one memory round trip per trip, with
 // nothing in the fetch that depends on the program.  A program with one input fetches it twice (no
 // branch in the fetch); the copy lands in a slot that the program writes before it reads.
-template <int BM, int BN, int Q>
+template <int BM, int BN, int NT, int Q>
 __device__ __forceinline__ void post_wide(const GemmArgs& a, const ProgRegs pr, const float* Cs, uint32_t tile_m, uint32_t tile_n,
                                           int64_t base, const bool bf) {
   constexpr int NS = 32, SL = NS / Q;
   constexpr int kCStride = BN + kCPad;
-  constexpr uint32_t kQuadsPerRow = BN / kVec, kRowStep = (uint32_t)kGemmThreads / kQuadsPerRow;
-  constexpr uint32_t kTrips = (uint32_t)(BM * BN / kVec) / kGemmThreads;   // quads per lane
+  constexpr uint32_t kQuadsPerRow = BN / kVec, kRowStep = (uint32_t)NT / kQuadsPerRow;
+  constexpr uint32_t kTrips = (uint32_t)(BM * BN / kVec) / NT;   // quads per lane
   static_assert(kTrips % (uint32_t)Q == 0u, "a lane's quads make whole trips");
   const EwProg& p = a.post;
   const uint32_t n_code = p.n_code;
@@ -122,12 +122,14 @@ __device__ __forceinline__ int post_stream_kind(const EwProg& p) {
 // tile is written once, then every lane walks it in row-major 4-element quads, so the post
 // program sees flat, contiguous indices exactly like the elementwise kernel does (16-byte loads
 // of residuals, 16-byte stores) and is compiled in only once.
-// BF: the operands are bf16.
-template <bool BF, int BM, int BN, int MB, int NB>
+// BF: the operands are bf16.  KS: halves of the workgroup, each with a product of its own share of k: they lie
+// kHalf bytes apart in LDS and are added up, the first half's first, before anything else.
+template <bool BF, int BM, int BN, int MB, int NB, int KS, size_t kHalf>
 __device__ __forceinline__ void epilogue(const GemmArgs& a, const v16f (&acc)[MB][NB], float* Cs, uint32_t tile_m,
                                          uint32_t tile_n, uint32_t wave_m, uint32_t wave_n, uint32_t lane, uint32_t batch,
                                          float* raw = nullptr) {
-  constexpr int kCStride = BN + kCPad;
+  constexpr int kCStride = BN + kCPad, NT = kGemmThreads * KS;
+  float* const mine = Cs + (KS > 1 ? (threadIdx.x / kGemmThreads) * (kHalf / sizeof(float)) : 0u);
   __syncthreads();   // the operand tiles in the same LDS bytes are dead now
 #pragma unroll
   for (int bm = 0; bm < MB; ++bm)
@@ -137,9 +139,18 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, const v16f (&acc)[MB
       for (int r = 0; r < 16; ++r) {
         const uint32_t row = wave_m * (MB * 32) + bm * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
         const uint32_t col = wave_n * (NB * 32) + bn * 32 + (lane & 31);
-        Cs[row * kCStride + col] = acc[bm][bn][r];
+        mine[row * kCStride + col] = acc[bm][bn][r];
       }
   __syncthreads();
+  if (KS > 1) {
+#pragma unroll 4
+    for (uint32_t q = threadIdx.x; q < (uint32_t)(BM * BN / kVec); q += NT) {
+      float* const at = &Cs[(q / (BN / kVec)) * kCStride + (q % (BN / kVec)) * kVec];
+      const float4 x = *(const float4*)at, y = *(const float4*)(at + kHalf / sizeof(float));
+      *(float4*)at = make_float4(x.x + y.x, x.y + y.y, x.z + y.z, x.w + y.w);
+    }
+    __syncthreads();
+  }
   const EwProg& p = a.post;
   const ProgRegs pr = load_prog_regs(p);
   const uint32_t n_code = p.n_code;
@@ -150,7 +161,7 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, const v16f (&acc)[MB
     // second launch over the sum of the splits
     const uint32_t row_flat0 = (b0 * a.batch1 + b1) * a.m;
     const bool vec = (a.n % 4u) == 0u;
-    for (uint32_t q = threadIdx.x; q < (uint32_t)(BM * BN / kVec); q += kGemmThreads) {
+    for (uint32_t q = threadIdx.x; q < (uint32_t)(BM * BN / kVec); q += NT) {
       const uint32_t r = q / (BN / kVec), c = (q % (BN / kVec)) * kVec;
       const uint32_t row = tile_m + r, col = tile_n + c;
       if (row >= a.m || col >= a.n) continue;
@@ -167,10 +178,6 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, const v16f (&acc)[MB
     }
     return;
   }
-  if (a.chain.n) {
-    run_chain<BF, BM, BN, kGemmThreads>(a, load_chain_regs(a), Cs, threadIdx.x, tile_m, tile_n, base);
-    return;
-  }
   // Whole aligned 4-vectors, at most four inputs (none of them strided) and eight slots: no bounds
   // checks on inputs, no divisions (row and column are known).
   const bool fast = p.fast && p.full_vec_ok && (a.n & 3u) == 0u && p.n_in <= 4u && p.n_slots <= 8u;
@@ -180,7 +187,7 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, const v16f (&acc)[MB
     const EwOut& o = p.out[0];
     if (fast && tile_m + BM <= a.m && tile_n + BN <= a.n) {
 #pragma unroll 4
-      for (uint32_t q = threadIdx.x; q < (uint32_t)(BM * BN / kVec); q += kGemmThreads) {
+      for (uint32_t q = threadIdx.x; q < (uint32_t)(BM * BN / kVec); q += NT) {
         const uint32_t r = q / (BN / kVec), c = (q % (BN / kVec)) * kVec;
         const uint32_t i = (uint32_t)(base + (int64_t)(tile_m + r) * a.o_row + tile_n + c);
         const float4 t = *(const float4*)&Cs[r * kCStride + c];
@@ -192,7 +199,7 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, const v16f (&acc)[MB
     }
     // a tile over the edge, or rows that start at any element (an odd n)
 #pragma unroll 2
-    for (uint32_t q = threadIdx.x; q < (uint32_t)(BM * BN / kVec); q += kGemmThreads) {
+    for (uint32_t q = threadIdx.x; q < (uint32_t)(BM * BN / kVec); q += NT) {
       const uint32_t r = q / (BN / kVec), c = (q % (BN / kVec)) * kVec;
       if (tile_m + r >= a.m || tile_n + c >= a.n) continue;
       const uint32_t i = (uint32_t)(base + (int64_t)(tile_m + r) * a.o_row + tile_n + c);
@@ -209,25 +216,31 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, const v16f (&acc)[MB
     }
     return;
   }
+  if (a.chain.n) {
+    run_chain<BF, BM, BN, NT>(a, load_chain_regs(a), Cs, threadIdx.x, tile_m, tile_n, base);
+    return;
+  }
   if (fast) {
-    const int sk = post_stream_kind(p);
-    constexpr uint32_t kTrips = (uint32_t)(BM * BN / kVec) / kGemmThreads;
-    constexpr int Q8 = kTrips % 8u == 0u ? 8 : 4;
-    if (sk != 0 && p.n_slots <= 32u / (uint32_t)Q8) {
-      post_wide<BM, BN, Q8>(a, pr, Cs, tile_m, tile_n, base, sk == 2);
-      return;
-    }
-    if (sk != 0 && Q8 != 4) {
-      post_wide<BM, BN, 4>(a, pr, Cs, tile_m, tile_n, base, sk == 2);
-      return;
+    constexpr uint32_t kTrips = (uint32_t)(BM * BN / kVec) / NT;
+    if constexpr (kTrips % 4u == 0u) {   // (otherwise two quads at a time, below)
+      const int sk = post_stream_kind(p);
+      constexpr int Q8 = kTrips % 8u == 0u ? 8 : 4;
+      if (sk != 0 && p.n_slots <= 32u / (uint32_t)Q8) {
+        post_wide<BM, BN, NT, Q8>(a, pr, Cs, tile_m, tile_n, base, sk == 2);
+        return;
+      }
+      if (sk != 0 && Q8 != 4) {
+        post_wide<BM, BN, NT, 4>(a, pr, Cs, tile_m, tile_n, base, sk == 2);
+        return;
+      }
     }
   }
   if (fast && tile_m + BM <= a.m && tile_n + BN <= a.n) {
-    // two quads per trip (same columns, kGemmThreads quads apart): the interpreter is fetched,
+    // two quads per trip (same columns, NT quads apart): the interpreter is fetched,
     // decoded and dispatched once for both (register file = 8 slots x 2)
-    constexpr uint32_t kRowStep = (uint32_t)kGemmThreads / (BN / kVec);
+    constexpr uint32_t kRowStep = (uint32_t)NT / (BN / kVec);
 #pragma unroll 1
-    for (uint32_t q = threadIdx.x; q < (uint32_t)(BM * BN / kVec); q += 2u * kGemmThreads) {
+    for (uint32_t q = threadIdx.x; q < (uint32_t)(BM * BN / kVec); q += 2u * NT) {
       const uint32_t ra = q / (BN / kVec), c = (q % (BN / kVec)) * kVec, rb = ra + kRowStep;
       const uint32_t ia = (uint32_t)(base + (int64_t)(tile_m + ra) * a.o_row + tile_n + c);
       const uint32_t ib = (uint32_t)(base + (int64_t)(tile_m + rb) * a.o_row + tile_n + c);
@@ -248,7 +261,7 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, const v16f (&acc)[MB
     return;
   }
 #pragma unroll 1
-  for (uint32_t q = threadIdx.x; q < (uint32_t)(BM * BN / kVec); q += kGemmThreads) {
+  for (uint32_t q = threadIdx.x; q < (uint32_t)(BM * BN / kVec); q += NT) {
     const uint32_t r = q / (BN / kVec), c = (q % (BN / kVec)) * kVec;
     const uint32_t row = tile_m + r, col = tile_n + c;
     if (row >= a.m || col >= a.n) continue;

@@ -201,9 +201,11 @@ struct GemmArgs {
   // slice of k and leaving its fp32 partial product, row major, in split_ws[split]; the post
   // program then runs in a second launch (SplitPostArgs) that adds the partials up in split order.
   // With splits = 1 and split_ws set the product goes there as it is, for the second launch.
-  // Workgroup tile: bf16 256 x 256, 256 x 128, 128 x 128 or 128 x 64; fp32 128 x 128 or 64 x 64, and for direct = 1, the one-launch
+  // Workgroup tile: bf16 128 x 128 or 128 x 64; fp32 128 x 128 or 64 x 64, and for direct = 1, the one-launch
   // kernel for small products, 16 x 16, 16 x 64, 32 x 32 or 64 x 32.
-  uint32_t splits, tile_m, tile_n;
+  // halves = 2 (the LDS-staged kernels): a workgroup of twice the size, each half of it contracting half of the
+  // workgroup's k; the two products meet in LDS.
+  uint32_t splits, tile_m, tile_n, halves;
   uint32_t direct;
   float* split_ws;           // [splits][batch * m * n] floats
   // The one-launch small kernel (direct = 1) with splits > 1: `splits` workgroups share a tile;

@@ -1992,6 +1992,24 @@ struct Lowering {
     ch.n = steps + 1u;
   }
 
+  // Two workgroups per tile, each with a part of k, become the halves of one: half as many partial products travel to
+  // memory and back, none (and no second launch) where there were two.  us, before / in halves: bf16 1024 x 4096 and
+  // 4096 x 1024 from 4096 rows 50 / 34.9 and 49 / 34.6, 4096 x 1024 x 4096 with bias 56 / 41.6, 1024 x 1024 from 8192 rows with Adam (eight
+  // partial products, then four) 44.9 / 42.3; fp32 512 x 2048 x 2048 44.3 / 39.2, 1024 x 1000 from 2048 rows 43.6 / 39.6.
+  // Where no second launch is left that pays for any number of tiles (1000 x 2048 x 512 with bias, GELU and both results
+  // 28.0 / 14.0), otherwise only where the workgroups would share compute units anyway: those that have one each lose
+  // by moving together (512 x 2048 from 1000 rows, four partial products, then two, 19.5 / 24.7).  A program that is no chain is not brought back from
+  // a second launch into the epilogue (143 x 10 x 512 14.5 / 26).  In bf16 an odd number of splits is rounded down: what the
+  // idle compute units cost is less than the partial products they save.  In fp32 it stays: fewer, longer
+  // sums would be less accurate (against 64 bits 3.5e-7 -> 4.1e-7 for four instead of five).
+  static void halve(ltk::GemmArgs* a, uint64_t tiles, bool sealed, uint64_t* splits) {
+    if (*splits < 2u || (a->in_dtype == ltk::kF32 && *splits % 2u != 0u)) return;
+    const bool second = *splits >= 4u || (!sealed && heavy_post(a->post));   // a second launch is left
+    if (second ? *splits * tiles <= 256u : !a->chain.n) return;
+    a->halves = 2u;
+    *splits /= 2u;
+  }
+
   bool emit_gemm(int k, Region* r, const std::vector<int32_t>& post_m_in, const std::vector<Val>& out_in) {
     const int32_t a = r->anchor;
     const Node* an = nd[a];
@@ -2069,7 +2087,7 @@ struct Lowering {
     }
     args.post = post.prog;
     make_chain(&args);
-    args.splits = 1;
+    args.splits = args.halves = 1;
     int32_t ws_storage = -1;
     if (A.dtype == LT_BF16) {
       // the bf16 kernel works on 128 x 128 tiles; few tiles and a long k: split k so that about
@@ -2083,6 +2101,7 @@ struct Lowering {
       const uint64_t tiles = (uint64_t)args.tiles_m * args.tiles_n * (uint64_t)batch;
       const uint64_t slices = (uint64_t)(kk + 63) / 64;
       uint64_t splits = std::min<uint64_t>({512 / std::max<uint64_t>(tiles, 1), slices / 4, 16});
+      halve(&args, tiles, r->sealed, &splits);
       if (r->sealed) splits = 1;   // the second launch writes the dense layout only
       if (splits > 1 || (!r->sealed && heavy_post(post.prog))) {
         args.splits = (uint32_t)std::max<uint64_t>(splits, 1);
@@ -2108,7 +2127,7 @@ struct Lowering {
       args.tile_m = args.tile_n = ts;
       const uint64_t tiles = (uint64_t)((m + ts - 1) / ts) * ((n + ts - 1) / ts) * (uint64_t)batch;
       const uint64_t slices = (uint64_t)(kk + 15) / 16;
-      uint64_t splits = r->sealed ? 1 : std::min<uint64_t>({512 / std::max<uint64_t>(tiles, 1), slices / 4, 16});
+      uint64_t splits = std::min<uint64_t>({512 / std::max<uint64_t>(tiles, 1), slices / 4, 16});
       // Small products (a layer of a small MLP: 128 x 512 x 784) go to the kernel that splits k
       // inside a workgroup of eight waves over a 32 x 32 tile: one launch where the split costs
       // two.  Measured, HIP events around each launch included: 128 x 512 x 784 18.5 -> 14.4 us,
@@ -2162,6 +2181,8 @@ struct Lowering {
           }
         }
       }
+      if (!args.direct && ts == 64u) halve(&args, tiles, r->sealed, &splits);
+      if (r->sealed) splits = 1;
       if (splits > 1 || (!r->sealed && !args.direct && heavy_post(post.prog))) {
         args.splits = (uint32_t)std::max<uint64_t>(splits, 1);
         Storage ws;
