@@ -218,6 +218,7 @@ __global__ __launch_bounds__(kGemmThreads * KS, BM == 64 ? 2 : 1) void lt_gemm_k
   constexpr int MB = BM / 64, NB = BN / 64, BK = Elem<T>::BK;
   constexpr size_t kHalf = Smem<T, BM, BN>::kBytes;
   __shared__ __attribute__((aligned(16))) char smem_all[KS * kHalf];
+  const uint32_t touched = touch_args<GemmArgs>();
   const uint32_t half = KS > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / kGemmThreads) : 0u;
   char* const smem = smem_all + half * kHalf;
   // LDS map: A buffer 0, A buffer 1, B buffer 0, B buffer 1 (the C tile of the epilogue reuses it)
@@ -381,6 +382,7 @@ __global__ __launch_bounds__(kGemmThreads * KS, BM == 64 ? 2 : 1) void lt_gemm_k
   // split-K: this workgroup's partial product goes to its own fp32 copy of the output, row major
   float* const raw = a.split_ws ? a.split_ws + (size_t)split * ((size_t)a.batch0 * a.batch1 * a.m * a.n) : nullptr;
   epilogue<false, BM, BN, MB, NB, KS, kHalf>(a, acc, (float*)smem_all, tile_m, tile_n, wave_m, wave_n, lane, batch, raw);
+  args_touched(touched);
 }
 
 // ---- small contractions -------------------------------------------------------------------------
