@@ -438,6 +438,22 @@ __device__ __forceinline__ SmallTile small_tile(const GemmArgs& a) {
   return t;
 }
 
+// The sum of a tile's partial quads, `stride` floats apart, in split order (deterministic).  They are all asked for before
+// the first is added: read one by one, each waits for its own way to memory and back.
+constexpr int kMaxShare = 8;
+__device__ __forceinline__ float4 sum_parts(const float* parts, uint32_t stride, uint32_t splits) {
+  float4 t[kMaxShare];
+#pragma unroll
+  for (uint32_t sp = 0; sp < (uint32_t)kMaxShare; ++sp) t[sp] = published4(parts + (size_t)min(sp, splits - 1u) * stride);
+  float4 sum = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+#pragma unroll
+  for (uint32_t sp = 0; sp < (uint32_t)kMaxShare; ++sp)
+    if (sp < splits) {
+      sum.x += t[sp].x; sum.y += t[sp].y; sum.z += t[sp].z; sum.w += t[sp].w;
+    }
+  return sum;
+}
+
 template <bool V>
 __device__ __forceinline__ void small_fetch(float (&v)[kSmallG][4], const float* base, int64_t s_k, uint32_t k0, uint32_t k_end) {
 #pragma unroll
@@ -624,13 +640,7 @@ __device__ __forceinline__ void small_tile32(const GemmArgs& a) {
     if (!is_last) return;
     if (has_quad) {
 #pragma unroll
-      for (uint32_t j = 0; j < QT; ++j) {
-        sum[j] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        for (uint32_t sp = 0; sp < a.splits; ++sp) {   // split order: deterministic
-          const float4 t = published4(parts + (size_t)sp * (NB * 1024u) + (size_t)((threadIdx.x + j * kSmallThreads) % kQuads) * 4u);
-          sum[j].x += t.x; sum[j].y += t.y; sum[j].z += t.z; sum[j].w += t.w;
-        }
-      }
+      for (uint32_t j = 0; j < QT; ++j) sum[j] = sum_parts(parts + (size_t)((threadIdx.x + j * kSmallThreads) % kQuads) * 4u, NB * 1024u, a.splits);
     }
   }
   if (!has_quad) return;
@@ -807,13 +817,7 @@ __device__ __forceinline__ void small_tile16(const GemmArgs& a) {
     }
     __syncthreads();
     if (!is_last) return;
-    if (has_quad) {
-      sum = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-      for (uint32_t sp = 0; sp < a.splits; ++sp) {   // split order: deterministic
-        const float4 t = published4(parts + (size_t)sp * (kQuads * 4u) + threadIdx.x * 4u);
-        sum.x += t.x; sum.y += t.y; sum.z += t.z; sum.w += t.w;
-      }
-    }
+    if (has_quad) sum = sum_parts(parts + threadIdx.x * 4u, kQuads * 4u, a.splits);
   }
   if (!has_quad) return;
   Quad anchor;
@@ -865,7 +869,7 @@ static hipError_t launch_small(const GemmArgs& args, hipStream_t s) {
   a.tiles_n = (a.n + a.tile_n - 1u) / a.tile_n;
   const uint64_t wgs = (uint64_t)a.tiles_m * a.tiles_n * a.batch0 * a.batch1;
   if (a.splits == 0u || wgs * a.splits > 0x7fffffffull || a.tiles_m > 65535u || (uint64_t)a.batch0 * a.batch1 > 65535u) return hipErrorInvalidValue;
-  if (a.splits > 1u && (!a.split_ws || !a.tickets)) return hipErrorInvalidValue;
+  if (a.splits > 1u && (a.splits > (uint32_t)kMaxShare || !a.split_ws || !a.tickets)) return hipErrorInvalidValue;
   // column sums ride along only with an unshared, unbatched product whose B is [k, n] with rows contiguous
   if (a.col_sum && (!t22 || a.splits != 1u || a.batch0 * a.batch1 != 1u || a.b.s_col != 1 || a.col_post.n_slots > 16u)) return hipErrorInvalidValue;
   if (wgs == 0u) return hipSuccess;
