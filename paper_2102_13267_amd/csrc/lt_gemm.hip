@@ -529,7 +529,8 @@ __device__ __forceinline__ void small_tile32(const GemmArgs& a) {
   const bool cols_mine = cols_here && bm == 0u;                 // (wave-uniform)
   const ProgRegs cpr = CS ? load_prog_regs(a.col_post) : ProgRegs{0u, 0.0f};
   float csum = 0.0f;
-  const bool fast = p.fast && p.full_vec_ok && p.n_in <= 4u && p.n_slots <= 8u && tile_m + 32u * TM <= a.m && tile_n + 32u * TN <= a.n;
+  // (a tile over the edge: quads past it read the last row's or column's inputs and are not stored)
+  const bool fast = p.fast && p.full_vec_ok && p.n_in <= 4u && p.n_slots <= 8u && (a.n & 3u) == 0u;
   uint32_t qrow[QT], qcol[QT], qi[QT];
 #pragma unroll
   for (uint32_t j = 0; j < QT; ++j) {
@@ -545,7 +546,10 @@ __device__ __forceinline__ void small_tile32(const GemmArgs& a) {
   Staged<4> staged[QT];
   if (fast && has_quad) {
 #pragma unroll
-    for (uint32_t j = 0; j < QT; ++j) staged[j] = fetch_inputs_at<4, false, false>(p, qi[j], (b0 * a.batch1 + b1) * a.m + qrow[j], qcol[j]);
+    for (uint32_t j = 0; j < QT; ++j) {
+      const uint32_t r = min(qrow[j], a.m - 1u), c = min(qcol[j], a.n - 4u);
+      staged[j] = fetch_inputs_at<4, false, false>(p, (uint32_t)((int64_t)b0 * a.o_b0 + (int64_t)b1 * a.o_b1 + (int64_t)r * a.o_row + c), (b0 * a.batch1 + b1) * a.m + r, c);
+    }
   }
 #pragma clang diagnostic pop
   v16f acc0, acc1;
@@ -653,7 +657,7 @@ __device__ __forceinline__ void small_tile32(const GemmArgs& a) {
       RF<16> f = place_inputs<16, 4, true, false, 0>(rf_zero<16>(), p, staged[j], kVec);
       f = rf_set<16>(f, p.anchor_slot, anchor);
       f = interp<16>(f, pr, n_code);
-      store_outputs<16, true, false, 0>(f, p, 0, qi[j], kVec);
+      if (qrow[j] < a.m && qcol[j] < a.n) store_outputs<16, true, false, 0>(f, p, 0, qi[j], kVec);
     } else if (qrow[j] < a.m && qcol[j] < a.n) {
       const uint32_t nvalid = a.n - qcol[j] >= (uint32_t)kVec ? (uint32_t)kVec : a.n - qcol[j];
       RF<16> f = load_inputs<16, kMaxIn, false, false>(rf_zero<16>(), p, 0, qi[j], nvalid);
@@ -737,13 +741,16 @@ __device__ __forceinline__ void small_tile16(const GemmArgs& a) {
   const uint32_t qrow = tile_m + (threadIdx.x % kQuads) / (4u * NB), qcol = tile_n + (threadIdx.x % (4u * NB)) * (uint32_t)kVec;
   const uint32_t qi = (uint32_t)((int64_t)b0 * a.o_b0 + (int64_t)b1 * a.o_b1 + (int64_t)qrow * a.o_row + qcol);
   const bool has_quad = threadIdx.x < kQuads;   // (wave-uniform)
-  const bool fast = p.fast && p.full_vec_ok && p.n_in <= 4u && p.n_slots <= 8u && tile_m + 16u <= a.m && tile_n + kCols <= a.n;
+  const bool fast = p.fast && p.full_vec_ok && p.n_in <= 4u && p.n_slots <= 8u && (a.n & 3u) == 0u;   // (quads past an edge: as above)
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Wuninitialized"
 #pragma clang diagnostic ignored "-Wsometimes-uninitialized"
   Staged<4> staged;
   if (k_begin < k_end) fetch(0, k_begin);
-  if (fast && has_quad) staged = fetch_inputs_at<4, false, false>(p, qi, (b0 * a.batch1 + b1) * a.m + qrow, qcol);
+  if (fast && has_quad) {
+    const uint32_t r = min(qrow, a.m - 1u), c = min(qcol, a.n - 4u);
+    staged = fetch_inputs_at<4, false, false>(p, (uint32_t)((int64_t)b0 * a.o_b0 + (int64_t)b1 * a.o_b1 + (int64_t)r * a.o_row + c), (b0 * a.batch1 + b1) * a.m + r, c);
+  }
 #pragma clang diagnostic pop
   typedef float v4f __attribute__((ext_vector_type(4)));
   v4f acc[2][NB];
@@ -827,7 +834,7 @@ __device__ __forceinline__ void small_tile16(const GemmArgs& a) {
     RF<16> f = place_inputs<16, 4, true, false, 0>(rf_zero<16>(), p, staged, kVec);
     f = rf_set<16>(f, p.anchor_slot, anchor);
     f = interp<16>(f, pr, n_code);
-    store_outputs<16, true, false, 0>(f, p, 0, qi, kVec);
+    if (qrow < a.m && qcol < a.n) store_outputs<16, true, false, 0>(f, p, 0, qi, kVec);
   } else if (qrow < a.m && qcol < a.n) {
     const uint32_t nvalid = a.n - qcol >= (uint32_t)kVec ? (uint32_t)kVec : a.n - qcol;
     RF<16> f = load_inputs<16, kMaxIn, false, false>(rf_zero<16>(), p, 0, qi, nvalid);
