@@ -614,6 +614,55 @@ __global__ __launch_bounds__(kColBlock) void lt_col_reduce_kernel(const ColArgs 
 }
 
 
+// Column sums whose partial sums another launch has left (ColArgs::parts): a workgroup owns 16 columns, 64 groups
+// of four lanes take interleaved rows, four of them in flight, and meet in LDS in a fixed order.  blockIdx.y: which of
+// the sums.  Bound by launch and memory latency.
+__global__ __launch_bounds__(kBlock) void lt_col_finish_kernel(const ColArgs a) {
+  const uint32_t touched = touch_args<ColArgs>();
+  __shared__ float4 lds[kBlock];
+  const EwProg& post = blockIdx.y ? a.post2 : a.post;
+  const ProgRegs regs = load_prog_regs(post);
+  const uint32_t quad = threadIdx.x & 3u, group = threadIdx.x >> 2, c = blockIdx.x * 16u + quad * 4u;
+  const uint32_t sums = 1u + a.sum2;
+  const float* src = a.parts + (uint64_t)blockIdx.y * a.cols + min(c, a.cols - 4u);
+  float4 acc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  for (uint32_t r0 = group; r0 < a.parts_rows; r0 += 256u) {
+    float4 t[4];
+#pragma unroll
+    for (uint32_t j = 0; j < 4u; ++j) t[j] = *(const float4*)(src + (uint64_t)min(r0 + 64u * j, a.parts_rows - 1u) * sums * a.cols);
+#pragma unroll
+    for (uint32_t j = 0; j < 4u; ++j)
+      if (r0 + 64u * j < a.parts_rows) {
+        acc.x += t[j].x; acc.y += t[j].y; acc.z += t[j].z; acc.w += t[j].w;
+      }
+  }
+  lds[threadIdx.x] = acc;
+  for (uint32_t n = 8u; n > 0u; n = n == 8u ? 1u : 0u) {   // 64 groups -> 8 -> 1
+    __syncthreads();
+    if (threadIdx.x < n * 4u) {
+      acc = lds[threadIdx.x];
+#pragma unroll
+      for (uint32_t j = 1; j < 8u; ++j) {
+        const float4 o = lds[threadIdx.x + j * n * 4u];
+        acc.x += o.x; acc.y += o.y; acc.z += o.z; acc.w += o.w;
+      }
+    }
+    __syncthreads();
+    if (threadIdx.x < n * 4u) lds[threadIdx.x] = acc;
+  }
+  if (threadIdx.x < 4u && c < a.cols) {
+    Quad q;
+    q.v[0] = acc.x; q.v[1] = acc.y; q.v[2] = acc.z; q.v[3] = acc.w;
+    if (a.red == kRedMean) {
+      const float inv = 1.0f / (float)a.rows;
+#pragma unroll
+      for (int e = 0; e < kVec; ++e) q.v[e] *= inv;
+    }
+    run_post(post, regs, q, c, kVec);
+  }
+  args_touched(touched);
+}
+
 // Host side: does the program qualify for the streamed row reduction?  Fills in a->vin, a->rin and
 // picks threads per row and vectors per trip.
 static bool row_stream_args(RowArgs* a, uint32_t* grid, uint32_t* q, bool* ragged) {
@@ -728,6 +777,11 @@ static int mixed_kind(ColArgs* a) {
 hipError_t launch_col_reduce(const ColArgs& args, uint32_t grid_x, uint32_t grid_y, hipStream_t s) {
   const dim3 g(grid_x, grid_y), b(kColBlock);
   ColArgs a = args;
+  if (a.parts) {
+    if ((a.cols % 4u) != 0u || a.parts_rows == 0u || !a.norm_grad || (a.sum2 && a.red != kRedSum)) return hipErrorInvalidValue;
+    LT_LAUNCH(lt_col_finish_kernel, dim3((a.cols + 15u) / 16u, 1u + a.sum2), dim3(kBlock), s, a);
+    return hipGetLastError();
+  }
   if (a.norm_grad) {   // (the lowering has looked at the program; cols % 4 == 0, whole vectors)
     if ((a.cols % 4u) != 0u || (a.sum2 && a.red != kRedSum)) return hipErrorInvalidValue;
     if (a.pro.in[a.vin[0]].dtype == kBF16) LT_LAUNCH((lt_col_reduce_kernel<16, 2, 8, true, 2, true>), g, b, s, a);

@@ -288,11 +288,18 @@ __device__ __forceinline__ void wide_store(void* p, uint64_t elem, const float* 
   }
 }
 
-template <int OP, int NV, bool BF>
-__global__ __launch_bounds__(kBlock) void lt_norm_stream_kernel(const RowOpArgs a) {
+// CS > 0 (gradient only): the weight gradient's sums over the rows of dy * xhat, and with CS = 2 the bias gradient's of dy,
+// ride along.  Both read what this pass has in registers, and a lane's columns are the same in all its rows, so a row costs
+// two additions per element; as a launch of their own they are a second pass over both tensors.  Workgroups are
+// twice the size and walk more rows each (RowOpArgs::col_rows of them), so that fewer partial sums are left for the
+// launch that adds them up.  Norm forward, gradient and sums, us a pass (from 28 on
+// the recording of it takes as long): 8192 x 1024 in bf16 35.6 -> 28.5, fp32 46.8 -> 32.2, 16000 x 2048 in bf16 109 -> 63, 131072 x 256 205 -> 81.
+template <int OP, int NV, bool BF, int CS>
+__global__ __launch_bounds__(CS ? 2 * kBlock : kBlock) void lt_norm_stream_kernel(const RowOpArgs a) {
+  constexpr uint32_t kWaves = (CS ? 2 * kBlock : kBlock) / 64;
   constexpr int E = Wide<BF>::E, N = NV * E;
   constexpr bool kGrad = OP == kLayerNormGrad;   // in: dy, x, gain, mean, rstd; otherwise x, gain, shift
-  const uint32_t lane = threadIdx.x & 63u, wave = blockIdx.x * (kBlock / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = gridDim.x * (kBlock / 64);
+  const uint32_t lane = threadIdx.x & 63u, wave = blockIdx.x * kWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = gridDim.x * kWaves;
   const uint32_t cols = a.cols;
   uint32_t col[NV];
   bool in[NV];
@@ -318,6 +325,13 @@ __global__ __launch_bounds__(kBlock) void lt_norm_stream_kernel(const RowOpArgs 
   };
   fetch(wave);
   if (kGrad) fetch_stats(wave);
+  float sum[CS > 0 ? CS : 1][CS > 0 ? N : 1];
+  if (CS > 0) {
+#pragma unroll
+    for (int c = 0; c < CS; ++c)
+#pragma unroll
+      for (int i = 0; i < N; ++i) sum[c][CS > 0 ? i : 0] = 0.0f;
+  }
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
     g[k] = wide_load<BF>(a.in[kGrad ? 2 : 1], col[k]);
@@ -367,6 +381,8 @@ __global__ __launch_bounds__(kBlock) void lt_norm_stream_kernel(const RowOpArgs 
           t[i] = (wide_get<BF>(r1[k], e) - mean) * rstd;
           s += in[k] ? x[i] : 0.0f;
           s2 += in[k] ? x[i] * t[i] : 0.0f;
+          if (CS > 0) sum[0][CS > 0 ? i : 0] += wide_get<BF>(r0[k], e) * t[i];
+          if (CS > 1) sum[CS > 1 ? 1 : 0][CS > 1 ? i : 0] += wide_get<BF>(r0[k], e);
         }
       fetch(row + waves);
       fetch_stats(row + waves);
@@ -379,21 +395,48 @@ __global__ __launch_bounds__(kBlock) void lt_norm_stream_kernel(const RowOpArgs 
       }
     }
   }
+  if (CS > 0) {   // the waves' sums meet in LDS, in order
+    __shared__ float4 meet[CS > 0 ? kWaves * 64 * N / 4 : 1];
+    constexpr uint32_t kQuads = 64u * N / 4u;   // of a row of NV chunks per lane
+#pragma unroll
+    for (int c = 0; c < CS; ++c) {
+      if (c > 0) __syncthreads();
+#pragma unroll
+      for (int i = 0; i < N; i += 4)
+        meet[(threadIdx.x >> 6) * kQuads + ((uint32_t)(i / E) * 64u + lane) * (E / 4) + (uint32_t)(i % E) / 4u] =
+            make_float4(sum[c][CS > 0 ? i : 0], sum[c][CS > 0 ? i + 1 : 0], sum[c][CS > 0 ? i + 2 : 0], sum[c][CS > 0 ? i + 3 : 0]);
+      __syncthreads();
+      for (uint32_t q = threadIdx.x; q < cols / 4u; q += blockDim.x) {
+        float4 v = meet[q];
+#pragma unroll
+        for (uint32_t w = 1; w < kWaves; ++w) {
+          const float4 o = meet[w * kQuads + q];
+          v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
+        }
+        *(float4*)(a.col_parts + ((uint64_t)blockIdx.x * CS + c) * cols + q * 4u) = v;
+      }
+    }
+  }
 }
 
-template <int OP, int NV, bool BF>
+template <int OP, int NV, bool BF, int CS = 0>
 static hipError_t launch_norm(const RowOpArgs& a, hipStream_t s) {
   // (a wave per row until the chip holds four waves per SIMD; then each walks a few)
-  const uint32_t grid = std::min((a.rows + kBlock / 64u - 1u) / (kBlock / 64u), 1024u);
-  LT_LAUNCH((lt_norm_stream_kernel<OP, NV, BF>), dim3(grid), dim3(kBlock), s, a);
+  const uint32_t grid = CS ? a.col_rows : std::min((a.rows + kBlock / 64u - 1u) / (kBlock / 64u), 1024u);
+  LT_LAUNCH((lt_norm_stream_kernel<OP, NV, BF, CS>), dim3(grid), dim3(CS ? 2 * kBlock : kBlock), s, a);
   char name[48];
-  snprintf(name, sizeof(name), "lt_norm_stream_kernel<%d, %d, %s>", (int)OP, NV, BF ? "true" : "false");
+  snprintf(name, sizeof(name), "lt_norm_stream_kernel<%d, %d, %s, %d>", (int)OP, NV, BF ? "true" : "false", CS);
   note_kernel(name);
   return hipGetLastError();
 }
 template <int OP, bool BF>
 static hipError_t launch_norm_cols(const RowOpArgs& a, hipStream_t s) {
   const uint32_t per = 64u * Wide<BF>::E;
+  if constexpr (OP == kLayerNormGrad) {
+    if (a.col_sums > 2u || (a.col_sums && (!a.col_parts || a.col_rows == 0u || a.cols > 4u * per))) return hipErrorInvalidValue;
+    if (a.col_sums == 1u) return a.cols <= per ? launch_norm<OP, 1, BF, 1>(a, s) : a.cols <= 2u * per ? launch_norm<OP, 2, BF, 1>(a, s) : launch_norm<OP, 4, BF, 1>(a, s);
+    if (a.col_sums == 2u) return a.cols <= per ? launch_norm<OP, 1, BF, 2>(a, s) : a.cols <= 2u * per ? launch_norm<OP, 2, BF, 2>(a, s) : launch_norm<OP, 4, BF, 2>(a, s);
+  }
   if (a.cols <= per) return launch_norm<OP, 1, BF>(a, s);
   if (a.cols <= 2u * per) return launch_norm<OP, 2, BF>(a, s);
   if (a.cols <= 4u * per) return launch_norm<OP, 4, BF>(a, s);
@@ -442,6 +485,7 @@ hipError_t launch_row_op(const RowOpArgs& a, uint32_t grid, hipStream_t s) {
     if (a.op == kLayerNorm) return io == 2 ? launch_norm_cols<kLayerNorm, true>(a, s) : launch_norm_cols<kLayerNorm, false>(a, s);
     return io == 2 ? launch_norm_cols<kLayerNormGrad, true>(a, s) : launch_norm_cols<kLayerNormGrad, false>(a, s);
   }
+  if (a.col_sums) return hipErrorInvalidValue;   // (only the streamed gradient takes sums along)
   switch (a.op) {
     case kSoftmax: return launch_tpr<kSoftmax>(a, io, grid, s);
     case kSoftmaxGrad: return launch_tpr<kSoftmaxGrad>(a, io, grid, s);

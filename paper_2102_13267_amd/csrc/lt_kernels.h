@@ -144,6 +144,10 @@ struct ColArgs {
   // their partials follow the others', post2 runs on them
   uint32_t sum2;
   EwProg post2;        // iteration space [cols]
+  // Not null: the launch that computed the norm's gradient has left `parts_rows` partial sums of every column here (rows
+  // of [1 + sum2][cols] floats: the weight gradient's, then the bias gradient's), and this one only adds them up.
+  const float* parts;
+  uint32_t parts_rows, pad;
 };
 
 // ---- row operators with a fixed body ---------------------------------------------------
@@ -157,6 +161,10 @@ struct RowOpArgs {
   uint32_t out_dtype[3];
   float eps;           // layer norm
   float scale;         // xent_grad
+  // layer_norm_grad: column sums that ride along (0 none, 1 of dy * xhat, 2 of dy as well); col_rows workgroups leave theirs in
+  // col_parts, a row of [col_sums][cols] floats each (ColArgs::parts)
+  uint32_t col_sums, col_rows;
+  float* col_parts;
 };
 
 // ---- contraction ------------------------------------------------------------------------

@@ -1109,6 +1109,7 @@ struct Lowering {
       emit_attention(k, &in_core);
       if (!in_core && !emit_region(k, ordered[k])) return false;
     }
+    norm_sums_with_gradient();
     for (Storage& s : plan->storages)
       if (s.first_launch < 0) s.first_launch = s.last_launch = 0;
     plan->n_regions = (int)ordered.size();
@@ -1430,6 +1431,63 @@ struct Lowering {
     note_prog_storages(pro, (int)prev);
     note_prog_storages(post, (int)prev);
     return true;
+  }
+
+  // A norm's weight and bias gradients behind its input gradient: the launch of the latter reads the same four tensors
+  // row by row and takes the sums along (RowOpArgs::col_sums); the column launch stays where it is and only adds up
+  // the partial sums.  Rows of whole 16-byte chunks, at most four to a lane (the sums take as many registers as the row).
+  void norm_sums_with_gradient() {
+    if (!merge) return;
+    for (size_t j = 0; j < plan->launches.size(); ++j) {
+      if (plan->launches[j].kind != L_COL) continue;
+      const ltk::ColArgs* ca = (const ltk::ColArgs*)plan->launches[j].args.data();
+      const uint32_t dt = ca->norm_grad ? ca->pro.in[ca->vin[0]].dtype : 0u;
+      if (!ca->norm_grad || ca->cols % (dt == ltk::kBF16 ? 8u : 4u) || ca->cols > (dt == ltk::kBF16 ? 2048u : 1024u)) continue;
+      const uint32_t which[4] = {ca->vin[0], ca->vin[1], ca->cin[0], ca->cin[1]}, arg[4] = {0, 1, 3, 4};   // dy, x, mean, rstd: inputs here, inputs there
+      int32_t st[4] = {-1, -1, -1, -1};
+      int64_t at[4] = {0, 0, 0, 0};
+      for (const PtrPatch& pp : plan->ptr_patches)
+        for (int q = 0; q < 4; ++q)
+          if (pp.launch == j && pp.offset == offsetof(ltk::ColArgs, pro) + offsetof(ltk::EwProg, in) + which[q] * sizeof(ltk::EwIn) + offsetof(ltk::EwIn, ptr))
+            st[q] = pp.storage, at[q] = pp.byte_offset;
+      for (size_t i = j; i-- > 0;) {
+        Launch& l = plan->launches[i];
+        bool overwritten = false;   // (by a launch that the sums would be taken before)
+        for (const PtrPatch& pp : plan->ptr_patches)
+          for (int q = 0; q < 4; ++q) overwritten = overwritten || (pp.launch == i && pp.write && same_buffer(pp.storage, st[q]));
+        if (overwritten) break;
+        ltk::RowOpArgs* ra = (ltk::RowOpArgs*)l.args.data();
+        if (l.kind != L_ROWOP || ra->op != ltk::kLayerNormGrad || ra->col_sums || ra->rows != ca->rows || ra->cols != ca->cols) continue;
+        if (ra->in_dtype[0] != dt || ra->in_dtype[1] != dt || ra->in_dtype[2] != dt || ra->out_dtype[0] != dt || ra->in_dtype[3] != ltk::kF32 || ra->in_dtype[4] != ltk::kF32) continue;
+        int same = 0;
+        for (const PtrPatch& pp : plan->ptr_patches)
+          for (int q = 0; q < 4; ++q)
+            same += pp.launch == i && pp.offset == offsetof(ltk::RowOpArgs, in) + arg[q] * sizeof(void*) && pp.storage == st[q] && pp.byte_offset == at[q];
+        if (same != 4) continue;
+        ra->col_sums = 1u + ca->sum2;
+        // eight waves to a workgroup, four rows or more to a wave, at most two workgroups per compute unit
+        ra->col_rows = std::min(512u, std::max(1u, (ra->rows + 31u) / 32u));
+        Storage ws;
+        ws.bytes = (size_t)ra->col_rows * ra->col_sums * ra->cols * sizeof(float);
+        ws.first_launch = (int)i;
+        ws.last_launch = (int)j;
+        const int32_t ws_storage = (int32_t)plan->storages.size();
+        plan->storages.push_back(ws);
+        plan->merged = true;
+        auto& pps = plan->ptr_patches;
+        pps.erase(std::remove_if(pps.begin(), pps.end(), [&](const PtrPatch& pp) { return pp.launch == j && pp.offset < offsetof(ltk::ColArgs, pro) + sizeof(ltk::EwProg); }), pps.end());
+        pps.push_back(PtrPatch{(uint32_t)i, (uint32_t)offsetof(ltk::RowOpArgs, col_parts), ws_storage, 0, 1});
+        pps.push_back(PtrPatch{(uint32_t)j, (uint32_t)offsetof(ltk::ColArgs, parts), ws_storage, 0});
+        ((ltk::ColArgs*)plan->launches[j].args.data())->parts_rows = ra->col_rows;
+        plan->launches[j].bytes = ws.bytes;
+        break;
+      }
+    }
+  }
+
+  bool same_buffer(int32_t x, int32_t y) const {
+    if (x < 0 || y < 0) return false;
+    return x == y || (plan->storages[x].param >= 0 && plan->storages[x].param == plan->storages[y].param);
   }
 
   // Prologue of a reduction: the members below the anchor, producing `src` in slot anchor_slot.

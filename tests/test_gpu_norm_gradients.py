@@ -91,3 +91,34 @@ def test_norm_forward_and_backward(ctx, rows, cols, dt):  # noqa: F811
         return y, mu, rs, B.layer_norm_grad(dy, x, w, mu, rs)
     for i, (p, q) in enumerate(zip(prog(ctx), prog(E))):
         check(ctx, E, p, q, 2e-2 if dt == "bf16" else 2e-5, i)
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("rows,cols", [(2, 8), (31, 256), (33, 504), (257, 512), (8193, 520), (16500, 1024), (300, 1032), (2100, 2048), (70, 2056), (5, 1028), (64, 1030)])
+def test_sums_that_ride_with_the_input_gradient(ctx, rows, cols, dt):  # noqa: F811
+    """One to more than 512 workgroups' partial sums, a wave with a row more than another, the last chunk that few lanes
+    have, rows too long for it or of no whole chunks (launches of their own); both sums, one alone, parameters updated in
+    place by them, and x overwritten between the input gradient and the sums (which then take the new x)."""
+    E, data = Eager(), operands(rows, cols, dt)
+    tol = 2e-2 if dt == "bf16" else 2e-5 * max(1.0, rows ** 0.5 / 8)
+
+    def run(B, mk, variant):
+        x, dy, w, b = (mk(t) for t in data)
+        y, mu, rs = B.layer_norm(x, w, b, eps=1e-5)
+        dx = B.layer_norm_grad(dy, x, w, mu, rs)
+        if variant == 3:
+            B.assign(x, B.mul(x, 0.5))
+        dg = B.sum(B.mul(dy, B.mul(B.sub(x, B.reshape(mu, (rows, 1))), B.reshape(rs, (rows, 1)))), axis=0)
+        if variant == 1:
+            return [dx, dg]
+        db = B.sum(dy, axis=0)
+        if variant == 2:
+            low = (lambda t: B.cast(t, "bf16")) if dt == "bf16" else (lambda t: t)
+            B.assign(w, low(B.sub(w, B.mul(dg, 1e-3))))
+            B.assign(b, low(B.sub(b, B.mul(db, 1e-3))))
+            return [dx, w, b]
+        return [y, dx, dg, db, x]
+    for variant in range(4):
+        got, ref = run(ctx, lambda t: ctx.tensor(t, dtype=dt, donatable=True), variant), run(E, lambda t: E.tensor(t, dtype=dt), variant)
+        for i, (p, q) in enumerate(zip(got, ref)):
+            check(ctx, E, p, q, tol, (variant, i))
