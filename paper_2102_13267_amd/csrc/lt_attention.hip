@@ -5,7 +5,7 @@
 //
 // What bounded the parts: they move the [heads, s, s] tensors through memory six times, their
 // products contract 32 to 128 deep (all prologue and epilogue), and rows of odd s defeat vector
-// access.  Measured, bf16, 128 heads of 200 x 64: forward 9.8, dq 16.8, dk + dv 12.7 us; the eight parts
+// access.  Measured, bf16, 128 heads of 200 x 64: forward 8.3, dq 9.3, dk + dv 12.7 us; the eight parts
 // take 80 us (107 before their ragged tiles had a path of their own).
 //
 // One workgroup of four waves takes 128 rows of one head (queries; keys in the dk / dv pass), each wave
@@ -58,7 +58,6 @@ template <typename T, int D> struct Geo {
 };
 
 template <typename T, int D> using Frags = U4[Geo<T, D>::NF];    // one row, half of it per half wave
-template <typename T, int D> using Block = U4[Geo<T, D>::N];     // a thread's share of a block of rows
 template <typename T, int D> using Acc = v16f[Geo<T, D>::DB];    // [d][x], d in blocks of 32
 
 // 16 bytes from any element boundary
@@ -85,24 +84,60 @@ __device__ __forceinline__ void row_frags(Frags<T, D>& f, const T* row, uint32_t
   for (int t = 0; t < Geo<T, D>::NF; ++t) f[t] = load16<T>(row + (2 * t + h) * (16 / sizeof(T)));
 }
 
-template <typename T, int D>
-__device__ __forceinline__ void block_fetch(Block<T, D>& r, const T* base, int64_t s_row, uint32_t row0, uint32_t rows) {
+// A workgroup's `threads` fetch `count` chunks each: rows from row0 on
+template <typename T, int D, int count, int threads>
+__device__ __forceinline__ void block_fetch(U4 (&r)[count], const T* base, int64_t s_row, uint32_t row0, uint32_t rows) {
   typedef Geo<T, D> G;
 #pragma unroll
-  for (int i = 0; i < G::N; ++i) {
-    const uint32_t e = i * kThreads + threadIdx.x, row = row0 + e / G::CH, c = e % G::CH;
+  for (int i = 0; i < count; ++i) {
+    const uint32_t e = i * threads + threadIdx.x, row = row0 + e / G::CH, c = e % G::CH;
     r[i] = load16<T>(base + (int64_t)min(row, rows - 1u) * s_row + c * (16 / sizeof(T)));
   }
 }
 
-template <typename T, int D>
-__device__ __forceinline__ void block_stash(const Block<T, D>& r, char* tile, uint32_t row0, uint32_t rows) {
+template <typename T, int D, int count, int threads>
+__device__ __forceinline__ void block_stash(const U4 (&r)[count], char* tile, uint32_t row0, uint32_t rows) {
   typedef Geo<T, D> G;
 #pragma unroll
-  for (int i = 0; i < G::N; ++i) {
-    const uint32_t e = i * kThreads + threadIdx.x, row = e / G::CH, c = e % G::CH;
+  for (int i = 0; i < count; ++i) {
+    const uint32_t e = i * threads + threadIdx.x, row = e / G::CH, c = e % G::CH;
     *(U4*)(tile + row * G::SB + c * 16) = row0 + row < rows ? r[i] : U4{0, 0, 0, 0};
   }
+}
+
+// The halves of a workgroup exchange accumulators through LDS (kSwap<D> bytes for one from each of a half's four waves)
+template <int D> constexpr int kSwap = 4 * (D / 32) * 16 * 64 * 4;
+template <typename T, int D>
+__device__ __forceinline__ void swap_put(char* lds, const Acc<T, D>& acc, uint32_t group, uint32_t lane) {
+#pragma unroll
+  for (int d = 0; d < Geo<T, D>::DB; ++d)
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      *(F4*)(lds + (((group * Geo<T, D>::DB + d) * 4 + g) * 64 + lane) * 16) = F4{acc[d][4 * g], acc[d][4 * g + 1], acc[d][4 * g + 2], acc[d][4 * g + 3]};
+}
+// acc * own + (what the other half put) * theirs
+template <typename T, int D>
+__device__ __forceinline__ void swap_add(const char* lds, Acc<T, D>& acc, float own, float theirs, uint32_t group, uint32_t lane) {
+#pragma unroll
+  for (int d = 0; d < Geo<T, D>::DB; ++d)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const F4 o = *(const F4*)(lds + (((group * Geo<T, D>::DB + d) * 4 + g) * 64 + lane) * 16);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[d][4 * g + e] = acc[d][4 * g + e] * own + o[e] * theirs;
+    }
+}
+
+// x * scale in the type's precision
+template <typename T, int count>
+__device__ __forceinline__ void scale_chunks(U4 (&x)[count], float scale) {
+  if (scale == 1.0f) return;
+#pragma unroll
+  for (int i = 0; i < count; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      x[i][j] = sizeof(T) == 2 ? f32_to_bf16_pair(__uint_as_float(x[i][j] << 16) * scale, __uint_as_float(x[i][j] & 0xffff0000u) * scale)
+                               : __float_as_uint(__uint_as_float(x[i][j]) * scale);
 }
 
 // 32 x 32 block of (LDS rows) . (register rows)^T
@@ -160,9 +195,10 @@ __device__ __forceinline__ void add_rows(Acc<T, D>& acc, const char* tile, uint3
   }
 }
 
-// acc[d][x] * scale to row x (= this lane's) of a head's output
+// acc[d][x] * scale, rounded, * post to row x (= this lane's) of a head's output
 template <typename T, int D>
-__device__ __forceinline__ void row_store(const Acc<T, D>& acc, float scale, T* row, uint32_t h) {
+__device__ __forceinline__ void row_store(const Acc<T, D>& acc, float scale, T* row, uint32_t h, float post = 1.0f) {
+  const bool twice = post != 1.0f;
 #pragma unroll
   for (int d = 0; d < Geo<T, D>::DB; ++d)
 #pragma unroll
@@ -170,6 +206,10 @@ __device__ __forceinline__ void row_store(const Acc<T, D>& acc, float scale, T* 
       Quad q;
 #pragma unroll
       for (int e = 0; e < 4; ++e) q.v[e] = acc[d][4 * g + e] * scale;
+      if (twice) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) q.v[e] = (sizeof(T) == 2 ? bf16_to_f32(f32_to_bf16(q.v[e])) : q.v[e]) * post;
+      }
       store_vec4_any(row, sizeof(T) == 2 ? kBF16 : kF32, (uint64_t)(d * 32 + g * 8 + 4 * h), q);
     }
 }
@@ -187,37 +227,40 @@ __device__ __forceinline__ float other_half(float x) { return __shfl_xor(x, 32);
 template <typename T, int D>
 __global__ __launch_bounds__(kThreads, D == 128 ? 1 : 2) void lt_attention_kernel(const AttnArgs a) {
   typedef Geo<T, D> G;
-  __shared__ __attribute__((aligned(16))) char Ks[G::TK * G::SB], Vs[G::TK * G::SB];
-  const uint32_t lane = threadIdx.x & 63u, h = lane >> 5, wave = threadIdx.x >> 6;
+  constexpr int kTileB = G::TK * G::SB;
+  __shared__ __attribute__((aligned(16))) char lds[2 * kTileB];
+  char *Ks = lds, *Vs = lds + kTileB;
+  const uint32_t lane = threadIdx.x & 63u, h = lane >> 5, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t tiles = (a.sq + kTile - 1u) / kTile, bh = blockIdx.x / tiles, b0 = bh / a.batch1, b1 = bh % a.batch1;
-  const uint32_t q0 = (blockIdx.x % tiles) * kTile + __builtin_amdgcn_readfirstlane(wave) * 32u, q = q0 + (lane & 31u);
+  const uint32_t q0 = (blockIdx.x % tiles) * kTile + wave * 32u, q = q0 + (lane & 31u);
   const bool busy = q0 < a.sq;
+  const T *kp = head<T>(a.k, b0, b1), *vp = head<T>(a.v, b0, b1);
+  U4 kr[G::N], vr[G::N];
+  block_fetch<T, D, G::N, kThreads>(kr, kp, a.k.s_row, 0, a.sk);
+  block_fetch<T, D, G::N, kThreads>(vr, vp, a.v.s_row, 0, a.sk);
   U4 qf[G::NF];
   row_frags<T, D>(qf, head<T>(a.q, b0, b1) + (int64_t)min(q, a.sq - 1u) * a.q.s_row, h);
-  const T *kp = head<T>(a.k, b0, b1), *vp = head<T>(a.v, b0, b1);
+  scale_chunks<T, G::NF>(qf, a.q_scale);
   v16f acc[G::DB];
   clear<T, D>(acc);
   float m = -INFINITY, l = 0.0f;   // of this lane's query; l over this half's rows
   // (a power of two of at most 1 / keys on every term, in l as well: unnormalised, values of the type's highest few
   // powers of two would add up to infinity)
   const float shrink = __builtin_amdgcn_ldexpf(1.0f, -(32 - (int)__clz((int)(a.sk - 1u))));
-  U4 kr[G::N], vr[G::N];
-  block_fetch<T, D>(kr, kp, a.k.s_row, 0, a.sk);
-  block_fetch<T, D>(vr, vp, a.v.s_row, 0, a.sk);
   for (uint32_t k0 = 0; k0 < a.sk; k0 += G::TK) {
     __syncthreads();
-    block_stash<T, D>(kr, Ks, k0, a.sk);
-    block_stash<T, D>(vr, Vs, k0, a.sk);
+    block_stash<T, D, G::N, kThreads>(kr, Ks, k0, a.sk);
+    block_stash<T, D, G::N, kThreads>(vr, Vs, k0, a.sk);
     __syncthreads();
-    block_fetch<T, D>(kr, kp, a.k.s_row, k0 + G::TK, a.sk);   // (past the end: the last row, unused)
-    block_fetch<T, D>(vr, vp, a.v.s_row, k0 + G::TK, a.sk);
+    block_fetch<T, D, G::N, kThreads>(kr, kp, a.k.s_row, k0 + G::TK, a.sk);   // (past the end: the last row, unused)
+    block_fetch<T, D, G::N, kThreads>(vr, vp, a.v.s_row, k0 + G::TK, a.sk);
     if (!busy) continue;
     v16f s[G::NB];
     float mx = m;
 #pragma unroll
     for (int b = 0; b < G::NB; ++b) {
       s[b] = dot_rows<T, D>(Ks, b, qf, lane);
-      if (k0 + G::TK > a.sk) {
+      if (k0 + b * 32u + 32u > a.sk) {
 #pragma unroll
         for (int r = 0; r < 16; ++r)
           if (k0 + b * 32u + (r >> 2) * 8u + 4u * h + (r & 3) >= a.sk) s[b][r] = -INFINITY;
@@ -244,10 +287,9 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 1 : 2) void lt_attention_kerne
       add_rows<T, D>(acc, Vs, b, s[b], lane);
     }
   }
-  if (!busy) return;
   l += other_half(l);
-  const float inv = 1.0f / l;
   if (q >= a.sq) return;
+  const float inv = 1.0f / l;
   row_store<T, D>(acc, inv, (T*)head<T>(a.o, b0, b1) + (int64_t)q * a.o.s_row, h);
   if (a.stats && h == 0u) {
     const uint64_t i = (uint64_t)bh * a.sq + q, n = (uint64_t)a.batch0 * a.batch1 * a.sq;
@@ -259,21 +301,24 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 1 : 2) void lt_attention_kerne
 template <typename T, int D>
 __global__ __launch_bounds__(kThreads, D == 128 ? 1 : 2) void lt_attention_dq_kernel(const AttnArgs a) {
   typedef Geo<T, D> G;
-  __shared__ __attribute__((aligned(16))) char Ks[G::TK * G::SB], Vs[G::TK * G::SB];
-  const uint32_t lane = threadIdx.x & 63u, h = lane >> 5, wave = threadIdx.x >> 6;
+  constexpr int kTileB = G::TK * G::SB;
+  __shared__ __attribute__((aligned(16))) char lds[2 * kTileB];
+  char *Ks = lds, *Vs = lds + kTileB;
+  const uint32_t lane = threadIdx.x & 63u, h = lane >> 5, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t tiles = (a.sq + kTile - 1u) / kTile, bh = blockIdx.x / tiles, b0 = bh / a.batch1, b1 = bh % a.batch1;
-  const uint32_t q0 = (blockIdx.x % tiles) * kTile + __builtin_amdgcn_readfirstlane(wave) * 32u, q = q0 + (lane & 31u);
+  const uint32_t q0 = (blockIdx.x % tiles) * kTile + wave * 32u, q = q0 + (lane & 31u);
   const uint32_t qc = min(q, a.sq - 1u);
   const bool busy = q0 < a.sq;
   const T *kp = head<T>(a.k, b0, b1), *vp = head<T>(a.v, b0, b1);
   U4 kr[G::N], vr[G::N];
-  block_fetch<T, D>(kr, kp, a.k.s_row, 0, a.sk);
-  block_fetch<T, D>(vr, vp, a.v.s_row, 0, a.sk);
+  block_fetch<T, D, G::N, kThreads>(kr, kp, a.k.s_row, 0, a.sk);
+  block_fetch<T, D, G::N, kThreads>(vr, vp, a.v.s_row, 0, a.sk);
   U4 qf[G::NF], df[G::NF];
   row_frags<T, D>(qf, head<T>(a.q, b0, b1) + (int64_t)qc * a.q.s_row, h);
   row_frags<T, D>(df, head<T>(a.dy, b0, b1) + (int64_t)qc * a.dy.s_row, h);
   const uint64_t i = (uint64_t)bh * a.sq + qc, n = (uint64_t)a.batch0 * a.batch1 * a.sq;
   const float m = a.stats[i], inv = a.stats[n + i];
+  scale_chunks<T, G::NF>(qf, a.q_scale);
   float delta = 0.0f;   // of this lane's query; this half's rows until the first walk is over
   v16f acc[G::DB];
   clear<T, D>(acc);
@@ -281,26 +326,27 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 1 : 2) void lt_attention_dq_ke
   // two walks over the keys: the row sum of p * (dy v^T) first, then the gradient
   for (uint32_t it = 0; it < 2u * blocks; ++it) {
     const uint32_t k0 = (it < blocks ? it : it - blocks) * G::TK, k1 = (it + 1u < blocks ? it + 1u : it + 1u - blocks) * G::TK;
+    if (it == blocks) delta += other_half(delta);
     __syncthreads();
-    block_stash<T, D>(kr, Ks, k0, a.sk);
-    block_stash<T, D>(vr, Vs, k0, a.sk);
+    block_stash<T, D, G::N, kThreads>(kr, Ks, k0, a.sk);
+    block_stash<T, D, G::N, kThreads>(vr, Vs, k0, a.sk);
     __syncthreads();
-    block_fetch<T, D>(kr, kp, a.k.s_row, k1, a.sk);
-    block_fetch<T, D>(vr, vp, a.v.s_row, k1, a.sk);
-    if (!busy) continue;
+    block_fetch<T, D, G::N, kThreads>(kr, kp, a.k.s_row, k1, a.sk);
+    block_fetch<T, D, G::N, kThreads>(vr, vp, a.v.s_row, k1, a.sk);
     const bool first = it < blocks;
-    if (it == blocks) {
-      delta += other_half(delta);
-      if (h == 0u && q < a.sq) a.stats[2u * n + i] = delta;
-    }
+    if (it == blocks && h == 0u && q < a.sq) a.stats[2u * n + i] = delta;
+    if (!busy) continue;
 #pragma unroll
     for (int b = 0; b < G::NB; ++b) {
+      if (k0 + b * 32u >= a.sk) continue;
       v16f s = dot_rows<T, D>(Ks, b, qf, lane);
       const v16f dp = dot_rows<T, D>(Vs, b, df, lane);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        s[r] = __builtin_amdgcn_exp2f((s[r] - m) * kLog2e) * inv;
-        if (k0 + b * 32u + (r >> 2) * 8u + 4u * h + (r & 3) >= a.sk) s[r] = 0.0f;
+      for (int r = 0; r < 16; ++r) s[r] = __builtin_amdgcn_exp2f((s[r] - m) * kLog2e) * inv;
+      if (k0 + b * 32u + 32u > a.sk) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (k0 + b * 32u + (r >> 2) * 8u + 4u * h + (r & 3) >= a.sk) s[r] = 0.0f;
       }
       if (first) {
 #pragma unroll
@@ -312,17 +358,19 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 1 : 2) void lt_attention_dq_ke
       }
     }
   }
-  if (q < a.sq) row_store<T, D>(acc, 1.0f, (T*)head<T>(a.dq, b0, b1) + (int64_t)q * a.dq.s_row, h);
+  if (q < a.sq) row_store<T, D>(acc, 1.0f, (T*)head<T>(a.dq, b0, b1) + (int64_t)q * a.dq.s_row, h, a.dq_scale);
 }
 
 template <typename T, int D>
 __global__ __launch_bounds__(kThreads, D == 128 ? 1 : 2) void lt_attention_dkv_kernel(const AttnArgs a) {
   typedef Geo<T, D> G;
-  __shared__ __attribute__((aligned(16))) char Qs[G::TK * G::SB], Ds[G::TK * G::SB];
+  constexpr int kTileB = G::TK * G::SB;
+  __shared__ __attribute__((aligned(16))) char lds[2 * kTileB];
   __shared__ __attribute__((aligned(16))) float st[3][G::TK];
-  const uint32_t lane = threadIdx.x & 63u, h = lane >> 5, wave = threadIdx.x >> 6;
+  char *Qs = lds, *Ds = lds + kTileB;
+  const uint32_t lane = threadIdx.x & 63u, h = lane >> 5, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t tiles = (a.sk + kTile - 1u) / kTile, bh = blockIdx.x / tiles, b0 = bh / a.batch1, b1 = bh % a.batch1;
-  const uint32_t k0 = (blockIdx.x % tiles) * kTile + __builtin_amdgcn_readfirstlane(wave) * 32u, key = k0 + (lane & 31u);
+  const uint32_t k0 = (blockIdx.x % tiles) * kTile + wave * 32u, key = k0 + (lane & 31u);
   const uint32_t kc = min(key, a.sk - 1u);
   const bool busy = k0 < a.sk;
   const T *qp = head<T>(a.q, b0, b1), *dp = head<T>(a.dy, b0, b1);
@@ -331,8 +379,8 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 1 : 2) void lt_attention_dkv_k
   U4 qr[G::N], dr[G::N];
   float sr[3] = {0.0f, 0.0f, 0.0f};
   auto fetch = [&](uint32_t q0) {
-    block_fetch<T, D>(qr, qp, a.q.s_row, q0, a.sq);
-    block_fetch<T, D>(dr, dp, a.dy.s_row, q0, a.sq);
+    block_fetch<T, D, G::N, kThreads>(qr, qp, a.q.s_row, q0, a.sq);
+    block_fetch<T, D, G::N, kThreads>(dr, dp, a.dy.s_row, q0, a.sq);
     const uint32_t q = q0 + threadIdx.x;
     if (threadIdx.x < (uint32_t)G::TK) {
 #pragma unroll
@@ -348,8 +396,9 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 1 : 2) void lt_attention_dkv_k
   clear<T, D>(dv);
   for (uint32_t q0 = 0; q0 < a.sq; q0 += G::TK) {
     __syncthreads();
-    block_stash<T, D>(qr, Qs, q0, ~0u);   // (past the end: the last query again, see the top)
-    block_stash<T, D>(dr, Ds, q0, a.sq);
+    scale_chunks<T, G::N>(qr, a.q_scale);
+    block_stash<T, D, G::N, kThreads>(qr, Qs, q0, ~0u);   // (past the end: the last query again, see the top)
+    block_stash<T, D, G::N, kThreads>(dr, Ds, q0, a.sq);
     if (threadIdx.x < (uint32_t)G::TK) {
 #pragma unroll
       for (int j = 0; j < 3; ++j) st[j][threadIdx.x] = sr[j];
@@ -359,6 +408,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 1 : 2) void lt_attention_dkv_k
     if (!busy) continue;
 #pragma unroll
     for (int b = 0; b < G::NB; ++b) {
+      if (q0 + b * 32u >= a.sq) continue;
       v16f s = dot_rows<T, D>(Qs, b, kf, lane);
       v16f ds = dot_rows<T, D>(Ds, b, vf, lane);
 #pragma unroll
@@ -381,16 +431,193 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 1 : 2) void lt_attention_dkv_k
   row_store<T, D>(dv, 1.0f, (T*)head<T>(a.dv, b0, b1) + (int64_t)key * a.dv.s_row, h);
 }
 
+// Up to 256 keys (bf16, heads of up to 64): the walk's cost was its chain of barriers, loads and, in the backward pass,
+// the second computation of everything, with one wave per SIMD.  Here all keys are in LDS at once, eight waves share
+// them (a group of 32 queries has two, one for every other block of 32 keys), and what the first use of a block computes stays in
+// registers for the second.  The halves' sums meet in LDS.  With events around the launch, us, before / now: 128 heads of
+// 200 x 64 forward 11.8 / 10.3, dq 18.5 / 11.3; 512 of 256 x 64 26.4 / 27.6 and 47.0 / 42.5; 256 of 128 x 64 9.2 / 9.4 and 13.6 / 10.8;
+// 128 of 200 x 32 9.4 / 8.5 and 14.4 / 8.7.  (Long walks gain nothing from two halves: at 200 x 64 forward 11.6, dk + dv 15.2 /
+// 14.6, at 256 x 64 and 512 heads dk + dv 40 / 53: the registers of both halves fit a compute unit only once.)
+template <typename T, int D, int KB>
+__global__ __launch_bounds__(2 * kThreads, 4) void lt_attention_kernel_short(const AttnArgs a) {
+  typedef Geo<T, D> G;
+  constexpr int kT = 2 * kThreads, kRows = 64 * KB, kCount = kRows * G::CH / kT < 1 ? 1 : kRows * G::CH / kT, kTileB = kRows * G::SB;
+  static_assert(kRows * G::CH % kT == 0 || kRows * G::CH < kT, "chunks per thread");
+  __shared__ __attribute__((aligned(16))) char lds[2 * kTileB > kSwap<D> ? 2 * kTileB : kSwap<D>];
+  __shared__ float st[2][kThreads];
+  char *Ks = lds, *Vs = lds + kTileB;
+  const uint32_t lane = threadIdx.x & 63u, h = lane >> 5, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), group = wave & 3u, half = wave >> 2;
+  const uint32_t tiles = (a.sq + kTile - 1u) / kTile, bh = blockIdx.x / tiles, b0 = bh / a.batch1, b1 = bh % a.batch1;
+  const uint32_t q0 = (blockIdx.x % tiles) * kTile + group * 32u, q = q0 + (lane & 31u);
+  const bool busy = q0 < a.sq;
+  {
+    U4 kr[kCount], vr[kCount];
+    block_fetch<T, D, kCount, kT>(kr, head<T>(a.k, b0, b1), a.k.s_row, 0, a.sk);
+    block_fetch<T, D, kCount, kT>(vr, head<T>(a.v, b0, b1), a.v.s_row, 0, a.sk);
+    if (kRows * G::CH >= kT || threadIdx.x < (uint32_t)(kRows * G::CH)) {
+      block_stash<T, D, kCount, kT>(kr, Ks, 0, a.sk);
+      block_stash<T, D, kCount, kT>(vr, Vs, 0, a.sk);
+    }
+  }
+  v16f acc[G::DB];
+  clear<T, D>(acc);
+  float m = -INFINITY, l = 0.0f;
+  const float shrink = __builtin_amdgcn_ldexpf(1.0f, -(32 - (int)__clz((int)(a.sk - 1u))));   // (see above)
+  U4 qf[G::NF];
+  row_frags<T, D>(qf, head<T>(a.q, b0, b1) + (int64_t)min(q, a.sq - 1u) * a.q.s_row, h);
+  scale_chunks<T, G::NF>(qf, a.q_scale);
+  __syncthreads();
+  if (busy && half * 32u < a.sk) {
+    v16f s[KB];
+#pragma unroll
+    for (int b = 0; b < KB; ++b) {
+      const uint32_t blk = 2u * b + half;
+      if (blk * 32u >= a.sk) continue;
+      s[b] = dot_rows<T, D>(Ks, blk, qf, lane);
+      if (blk * 32u + 32u > a.sk) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (blk * 32u + (r >> 2) * 8u + 4u * h + (r & 3) >= a.sk) s[b][r] = -INFINITY;
+      }
+#pragma unroll
+      for (int r = 0; r < 16; ++r) m = fmaxf(m, s[b][r]);
+    }
+    m = fmaxf(m, other_half(m));
+    const float base = m == -INFINITY ? 0.0f : m;
+#pragma unroll
+    for (int b = 0; b < KB; ++b) {
+      const uint32_t blk = 2u * b + half;
+      if (blk * 32u >= a.sk) continue;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        s[b][r] = __builtin_amdgcn_exp2f((s[b][r] - base) * kLog2e) * shrink;
+        l += s[b][r];
+      }
+      add_rows<T, D>(acc, Vs, blk, s[b], lane);
+    }
+  }
+  l += other_half(l);
+  __syncthreads();   // (the tiles have been read)
+  const uint32_t i = group * 64u + lane;
+  if (half == 1u) {
+    swap_put<T, D>(lds, acc, group, lane);
+    st[0][i] = m;
+    st[1][i] = l;
+  }
+  __syncthreads();
+  if (half == 1u || q >= a.sq) return;
+  const float m1 = st[0][i], mx = fmaxf(m, m1), base = mx == -INFINITY ? 0.0f : mx;
+  const float own = __builtin_amdgcn_exp2f((m - base) * kLog2e), theirs = __builtin_amdgcn_exp2f((m1 - base) * kLog2e);
+  l = l * own + st[1][i] * theirs;
+  swap_add<T, D>(lds, acc, own, theirs, group, lane);
+  const float inv = 1.0f / l;
+  row_store<T, D>(acc, inv, (T*)head<T>(a.o, b0, b1) + (int64_t)q * a.o.s_row, h);
+  if (a.stats && h == 0u) {
+    const uint64_t j = (uint64_t)bh * a.sq + q, n = (uint64_t)a.batch0 * a.batch1 * a.sq;
+    a.stats[j] = mx;
+    a.stats[n + j] = inv * shrink;
+  }
+}
+
+// The backward half of it: a block's probabilities and their gradients wait in registers for the row sum
+template <typename T, int D, int KB>
+__global__ __launch_bounds__(2 * kThreads, 2) void lt_attention_dq_kernel_short(const AttnArgs a) {
+  typedef Geo<T, D> G;
+  constexpr int kT = 2 * kThreads, kRows = 64 * KB, kCount = kRows * G::CH / kT < 1 ? 1 : kRows * G::CH / kT, kTileB = kRows * G::SB;
+  static_assert(kRows * G::CH % kT == 0 || kRows * G::CH < kT, "chunks per thread");
+  __shared__ __attribute__((aligned(16))) char lds[2 * kTileB > kSwap<D> ? 2 * kTileB : kSwap<D>];
+  __shared__ float st[2][kThreads];
+  char *Ks = lds, *Vs = lds + kTileB;
+  const uint32_t lane = threadIdx.x & 63u, h = lane >> 5, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), group = wave & 3u, half = wave >> 2;
+  const uint32_t tiles = (a.sq + kTile - 1u) / kTile, bh = blockIdx.x / tiles, b0 = bh / a.batch1, b1 = bh % a.batch1;
+  const uint32_t q0 = (blockIdx.x % tiles) * kTile + group * 32u, q = q0 + (lane & 31u);
+  const uint32_t qc = min(q, a.sq - 1u);
+  const bool busy = q0 < a.sq;
+  U4 kr[kCount], vr[kCount], qf[G::NF], df[G::NF];
+  block_fetch<T, D, kCount, kT>(kr, head<T>(a.k, b0, b1), a.k.s_row, 0, a.sk);
+  block_fetch<T, D, kCount, kT>(vr, head<T>(a.v, b0, b1), a.v.s_row, 0, a.sk);
+  row_frags<T, D>(qf, head<T>(a.q, b0, b1) + (int64_t)qc * a.q.s_row, h);
+  row_frags<T, D>(df, head<T>(a.dy, b0, b1) + (int64_t)qc * a.dy.s_row, h);
+  const uint64_t i = (uint64_t)bh * a.sq + qc, n = (uint64_t)a.batch0 * a.batch1 * a.sq;
+  const float m = a.stats[i], inv = a.stats[n + i];
+  scale_chunks<T, G::NF>(qf, a.q_scale);
+  if (kRows * G::CH >= kT || threadIdx.x < (uint32_t)(kRows * G::CH)) {
+    block_stash<T, D, kCount, kT>(kr, Ks, 0, a.sk);
+    block_stash<T, D, kCount, kT>(vr, Vs, 0, a.sk);
+  }
+  __syncthreads();
+  v16f s[KB], dp[KB], acc[G::DB];
+  clear<T, D>(acc);
+  float delta = 0.0f;
+  if (busy) {
+#pragma unroll
+    for (int b = 0; b < KB; ++b) {
+      const uint32_t blk = 2u * b + half;
+      if (blk * 32u >= a.sk) continue;
+      s[b] = dot_rows<T, D>(Ks, blk, qf, lane);
+      dp[b] = dot_rows<T, D>(Vs, blk, df, lane);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[b][r] = __builtin_amdgcn_exp2f((s[b][r] - m) * kLog2e) * inv;
+      if (blk * 32u + 32u > a.sk) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (blk * 32u + (r >> 2) * 8u + 4u * h + (r & 3) >= a.sk) s[b][r] = 0.0f;
+      }
+#pragma unroll
+      for (int r = 0; r < 16; ++r) delta = fmaf(s[b][r], dp[b][r], delta);
+    }
+  }
+  delta += other_half(delta);
+  st[half][group * 64u + lane] = delta;
+  __syncthreads();
+  delta = st[0][group * 64u + lane] + st[1][group * 64u + lane];
+  if (half == 0u && h == 0u && q < a.sq) a.stats[2u * n + i] = delta;
+  if (busy) {
+#pragma unroll
+    for (int b = 0; b < KB; ++b) {
+      const uint32_t blk = 2u * b + half;
+      if (blk * 32u >= a.sk) continue;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[b][r] *= dp[b][r] - delta;
+      add_rows<T, D>(acc, Ks, blk, s[b], lane);
+    }
+  }
+  __syncthreads();
+  if (half == 1u) swap_put<T, D>(lds, acc, group, lane);
+  __syncthreads();
+  if (half == 1u) return;
+  swap_add<T, D>(lds, acc, 1.0f, 1.0f, group, lane);
+  if (q < a.sq) row_store<T, D>(acc, 1.0f, (T*)head<T>(a.dq, b0, b1) + (int64_t)q * a.dq.s_row, h, a.dq_scale);
+}
+
+template <typename T, int D, int KB>
+static void launch_short(const AttnArgs& a, dim3 grid, hipStream_t s) {
+  const dim3 block(2 * kThreads);
+  if (a.pass == kAttnForward) LT_LAUNCH((lt_attention_kernel_short<T, D, KB>), grid, block, s, a);
+  else LT_LAUNCH((lt_attention_dq_kernel_short<T, D, KB>), grid, block, s, a);
+}
+
 template <typename T, int D>
 static hipError_t launch_d(const AttnArgs& a, hipStream_t s) {
   const uint64_t wgs = (uint64_t)a.batch0 * a.batch1 * (((a.pass == kAttnDkv ? a.sk : a.sq) + kTile - 1u) / kTile);
   if (wgs > 0x7fffffffull) return hipErrorInvalidValue;
   const dim3 grid((uint32_t)wgs), block(kThreads);
-  if (a.pass == kAttnForward) LT_LAUNCH((lt_attention_kernel<T, D>), grid, block, s, a);
-  else if (a.pass == kAttnDq) LT_LAUNCH((lt_attention_dq_kernel<T, D>), grid, block, s, a);
-  else LT_LAUNCH((lt_attention_dkv_kernel<T, D>), grid, block, s, a);
-  char name[48];
-  snprintf(name, sizeof(name), "lt_attention%s_kernel<%s, %d>", a.pass == kAttnForward ? "" : a.pass == kAttnDq ? "_dq" : "_dkv", sizeof(T) == 2 ? "bf16" : "float", D);
+  const char* const pass = a.pass == kAttnForward ? "" : a.pass == kAttnDq ? "_dq" : "_dkv";
+  char name[64];
+  if (sizeof(T) == 2 && D <= 64 && a.pass != kAttnDkv && a.sk <= 256u) {
+    const int kb = a.sk <= 64u ? 1 : a.sk <= 128u ? 2 : 4;
+    if constexpr (sizeof(T) == 2 && D <= 64) {
+      if (kb == 1) launch_short<T, D, 1>(a, grid, s);
+      else if (kb == 2) launch_short<T, D, 2>(a, grid, s);
+      else launch_short<T, D, 4>(a, grid, s);
+    }
+    snprintf(name, sizeof(name), "lt_attention%s_kernel_short<bf16, %d, %d>", pass, D, kb);
+  } else {
+    if (a.pass == kAttnForward) LT_LAUNCH((lt_attention_kernel<T, D>), grid, block, s, a);
+    else if (a.pass == kAttnDq) LT_LAUNCH((lt_attention_dq_kernel<T, D>), grid, block, s, a);
+    else LT_LAUNCH((lt_attention_dkv_kernel<T, D>), grid, block, s, a);
+    snprintf(name, sizeof(name), "lt_attention%s_kernel<%s, %d>", pass, sizeof(T) == 2 ? "bf16" : "float", D);
+  }
   note_kernel(name);
   return hipGetLastError();
 }

@@ -249,6 +249,8 @@ enum : uint32_t { kAttnForward = 0, kAttnDq, kAttnDkv };
 
 struct AttnArgs {
   uint32_t pass, dtype, d, sq, sk, batch0, batch1, pad;
+  // q is taken as q * q_scale, rounded to its type; dq, rounded, is stored times dq_scale
+  float q_scale, dq_scale;
   GemmOperand q, k, v, o, dy;
   GemmOperand dq, dk, dv;
   // [3][batch0 * batch1 * sq]: row maxima and reciprocal row sums (written by the forward pass unless

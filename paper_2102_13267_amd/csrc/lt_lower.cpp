@@ -1706,6 +1706,8 @@ struct Lowering {
     int32_t st[9] = {-1, -1, -1, -1, -1, -1, -1, -1, -1};      // storages of q, k, v, o, dy, dq, dk, dv, stats
     int64_t off[9] = {0};                                      // byte offsets (inputs)
     int group[2] = {-1, -1};
+    int scal[2] = {-1, -1};                                    // scalars that q_scale and dq_scale are patched from, or -1
+    int32_t sc_node = -1, dq_node = -1, dk_node = -1;
   };
   std::vector<Attn> attns;
 
@@ -1739,6 +1741,7 @@ struct Lowering {
     const Val sc = rins[sm][0];
     if (is_root[sc.node] || users[sc.node].size() != 1 || (t->qk = bare_mm(sc.node, false)) < 0 || out_dtype(sc) != dt) return false;
     t->sm = sm_pos;
+    t->sc_node = sc.node;
     int32_t sg = -1, dvn = -1, pvn = -1;
     for (int32_t u : users[sm]) {
       if (nd[u]->op == LT_OP_SOFTMAX_GRAD && sg < 0 && rins[u][1].node == sm && rins[u][0].node != sm) {
@@ -1765,6 +1768,7 @@ struct Lowering {
     if (out_dtype(Val{pvn, 0}) != dt) return false;
     ltk::AttnArgs& a = t->args;
     a.dtype = dt;
+    a.q_scale = a.dq_scale = 1.0f;
     a.d = (uint32_t)d;
     a.sq = (uint32_t)sq;
     a.sk = (uint32_t)sk;
@@ -1803,6 +1807,8 @@ struct Lowering {
         slot = u;
       }
       if (dqn < 0 || dkn < 0) return false;
+      t->dq_node = dqn;
+      t->dk_node = dkn;
       t->dq = bare_mm(dqn, true);
       t->dk = bare_mm(dkn, true);
       t->dv = bare_mm(dvn, true);
@@ -1828,6 +1834,79 @@ struct Lowering {
       for (int r = 0; r < 8; ++r)
         if (w != r && t->st[w] >= 0 && t->st[r] >= 0 && buffer_of(w) == buffer_of(r)) return false;
     return true;
+  }
+
+  // node = x * (an immediate) of the core's element type, a region by itself that has a launch: x and the immediate
+  bool is_scaling(int32_t node, uint8_t dt, Val* x, Val* imm) const {
+    const Region* r = region_of[node];
+    if (cls[node] != C_EW || nd[node]->op != LT_OP_MUL || !r || r->members.size() != 1 || elided[std::find(ordered.begin(), ordered.end(), r) - ordered.begin()]) return false;
+    const int i = is_imm(rins[node][0]) ? 1 : 0;
+    *x = rins[node][i];
+    *imm = rins[node][1 - i];
+    return is_imm(*imm) && !is_imm(*x) && out_dtype(*x) == dt && out_dtype(Val{node, 0}) == dt && out_shape(*x) == shape_of(node);
+  }
+  void scale_from(Val imm, float* value, int* scalar) const {
+    while (nd[imm.node]->op == LT_OP_EXPAND || nd[imm.node]->op == LT_OP_RESHAPE) imm = rins[imm.node][0];
+    if (nd[imm.node]->op == OP_CONSTANT) *value = (float)(nd[imm.node]->attrs[0].is_float ? nd[imm.node]->attrs[0].v.f : (double)nd[imm.node]->attrs[0].v.i);
+    else *scalar = scalar_ordinal[imm.node];
+  }
+  void drop_launch(int32_t node, int32_t storage) {
+    elided[std::find(ordered.begin(), ordered.end(), region_of[node]) - ordered.begin()] = 1;
+    plan->storages[storage].bytes = 0;   // (never in memory)
+  }
+
+  // Queries that are scaled for this core alone are scaled (and rounded) where the launches load them, and a query gradient that
+  // only a scaling reads is scaled where it is stored: a launch of 4 to 10 us and its way through memory less for each
+  // (8 x 200 and 32 x 256 rows of 1024, bf16: 6.4 to 8.1 and 10.6 to 11.5 us with events around them).  The scaled tensors must
+  // be dense and not results the host sees, and what the launches now read later must not be what another launch overwrites.
+  void fold_scales(Attn* t) {
+    const uint8_t dt = (uint8_t)t->args.dtype;
+    Val x, imm;
+    const int32_t qn = base(rins[t->sc_node][0]).node;
+    bool ours = !is_root[qn] && is_scaling(qn, dt, &x, &imm) && cls[x.node] != C_VIEW && storage_of[qn][0] == t->st[0] && plan->storages[t->st[0]].param < 0;
+    if (ours) {
+      std::vector<int32_t> stack{qn};
+      while (!stack.empty() && ours) {
+        const int32_t n = stack.back();
+        stack.pop_back();
+        for (int32_t u : users[n]) {
+          if (cls[u] == C_VIEW) stack.push_back(u);
+          else ours = ours && (u == t->sc_node || u == t->dk_node);
+        }
+      }
+      // (k, v and dy are not views of it: their readers would be others)
+      const int32_t from = storage_of[x.node][x.slot];
+      ours = ours && from >= 0 && base(rins[t->sc_node][1]).node != qn && (t->dk_node < 0 || base(rins[t->dk_node][0]).node != qn);
+      if (ours) {
+        int holders = 0;   // storages of x's buffer
+        for (const Storage& st : plan->storages) holders += plan->storages[from].param >= 0 && st.param == plan->storages[from].param;
+        ours = holders <= 1;
+        for (int w : {3, 5, 6, 7}) ours = ours && t->st[w] != from;
+      }
+      if (ours) {
+        scale_from(imm, &t->args.q_scale, &t->scal[0]);
+        drop_launch(qn, t->st[0]);
+        t->st[0] = from;
+      }
+    }
+    if (t->dq_node < 0) return;
+    // the region's result (the product, or the permutation it ends in), through reshapes to its one reader
+    const Region* r = ordered[t->dq];
+    int32_t n = r->sealed ? (r->members[0] == t->dq_node ? r->members[1] : r->members[0]) : t->dq_node;
+    const int32_t own = t->st[5];
+    if (plan->storages[own].param >= 0 || plan->storages[own].bound_to_root) return;
+    for (;;) {
+      if (is_root[n] || users[n].size() != 1) return;
+      n = users[n][0];
+      if (cls[n] != C_VIEW) break;
+      if (nd[n]->op != LT_OP_RESHAPE) return;
+    }
+    if (!is_scaling(n, dt, &x, &imm)) return;
+    const int32_t to = storage_of[n][0];
+    if (to < 0 || to == own || plan->storages[to].param >= 0) return;
+    scale_from(imm, &t->args.dq_scale, &t->scal[1]);
+    drop_launch(n, own);
+    t->st[5] = to;
   }
 
   // The order in which regions are lowered: that of `ordered`, with the regions of an attention core's
@@ -1873,6 +1952,7 @@ struct Lowering {
       }
       if ((int)order.size() == n) {
         plan->merged = true;
+        for (Attn& t : attns) fold_scales(&t);
         return order;
       }
       attns.pop_back();
@@ -1912,6 +1992,8 @@ struct Lowering {
           plan->ptr_patches.push_back(PtrPatch{(uint32_t)launch, (uint32_t)(at[i] + (i < 8 ? offsetof(ltk::GemmOperand, ptr) : 0)), t.st[i], t.off[i], 1});
           touch(t.st[i], launch);
         }
+        if (t.scal[0] >= 0) plan->scal_patches.push_back(ScalPatch{(uint32_t)launch, (uint32_t)offsetof(ltk::AttnArgs, q_scale), t.scal[0], 0});
+        if (t.scal[1] >= 0) plan->scal_patches.push_back(ScalPatch{(uint32_t)launch, (uint32_t)offsetof(ltk::AttnArgs, dq_scale), t.scal[1], 0});
       };
       if (fwd && t.group[0] < 0) {
         t.group[0] = k;
