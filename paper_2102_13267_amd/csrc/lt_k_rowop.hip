@@ -214,7 +214,10 @@ __global__ __launch_bounds__(kBlock) void lt_row_op_kernel(const RowOpArgs a) {
           ex.v[k].z = expf(x.v[k].z - m); ex.v[k].w = expf(x.v[k].w - m);
         }
         const float s = row_reduce_regs<TPR>(kRedSum, ex, lds);
-        if (OP == kXent) {
+        // A loss and its gradient read the same logits and need the same maximum and sum: one launch and one pass for
+        // both (128 x 10: 6.2 + 6.1 -> 6.3 us with events around them, 2048 x 1000: 7.1 + 7.9 -> 8.9).
+        void* const loss = OP == kXent ? a.out[0] : a.out[1];
+        if (loss) {
           // the picked logit: only the lane holding column `label` contributes
           float picked = 0.0f;
 #pragma unroll
@@ -230,8 +233,9 @@ __global__ __launch_bounds__(kBlock) void lt_row_op_kernel(const RowOpArgs a) {
           for (int k = 0; k < kRowVecs; ++k) pk.v[k] = make_float4(0.f, 0.f, 0.f, 0.f);
           pk.v[0].x = picked;
           const float pv = row_reduce_regs<TPR>(kRedSum, pk, lds);
-          if (lane == 0 && live) store_elem(a.out[0], a.out_dtype[0], row, logf(s) + m - pv);
-        } else {
+          if (lane == 0 && live) store_elem(loss, a.out_dtype[OP == kXent ? 0 : 1], row, logf(s) + m - pv);
+        }
+        if (OP == kXentGrad) {
           const float inv = 1.0f / s;
 #pragma unroll
           for (int k = 0; k < kRowVecs; ++k) {

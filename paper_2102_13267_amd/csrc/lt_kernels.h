@@ -157,7 +157,7 @@ struct RowOpArgs {
   uint32_t op, rows, cols, threads_per_row;
   const void* in[5];
   uint32_t in_dtype[5];
-  void* out[3];
+  void* out[3];        // (out[1] of xent_grad: null, or the losses, which ride along)
   uint32_t out_dtype[3];
   float eps;           // layer norm
   float scale;         // xent_grad

@@ -1591,12 +1591,75 @@ struct Lowering {
     return true;
   }
 
+  // A cross-entropy and its gradient over the same logits and labels: whichever comes second joins the launch of the
+  // first (which becomes the gradient's, with the losses as its second output).  Its result is written earlier than its
+  // place, so it must be memory of its own.  (What it reads is what the first one reads.)
+  bool ride_with_xent(int32_t a) {
+    const bool grad = nd[a]->op == LT_OP_XENT_GRAD;
+    if (!merge || (!grad && nd[a]->op != LT_OP_XENT)) return false;
+    const int32_t st = storage_of[a][0];
+    Access acc[2];
+    if (st < 0 || plan->storages[st].param >= 0 || (grad && !is_imm(rins[a][2]))) return false;
+    for (int q = 0; q < 2; ++q) {
+      const std::vector<int64_t> vs = out_shape(rins[a][q]);
+      if (!quiet(make_access(rins[a][q], vs, -1, &acc[q])) || acc[q].offset != 0) return false;
+      const std::vector<int64_t> cs = contiguous(vs);
+      for (size_t d = 0; d < vs.size(); ++d)
+        if (vs[d] != 1 && acc[q].stride[d] != cs[d]) return false;
+    }
+    for (size_t i = 0; i < plan->launches.size(); ++i) {
+      Launch& l = plan->launches[i];
+      ltk::RowOpArgs* ra = (ltk::RowOpArgs*)l.args.data();
+      if (l.kind != L_ROWOP || ra->op != (grad ? ltk::kXent : ltk::kXentGrad) || ra->out_dtype[1] != kNoLoss) continue;
+      const std::vector<int64_t> xs = out_shape(rins[a][0]);
+      if (ra->cols != (uint32_t)xs.back() || (int64_t)ra->rows * ra->cols != count(xs) || ra->in_dtype[0] != acc[0].dtype) continue;
+      int same = 0;
+      size_t out0 = plan->ptr_patches.size();
+      for (size_t j = 0; j < plan->ptr_patches.size(); ++j) {
+        const PtrPatch& pp = plan->ptr_patches[j];
+        if (pp.launch != i) continue;
+        for (int q = 0; q < 2; ++q) same += pp.offset == offsetof(ltk::RowOpArgs, in) + q * sizeof(void*) && pp.storage == acc[q].storage && pp.byte_offset == 0;
+        if (pp.offset == offsetof(ltk::RowOpArgs, out)) out0 = j;
+      }
+      if (same != 2 || out0 == plan->ptr_patches.size()) continue;
+      const uint32_t loss = (uint32_t)(offsetof(ltk::RowOpArgs, out) + sizeof(void*));
+      if (grad) {
+        ra->op = ltk::kXentGrad;
+        ra->out_dtype[1] = ra->out_dtype[0];
+        plan->ptr_patches[out0].offset = loss;
+        plan->ptr_patches.push_back(PtrPatch{(uint32_t)i, (uint32_t)offsetof(ltk::RowOpArgs, out), st, 0, 1});
+        ra->out_dtype[0] = out_dtype(Val{a, 0});
+        patch_xent_scale(a, i);
+      } else {
+        ra->out_dtype[1] = out_dtype(Val{a, 0});
+        plan->ptr_patches.push_back(PtrPatch{(uint32_t)i, loss, st, 0, 1});
+      }
+      touch(st, (int)i);
+      l.bytes += (uint64_t)count(out_shape(Val{a, 0})) * dtype_size(out_dtype(Val{a, 0}));
+      plan->merged = true;
+      return true;
+    }
+    return false;
+  }
+  static constexpr uint32_t kNoLoss = 0xffffffffu;   // out_dtype[1] of a cross-entropy launch that nothing has joined
+  // the scale is a rank-0 operand: an immediate or a dynamic scalar
+  void patch_xent_scale(int32_t a, size_t launch) {
+    Val b = rins[a][2];
+    while (nd[b.node]->op == LT_OP_EXPAND || nd[b.node]->op == LT_OP_RESHAPE) b = rins[b.node][0];
+    if (nd[b.node]->op == OP_CONSTANT)
+      ((ltk::RowOpArgs*)plan->launches[launch].args.data())->scale = (float)(nd[b.node]->attrs[0].is_float ? nd[b.node]->attrs[0].v.f : (double)nd[b.node]->attrs[0].v.i);
+    else
+      plan->scal_patches.push_back(ScalPatch{(uint32_t)launch, (uint32_t)offsetof(ltk::RowOpArgs, scale), scalar_ordinal[b.node], 0});
+  }
+
   bool emit_row_op(int k, Region* r, const std::vector<Val>& out) {
     const int32_t a = r->anchor;
     const Node* an = nd[a];
     if (r->members.size() != 1) return bad(LT_ERR_UNSUPPORTED, "internal: fixed row operator with fused members");
+    if (ride_with_xent(a)) return true;
     const int launch = (int)plan->launches.size();
     ltk::RowOpArgs args{};
+    bool scaled = false;   // (an xent_grad)
     const std::vector<int64_t> xs = out_shape(rins[a][an->op == LT_OP_LAYER_NORM_GRAD ? 1 : 0]);
     args.cols = (uint32_t)xs.back();
     args.rows = (uint32_t)(count(xs) / std::max<int64_t>(1, xs.back()));
@@ -1632,16 +1695,8 @@ struct Lowering {
       bytes += (uint64_t)count(vs) * dtype_size(acc.dtype);
     }
     if (an->op == LT_OP_XENT_GRAD) {
-      // the scale is a rank-0 operand: an immediate or a dynamic scalar
-      const Val s = rins[a][2];
-      if (!is_imm(s)) return bad(LT_ERR_UNSUPPORTED, "xent_grad: scale must be a scalar constant or parameter");
-      Val b = s;
-      while (nd[b.node]->op == LT_OP_EXPAND || nd[b.node]->op == LT_OP_RESHAPE) b = rins[b.node][0];
-      if (nd[b.node]->op == OP_CONSTANT) {
-        ((ltk::RowOpArgs*)l.args.data())->scale = (float)(nd[b.node]->attrs[0].is_float ? nd[b.node]->attrs[0].v.f : (double)nd[b.node]->attrs[0].v.i);
-      } else {
-        plan->scal_patches.push_back(ScalPatch{(uint32_t)launch, (uint32_t)offsetof(ltk::RowOpArgs, scale), scalar_ordinal[b.node], 0});
-      }
+      if (!is_imm(rins[a][2])) return bad(LT_ERR_UNSUPPORTED, "xent_grad: scale must be a scalar constant or parameter");
+      scaled = true;
     }
     // outputs: every slot of the anchor that is needed; unneeded layer-norm statistics still
     // need somewhere to go, so they get storage as well
@@ -1662,7 +1717,9 @@ struct Lowering {
     }
     (void)out;
     l.bytes = bytes;
+    if (an->op == LT_OP_XENT || scaled) ((ltk::RowOpArgs*)l.args.data())->out_dtype[1] = kNoLoss;
     plan->launches.push_back(std::move(l));
+    if (scaled) patch_xent_scale(a, launch);
     return true;
   }
 
