@@ -451,6 +451,10 @@ static lt_status execute(lt_ctx* ctx, Plan* plan, const std::vector<BufRef>& par
         ltk::ColArgs* a = (ltk::ColArgs*)args.data();
         a->partials = red_partials + l.scratch_slot * (kPartialFloats / kScratchSlots);
         a->tickets = red_tickets + l.scratch_slot * (kTickets / kScratchSlots);
+      } else if (row_op_total(l)) {
+        ltk::RowOpArgs* a = (ltk::RowOpArgs*)args.data();
+        a->total_parts = red_partials + l.scratch_slot * (kPartialFloats / kScratchSlots);
+        a->total_ticket = red_tickets + l.scratch_slot * (kTickets / kScratchSlots);
       } else if (gemm_shared_tiles(l) != 0) {
         ltk::GemmArgs* a = (ltk::GemmArgs*)args.data();
         a->split_ws = red_partials + l.scratch_slot * (kPartialFloats / kScratchSlots);

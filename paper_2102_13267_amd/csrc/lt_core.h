@@ -329,6 +329,7 @@ void schedule_streams(Plan* plan);
 // 32 x 32 tiles of a one-launch small contraction whose workgroups share tiles (they exchange partial
 // tiles through the reduction scratch and take tickets); 0 for every other launch
 uint64_t gemm_shared_tiles(const Launch& l);
+bool row_op_total(const Launch& l);   // a row operator whose workgroups exchange a sum
 
 }  // namespace lt
 #endif  // LT_CORE_H_

@@ -165,6 +165,12 @@ struct RowOpArgs {
   // col_parts, a row of [col_sums][cols] floats each (ColArgs::parts)
   uint32_t col_sums, col_rows;
   float* col_parts;
+  // xent and xent_grad: the sum or mean (kRedSum, kRedMean) of the losses goes to `total` as well; the workgroups exchange
+  // theirs through total_parts[gridDim.x] and the ticket (zero before the launch; reset by the kernel)
+  uint32_t has_total, total_red;
+  float* total;
+  float* total_parts;
+  uint32_t* total_ticket;
 };
 
 // ---- contraction ------------------------------------------------------------------------

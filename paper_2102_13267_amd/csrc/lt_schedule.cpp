@@ -53,6 +53,8 @@ uint64_t gemm_shared_tiles(const Launch& l) {
   return (uint64_t)((a->m + a->tile_m - 1u) / a->tile_m) * ((a->n + a->tile_n - 1u) / a->tile_n) * a->batch0 * a->batch1;
 }
 
+bool row_op_total(const Launch& l) { return l.kind == L_ROWOP && ((const ltk::RowOpArgs*)l.args.data())->has_total != 0u; }
+
 void schedule_streams(Plan* plan) {
   const size_t n = plan->launches.size();
   plan->n_streams = 1;
@@ -81,7 +83,7 @@ void schedule_streams(Plan* plan) {
     l.scratch_slot = 0;
     l.waits.clear();
     const uint64_t shared_tiles = gemm_shared_tiles(l);   // (a small contraction whose workgroups share tiles)
-    if (l.kind != L_ALL && l.kind != L_COL && shared_tiles == 0) continue;
+    if (l.kind != L_ALL && l.kind != L_COL && shared_tiles == 0 && !row_op_total(l)) continue;
     uint64_t floats = l.grid_x, tickets = 1;
     if (l.kind == L_COL) {
       const ltk::ColArgs* a = (const ltk::ColArgs*)l.args.data();

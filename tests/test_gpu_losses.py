@@ -23,11 +23,11 @@ def step(B, z, w, labels, other, form):
         d, loss = B.xent_grad(z, labels, 0.25), B.xent(z, other)
     else:
         d, loss = B.xent_grad(z, labels, 0.25), B.xent(z, labels)
-    return [d, loss, B.sum(d, axis=0)]
+    return [d, loss, B.sum(d, axis=0)] + ([B.sum(loss)] if form == "gradient first" else [])
 
 
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
-@pytest.mark.parametrize("rows,cols", [(1, 2), (17, 10), (33, 256), (5, 257), (40, 1000), (3, 1025), (2, 4096)])
+@pytest.mark.parametrize("rows,cols", [(1, 2), (17, 10), (33, 256), (5, 257), (40, 1000), (3, 1025), (2, 4096), (512, 300), (513, 300)])
 @pytest.mark.parametrize("form", ["gradient first", "loss first", "gradient overwrites logits", "other labels"])
 def test_loss_with_its_gradient(ctx, dt, rows, cols, form):  # noqa: F811
     E, g = Eager(), rng(rows * 5000 + cols)
@@ -42,8 +42,11 @@ def test_loss_with_its_gradient(ctx, dt, rows, cols, form):  # noqa: F811
             out.append(step(B, B.tensor(z, dtype=dt), B.tensor(w, dtype=dt, **mk), B.tensor(labels), B.tensor(other), form))
         ctx.set_profiling(True)
         ctx.barrier()
-        n = sum("row_op" in r["kernel"] for r in ctx.last_launches())
+        names = [r["kernel"] for r in ctx.last_launches()]
+        n, totals = sum("row_op" in k for k in names), sum("all_reduce" in k for k in names)
         ctx.set_profiling(False)
+        # (one loss is its own sum; a launch of more than 128 workgroups leaves the sum to another)
+        assert totals == (form in ("gradient first", "loss first") and (rows == 1 or rows == 513)), names
         assert n == (2 if form == "other labels" else 1) or form == "gradient overwrites logits", n
         for i, (x, y) in enumerate(zip(*out)):
             check(ctx, E, x, y, 1e-2 if dt == "bf16" else 1e-5, i)
