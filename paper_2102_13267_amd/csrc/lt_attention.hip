@@ -5,7 +5,7 @@
 //
 // What bounded the parts: they move the [heads, s, s] tensors through memory six times, their
 // products contract 32 to 128 deep (all prologue and epilogue), and rows of odd s defeat vector
-// access.  Measured, bf16, 128 heads of 200 x 64: forward 8.3, dq 9.3, dk + dv 12.7 us; the eight parts
+// access.  Measured with events, bf16, 128 heads of 200 x 64: forward 10.3, dq 11.3, dk + dv 14.2 us; the eight parts
 // take 80 us (107 before their ragged tiles had a path of their own).
 //
 // One workgroup of four waves takes 128 rows of one head (queries; keys in the dk / dv pass), each wave
