@@ -1438,12 +1438,14 @@ struct Lowering {
   // A norm's weight and bias gradients behind its input gradient: the launch of the latter reads the same four tensors
   // row by row and takes the sums along (RowOpArgs::col_sums); the column launch stays where it is and only adds up
   // the partial sums.  Rows of whole 16-byte chunks, at most four to a lane (the sums take as many registers as the row).
+  // (Sums and means: a column maximum of the same program is no sum of partial results.)
   void norm_sums_with_gradient() {
     if (!merge) return;
     for (size_t j = 0; j < plan->launches.size(); ++j) {
       if (plan->launches[j].kind != L_COL) continue;
       const ltk::ColArgs* ca = (const ltk::ColArgs*)plan->launches[j].args.data();
       const uint32_t dt = ca->norm_grad ? ca->pro.in[ca->vin[0]].dtype : 0u;
+      if (ca->red != ltk::kRedSum && ca->red != ltk::kRedMean) continue;
       if (!ca->norm_grad || ca->cols % (dt == ltk::kBF16 ? 8u : 4u) || ca->cols > (dt == ltk::kBF16 ? 2048u : 1024u)) continue;
       const uint32_t which[4] = {ca->vin[0], ca->vin[1], ca->cin[0], ca->cin[1]}, arg[4] = {0, 1, 3, 4};   // dy, x, mean, rstd: inputs here, inputs there
       int32_t st[4] = {-1, -1, -1, -1};

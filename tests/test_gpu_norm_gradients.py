@@ -122,3 +122,19 @@ def test_sums_that_ride_with_the_input_gradient(ctx, rows, cols, dt):  # noqa: F
         got, ref = run(ctx, lambda t: ctx.tensor(t, dtype=dt, donatable=True), variant), run(E, lambda t: E.tensor(t, dtype=dt), variant)
         for i, (p, q) in enumerate(zip(got, ref)):
             check(ctx, E, p, q, tol, (variant, i))
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("reduce", ["mean", "amax"])
+@pytest.mark.parametrize("rows,cols", [(2, 8), (64, 256), (257, 512), (8193, 520)])
+def test_other_reductions_of_the_same_program(ctx, rows, cols, reduce, dt):  # noqa: F811
+    """A column's mean and its largest value of dy * xhat next to the input gradient."""
+    E, data = Eager(), operands(rows, cols, dt)
+
+    def prog(B):
+        x, dy, w, b = (B.tensor(t, dtype=dt) for t in data)
+        y, mu, rs = B.layer_norm(x, w, b, eps=1e-5)
+        xhat = B.mul(B.sub(x, B.reshape(mu, (rows, 1))), B.reshape(rs, (rows, 1)))
+        return B.layer_norm_grad(dy, x, w, mu, rs), getattr(B, reduce)(B.mul(dy, xhat), axis=0), B.sum(dy, axis=0)
+    for i, (p, q) in enumerate(zip(prog(ctx), prog(E))):
+        check(ctx, E, p, q, 2e-2 if dt == "bf16" else 2e-5 * max(1.0, rows ** 0.5 / 8), (reduce, i))
