@@ -5,7 +5,7 @@
 //
 // What bounded the parts: they move the [heads, s, s] tensors through memory six times, their
 // products contract 32 to 128 deep (all prologue and epilogue), and rows of odd s defeat vector
-// access.  Measured with events, bf16, 128 heads of 200 x 64: forward 10.3, dq 11.3, dk + dv 14.2 us; the eight parts
+// access.  Measured with events, bf16, 128 heads of 200 x 64: forward 11.3, dq 11.2, dk + dv 14.5 us; the eight parts
 // take 80 us (107 before their ragged tiles had a path of their own).
 //
 // One workgroup of four waves takes 128 rows of one head (queries; keys in the dk / dv pass), each wave
@@ -431,13 +431,13 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 1 : 2) void lt_attention_dkv_k
   row_store<T, D>(dv, 1.0f, (T*)head<T>(a.dv, b0, b1) + (int64_t)key * a.dv.s_row, h);
 }
 
-// Up to 256 keys (bf16, heads of up to 64): the walk's cost was its chain of barriers, loads and, in the backward pass,
-// the second computation of everything, with one wave per SIMD.  Here all keys are in LDS at once, eight waves share
+// Up to 256 keys (bf16, heads of up to 64), few workgroups: the walk's cost is its chain of barriers, loads and, in the
+// backward pass, the second computation of everything, with one wave per SIMD.  Here all keys are in LDS at once, eight waves share
 // them (a group of 32 queries has two, one for every other block of 32 keys), and what the first use of a block computes stays in
-// registers for the second.  The halves' sums meet in LDS.  With events around the launch, us, before / now: 128 heads of
-// 200 x 64 forward 11.8 / 10.3, dq 18.5 / 11.3; 512 of 256 x 64 26.4 / 27.6 and 47.0 / 42.5; 256 of 128 x 64 9.2 / 9.4 and 13.6 / 10.8;
-// 128 of 200 x 32 9.4 / 8.5 and 14.4 / 8.7.  (Long walks gain nothing from two halves: at 200 x 64 forward 11.6, dk + dv 15.2 /
-// 14.6, at 256 x 64 and 512 heads dk + dv 40 / 53: the registers of both halves fit a compute unit only once.)
+// registers for the second.  The halves' sums meet in LDS.  With events around the launch, us, walking / this: 128 heads of
+// 200 x 64 forward 12.3 / 11.3, dq 16.9 / 11.2; of 200 x 32 10.1 / 9.1 and 13.3 / 9.1.  Where the launches run which, and why: launch_d.
+// (Long walks gain nothing from two halves: at 200 x 64 forward 11.6, dk + dv 15.2 / 14.6, at 256 x 64 and 512 heads dk + dv 40 / 53:
+// the registers of both halves fit a compute unit only once.)
 template <typename T, int D, int KB>
 __global__ __launch_bounds__(2 * kThreads, 4) void lt_attention_kernel_short(const AttnArgs a) {
   typedef Geo<T, D> G;
@@ -590,11 +590,33 @@ __global__ __launch_bounds__(2 * kThreads, 2) void lt_attention_dq_kernel_short(
   if (q < a.sq) row_store<T, D>(acc, 1.0f, (T*)head<T>(a.dq, b0, b1) + (int64_t)q * a.dq.s_row, h, a.dq_scale);
 }
 
-template <typename T, int D, int KB>
-static void launch_short(const AttnArgs& a, dim3 grid, hipStream_t s) {
+// Which of the two is faster depends on how many workgroups a compute unit gets: few wait for latency, and the short kernels wait
+// less; many overlap, and then twice the waves and the exchange of the halves are work on top.  With events round the launch, us,
+// walking / short, over 144 to 256 keys and 128 to 1024 queries (heads of 64 unless said otherwise):
+//   forward, more than 128 keys: 128 workgroups 9.8 to 11.5 / 9.4 to 10.7, 256 10.8 to 12.8 / 10.3 to 12.9, 384 13.2 to 16.0 / 12.8 to 15.8
+//   (on average 3 % less), 512 13.8 to 16.8 / 13.5 to 18.0 (1 % more), 768 17.6 to 21.0 / 19.0 to 23.8, 2048 33 to 42 / 37 to 49.  Up to 128 keys the
+//   walk is a step or two: at 16 to 1024 heads of 64 x 64 6.3 to 11.0 / 6.9 to 11.5, of 128 x 64 8.2 to 18.5 / 8.3 to 20.8.
+//   dq, more than 128 keys: 256 13.5 to 17.5 / 10.3 to 12.0, 512 17.6 to 25.2 / 17.6 to 23.4, 768 26.6 to 33.3 / 26.4 to 32.8, 1024 31.8 to 44.4 /
+//   33.8 to 41.8 (3 % more on average), 2048 53 to 72 / 58 to 78; heads of 32: 1024 16 to 39 / 16 to 34, 2048 36 to 61 / 36 to 59, 4096 55 to 113 / 65 to
+//   107.  Up to 128 keys the second walk is what costs: 6.6 to 131 / 6.6 to 132, from 512 workgroups on up to a fifth less.
+template <int D>
+static bool short_walk(const AttnArgs& a, uint64_t wgs) {
+  if (a.pass == kAttnForward) return a.sk > 128u && a.sk <= 256u && wgs <= 384u;
+  return a.pass == kAttnDq && (a.sk <= 128u || (a.sk <= 256u && wgs <= (D == 32 ? 2048u : 768u)));
+}
+
+template <typename T, int D>
+static int launch_short(const AttnArgs& a, dim3 grid, hipStream_t s) {   // (returns KB)
   const dim3 block(2 * kThreads);
-  if (a.pass == kAttnForward) LT_LAUNCH((lt_attention_kernel_short<T, D, KB>), grid, block, s, a);
-  else LT_LAUNCH((lt_attention_dq_kernel_short<T, D, KB>), grid, block, s, a);
+  if (a.pass == kAttnForward) {
+    LT_LAUNCH((lt_attention_kernel_short<T, D, 4>), grid, block, s, a);
+    return 4;
+  }
+  const int kb = a.sk <= 64u ? 1 : a.sk <= 128u ? 2 : 4;
+  if (kb == 1) LT_LAUNCH((lt_attention_dq_kernel_short<T, D, 1>), grid, block, s, a);
+  else if (kb == 2) LT_LAUNCH((lt_attention_dq_kernel_short<T, D, 2>), grid, block, s, a);
+  else LT_LAUNCH((lt_attention_dq_kernel_short<T, D, 4>), grid, block, s, a);
+  return kb;
 }
 
 template <typename T, int D>
@@ -604,13 +626,11 @@ static hipError_t launch_d(const AttnArgs& a, hipStream_t s) {
   const dim3 grid((uint32_t)wgs), block(kThreads);
   const char* const pass = a.pass == kAttnForward ? "" : a.pass == kAttnDq ? "_dq" : "_dkv";
   char name[64];
-  if (sizeof(T) == 2 && D <= 64 && a.pass != kAttnDkv && a.sk <= 256u) {
-    const int kb = a.sk <= 64u ? 1 : a.sk <= 128u ? 2 : 4;
-    if constexpr (sizeof(T) == 2 && D <= 64) {
-      if (kb == 1) launch_short<T, D, 1>(a, grid, s);
-      else if (kb == 2) launch_short<T, D, 2>(a, grid, s);
-      else launch_short<T, D, 4>(a, grid, s);
-    }
+  int kb = 0;
+  if constexpr (sizeof(T) == 2 && D <= 64) {
+    if (short_walk<D>(a, wgs)) kb = launch_short<T, D>(a, grid, s);
+  }
+  if (kb > 0) {
     snprintf(name, sizeof(name), "lt_attention%s_kernel_short<bf16, %d, %d>", pass, D, kb);
   } else {
     if (a.pass == kAttnForward) LT_LAUNCH((lt_attention_kernel<T, D>), grid, block, s, a);

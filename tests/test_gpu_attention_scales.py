@@ -59,3 +59,20 @@ def test_scalings_that_others_see(ctx, dt, form, extra):  # noqa: F811
         ref = scaled_core(E, *(mk(E, i, t) for i, t in enumerate(data)), b, s, s, h, d, scale, form)
         for i, (x, y) in enumerate(zip(got, ref)):
             check(ctx, E, x, y, 2e-2 if dt == "bf16" else 2e-5, i)
+
+
+@pytest.mark.parametrize("heads,sk,d,forward,dq", [(4, 64, 64, "walk", 1), (4, 65, 64, "walk", 2), (4, 128, 64, "walk", 2), (4, 129, 64, "short", 4), (4, 256, 32, "short", 4),
+                                                   (4, 257, 64, "walk", 0), (4, 200, 128, "walk", 0), (384, 130, 64, "short", 4), (385, 130, 64, "walk", 4),
+                                                   (768, 130, 64, "walk", 4), (769, 130, 64, "walk", 0), (2048, 130, 32, "walk", 4), (2049, 130, 32, "walk", 0),
+                                                   (2049, 20, 32, "walk", 1)])
+def test_kernels_on_both_sides_of_a_line(ctx, heads, sk, d, forward, dq):  # noqa: F811
+    """All keys at once only where that was measured to be faster: by pass, keys and workgroups (three queries: one for each head)."""
+    data, E = operands(heads + sk, "bf16", heads, 3, sk, 1, d), Eager()
+    args = (heads, 3, sk, 1, d, 0.7, "")
+    got = scaled_core(ctx, *(ctx.tensor(t, dtype="bf16") for t in data), *args)
+    names = kinds(ctx)
+    assert names[0] == (f"lt_attention_kernel_short<bf16, {d}, 4>" if forward == "short" else f"lt_attention_kernel<bf16, {d}>"), names
+    assert names[1] == (f"lt_attention_dq_kernel_short<bf16, {d}, {dq}>" if dq else f"lt_attention_dq_kernel<bf16, {d}>"), names
+    ref = scaled_core(E, *(E.tensor(t, dtype="bf16") for t in data), *args)
+    for i, (x, y) in enumerate(zip(got, ref)):
+        check(ctx, E, x, y, 2e-2, i)
