@@ -120,7 +120,7 @@ __device__ __forceinline__ Offsets<BX> unaligned_offsets(int64_t s_x, int64_t s_
   Offsets<BX> off;
 #pragma unroll
   for (int it = 0; it < Groups<float, BX>::N; ++it) {
-    const uint32_t e = it * kGemmThreads + threadIdx.x;
+    const uint32_t e = it * kGemmThreads + threadIdx.x % kGemmThreads;
     off.o[it] = chunk_offset<KC>(e / per_row, (e % per_row) * 4u, s_x, s_k, left);
   }
   return off;

@@ -62,3 +62,28 @@ def test_ragged_attention_products(ctx, s, h, d):  # noqa: F811
     ref = prog(E, *(E.tensor(t, dtype="bf16") for t in (q, k, v, dc)))
     for i, (x, y) in enumerate(zip(got, ref)):
         check(ctx, E, x, y, 2e-2, i)
+
+
+# the second of each type leaves several partial products to a second launch
+@pytest.mark.parametrize("dt,m,n,k", [("bf16", 600, 600, 500), ("bf16", 1000, 1000, 2100), ("bf16", 129, 1544, 583), ("bf16", 3100, 64, 600), ("bf16", 257, 1096, 545),
+                                      ("f32", 1000, 1000, 136), ("f32", 500, 1000, 2050), ("f32", 997, 1000, 137), ("f32", 960, 968, 203), ("f32", 1000, 1024, 257), ("f32", 1400, 257, 512)])
+@pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, False), (True, True)])
+def test_halves_of_a_workgroup(ctx, dt, m, n, k, ta, tb):  # noqa: F811
+    """Shapes whose workgroups are two halves that share k: odd numbers of slices, a rest of k, tiles over both edges, rows that start off a
+    16-byte boundary, narrow tiles; as it is, with bias and GELU, and added to a residual.  Bars as above."""
+    E, g = Eager(), rng(m * 7 + n * 11 + k)
+    rnd = round_to_bf16 if dt == "bf16" else (lambda t: t)
+
+    def operand(rows, cols, std=1.0):
+        t = np.full((rows + 2, cols), np.nan, np.float32)
+        t[1:-1] = rnd(g.standard_normal((rows, cols), dtype=np.float32) * np.float32(std))
+        return t
+    a, b = operand(*((k, m) if ta else (m, k))), operand(*((n, k) if tb else (k, n)), std=k ** -0.5)
+    bias, res = (rnd(g.standard_normal(s, dtype=np.float32)) for s in ((n,), (m, n)))
+
+    def prog(B, post):
+        a_, b_, bias_, res_ = (B.tensor(t, dtype=dt) for t in (a, b, bias, res))
+        p = B.matmul(window(B, a_, a.shape[0] - 2), window(B, b_, b.shape[0] - 2), trans_a=ta, trans_b=tb)
+        return p if post == "plain" else B.gelu(B.add(p, bias_)) if post == "gelu" else B.add(res_, p, alpha=0.5)
+    for post in ("plain", "gelu", "residual"):
+        check(ctx, E, prog(ctx, post), prog(E, post), 2e-2 if dt == "bf16" else max(1e-5, 1e-6 * k ** 0.5), post)
