@@ -911,7 +911,7 @@ static void launch_variant(const GemmArgs& a, const dim3 grid, hipStream_t s) {
   else if (bkc) LT_LAUNCH((lt_gemm_kernel<T, BM, BN, false, true, AL, KS>), grid, dim3(kGemmThreads * KS), s, a);
   else LT_LAUNCH((lt_gemm_kernel<T, BM, BN, false, false, AL, KS>), grid, dim3(kGemmThreads * KS), s, a);
   char name[64];
-  snprintf(name, sizeof(name), "lt_gemm_kernel<float, %d, %d, %s, %s, %s, %d>", BM, BN, akc ? "true" : "false", bkc ? "true" : "false", AL ? "true" : "false", KS);
+  snprintf(name, sizeof(name), "lt_gemm_kernel<float,%d,%d,%s,%s,%s,%d>", BM, BN, akc ? "true" : "false", bkc ? "true" : "false", AL ? "true" : "false", KS);
   note_kernel(name);
 }
 

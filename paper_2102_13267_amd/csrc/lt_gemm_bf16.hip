@@ -513,8 +513,8 @@ static void launch_layout(const GemmArgs& a, dim3 grid, hipStream_t s) {
   else if (akc) LT_LAUNCH((lt_gemm_bf16_kernel<BM, BN, true, false, AL, KS>), grid, block, s, a);
   else if (bkc) LT_LAUNCH((lt_gemm_bf16_kernel<BM, BN, false, true, AL, KS>), grid, block, s, a);
   else LT_LAUNCH((lt_gemm_bf16_kernel<BM, BN, false, false, AL, KS>), grid, block, s, a);
-  char name[64];
-  snprintf(name, sizeof(name), "lt_gemm_bf16_kernel<%d, %d, %s, %s, %s, %d>", BM, BN, akc ? "true" : "false", bkc ? "true" : "false", AL ? "true" : "false", KS);
+  char name[64];   // (no spaces: a launch record holds 47 characters, all but the last bracket)
+  snprintf(name, sizeof(name), "lt_gemm_bf16_kernel<%d,%d,%s,%s,%s,%d>", BM, BN, akc ? "true" : "false", bkc ? "true" : "false", AL ? "true" : "false", KS);
   note_kernel(name);
 }
 

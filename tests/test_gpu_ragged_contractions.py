@@ -64,11 +64,13 @@ def test_ragged_attention_products(ctx, s, h, d):  # noqa: F811
         check(ctx, E, x, y, 2e-2, i)
 
 
-# the second of each type leaves several partial products to a second launch
-@pytest.mark.parametrize("dt,m,n,k", [("bf16", 600, 600, 500), ("bf16", 1000, 1000, 2100), ("bf16", 129, 1544, 583), ("bf16", 3100, 64, 600), ("bf16", 257, 1096, 545),
-                                      ("f32", 1000, 1000, 136), ("f32", 500, 1000, 2050), ("f32", 997, 1000, 137), ("f32", 960, 968, 203), ("f32", 1000, 1024, 257), ("f32", 1400, 257, 512)])
+# second: several partial products are left, and a launch that adds them up
+@pytest.mark.parametrize("dt,m,n,k,second", [("bf16", 600, 600, 500, False), ("bf16", 1000, 1000, 2100, True), ("bf16", 129, 1544, 583, False),
+                                             ("bf16", 3100, 64, 600, False), ("bf16", 257, 1096, 545, False), ("f32", 1000, 1000, 136, False),
+                                             ("f32", 500, 1000, 2050, True), ("f32", 997, 1000, 137, False), ("f32", 960, 968, 203, False),
+                                             ("f32", 1000, 1024, 257, False), ("f32", 1400, 257, 512, True)])
 @pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, False), (True, True)])
-def test_halves_of_a_workgroup(ctx, dt, m, n, k, ta, tb):  # noqa: F811
+def test_halves_of_a_workgroup(ctx, dt, m, n, k, second, ta, tb):  # noqa: F811
     """Shapes whose workgroups are two halves that share k: odd numbers of slices, a rest of k, tiles over both edges, rows that start off a
     16-byte boundary, narrow tiles; as it is, with bias and GELU, and added to a residual.  Bars as above."""
     E, g = Eager(), rng(m * 7 + n * 11 + k)
@@ -86,4 +88,10 @@ def test_halves_of_a_workgroup(ctx, dt, m, n, k, ta, tb):  # noqa: F811
         p = B.matmul(window(B, a_, a.shape[0] - 2), window(B, b_, b.shape[0] - 2), trans_a=ta, trans_b=tb)
         return p if post == "plain" else B.gelu(B.add(p, bias_)) if post == "gelu" else B.add(res_, p, alpha=0.5)
     for post in ("plain", "gelu", "residual"):
-        check(ctx, E, prog(ctx, post), prog(E, post), 2e-2 if dt == "bf16" else max(1e-5, 1e-6 * k ** 0.5), post)
+        got = prog(ctx, post)
+        ctx.set_profiling(True)
+        ctx.barrier()
+        names = [r["kernel"] for r in ctx.last_launches()]
+        ctx.set_profiling(False)
+        assert names[0].startswith("lt_gemm") and names[0].rstrip(">").endswith(",2") and len(names) == (2 if second else 1), names
+        check(ctx, E, got, prog(E, post), 2e-2 if dt == "bf16" else max(1e-5, 1e-6 * k ** 0.5), post)
