@@ -258,8 +258,13 @@ __global__ __launch_bounds__(kGemmThreads * KS, BM == 64 ? 2 : 1) void lt_gemm_k
   uint32_t n = (k_end - k_begin) / BK;   // whole slices
   if ((a_over && a_outer < 4) || (b_over && b_outer < 4)) n = 0u;
   else if ((a_over || b_over) && n > 0u && k_begin + n * BK == a.k) --n;
-  if (KS > 1) n /= 2u;                   // the same number for both halves; an odd one is left to the rest
-  const uint32_t k_first = k_begin + half * n * BK, k_rest = k_begin + KS * n * BK;
+  // The halves walk theirs in the same n steps, between the same barriers.  Of an odd number the first takes one more; the
+  // second has nothing to multiply in the last step: as a slice of the rest it took 1 to 2 us (1000 x 1024 x 800 21.6 -> 20.2, 600 x 768
+  // x 800 19.8 -> 17.7).  (A single slice is left to the rest.)
+  if (KS > 1 && n < 2u) n = 0u;
+  const uint32_t both = KS > 1 ? n / 2u : n, k_rest = k_begin + n * BK;   // steps in which every half multiplies
+  if (KS > 1) n -= both;
+  const uint32_t mine = half == 0u ? n : both, k_first = k_begin + half * n * BK;
   const T* const pa = A + (int64_t)tile_m * a.a.s_row + (int64_t)k_first * a.a.s_col;
   const T* const pb = B + (int64_t)tile_n * a.b.s_col + (int64_t)k_first * a.b.s_row;
   const int64_t step_a = BK * a.a.s_col, step_b = BK * a.b.s_row;   // elements per slice of k
@@ -307,7 +312,7 @@ __global__ __launch_bounds__(kGemmThreads * KS, BM == 64 ? 2 : 1) void lt_gemm_k
     };
 #define LT_COPY(I, STAGE)                                                                  \
   {                                                                                       \
-    const int64_t sl = min((uint32_t)(I), n - 1u);                                        \
+    const int64_t sl = min((uint32_t)(I), mine - 1u);                                     \
     DA::copy(pa + sl * step_a, a_off, lds0 + (STAGE) * kStage, wave_u);                   \
     DB::copy(pb + sl * step_b, b_off, lds0 + (STAGE) * kStage + DA::kBytes, wave_u);      \
   }
@@ -317,7 +322,7 @@ __global__ __launch_bounds__(kGemmThreads * KS, BM == 64 ? 2 : 1) void lt_gemm_k
     __syncthreads();                              \
     LT_COPY(i + (J) + 4u, (J) & 3);               \
     NEXT = frags(((J) + 1) & 3);                  \
-    if (!(GUARD) || i + (J) < n) mma(CUR);        \
+    if (!(GUARD) || i + (J) < mine) mma(CUR);     \
   }
     LT_COPY(0, 0);
     LT_COPY(1, 1);
@@ -327,7 +332,7 @@ __global__ __launch_bounds__(kGemmThreads * KS, BM == 64 ? 2 : 1) void lt_gemm_k
     __syncthreads();
     Frags f0 = frags(0), f1;
     uint32_t i = 0;
-    for (; i + 4u <= n; i += 4u) {
+    for (; i + 4u <= both; i += 4u) {
       LT_SLICE(0, f0, f1, false);
       LT_SLICE(1, f1, f0, false);
       LT_SLICE(2, f0, f1, false);
@@ -337,6 +342,7 @@ __global__ __launch_bounds__(kGemmThreads * KS, BM == 64 ? 2 : 1) void lt_gemm_k
       LT_SLICE(0, f0, f1, true);
       LT_SLICE(1, f1, f0, true);
       LT_SLICE(2, f0, f1, true);
+      if (KS > 1 && i + 3u < n) LT_SLICE(3, f1, f0, true);   // (the first half's odd one)
     }
     landed<0>();   // nothing may still be on its way into LDS when it is used again
 #undef LT_SLICE
@@ -348,25 +354,31 @@ __global__ __launch_bounds__(kGemmThreads * KS, BM == 64 ? 2 : 1) void lt_gemm_k
     const Offsets<BN> b_off = unaligned_offsets<BN, BKC>(a.b.s_col, a.b.s_row, left_n);
     fetch_unaligned<BM>(ga, pa, a_off);
     fetch_unaligned<BN>(gb, pb, b_off);
-#pragma unroll 1
-    for (uint32_t j = 0; j < n; ++j) {
+    auto step = [&](uint32_t j, bool multiply) {
       stash_tile<BM, AKC>(ga, As(j & 1u));
       stash_tile<BN, BKC>(gb, Bs(j & 1u));
-      const int64_t nx = min(j + 1u, n - 1u);
+      const int64_t nx = min(j + 1u, mine - 1u);
       fetch_unaligned<BM>(ga, pa + nx * step_a, a_off);
       fetch_unaligned<BN>(gb, pb + nx * step_b, b_off);
       __syncthreads();
-      mma_slice<BM, BN, MB, NB, AKC, BKC, NCH>(accs, As(j & 1u), Bs(j & 1u), wave_m, wave_n, lane);
-    }
+      if (multiply) mma_slice<BM, BN, MB, NB, AKC, BKC, NCH>(accs, As(j & 1u), Bs(j & 1u), wave_m, wave_n, lane);
+    };
+#pragma unroll 1
+    for (uint32_t j = 0; j < both; ++j) step(j, true);
+    if (KS > 1 && both < n) step(both, half == 0u);   // (the first half's odd one)
   }
-  // the rest of k: every access checked, one slice at a time, multiplied by the first half
+  // the rest of k: every access checked, one slice at a time, by the first half
 #pragma unroll 1
   for (uint32_t k0 = k_rest; k0 < k_end; k0 += BK) {
-    fetch_tile<T, BM, AKC>(ga, A, a.a.s_row, a.a.s_col, tile_m, k0, a.m, k_end);
-    fetch_tile<T, BN, BKC>(gb, B, a.b.s_col, a.b.s_row, tile_n, k0, a.n, k_end);
+    if (half == 0u) {
+      fetch_tile<T, BM, AKC>(ga, A, a.a.s_row, a.a.s_col, tile_m, k0, a.m, k_end);
+      fetch_tile<T, BN, BKC>(gb, B, a.b.s_col, a.b.s_row, tile_n, k0, a.n, k_end);
+    }
     __syncthreads();
-    stash_tile<BM, AKC>(ga, As(0));
-    stash_tile<BN, BKC>(gb, Bs(0));
+    if (half == 0u) {
+      stash_tile<BM, AKC>(ga, As(0));
+      stash_tile<BN, BKC>(gb, Bs(0));
+    }
     __syncthreads();
     if (half == 0u) mma_slice<BM, BN, MB, NB, AKC, BKC, NCH>(accs, As(0), Bs(0), wave_m, wave_n, lane);
   }

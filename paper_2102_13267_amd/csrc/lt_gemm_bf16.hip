@@ -334,8 +334,13 @@ __global__ __launch_bounds__(kGemmThreads * KS, 2) void lt_gemm_bf16_kernel(cons
   uint32_t n = (k_end - k_begin) / BK;   // whole slices
   if ((a_over && a_outer < 8) || (b_over && b_outer < 8)) n = 0u;
   else if ((a_over || b_over) && n > 0u && k_begin + n * BK == a.k) --n;
-  if (KS > 1) n /= 2u;                   // the same number for both halves; an odd one is left to the rest
-  const uint32_t k_first = k_begin + half * n * BK, k_rest = k_begin + KS * n * BK;
+  // The halves walk theirs in the same n steps, between the same barriers.  Of an odd number the first takes one more; the
+  // second has nothing to multiply in the last step: as a slice of the rest it took 2 to 4 us (512 x 768 x 700 17.7 -> 13.2, 768 x 768 x
+  // 4096 28.6 -> 23.3).  (A single slice is left to the rest.)
+  if (KS > 1 && n < 2u) n = 0u;
+  const uint32_t both = KS > 1 ? n / 2u : n, k_rest = k_begin + n * BK;   // steps in which every half multiplies
+  if (KS > 1) n -= both;
+  const uint32_t mine = half == 0u ? n : both, k_first = k_begin + half * n * BK;
   const uint16_t* const pa = A + (int64_t)tile_m * a.a.s_row + (int64_t)k_first * a.a.s_col;
   const uint16_t* const pb = B + (int64_t)tile_n * a.b.s_col + (int64_t)k_first * a.b.s_row;
   const int64_t step_a = BK * a.a.s_col, step_b = BK * a.b.s_row;   // elements per slice of k
@@ -357,13 +362,13 @@ __global__ __launch_bounds__(kGemmThreads * KS, 2) void lt_gemm_bf16_kernel(cons
     for (uint32_t it = 0; it < Dense<BN, BKC>::kInstr; ++it) b_off[it] = dma_lane_offset<BN, BKC>(it, a.b.s_col, a.b.s_row, left_n);
 #define LT_COPY(I, STAGE)                                                                                  \
   {                                                                                                       \
-    const int64_t sl = min((uint32_t)(I), n - 1u);                                                        \
+    const int64_t sl = min((uint32_t)(I), mine - 1u);                                                     \
     dma_tile<BM, AKC>(pa + sl * step_a, a_off, lds0 + (STAGE) * kDenseStage, wave_u);                     \
     dma_tile<BN, BKC>(pb + sl * step_b, b_off, lds0 + (STAGE) * kDenseStage + Dense<BM, AKC>::kBytes, wave_u); \
   }
 #define LT_COPY2(I0, S0, I1, S1)                                                                           \
   {                                                                                                       \
-    const int64_t sa = min((uint32_t)(I0), n - 1u), sb = min((uint32_t)(I1), n - 1u);                     \
+    const int64_t sa = min((uint32_t)(I0), mine - 1u), sb = min((uint32_t)(I1), mine - 1u);               \
     dma_tile2<BM, AKC>(pa + sa * step_a, pa + sb * step_a, a_off, lds0 + (S0) * kDenseStage, lds0 + (S1) * kDenseStage, wave_u); \
     dma_tile2<BN, BKC>(pb + sa * step_b, pb + sb * step_b, b_off, lds0 + (S0) * kDenseStage + Dense<BM, AKC>::kBytes, \
                        lds0 + (S1) * kDenseStage + Dense<BM, AKC>::kBytes, wave_u);                       \
@@ -389,7 +394,7 @@ __global__ __launch_bounds__(kGemmThreads * KS, 2) void lt_gemm_bf16_kernel(cons
       if (n > 2u) LT_COPY(2, 2);
       landed<0>();
       __syncthreads();
-      for (uint32_t j = 0; j < n; ++j) {
+      for (uint32_t j = 0; j < mine; ++j) {
         const Frags f = j == 0u ? dense_frags(0) : j == 1u ? dense_frags(1) : dense_frags(2);
         mma(f);
       }
@@ -435,19 +440,20 @@ __global__ __launch_bounds__(kGemmThreads * KS, 2) void lt_gemm_bf16_kernel(cons
       LT_COPY(i + (J) + 4u, (J) & 3);                                          \
     }                                                                          \
     NEXT = dense_frags(((J) + 1) & 3);                                         \
-    if (!(GUARD) || i + (J) < n) mma(CUR);                                     \
+    if (!(GUARD) || i + (J) < mine) mma(CUR);                                  \
   }
     uint32_t i = 0;
-    for (; i + 4u <= n; i += 4u) {   // straight-line code: copies, LDS reads and MFMAs interleave
+    for (; i + 4u <= both; i += 4u) {   // straight-line code: copies, LDS reads and MFMAs interleave
       LT_SLICE(0, f0, f1, false);
       LT_SLICE(1, f1, f0, false);
       LT_SLICE(2, f0, f1, false);
       LT_SLICE(3, f1, f0, false);
     }
-    if (i < n) {                     // one to three slices left
+    if (i < n) {                     // one to three steps left, or four
       LT_SLICE(0, f0, f1, true);
       LT_SLICE(1, f1, f0, true);
       LT_SLICE(2, f0, f1, true);
+      if (KS > 1 && i + 3u < n) LT_SLICE(3, f1, f0, true);   // (the first half's odd one)
     }
     landed<0>();   // nothing may still be on its way into LDS when it is used again
     }
@@ -473,27 +479,35 @@ __global__ __launch_bounds__(kGemmThreads * KS, 2) void lt_gemm_bf16_kernel(cons
     }
     Chunks<Geo<BM>::kChunks> ca = fetch_unaligned<BM, AKC>(pa, a_off);
     Chunks<Geo<BN>::kChunks> cb = fetch_unaligned<BN, BKC>(pb, b_off);
-#pragma unroll 1
-    for (uint32_t j = 0; j < n; ++j) {
+    auto step = [&](uint32_t j, bool multiply) {
       char* const st = smem + (j & 1u) * kStage;
       stash<BM, AKC>(ca, st);
       stash<BN, BKC>(cb, st + Geo<BM>::kBytes);
-      const int64_t nx = min(j + 1u, n - 1u);   // (past the end: the last slice again, unused)
+      const int64_t nx = min(j + 1u, mine - 1u);   // (past the end: the last slice again, unused)
       ca = fetch_unaligned<BM, AKC>(pa + nx * step_a, a_off);
       cb = fetch_unaligned<BN, BKC>(pb + nx * step_b, b_off);
       __syncthreads();
-      mma(load_frags(j & 1u));
-    }
+      if (multiply) mma(load_frags(j & 1u));
+    };
+#pragma unroll 1
+    for (uint32_t j = 0; j < both; ++j) step(j, true);
+    if (KS > 1 && both < n) step(both, half == 0u);   // (the first half's odd one)
   }
   if (k_rest < k_end) {
-    // the rest of k: every address checked, one slice at a time, multiplied by the first half
+    // the rest of k: every address checked, one slice at a time, by the first half
 #pragma unroll 1
     for (uint32_t k0 = k_rest; k0 < k_end; k0 += BK) {
-      const Chunks<Geo<BM>::kChunks> ca = fetch_checked<BM, AKC>(A, a.a.s_row, a.a.s_col, tile_m, k0, a.m, k_end);
-      const Chunks<Geo<BN>::kChunks> cb = fetch_checked<BN, BKC>(B, a.b.s_col, a.b.s_row, tile_n, k0, a.n, k_end);
+      Chunks<Geo<BM>::kChunks> ca;
+      Chunks<Geo<BN>::kChunks> cb;
+      if (half == 0u) {
+        ca = fetch_checked<BM, AKC>(A, a.a.s_row, a.a.s_col, tile_m, k0, a.m, k_end);
+        cb = fetch_checked<BN, BKC>(B, a.b.s_col, a.b.s_row, tile_n, k0, a.n, k_end);
+      }
       __syncthreads();
-      stash<BM, AKC>(ca, smem);
-      stash<BN, BKC>(cb, smem + Geo<BM>::kBytes);
+      if (half == 0u) {
+        stash<BM, AKC>(ca, smem);
+        stash<BN, BKC>(cb, smem + Geo<BM>::kBytes);
+      }
       __syncthreads();
       if (half == 0u) mma(load_frags(0));
     }

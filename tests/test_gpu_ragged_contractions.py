@@ -66,7 +66,8 @@ def test_ragged_attention_products(ctx, s, h, d):  # noqa: F811
 
 # second: several partial products are left, and a launch that adds them up
 @pytest.mark.parametrize("dt,m,n,k,second", [("bf16", 600, 600, 500, False), ("bf16", 1000, 1000, 2100, True), ("bf16", 129, 1544, 583, False),
-                                             ("bf16", 3100, 64, 600, False), ("bf16", 257, 1096, 545, False), ("f32", 1000, 1000, 136, False),
+                                             ("bf16", 3100, 64, 600, False), ("bf16", 257, 1096, 545, False), ("bf16", 600, 600, 549, False),
+                                             ("f32", 1000, 1000, 136, False), ("f32", 1000, 1000, 163, False), ("f32", 1000, 1000, 240, False),
                                              ("f32", 500, 1000, 2050, True), ("f32", 997, 1000, 137, False), ("f32", 960, 968, 203, False),
                                              ("f32", 1000, 1024, 257, False), ("f32", 1400, 257, 512, True)])
 @pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, False), (True, True)])
