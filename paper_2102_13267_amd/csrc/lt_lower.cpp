@@ -2124,16 +2124,30 @@ struct Lowering {
   // memory and back, none (and no second launch) where there were two.  us, before / in halves: bf16 1024 x 4096 and
   // 4096 x 1024 from 4096 rows 50 / 34.9 and 49 / 34.6, 4096 x 1024 x 4096 with bias 56 / 41.6, 1024 x 1024 from 8192 rows with Adam (eight
   // partial products, then four) 44.9 / 42.3; fp32 512 x 2048 x 2048 44.3 / 39.2, 1024 x 1000 from 2048 rows 43.6 / 39.6.
-  // Where no second launch is left that pays for any number of tiles (1000 x 2048 x 512 with bias, GELU and both results
-  // 28.0 / 14.0), otherwise only where the workgroups would share compute units anyway: those that have one each lose
+  // (Times with the GPU never idle, before / in halves.)
+  // Where no second launch is left: a product stored as it is always gains (256 x 256 x 512 10.6 / 9.0, 1000 x 3072 x 4096 47.5 / 43.0).  A
+  // program in the epilogue is exposed in as many workgroups as there are tiles, which a second launch spreads over the chip, so it has
+  // to save that launch enough of its way through memory: bias, GELU and both results, two products (k = 512) 32 x 4096 10.9 / 11.7, 100 x 1024
+  // 11.6 / 11.9, 256 x 768 12.1 / 12.1, 1000 x 256 12.2 / 11.9, 100 x 3072 12.5 / 12.1, 512 x 1024 13.5 / 12.1, 512 x 4096 26.5 / 13.1; three (768 and 900)
+  // 100 x 1024 12.1 to 14.5 / 13.3 to 16.9, 512 x 768 14.1 to 16.5 / 13.4 to 17.2, 512 x 1024 14.9 to 17.3 / 13.5 to 17.2, 1000 x 768 16.8 to 19.1 / 13.6 to 17.3.
+  // Where one is left: only if the workgroups would share compute units anyway; those that have one each lose
   // by moving together (512 x 2048 from 1000 rows, four partial products, then two, 19.5 / 24.7).  A program that is no chain is not brought back from
-  // a second launch into the epilogue (143 x 10 x 512 14.5 / 26).  In bf16 an odd number of splits is rounded down: what the
-  // idle compute units cost is less than the partial products they save.  In fp32 it stays: fewer, longer
-  // sums would be less accurate (against 64 bits 3.5e-7 -> 4.1e-7 for four instead of five).
+  // a second launch into the epilogue (143 x 10 x 512 14.5 / 26).
+  // An odd number of splits is rounded down where every result is bf16 and k is not so long that the idle compute units cost more than the
+  // partial products (768 x 3072, three: k = 1024 24.0 / 15.5, 4096 40.7 / 40.6, 4992 50.2 / 52.0; 512 x 3072, five, then four: 2000 26.2 /
+  // 24.9, 4096 32.4 / 31.1, 4992 39.4 / 40.0).  Where fp32 comes out (any fp32 product, an optimiser's moments) it stays: fewer, longer sums
+  // are less accurate (root mean square error against 64 bits: fp32 3.5e-7 -> 4.1e-7 for four instead of five; bf16 1280 x 1664 from 8192 rows, fp32
+  // moments, 3.2e-7 -> 4.0e-7 for two instead of three; rounded to bf16 both are 1.6555e-3 off).
   static void halve(ltk::GemmArgs* a, uint64_t tiles, bool sealed, uint64_t* splits) {
-    if (*splits < 2u || (a->in_dtype == ltk::kF32 && *splits % 2u != 0u)) return;
+    if (*splits < 2u) return;
+    const bool bf16 = a->in_dtype == ltk::kBF16, odd = *splits % 2u != 0u;
+    bool rounded = bf16;
+    for (uint32_t o = 0; o < a->post.n_out; ++o) rounded = rounded && a->post.out[o].dtype == ltk::kBF16;
+    if (odd && (!rounded || (!sealed && a->k > 4096u))) return;
     const bool second = *splits >= 4u || (!sealed && heavy_post(a->post));   // a second launch is left
     if (second ? *splits * tiles <= 256u : !a->chain.n) return;
+    const uint64_t results = (uint64_t)a->batch0 * a->batch1 * a->m * a->n;
+    if (bf16 && !second && !sealed && a->chain.n > 1u && results < (odd ? 8u << 16 : 3u << 16)) return;
     a->halves = 2u;
     *splits /= 2u;
   }

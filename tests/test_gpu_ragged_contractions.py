@@ -96,3 +96,34 @@ def test_halves_of_a_workgroup(ctx, dt, m, n, k, second, ta, tb):  # noqa: F811
         ctx.set_profiling(False)
         assert names[0].startswith("lt_gemm") and names[0].rstrip(">").endswith(",2") and len(names) == (2 if second else 1), names
         check(ctx, E, got, prog(E, post), 2e-2 if dt == "bf16" else max(1e-5, 1e-6 * k ** 0.5), post)
+
+
+@pytest.mark.parametrize("m,n,k,post,halves", [(100, 256, 520, "plain", 2), (100, 256, 520, "gelu", 1), (500, 704, 520, "gelu", 2), (600, 704, 800, "plain", 2),
+                                               (600, 704, 800, "gelu", 1), (800, 904, 800, "gelu", 2), (1280, 1280, 800, "moments", 1), (1280, 1280, 800, "plain", 2),
+                                               (1024, 1024, 1400, "plain", 2), (1024, 1024, 1400, "moments", 1), (512, 768, 4200, "plain", 2), (512, 3072, 4200, "plain", 1)])
+def test_where_halves_are_taken(ctx, m, n, k, post, halves):  # noqa: F811
+    """bf16: few tiles with a program in the epilogue, an odd number of partial products of which fp32 results come or whose
+    k is long, keep a workgroup for each.  Bar: 2e-2 of the largest value, also of fp32 results, as the oracle rounds the product that
+    the launch combines them with as it is."""
+    E, g = Eager(), rng(m + n + k)
+    mk = lambda *s: round_to_bf16(g.standard_normal(s, dtype=np.float32))                     # noqa: E731
+    a, b, bias = mk(m, k), round_to_bf16(g.standard_normal((k, n), dtype=np.float32) * np.float32(k ** -0.5)), mk(n)
+    m0, v0 = (g.standard_normal((m, n), dtype=np.float32) for _ in range(2))
+
+    def prog(B):
+        p = B.matmul(B.tensor(a, dtype="bf16"), B.tensor(b, dtype="bf16"))
+        if post == "plain":
+            return [p]
+        if post == "gelu":
+            u = B.add(p, B.tensor(bias, dtype="bf16"))
+            return [u, B.gelu(u)]
+        m1, v1 = B.add(B.mul(B.tensor(m0), 0.9), p, alpha=0.1), B.add(B.mul(B.abs(B.tensor(v0)), 0.99), B.square(p), alpha=0.01)
+        return [m1, v1, B.div(m1, B.add(B.sqrt(v1), 0.5))]
+    got = prog(ctx)
+    ctx.set_profiling(True)
+    ctx.barrier()
+    names = [r["kernel"] for r in ctx.last_launches()]
+    ctx.set_profiling(False)
+    assert names[0].endswith(f",{halves}>"), names
+    for i, (x, y) in enumerate(zip(got, prog(E))):
+        check(ctx, E, x, y, 2e-2, (post, i))
