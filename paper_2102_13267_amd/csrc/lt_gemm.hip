@@ -451,19 +451,26 @@ __device__ __forceinline__ SmallTile small_tile(const GemmArgs& a) {
 }
 
 // The sum of a tile's partial quads, `stride` floats apart, in split order (deterministic).  They are all asked for before
-// the first is added: read one by one, each waits for its own way to memory and back.
+// the first is added: read one by one, each waits for its own way to memory and back.  (And no more of them than there are, to the
+// next power of two: these loads pass by the caches.)
 constexpr int kMaxShare = 8;
-__device__ __forceinline__ float4 sum_parts(const float* parts, uint32_t stride, uint32_t splits) {
-  float4 t[kMaxShare];
+template <int N>
+__device__ __forceinline__ float4 sum_parts_of(const float* parts, uint32_t stride, uint32_t splits) {
+  float4 t[N];
 #pragma unroll
-  for (uint32_t sp = 0; sp < (uint32_t)kMaxShare; ++sp) t[sp] = published4(parts + (size_t)min(sp, splits - 1u) * stride);
+  for (uint32_t sp = 0; sp < (uint32_t)N; ++sp) t[sp] = published4(parts + (size_t)min(sp, splits - 1u) * stride);
   float4 sum = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 #pragma unroll
-  for (uint32_t sp = 0; sp < (uint32_t)kMaxShare; ++sp)
+  for (uint32_t sp = 0; sp < (uint32_t)N; ++sp)
     if (sp < splits) {
       sum.x += t[sp].x; sum.y += t[sp].y; sum.z += t[sp].z; sum.w += t[sp].w;
     }
   return sum;
+}
+__device__ __forceinline__ float4 sum_parts(const float* parts, uint32_t stride, uint32_t splits) {
+  if (splits <= 2u) return sum_parts_of<2>(parts, stride, splits);
+  if (splits <= 4u) return sum_parts_of<4>(parts, stride, splits);
+  return sum_parts_of<kMaxShare>(parts, stride, splits);
 }
 
 template <bool V>
@@ -751,18 +758,17 @@ __device__ __forceinline__ void small_tile16(const GemmArgs& a) {
   const EwProg& p = a.post;
   const ProgRegs pr = load_prog_regs(p);
   const uint32_t qrow = tile_m + (threadIdx.x % kQuads) / (4u * NB), qcol = tile_n + (threadIdx.x % (4u * NB)) * (uint32_t)kVec;
-  const uint32_t qi = (uint32_t)((int64_t)b0 * a.o_b0 + (int64_t)b1 * a.o_b1 + (int64_t)qrow * a.o_row + qcol);
+  // (a quad past an edge reads the last row's or column's inputs and is not stored)
+  const uint32_t in_row = min(qrow, a.m - 1u), in_col = (a.n & 3u) == 0u ? min(qcol, a.n - 4u) : qcol;
+  const uint32_t qi = (uint32_t)((int64_t)b0 * a.o_b0 + (int64_t)b1 * a.o_b1 + (int64_t)in_row * a.o_row + in_col);
   const bool has_quad = threadIdx.x < kQuads;   // (wave-uniform)
-  const bool fast = p.fast && p.full_vec_ok && p.n_in <= 4u && p.n_slots <= 8u && (a.n & 3u) == 0u;   // (quads past an edge: as above)
+  const bool fast = p.fast && p.full_vec_ok && p.n_in <= 4u && p.n_slots <= 8u && (a.n & 3u) == 0u;
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Wuninitialized"
 #pragma clang diagnostic ignored "-Wsometimes-uninitialized"
   Staged<4> staged;
   if (k_begin < k_end) fetch(0, k_begin);
-  if (fast && has_quad) {
-    const uint32_t r = min(qrow, a.m - 1u), c = min(qcol, a.n - 4u);
-    staged = fetch_inputs_at<4, false, false>(p, (uint32_t)((int64_t)b0 * a.o_b0 + (int64_t)b1 * a.o_b1 + (int64_t)r * a.o_row + c), (b0 * a.batch1 + b1) * a.m + r, c);
-  }
+  if (fast && has_quad) staged = fetch_inputs_at<4, false, false>(p, qi, (b0 * a.batch1 + b1) * a.m + in_row, in_col);
 #pragma clang diagnostic pop
   typedef float v4f __attribute__((ext_vector_type(4)));
   v4f acc[2][NB];

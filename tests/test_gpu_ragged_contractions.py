@@ -127,3 +127,22 @@ def test_where_halves_are_taken(ctx, m, n, k, post, halves):  # noqa: F811
     assert names[0].endswith(f",{halves}>"), names
     for i, (x, y) in enumerate(zip(got, prog(E))):
         check(ctx, E, x, y, 2e-2, (post, i))
+
+
+@pytest.mark.parametrize("m,n,k,share", [(70, 1000, 2000, 2), (33, 1300, 1100, 3), (33, 1000, 2000, 4), (33, 800, 2000, 5), (33, 650, 2000, 6), (20, 1000, 2100, 8),
+                                         (100, 1024, 1300, 2), (70, 1024, 1300, 3), (40, 1088, 1300, 5), (20, 1024, 2000, 8)])
+def test_shared_tiles(ctx, m, n, k, share):  # noqa: F811
+    """Workgroups that share a tile (two to eight of them; tiles of 32 x 32, 64 x 32 and 16 x 64) and add up one another's
+    partial products, in fp32.  Bar as above."""
+    E, g = Eager(), rng(m + n + k)
+    a, b, bias, res = (g.standard_normal(s, dtype=np.float32) for s in ((m, k), (k, n), (n,), (m, n)))
+
+    def prog(B):
+        return B.add(B.relu(B.add(B.matmul(B.tensor(a), B.tensor(b)), B.tensor(bias))), B.tensor(res))
+    got = prog(ctx)
+    ctx.set_profiling(True)
+    ctx.barrier()
+    names = [r["kernel"] for r in ctx.last_launches()]
+    ctx.set_profiling(False)
+    assert len(names) == 1 and names[0].startswith("lt_gemm_small_kernel"), names
+    check(ctx, E, got, prog(E), max(1e-5, 1e-6 * k ** 0.5), share)
