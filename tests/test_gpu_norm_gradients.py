@@ -98,7 +98,9 @@ def test_norm_forward_and_backward(ctx, rows, cols, dt):  # noqa: F811
 def test_sums_that_ride_with_the_input_gradient(ctx, rows, cols, dt):  # noqa: F811
     """One to more than 512 workgroups' partial sums, a wave with a row more than another, the last chunk that few lanes
     have, rows too long for it or of no whole chunks (launches of their own); both sums, one alone, parameters updated in
-    place by them, and x overwritten between the input gradient and the sums (which then take the new x)."""
+    place by them, and x overwritten between the input gradient and the sums (which then take the new x, in a launch of their own)."""
+    chunk = 8 if dt == "bf16" else 4
+    rides = cols % chunk == 0 and cols <= 4 * 64 * chunk
     E, data = Eager(), operands(rows, cols, dt)
     tol = 2e-2 if dt == "bf16" else 2e-5 * max(1.0, rows ** 0.5 / 8)
 
@@ -119,7 +121,14 @@ def test_sums_that_ride_with_the_input_gradient(ctx, rows, cols, dt):  # noqa: F
             return [dx, w, b]
         return [y, dx, dg, db, x]
     for variant in range(4):
-        got, ref = run(ctx, lambda t: ctx.tensor(t, dtype=dt, donatable=True), variant), run(E, lambda t: E.tensor(t, dtype=dt), variant)
+        got = run(ctx, lambda t: ctx.tensor(t, dtype=dt, donatable=True), variant)
+        ctx.set_profiling(True)
+        ctx.barrier()
+        names = [r["kernel"] for r in ctx.last_launches()]
+        ctx.set_profiling(False)
+        (sums,) = [int(n[:-1].split(", ")[-1]) for n in names if n.startswith("lt_norm_stream_kernel<3,")] or [0]
+        assert sums == ((2, 1, 1, 0)[variant] if rides else 0), names    # (updated in place the bias's sum stands first, in a launch of its own)
+        ref = run(E, lambda t: E.tensor(t, dtype=dt), variant)
         for i, (p, q) in enumerate(zip(got, ref)):
             check(ctx, E, p, q, tol, (variant, i))
 
