@@ -323,8 +323,8 @@ __device__ __forceinline__ void wide_store(void* p, uint64_t elem, const float* 
 // ride along.  Both read what this pass has in registers, and a lane's columns are the same in all its rows, so a row costs
 // two additions per element; as a launch of their own they are a second pass over both tensors.  Workgroups are
 // twice the size and walk more rows each (RowOpArgs::col_rows of them), so that fewer partial sums are left for the
-// launch that adds them up.  Norm forward, gradient and sums, us a pass (from 28 on
-// the recording of it takes as long): 8192 x 1024 in bf16 35.6 -> 28.5, fp32 46.8 -> 32.2, 16000 x 2048 in bf16 109 -> 63, 131072 x 256 205 -> 81.
+// launch that adds them up.  Norm forward, gradient and sums, us a pass (28 to 31 of it are the
+// host's time): 8192 x 1024 in bf16 35.4 -> 31.5, fp32 52.8 -> 36.5, 16000 x 2048 in bf16 118.6 -> 70.1, 131072 x 256 216 -> 90.
 template <int OP, int NV, bool BF, int CS>
 __global__ __launch_bounds__(CS ? 2 * kBlock : kBlock) void lt_norm_stream_kernel(const RowOpArgs a) {
   constexpr uint32_t kWaves = (CS ? 2 * kBlock : kBlock) / 64;
