@@ -150,7 +150,10 @@ template <int BX, bool KC> struct Dense {
   }
   __device__ static __forceinline__ void copy(const float* src, const uint32_t (&off)[kInstr], uint32_t tile, uint32_t wave) {
 #pragma unroll
-    for (uint32_t it = 0; it < kInstr; ++it) copy_1k(src, off[it], tile + (it * (uint32_t)kGemmThreads + wave * 64u) * 16u);
+    for (uint32_t it = 0; it < kInstr; ++it) copy_part(src, off, it, tile, wave);
+  }
+  __device__ static __forceinline__ void copy_part(const float* src, const uint32_t (&off)[kInstr], uint32_t it, uint32_t tile, uint32_t wave) {
+    copy_1k(src, off[it], tile + (it * (uint32_t)kGemmThreads + wave * 64u) * 16u);
   }
   // This lane's values of row / column x for the k of group g (eight k: four for each half wave).  Which
   // k goes into which of a group's four MFMAs is free as long as both operands agree.
@@ -286,29 +289,22 @@ __global__ __launch_bounds__(kGemmThreads * KS, BM == 64 ? 2 : 1) void lt_gemm_k
     struct Frags {
       RawVec a[BK / 8][MB], b[BK / 8][NB];
     };
-    auto frags = [&](uint32_t stage) {
-      const char* At = smem + stage * kStage;
-      const char* Bt = At + DA::kBytes;
-      Frags f;
+    // this lane's part of group g of the slice in `stage`, of A or of B
+    auto read_a = [&](Frags& f, uint32_t stage, int g) {
 #pragma unroll
-      for (uint32_t g = 0; g < BK / 8; ++g) {
-#pragma unroll
-        for (int i = 0; i < MB; ++i) f.a[g][i] = DA::group(At, wave_m * (BM / 2) + i * 32u + (lane & 31u), g, h);
-#pragma unroll
-        for (int j = 0; j < NB; ++j) f.b[g][j] = DB::group(Bt, wave_n * (BN / 2) + j * 32u + (lane & 31u), g, h);
-      }
-      return f;
+      for (int i = 0; i < MB; ++i) f.a[g][i] = DA::group(smem + stage * kStage, wave_m * (BM / 2) + i * 32u + (lane & 31u), (uint32_t)g, h);
     };
-    auto mma = [&](const Frags& f) {
+    auto read_b = [&](Frags& f, uint32_t stage, int g) {
 #pragma unroll
-      for (int g = 0; g < BK / 8; ++g)
+      for (int j = 0; j < NB; ++j) f.b[g][j] = DB::group(smem + stage * kStage + DA::kBytes, wave_n * (BN / 2) + j * 32u + (lane & 31u), (uint32_t)g, h);
+    };
+    // k step e of group g
+    auto mma = [&](const Frags& f, int g, int e) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
+      for (int i = 0; i < MB; ++i)
 #pragma unroll
-          for (int i = 0; i < MB; ++i)
-#pragma unroll
-            for (int j = 0; j < NB; ++j)
-              accs[e % NCH][i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(f.a[g][i][e], f.b[g][j][e], accs[e % NCH][i][j], 0, 0, 0);
+        for (int j = 0; j < NB; ++j)
+          accs[e % NCH][i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(f.a[g][i][e], f.b[g][j][e], accs[e % NCH][i][j], 0, 0, 0);
     };
 #define LT_COPY(I, STAGE)                                                                  \
   {                                                                                       \
@@ -316,13 +312,52 @@ __global__ __launch_bounds__(kGemmThreads * KS, BM == 64 ? 2 : 1) void lt_gemm_k
     DA::copy(pa + sl * step_a, a_off, lds0 + (STAGE) * kStage, wave_u);                   \
     DB::copy(pb + sl * step_b, b_off, lds0 + (STAGE) * kStage + DA::kBytes, wave_u);      \
   }
-#define LT_SLICE(J, CUR, NEXT, GUARD)             \
-  {                                               \
-    landed_and_read<2 * kPer>();                  \
-    __syncthreads();                              \
-    LT_COPY(i + (J) + 4u, (J) & 3);               \
-    NEXT = frags(((J) + 1) & 3);                  \
-    if (!(GUARD) || i + (J) < mine) mma(CUR);     \
+    // One slice.  A wave issues in order, and the compiler, left alone, put the LDS reads of the next slice behind the
+    // MFMAs and waited for them, twice a slice.  So every MFMA step is followed by one piece of the other work, and nothing
+    // moves across: first the reads of the next slice, which have to be back at its barrier, then the copies.  Of the two
+    // workgroups of 1024 x 2048 x 2048 on a compute unit the hardware serves the older one first: its loop 41 -> 33.5 us, the
+    // other's 70 -> 66, which is what all their MFMAs take at the 2.0 GHz that the card keeps under them; twelve such layers
+    // 850 -> 812 us, a head's three products (2048 x 1024 x 1000) 131.6 -> 124.7.
+    auto slice = [&](const Frags& cur, Frags& next, uint32_t next_stage, uint32_t copy_slice, uint32_t copy_stage) {
+      const int64_t sl = min(copy_slice, mine - 1u);   // (past the end: the last slice again, unused)
+      const float* const ca = pa + sl * step_a;
+      const float* const cb = pb + sl * step_b;
+      const uint32_t at = lds0 + copy_stage * kStage;
+#pragma unroll
+      for (int s = 0; s < BK / 2; ++s) {
+        mma(cur, s / 4, s % 4);
+        if (s < BK / 4 && s % 2 == 0) read_a(next, next_stage, s / 2);
+        if (s < BK / 4 && s % 2 == 1) read_b(next, next_stage, s / 2);
+        if (s >= BK / 4) {
+#pragma unroll
+          for (uint32_t it = 0; it < kPer; ++it)
+            if (it * 8u / kPer == (uint32_t)s - BK / 4) {
+              if (it < DA::kInstr) DA::copy_part(ca, a_off, it, at, wave_u);
+              else DB::copy_part(cb, b_off, it - DA::kInstr, at + DA::kBytes, wave_u);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+#define LT_SLICE(J, CUR, NEXT)                                                       \
+  {                                                                                  \
+    landed_and_read<2 * kPer>();                                                     \
+    __syncthreads();                                                                 \
+    __builtin_amdgcn_sched_barrier(0);                                               \
+    slice(CUR, NEXT, ((J) + 1) & 3, i + (J) + 4u, (J) & 3);                          \
+  }
+// the last ones: a half may have nothing left to multiply
+#define LT_LAST(J, CUR, NEXT)                      \
+  {                                                \
+    landed_and_read<0>();                          \
+    __syncthreads();                               \
+    if (i + (J) < mine) {                          \
+      _Pragma("unroll") for (int g = 0; g < BK / 8; ++g) { \
+        read_a(NEXT, ((J) + 1) & 3, g);            \
+        read_b(NEXT, ((J) + 1) & 3, g);            \
+      }                                            \
+      _Pragma("unroll") for (int s = 0; s < BK / 2; ++s) mma(CUR, s / 4, s % 4); \
+    }                                              \
   }
     LT_COPY(0, 0);
     LT_COPY(1, 1);
@@ -330,21 +365,27 @@ __global__ __launch_bounds__(kGemmThreads * KS, BM == 64 ? 2 : 1) void lt_gemm_k
     LT_COPY(3, 3);
     landed<3 * kPer>();
     __syncthreads();
-    Frags f0 = frags(0), f1;
+    Frags f0, f1;
+#pragma unroll
+    for (int g = 0; g < BK / 8; ++g) {
+      read_a(f0, 0, g);
+      read_b(f0, 0, g);
+    }
     uint32_t i = 0;
     for (; i + 4u <= both; i += 4u) {
-      LT_SLICE(0, f0, f1, false);
-      LT_SLICE(1, f1, f0, false);
-      LT_SLICE(2, f0, f1, false);
-      LT_SLICE(3, f1, f0, false);
+      LT_SLICE(0, f0, f1);
+      LT_SLICE(1, f1, f0);
+      LT_SLICE(2, f0, f1);
+      LT_SLICE(3, f1, f0);
     }
-    if (i < n) {
-      LT_SLICE(0, f0, f1, true);
-      LT_SLICE(1, f1, f0, true);
-      LT_SLICE(2, f0, f1, true);
-      if (KS > 1 && i + 3u < n) LT_SLICE(3, f1, f0, true);   // (the first half's odd one)
+    if (i < n) {   // (everything has been copied by now)
+      LT_LAST(0, f0, f1);
+      LT_LAST(1, f1, f0);
+      LT_LAST(2, f0, f1);
+      if (KS > 1 && i + 3u < n) LT_LAST(3, f1, f0);   // (the first half's odd one)
     }
     landed<0>();   // nothing may still be on its way into LDS when it is used again
+#undef LT_LAST
 #undef LT_SLICE
 #undef LT_COPY
   }
