@@ -56,6 +56,10 @@ template <typename T, int BX> struct Groups {
 // (a native vector type, not HIP's uint4 struct: sets of the struct kind that are only ever moved
 // whole were left in scratch memory by the compiler)
 typedef uint32_t U32x4 __attribute__((ext_vector_type(4)));
+template <uint32_t N> struct Num {
+  static constexpr uint32_t value = N;
+};
+
 template <int N> struct GroupRegs {
   U32x4 g[N];
 };
@@ -216,11 +220,16 @@ template <typename T, int BM, int BN> struct Smem {
 // aligned (the launcher looks).
 // KS: halves of the workgroup that share its k (GemmArgs::halves); each has LDS stages of its own, and they
 // walk their slices side by side.
-template <typename T, int BM, int BN, bool AKC, bool BKC, bool AL, int KS>
+// CS: column sums of B ride along (GemmArgs::col_sum; AKC and BKC false).  The workgroups of the first tile row take them from
+// the B fragments that they multiply anyway, half of each slice by either wave row.  A slice's values are added pairwise before
+// they join one of four running sums: one by one, 4096 rows of N(0, 1) would be 4e-7 from 64 bits.
+template <typename T, int BM, int BN, bool AKC, bool BKC, bool AL, int KS, bool CS>
 __global__ __launch_bounds__(kGemmThreads * KS, BM == 64 ? 2 : 1) void lt_gemm_kernel(const GemmArgs a) {
+  static_assert(!CS || (!AKC && !BKC), "a weight gradient");
   constexpr int MB = BM / 64, NB = BN / 64, BK = Elem<T>::BK;
   constexpr size_t kHalf = Smem<T, BM, BN>::kBytes;
   __shared__ __attribute__((aligned(16))) char smem_all[KS * kHalf];
+  __shared__ __attribute__((aligned(16))) float col_lds[CS ? KS * 2 * BN : 4];   // [half][wave row][column]
   const uint32_t touched = touch_args<GemmArgs>();
   const uint32_t half = KS > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / kGemmThreads) : 0u;
   char* const smem = smem_all + half * kHalf;
@@ -250,6 +259,23 @@ __global__ __launch_bounds__(kGemmThreads * KS, BM == 64 ? 2 : 1) void lt_gemm_k
 #pragma unroll
         for (int r = 0; r < 16; ++r) accs[c][i][j][r] = 0.0f;
 
+  const bool summing = CS && tile_m == 0u;
+  float csum[4][NB];
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) csum[c][j] = 0.0f;
+  // this wave row's half of a slice in a padded tile: eight k for each half wave
+  auto add_columns = [&](const T* tile) {
+    const T* p = tile + ((lane >> 5) * 16u + wave_m * 8u) * Tile<T, BN>::stride(false) + wave_n * (NB * 32) + (lane & 31u);
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      float t[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) t[e] = p[e * Tile<T, BN>::stride(false) + j * 32];
+      csum[0][j] += ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
+    }
+  };
   GroupRegs<Groups<T, BM>::N> ga;
   GroupRegs<Groups<T, BN>::N> gb;
   // Whole slices of k are fetched in 16-byte chunks with no checks; what is left of k goes through the
@@ -312,13 +338,23 @@ __global__ __launch_bounds__(kGemmThreads * KS, BM == 64 ? 2 : 1) void lt_gemm_k
     DA::copy(pa + sl * step_a, a_off, lds0 + (STAGE) * kStage, wave_u);                   \
     DB::copy(pb + sl * step_b, b_off, lds0 + (STAGE) * kStage + DA::kBytes, wave_u);      \
   }
+    auto add_frags = [&](const Frags& f, auto sum, int set) __attribute__((always_inline)) {
+      constexpr int g = decltype(sum)::value > 0 ? 2 * (int)decltype(sum)::value - 2 : 0;
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        const RawVec x = f.b[g][j], y = f.b[g + 1][j];
+        csum[set][j] += ((x.x + x.y) + (x.z + x.w)) + ((y.x + y.y) + (y.z + y.w));
+      }
+    };
     // One slice.  A wave issues in order, and the compiler, left alone, put the LDS reads of the next slice behind the
     // MFMAs and waited for them, twice a slice.  So every MFMA step is followed by one piece of the other work, and nothing
     // moves across: first the reads of the next slice, which have to be back at its barrier, then the copies.  Of the two
     // workgroups of 1024 x 2048 x 2048 on a compute unit the hardware serves the older one first: its loop 41 -> 33.5 us, the
     // other's 70 -> 66, which is what all their MFMAs take at the 2.0 GHz that the card keeps under them; twelve such layers
     // 850 -> 812 us, a head's three products (2048 x 1024 x 1000) 131.6 -> 124.7.
-    auto slice = [&](const Frags& cur, Frags& next, uint32_t next_stage, uint32_t copy_slice, uint32_t copy_stage) {
+    // (sum: not 0: this wave adds up the columns of groups 2 sum - 2 and 2 sum - 1 as well.)
+    auto slice = [&](const Frags& cur, Frags& next, uint32_t next_stage, uint32_t copy_slice, uint32_t copy_stage, auto sum, int set) __attribute__((always_inline)) {
+      constexpr int kSum = (int)decltype(sum)::value;
       const int64_t sl = min(copy_slice, mine - 1u);   // (past the end: the last slice again, unused)
       const float* const ca = pa + sl * step_a;
       const float* const cb = pb + sl * step_b;
@@ -336,6 +372,7 @@ __global__ __launch_bounds__(kGemmThreads * KS, BM == 64 ? 2 : 1) void lt_gemm_k
               else DB::copy_part(cb, b_off, it - DA::kInstr, at + DA::kBytes, wave_u);
             }
         }
+        if (kSum > 0 && s == BK / 2 - 2) add_frags(cur, sum, set);
         __builtin_amdgcn_sched_barrier(0);
       }
     };
@@ -344,7 +381,7 @@ __global__ __launch_bounds__(kGemmThreads * KS, BM == 64 ? 2 : 1) void lt_gemm_k
     landed_and_read<2 * kPer>();                                                     \
     __syncthreads();                                                                 \
     __builtin_amdgcn_sched_barrier(0);                                               \
-    slice(CUR, NEXT, ((J) + 1) & 3, i + (J) + 4u, (J) & 3);                          \
+    slice(CUR, NEXT, ((J) + 1) & 3, i + (J) + 4u, (J) & 3, sum, (J));                \
   }
 // the last ones: a half may have nothing left to multiply
 #define LT_LAST(J, CUR, NEXT)                      \
@@ -357,6 +394,7 @@ __global__ __launch_bounds__(kGemmThreads * KS, BM == 64 ? 2 : 1) void lt_gemm_k
         read_b(NEXT, ((J) + 1) & 3, g);            \
       }                                            \
       _Pragma("unroll") for (int s = 0; s < BK / 2; ++s) mma(CUR, s / 4, s % 4); \
+      if (kSum > 0) add_frags(CUR, sum, J);        \
     }                                              \
   }
     LT_COPY(0, 0);
@@ -365,25 +403,32 @@ __global__ __launch_bounds__(kGemmThreads * KS, BM == 64 ? 2 : 1) void lt_gemm_k
     LT_COPY(3, 3);
     landed<3 * kPer>();
     __syncthreads();
-    Frags f0, f1;
-#pragma unroll
-    for (int g = 0; g < BK / 8; ++g) {
-      read_a(f0, 0, g);
-      read_b(f0, 0, g);
-    }
-    uint32_t i = 0;
-    for (; i + 4u <= both; i += 4u) {
-      LT_SLICE(0, f0, f1);
-      LT_SLICE(1, f1, f0);
-      LT_SLICE(2, f0, f1);
-      LT_SLICE(3, f1, f0);
-    }
-    if (i < n) {   // (everything has been copied by now)
-      LT_LAST(0, f0, f1);
-      LT_LAST(1, f1, f0);
-      LT_LAST(2, f0, f1);
-      if (KS > 1 && i + 3u < n) LT_LAST(3, f1, f0);   // (the first half's odd one)
-    }
+    // (every version has the same barriers)
+    auto pipeline = [&](auto sum) __attribute__((always_inline)) {
+      constexpr int kSum = (int)decltype(sum)::value;
+      Frags f0, f1;
+  #pragma unroll
+      for (int g = 0; g < BK / 8; ++g) {
+        read_a(f0, 0, g);
+        read_b(f0, 0, g);
+      }
+      uint32_t i = 0;
+      for (; i + 4u <= both; i += 4u) {
+        LT_SLICE(0, f0, f1);
+        LT_SLICE(1, f1, f0);
+        LT_SLICE(2, f0, f1);
+        LT_SLICE(3, f1, f0);
+      }
+      if (i < n) {   // (everything has been copied by now)
+        LT_LAST(0, f0, f1);
+        LT_LAST(1, f1, f0);
+        LT_LAST(2, f0, f1);
+        if (KS > 1 && i + 3u < n) LT_LAST(3, f1, f0);   // (the first half's odd one)
+      }
+    };
+    if (!CS || !summing) pipeline(Num<0>());
+    else if (wave_m == 0u) pipeline(Num<1>());
+    else pipeline(Num<2>());
     landed<0>();   // nothing may still be on its way into LDS when it is used again
 #undef LT_LAST
 #undef LT_SLICE
@@ -402,7 +447,10 @@ __global__ __launch_bounds__(kGemmThreads * KS, BM == 64 ? 2 : 1) void lt_gemm_k
       fetch_unaligned<BM>(ga, pa + nx * step_a, a_off);
       fetch_unaligned<BN>(gb, pb + nx * step_b, b_off);
       __syncthreads();
-      if (multiply) mma_slice<BM, BN, MB, NB, AKC, BKC, NCH>(accs, As(j & 1u), Bs(j & 1u), wave_m, wave_n, lane);
+      if (multiply) {
+        mma_slice<BM, BN, MB, NB, AKC, BKC, NCH>(accs, As(j & 1u), Bs(j & 1u), wave_m, wave_n, lane);
+        if (summing) add_columns(Bs(j & 1u));
+      }
     };
 #pragma unroll 1
     for (uint32_t j = 0; j < both; ++j) step(j, true);
@@ -421,7 +469,10 @@ __global__ __launch_bounds__(kGemmThreads * KS, BM == 64 ? 2 : 1) void lt_gemm_k
       stash_tile<BN, BKC>(gb, Bs(0));
     }
     __syncthreads();
-    if (half == 0u) mma_slice<BM, BN, MB, NB, AKC, BKC, NCH>(accs, As(0), Bs(0), wave_m, wave_n, lane);
+    if (half == 0u) {
+      mma_slice<BM, BN, MB, NB, AKC, BKC, NCH>(accs, As(0), Bs(0), wave_m, wave_n, lane);
+      if (summing) add_columns(Bs(0));
+    }
   }
   v16f (&acc)[MB][NB] = accs[0];
   if (NCH > 1) {
@@ -432,9 +483,19 @@ __global__ __launch_bounds__(kGemmThreads * KS, BM == 64 ? 2 : 1) void lt_gemm_k
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[i][j][r] += accs[NCH - 1][i][j][r];
   }
+  if (summing) {
+    // (read behind the epilogue's barriers)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      float t = (csum[0][j] + csum[1][j]) + (csum[2][j] + csum[3][j]);
+      t += __shfl_xor(t, 32);
+      if (lane < 32u) col_lds[(half * 2u + wave_m) * BN + wave_n * (BN / 2) + j * 32u + lane] = t;
+    }
+  }
   // split-K: this workgroup's partial product goes to its own fp32 copy of the output, row major
   float* const raw = a.split_ws ? a.split_ws + (size_t)split * ((size_t)a.batch0 * a.batch1 * a.m * a.n) : nullptr;
   epilogue<false, BM, BN, MB, NB, KS, kHalf>(a, acc, (float*)smem_all, tile_m, tile_n, wave_m, wave_n, lane, batch, raw);
+  if (summing) finish_columns<BN, 2 * KS>(a, col_lds, tile_n, split);
   args_touched(touched);
 }
 
@@ -964,12 +1025,19 @@ static hipError_t launch_small(const GemmArgs& args, hipStream_t s) {
 
 template <typename T, int BM, int BN, bool AL, int KS>
 static void launch_variant(const GemmArgs& a, const dim3 grid, hipStream_t s) {
+  const dim3 block(kGemmThreads * KS);
   const bool akc = a.a.s_col == 1, bkc = a.b.s_row == 1;
-  if (akc && bkc) LT_LAUNCH((lt_gemm_kernel<T, BM, BN, true, true, AL, KS>), grid, dim3(kGemmThreads * KS), s, a);
-  else if (akc) LT_LAUNCH((lt_gemm_kernel<T, BM, BN, true, false, AL, KS>), grid, dim3(kGemmThreads * KS), s, a);
-  else if (bkc) LT_LAUNCH((lt_gemm_kernel<T, BM, BN, false, true, AL, KS>), grid, dim3(kGemmThreads * KS), s, a);
-  else LT_LAUNCH((lt_gemm_kernel<T, BM, BN, false, false, AL, KS>), grid, dim3(kGemmThreads * KS), s, a);
   char name[64];
+  if (a.col_sum) {
+    LT_LAUNCH((lt_gemm_kernel<T, BM, BN, false, false, AL, KS, true>), grid, block, s, a);
+    snprintf(name, sizeof(name), "lt_gemm_kernel<float,%d,%d,sums,%s,%d>", BM, BN, AL ? "true" : "false", KS);
+    note_kernel(name);
+    return;
+  }
+  if (akc && bkc) LT_LAUNCH((lt_gemm_kernel<T, BM, BN, true, true, AL, KS, false>), grid, block, s, a);
+  else if (akc) LT_LAUNCH((lt_gemm_kernel<T, BM, BN, true, false, AL, KS, false>), grid, block, s, a);
+  else if (bkc) LT_LAUNCH((lt_gemm_kernel<T, BM, BN, false, true, AL, KS, false>), grid, block, s, a);
+  else LT_LAUNCH((lt_gemm_kernel<T, BM, BN, false, false, AL, KS, false>), grid, block, s, a);
   snprintf(name, sizeof(name), "lt_gemm_kernel<float,%d,%d,%s,%s,%s,%d>", BM, BN, akc ? "true" : "false", bkc ? "true" : "false", AL ? "true" : "false", KS);
   note_kernel(name);
 }
@@ -981,6 +1049,7 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
   const uint32_t batch = a.batch0 * a.batch1;
   if (a.direct) return launch_small(a, s);
   if (a.tile_m != a.tile_n || (a.tile_m != 64u && a.tile_m != 128u)) return hipErrorInvalidValue;
+  if (a.col_sum && !columns_ride(a, batch)) return hipErrorInvalidValue;
   const bool big = a.tile_m == 128u;   // the host picks big tiles only when they still give every compute unit work
   const uint32_t bm = a.tile_m;
   if (a.halves != 1u && (a.halves != 2u || big)) return hipErrorInvalidValue;

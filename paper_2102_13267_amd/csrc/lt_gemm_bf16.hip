@@ -65,6 +65,10 @@ template <int BX> struct Geo {
   static constexpr int kBytes = BX * kStrideKC;        // >= 32 * kStrideXC
 };
 
+template <uint32_t N> struct Num {
+  static constexpr uint32_t value = N;
+};
+
 template <int N> struct Chunks {
   uint4 g[N];
 };
@@ -255,11 +259,17 @@ template <int BM, int BN> struct Smem {
 // that the other one takes costs registers in the main loop.
 // KS: halves of the workgroup that share its k (GemmArgs::halves); each has LDS stages of its own, and they
 // walk their slices side by side.
-template <int BM, int BN, bool AKC, bool BKC, bool AL, int KS>
+// CS: column sums of B ride along (GemmArgs::col_sum; AKC and BKC false).  The workgroups of the first tile row take them
+// from the B fragments that they multiply anyway: each of a wave row's two k16 steps of a slice by one of the two
+// wave rows, a dot product with ones per register, eight next to a wave's eight MFMAs.  A slice's sum starts afresh and joins
+// one of two running sums, so that no chain is long.
+template <int BM, int BN, bool AKC, bool BKC, bool AL, int KS, bool CS>
 __global__ __launch_bounds__(kGemmThreads * KS, 2) void lt_gemm_bf16_kernel(const GemmArgs a) {
+  static_assert(!CS || (!AKC && !BKC && BM == 128), "a weight gradient");
   constexpr int MB = BM / 64, NB = BN / 64;   // 32 x 32 blocks per wave: rows, columns
   constexpr size_t kHalf = Smem<BM, BN>::kBytes;
   __shared__ __attribute__((aligned(16))) char smem_all[KS * kHalf];
+  __shared__ __attribute__((aligned(16))) float col_lds[CS ? KS * 2 * BN : 4];   // [half][wave row][column]
   const uint32_t touched = touch_args<GemmArgs>();   // (0.4 to 1 us of a launch of 7 to 20)
   const uint32_t half = KS > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / kGemmThreads) : 0u;
   char* const smem = smem_all + half * kHalf;
@@ -323,6 +333,29 @@ __global__ __launch_bounds__(kGemmThreads * KS, 2) void lt_gemm_bf16_kernel(cons
       for (int i = 0; i < MB; ++i)
 #pragma unroll
         for (int j = 0; j < NB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[kk][i], f.b[kk][j], acc[i][j], 0, 0, 0);
+  };
+  const bool summing = CS && tile_m == 0u;
+  float csum[2][NB];
+#pragma unroll
+  for (int j = 0; j < NB; ++j) csum[0][j] = csum[1][j] = 0.0f;
+  // the sums of the B fragments of k16 step kk
+  auto add_columns = [&](const Frags& f, int kk, int set) {
+    typedef __bf16 V2 __attribute__((ext_vector_type(2)));
+    const V2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      float t = 0.0f;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) t = __builtin_amdgcn_fdot2_f32_bf16(V2{f.b[kk][j][2 * q], f.b[kk][j][2 * q + 1]}, ones, t, false);
+      csum[set][j] += t;
+    }
+  };
+  auto mma_and_sum = [&](const Frags& f) {
+    mma(f);
+    if (summing) {
+      if (wave_m == 0u) add_columns(f, 0, 0);
+      else add_columns(f, 1, 0);
+    }
   };
   // Whole slices of k are fetched in 16-byte chunks with no checks; what is left of k goes through
   // fetch_checked as one last slice.  A tile that hangs over the operand's edge is filled with copies
@@ -396,7 +429,7 @@ __global__ __launch_bounds__(kGemmThreads * KS, 2) void lt_gemm_bf16_kernel(cons
       __syncthreads();
       for (uint32_t j = 0; j < mine; ++j) {
         const Frags f = j == 0u ? dense_frags(0) : j == 1u ? dense_frags(1) : dense_frags(2);
-        mma(f);
+        mma_and_sum(f);
       }
     } else {
     // Four slices per trip: stage numbers and the two fragment sets are compile-time.
@@ -425,6 +458,9 @@ __global__ __launch_bounds__(kGemmThreads * KS, 2) void lt_gemm_bf16_kernel(cons
       landed<3 * kPer>();   // slice 0
     }
     __syncthreads();
+    // (SUM: the k16 step, plus one, of which this wave adds up the columns; every version has the same barriers)
+    auto pipeline = [&](auto sum) __attribute__((always_inline)) {
+    constexpr int kSum = (int)decltype(sum)::value;
     Frags f0 = dense_frags(0), f1;
 #define LT_SLICE(J, CUR, NEXT, GUARD)                                            \
   {                                                                            \
@@ -440,7 +476,10 @@ __global__ __launch_bounds__(kGemmThreads * KS, 2) void lt_gemm_bf16_kernel(cons
       LT_COPY(i + (J) + 4u, (J) & 3);                                          \
     }                                                                          \
     NEXT = dense_frags(((J) + 1) & 3);                                         \
-    if (!(GUARD) || i + (J) < mine) mma(CUR);                                  \
+    if (!(GUARD) || i + (J) < mine) {                                          \
+      mma(CUR);                                                                \
+      if (kSum > 0) add_columns(CUR, kSum - 1, (J) & 1);                       \
+    }                                                                          \
   }
     uint32_t i = 0;
     for (; i + 4u <= both; i += 4u) {   // straight-line code: copies, LDS reads and MFMAs interleave
@@ -455,6 +494,10 @@ __global__ __launch_bounds__(kGemmThreads * KS, 2) void lt_gemm_bf16_kernel(cons
       LT_SLICE(2, f0, f1, true);
       if (KS > 1 && i + 3u < n) LT_SLICE(3, f1, f0, true);   // (the first half's odd one)
     }
+    };
+    if (!CS || !summing) pipeline(Num<0>());
+    else if (wave_m == 0u) pipeline(Num<1>());
+    else pipeline(Num<2>());
     landed<0>();   // nothing may still be on its way into LDS when it is used again
     }
 #undef LT_SLICE
@@ -487,7 +530,7 @@ __global__ __launch_bounds__(kGemmThreads * KS, 2) void lt_gemm_bf16_kernel(cons
       ca = fetch_unaligned<BM, AKC>(pa + nx * step_a, a_off);
       cb = fetch_unaligned<BN, BKC>(pb + nx * step_b, b_off);
       __syncthreads();
-      if (multiply) mma(load_frags(j & 1u));
+      if (multiply) mma_and_sum(load_frags(j & 1u));
     };
 #pragma unroll 1
     for (uint32_t j = 0; j < both; ++j) step(j, true);
@@ -509,13 +552,23 @@ __global__ __launch_bounds__(kGemmThreads * KS, 2) void lt_gemm_bf16_kernel(cons
         stash<BN, BKC>(cb, smem + Geo<BM>::kBytes);
       }
       __syncthreads();
-      if (half == 0u) mma(load_frags(0));
+      if (half == 0u) mma_and_sum(load_frags(0));
     }
   }
 
+  if (summing) {
+    // (read behind the epilogue's barriers)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      float t = csum[0][j] + csum[1][j];
+      t += __shfl_xor(t, 32);
+      if (lane < 32u) col_lds[(half * 2u + wave_m) * BN + wave_n * (BN / 2) + j * 32u + lane] = t;
+    }
+  }
   // split-K: this workgroup's partial product goes to its own fp32 copy of the output, row major
   float* const raw = a.split_ws ? a.split_ws + (size_t)split * ((size_t)a.batch0 * a.batch1 * a.m * a.n) : nullptr;
   epilogue<true, BM, BN, MB, NB, KS, kHalf>(a, acc, (float*)smem_all, tile_m, tile_n, wave_m, wave_n, lane, batch, raw);
+  if (summing) finish_columns<BN, 2 * KS>(a, col_lds, tile_n, split);
   args_touched(touched);
 }
 
@@ -523,11 +576,19 @@ template <int BM, int BN, bool AL, int KS>
 static void launch_layout(const GemmArgs& a, dim3 grid, hipStream_t s) {
   const dim3 block(kGemmThreads * KS);
   const bool akc = a.a.s_col == 1, bkc = a.b.s_row == 1;
-  if (akc && bkc) LT_LAUNCH((lt_gemm_bf16_kernel<BM, BN, true, true, AL, KS>), grid, block, s, a);
-  else if (akc) LT_LAUNCH((lt_gemm_bf16_kernel<BM, BN, true, false, AL, KS>), grid, block, s, a);
-  else if (bkc) LT_LAUNCH((lt_gemm_bf16_kernel<BM, BN, false, true, AL, KS>), grid, block, s, a);
-  else LT_LAUNCH((lt_gemm_bf16_kernel<BM, BN, false, false, AL, KS>), grid, block, s, a);
   char name[64];   // (no spaces: a launch record holds 47 characters, all but the last bracket)
+  if (a.col_sum) {
+    if constexpr (BN == 128) {
+      LT_LAUNCH((lt_gemm_bf16_kernel<BM, BN, false, false, AL, KS, true>), grid, block, s, a);
+      snprintf(name, sizeof(name), "lt_gemm_bf16_kernel<%d,%d,sums,%s,%d>", BM, BN, AL ? "true" : "false", KS);
+      note_kernel(name);
+    }
+    return;
+  }
+  if (akc && bkc) LT_LAUNCH((lt_gemm_bf16_kernel<BM, BN, true, true, AL, KS, false>), grid, block, s, a);
+  else if (akc) LT_LAUNCH((lt_gemm_bf16_kernel<BM, BN, true, false, AL, KS, false>), grid, block, s, a);
+  else if (bkc) LT_LAUNCH((lt_gemm_bf16_kernel<BM, BN, false, true, AL, KS, false>), grid, block, s, a);
+  else LT_LAUNCH((lt_gemm_bf16_kernel<BM, BN, false, false, AL, KS, false>), grid, block, s, a);
   snprintf(name, sizeof(name), "lt_gemm_bf16_kernel<%d,%d,%s,%s,%s,%d>", BM, BN, akc ? "true" : "false", bkc ? "true" : "false", AL ? "true" : "false", KS);
   note_kernel(name);
 }
@@ -562,6 +623,7 @@ hipError_t launch_gemm_bf16(const GemmArgs& a, hipStream_t s) {
   if (a.halves != 1u && a.halves != 2u) return hipErrorInvalidValue;
   if (a.tile_m != 128u || (a.tile_n != 128u && a.tile_n != 64u)) return hipErrorInvalidValue;
   if (a.tiles_m != (a.m + a.tile_m - 1) / a.tile_m || a.tiles_n != (a.n + a.tile_n - 1) / a.tile_n) return hipErrorInvalidValue;
+  if (a.col_sum && !(a.tile_n == 128u && columns_ride(a, batch))) return hipErrorInvalidValue;
   const dim3 grid(tiles, batch * a.splits);
   if (a.tile_n == 64u) bf::launch_tile<128, 64>(a, grid, s);
   else bf::launch_tile<128, 128>(a, grid, s);

@@ -277,5 +277,42 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, const v16f (&acc)[MB
   }
 }
 
+// ---- column sums that ride along ---------------------------------------------------------------
+// What the workgroups of the first tile row do with the column sums that their waves have left in LDS ([PARTS][BN], added up in
+// this order): they go to col_parts, or the column program runs on them.  (Called by whole workgroups.)
+template <int BN, int PARTS>
+__device__ __forceinline__ void finish_columns(const GemmArgs& a, const float* lds, uint32_t tile_n, uint32_t split) {
+  const ProgRegs pr = load_prog_regs(a.col_post);
+  const uint32_t c = threadIdx.x * (uint32_t)kVec, col = tile_n + c;
+  if (c >= (uint32_t)BN || col >= a.n) return;
+  Quad q;
+#pragma unroll
+  for (int e = 0; e < kVec; ++e) q.v[e] = lds[c + (uint32_t)e];
+#pragma unroll
+  for (int w = 1; w < PARTS; ++w)
+#pragma unroll
+    for (int e = 0; e < kVec; ++e) q.v[e] += lds[(uint32_t)w * BN + c + (uint32_t)e];
+  if (a.col_parts) {
+    *(float4*)(a.col_parts + (size_t)split * a.n + col) = make_float4(q.v[0], q.v[1], q.v[2], q.v[3]);
+    return;
+  }
+  if (a.col_red == kRedMean) {
+#pragma unroll
+    for (int e = 0; e < kVec; ++e) q.v[e] = q.v[e] / (float)a.k;
+  }
+  const EwProg& p = a.col_post;
+  const uint32_t nv = a.n - col >= (uint32_t)kVec ? (uint32_t)kVec : a.n - col;
+  RF<16> f = load_inputs<16, kMaxIn, false, false>(rf_zero<16>(), p, 0, col, nv);
+  f = rf_set<16>(f, p.anchor_slot, q);
+  f = interp<16>(f, pr, p.n_code);
+  store_outputs<16, false, false>(f, p, 0, col, nv);
+}
+
+// Can they (launchers)?
+inline bool columns_ride(const GemmArgs& a, uint32_t batch) {
+  return batch == 1u && a.a.s_row == 1 && a.a.s_col != 1 && a.b.s_col == 1 && a.b.s_row != 1 &&
+         (a.col_parts ? a.n % 4u == 0u : a.splits == 1u && a.col_post.n_slots <= 16u);
+}
+
 }  // namespace ltk
 #endif  // LT_GEMM_EPILOGUE_H_

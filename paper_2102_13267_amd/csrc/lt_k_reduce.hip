@@ -778,7 +778,7 @@ hipError_t launch_col_reduce(const ColArgs& args, uint32_t grid_x, uint32_t grid
   const dim3 g(grid_x, grid_y), b(kColBlock);
   ColArgs a = args;
   if (a.parts) {
-    if ((a.cols % 4u) != 0u || a.parts_rows == 0u || !a.norm_grad || (a.red != kRedSum && (a.red != kRedMean || a.sum2))) return hipErrorInvalidValue;
+    if ((a.cols % 4u) != 0u || a.parts_rows == 0u || (!a.norm_grad && a.sum2) || (a.red != kRedSum && (a.red != kRedMean || a.sum2))) return hipErrorInvalidValue;
     LT_LAUNCH(lt_col_finish_kernel, dim3((a.cols + 15u) / 16u, 1u + a.sum2), dim3(kBlock), s, a);
     return hipGetLastError();
   }

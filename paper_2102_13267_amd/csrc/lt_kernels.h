@@ -144,8 +144,9 @@ struct ColArgs {
   // their partials follow the others', post2 runs on them
   uint32_t sum2;
   EwProg post2;        // iteration space [cols]
-  // Not null: the launch that computed the norm's gradient has left `parts_rows` partial sums of every column here (rows
-  // of [1 + sum2][cols] floats: the weight gradient's, then the bias gradient's), and this one only adds them up.
+  // Not null: the launch that computed the norm's gradient, or a contraction that reads the summed tensor, has left
+  // `parts_rows` partial sums of every column here (rows of [1 + sum2][cols] floats: a norm's weight gradient's, then its
+  // bias gradient's), and this one only adds them up.
   const float* parts;
   uint32_t parts_rows, pad;
 };
@@ -235,7 +236,11 @@ struct GemmArgs {
   // contiguous) along: a weight gradient x^T dy and the bias gradient sum_rows(dy) read the same
   // dy.  col_sum = 1: the workgroups of the first tile row add up the columns of B they fetch
   // anyway (col_red: kRedSum or kRedMean) and run col_post on them, iteration space [n].
+  // The LDS-staged kernels do so too where A is [k, m] and B [k, n], rows contiguous, in an unbatched product (bf16: tiles of 128
+  // columns).  With col_parts set (k splits; n a multiple of four) each split leaves its sums there, [splits][n], for
+  // ColArgs::parts, and col_post is not used.
   uint32_t col_sum, col_red;
+  float* col_parts;
   EwProg col_post;
 };
 
