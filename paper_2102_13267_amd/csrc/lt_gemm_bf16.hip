@@ -247,6 +247,33 @@ __device__ __forceinline__ v8bf fragment_dense(const char* tile, uint32_t x_blk,
   }
 }
 
+// ---- slabs: whole tiles of a workgroup in halves ----------------------------------------------------
+// The halves of a workgroup walk its k together, slabs of 64 that all eight waves copy: the first half multiplies
+// the first 32 k of each, the other one the rest.  A row of an [x][k] slab is then a whole cache line, four slabs fit in LDS and
+// copies go out three slabs ahead.  (With stages of their own, contiguous shares of k and pairs of half lines, two slices
+// ahead, the halves waited: 4096 x 1024 x 4096 with k contiguous kept the matrix cores 48 % busy; its loop 35 -> 28.7 us, the
+// launch 45.4 -> 39.8.  With both operands across k, whose stages were four slices deep already, nothing changes: 28.7.)
+//   [x][k] slab: rows of 128 bytes, chunk c of row x at position c ^ ((x >> 1) & 7);  [k][x] slab: as above, 64 rows.
+template <int BX, bool KC> struct Slab {
+  static constexpr uint32_t kBytes = BX * 128, kInstr = BX / 64, kPerRow = KC ? 8 : BX / 8;   // (wave instructions: 8 waves x 1 KiB each)
+  __device__ static __forceinline__ uint32_t swz(uint32_t row) { return KC ? (row >> 1) & 7u : Dense<BX, false>::swz_k(row); }
+  // byte offset of this lane's chunk for wave instruction `it`; *second: how far to go back if it lies in the second half of k
+  // and the slab has only the first
+  __device__ static __forceinline__ uint32_t lane_offset(uint32_t it, int64_t s_x, int64_t s_k, uint32_t left, uint32_t* second) {
+    const uint32_t e = it * 2u * (uint32_t)kGemmThreads + threadIdx.x, row = e / kPerRow, c = (e % kPerRow) ^ swz(row);
+    *second = KC ? (c >= 4u ? 64u : 0u) : (row >= 32u ? (uint32_t)(64 * s_k) : 0u);
+    return (uint32_t)(2 * chunk_offset<BX, KC>(row, c * 8u, s_x, s_k, left));
+  }
+  // the fragment of a 32-row (or 32-column) block, k16 step kk of the given half
+  __device__ static __forceinline__ v8bf fragment(const char* slab, uint32_t half, uint32_t x_blk, uint32_t kk, uint32_t lane) {
+    if (KC) {
+      const uint32_t row = x_blk + (lane & 31u), c = half * 4u + kk * 2u + (lane >> 5);
+      return *(const v8bf*)(slab + row * 128u + ((c ^ swz(row)) << 4));
+    }
+    return fragment_dense<BX, false>(slab + half * (BX * 64u), x_blk, kk, lane);   // (32 rows on: the same swizzle)
+  }
+};
+
 template <int BM, int BN> struct Smem {
   static constexpr size_t kStage = Geo<BM>::kBytes + Geo<BN>::kBytes;
   static constexpr size_t kStripBytes = (size_t)BM * (BN + kCPad) * sizeof(float);   // the whole tile
@@ -257,8 +284,8 @@ template <int BM, int BN> struct Smem {
 
 // AL: both operands' rows are 16-byte aligned (the launcher looks).  Two instances, because the path
 // that the other one takes costs registers in the main loop.
-// KS: halves of the workgroup that share its k (GemmArgs::halves); each has LDS stages of its own, and they
-// walk their slices side by side.
+// KS: halves of the workgroup that share its k (GemmArgs::halves): slabs, above; unaligned rows: each has LDS stages
+// and a contiguous share of its own.
 // CS: column sums of B ride along (GemmArgs::col_sum; AKC and BKC false).  The workgroups of the first tile row take them
 // from the B fragments that they multiply anyway: each of a wave row's two k16 steps of a slice by one of the two
 // wave rows, a dot product with ones per register, eight next to a wave's eight MFMAs.  A slice's sum starts afresh and joins
@@ -373,11 +400,94 @@ __global__ __launch_bounds__(kGemmThreads * KS, 2) void lt_gemm_bf16_kernel(cons
   if (KS > 1 && n < 2u) n = 0u;
   const uint32_t both = KS > 1 ? n / 2u : n, k_rest = k_begin + n * BK;   // steps in which every half multiplies
   if (KS > 1) n -= both;
-  const uint32_t mine = half == 0u ? n : both, k_first = k_begin + half * n * BK;
+  const uint32_t mine = half == 0u ? n : both, k_first = KS > 1 && AL ? k_begin : k_begin + half * n * BK;   // (AL: in slabs, below)
   const uint16_t* const pa = A + (int64_t)tile_m * a.a.s_row + (int64_t)k_first * a.a.s_col;
   const uint16_t* const pb = B + (int64_t)tile_n * a.b.s_col + (int64_t)k_first * a.b.s_row;
   const int64_t step_a = BK * a.a.s_col, step_b = BK * a.b.s_row;   // elements per slice of k
-  if (AL && n > 0u) {
+  if constexpr (AL && KS == 2) {
+    if (n > 0u) {
+      // Slabs 0 .. n-1, four stages: the MFMAs of slab j run from fragment registers, the fragments of slab j + 1 are read
+      // from its stage, later ones are on their way.  Behind the barrier of slab j slab j + 1 has landed for every wave, and every
+      // wave's reads of slab j's stage, which is copied into next, have returned.  (Copies past the end: the last slab again, unused.)
+      typedef Slab<BM, AKC> SA;
+      typedef Slab<BN, BKC> SB;
+      constexpr uint32_t kStageBytes = SA::kBytes + SB::kBytes, kPer = SA::kInstr + SB::kInstr;
+      static_assert(4 * kStageBytes <= KS * kHalf, "four slabs fit the tile's LDS");
+      const uint32_t wave8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+      const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem_all;
+      const bool odd = both < n;
+      uint32_t a_off[SA::kInstr], a_back[SA::kInstr], b_off[SB::kInstr], b_back[SB::kInstr];
+#pragma unroll
+      for (uint32_t it = 0; it < SA::kInstr; ++it) a_off[it] = SA::lane_offset(it, a.a.s_row, a.a.s_col, left_m, &a_back[it]);
+#pragma unroll
+      for (uint32_t it = 0; it < SB::kInstr; ++it) b_off[it] = SB::lane_offset(it, a.b.s_col, a.b.s_row, left_n, &b_back[it]);
+      auto copy = [&](uint32_t slab, uint32_t stage) __attribute__((always_inline)) {
+        const uint32_t sl = min(slab, n - 1u), cut = odd && sl == n - 1u ? ~0u : 0u;   // (the last one may have only its first half)
+        const uint16_t* const ca = pa + (int64_t)sl * (2 * step_a);
+        const uint16_t* const cb = pb + (int64_t)sl * (2 * step_b);
+        const uint32_t at = lds0 + stage * kStageBytes;
+#pragma unroll
+        for (uint32_t it = 0; it < SA::kInstr; ++it) copy_1k(ca, a_off[it] - (a_back[it] & cut), at + (it * 2u * (uint32_t)kGemmThreads + wave8 * 64u) * 16u);
+#pragma unroll
+        for (uint32_t it = 0; it < SB::kInstr; ++it)
+          copy_1k(cb, b_off[it] - (b_back[it] & cut), at + SA::kBytes + (it * 2u * (uint32_t)kGemmThreads + wave8 * 64u) * 16u);
+      };
+      auto frags = [&](uint32_t stage) {
+        const char* As = smem_all + stage * kStageBytes;
+        const char* Bs = As + SA::kBytes;
+        Frags f;
+#pragma unroll
+        for (uint32_t kk = 0; kk < BK / 16; ++kk) {
+#pragma unroll
+          for (int i = 0; i < MB; ++i) f.a[kk][i] = SA::fragment(As, half, wave_m * (BM / 2) + i * 32u, kk, lane);
+#pragma unroll
+          for (int j = 0; j < NB; ++j) f.b[kk][j] = SB::fragment(Bs, half, wave_n * (BN / 2) + j * 32u, kk, lane);
+        }
+        return f;
+      };
+      copy(0, 0);
+      copy(1, 1);
+      copy(2, 2);
+      copy(3, 3);
+      landed<3 * kPer>();
+      __syncthreads();
+      // (sum: the k16 step, plus one, of which this wave adds up the columns; every version has the same barriers)
+      auto pipeline = [&](auto sum) __attribute__((always_inline)) {
+        constexpr int kSum = (int)decltype(sum)::value;
+        Frags f0 = frags(0), f1;
+#define LT_SLAB(J, CUR, NEXT, GUARD)                           \
+  {                                                            \
+    landed_and_read<2 * kPer>();                               \
+    __syncthreads();                                           \
+    copy(i + (J) + 4u, (J) & 3);                               \
+    NEXT = frags(((J) + 1) & 3);                               \
+    if (!(GUARD) || i + (J) < mine) {                          \
+      mma(CUR);                                                \
+      if (kSum > 0) add_columns(CUR, kSum - 1, (J) & 1);       \
+    }                                                          \
+  }
+        uint32_t i = 0;
+        for (; i + 4u <= both; i += 4u) {
+          LT_SLAB(0, f0, f1, false);
+          LT_SLAB(1, f1, f0, false);
+          LT_SLAB(2, f0, f1, false);
+          LT_SLAB(3, f1, f0, false);
+        }
+        if (i < n) {
+          LT_SLAB(0, f0, f1, true);
+          LT_SLAB(1, f1, f0, true);
+          LT_SLAB(2, f0, f1, true);
+          if (i + 3u < n) LT_SLAB(3, f1, f0, true);   // (the first half's odd one)
+        }
+#undef LT_SLAB
+      };
+      if (!CS || !summing) pipeline(Num<0>());
+      else if (wave_m == 0u) pipeline(Num<1>());
+      else pipeline(Num<2>());
+      landed<0>();   // nothing may still be on its way into LDS when it is used again
+    }
+  }
+  if (AL && KS == 1 && n > 0u) {
     // Software pipeline over slices j = 0 .. n-1, four LDS stages: the MFMAs of slice j run from
     // fragment registers, the fragments of slice j+1 are read from the stage that holds it, and
     // later slices are on their way from global memory straight into their stages -- no
@@ -482,17 +592,16 @@ __global__ __launch_bounds__(kGemmThreads * KS, 2) void lt_gemm_bf16_kernel(cons
     }                                                                          \
   }
     uint32_t i = 0;
-    for (; i + 4u <= both; i += 4u) {   // straight-line code: copies, LDS reads and MFMAs interleave
+    for (; i + 4u <= n; i += 4u) {   // straight-line code: copies, LDS reads and MFMAs interleave
       LT_SLICE(0, f0, f1, false);
       LT_SLICE(1, f1, f0, false);
       LT_SLICE(2, f0, f1, false);
       LT_SLICE(3, f1, f0, false);
     }
-    if (i < n) {                     // one to three steps left, or four
+    if (i < n) {                     // one to three left
       LT_SLICE(0, f0, f1, true);
       LT_SLICE(1, f1, f0, true);
       LT_SLICE(2, f0, f1, true);
-      if (KS > 1 && i + 3u < n) LT_SLICE(3, f1, f0, true);   // (the first half's odd one)
     }
     };
     if (!CS || !summing) pipeline(Num<0>());
