@@ -575,10 +575,10 @@ __device__ __forceinline__ float4 sum_parts(const float* parts, uint32_t stride,
   return sum_parts_of<kMaxShare>(parts, stride, splits);
 }
 
-template <bool V>
-__device__ __forceinline__ void small_fetch(float (&v)[kSmallG][4], const float* base, int64_t s_k, uint32_t k0, uint32_t k_end) {
+template <bool V, int G>
+__device__ __forceinline__ void small_fetch(float (&v)[G][4], const float* base, int64_t s_k, uint32_t k0, uint32_t k_end) {
 #pragma unroll
-  for (int g = 0; g < kSmallG; ++g) {
+  for (int g = 0; g < G; ++g) {
     const uint32_t kg = k0 + (uint32_t)g * 8u;
     if (V) {   // k is contiguous and a multiple of 4: the four are valid together
       const bool ok = kg < k_end;
@@ -595,9 +595,10 @@ __device__ __forceinline__ void small_fetch(float (&v)[kSmallG][4], const float*
   }
 }
 
-__device__ __forceinline__ void small_mma(v16f& acc0, v16f& acc1, const float (&av)[kSmallG][4], const float (&bv)[kSmallG][4]) {
+template <int G>
+__device__ __forceinline__ void small_mma(v16f& acc0, v16f& acc1, const float (&av)[G][4], const float (&bv)[G][4]) {
 #pragma unroll
-  for (int g = 0; g < kSmallG; ++g) {
+  for (int g = 0; g < G; ++g) {
     acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(av[g][0], bv[g][0], acc0, 0, 0, 0);
     acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(av[g][1], bv[g][1], acc1, 0, 0, 0);
     acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(av[g][2], bv[g][2], acc0, 0, 0, 0);
@@ -605,11 +606,45 @@ __device__ __forceinline__ void small_mma(v16f& acc0, v16f& acc1, const float (&
   }
 }
 
-__device__ __forceinline__ float small_colsum(const float (&bv)[kSmallG][4]) {
+template <int G>
+__device__ __forceinline__ float small_colsum(const float (&bv)[G][4]) {
   float s = 0.0f;
 #pragma unroll
-  for (int g = 0; g < kSmallG; ++g) s += (bv[g][0] + bv[g][1]) + (bv[g][2] + bv[g][3]);
+  for (int g = 0; g < G; ++g) s += (bv[g][0] + bv[g][1]) + (bv[g][2] + bv[g][3]);
   return s;
+}
+
+// Programs whose inputs are fp32 and read in full, by column or as one value: an output whose rows are no whole vectors
+// (n = 10) still has its inputs asked for under the contraction, element by element.
+__device__ __forceinline__ bool single_elements(const EwProg& p) {
+  if (p.n_in > 2u || p.n_slots > 16u) return false;
+  bool ok = true;
+  for (uint32_t k = 0; k < p.n_in; ++k) ok = ok && p.in[k].dtype == kF32 && (p.in[k].mode == kFull || p.in[k].mode == kRowVec || p.in[k].mode == kScalar);
+  return ok;
+}
+// `i`: the quad's flat index in the output, `col` its column, n columns (what would be past the row's end: its last element again)
+template <int N>
+__device__ __forceinline__ void fetch_elements(Staged<N>& st, const EwProg& p, uint32_t i, uint32_t col, uint32_t n) {
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    if ((uint32_t)k < p.n_in) {
+      const EwIn& in = p.in[k];
+      const float* src = (const float*)in.ptr;
+#pragma unroll
+      for (uint32_t e = 0; e < (uint32_t)kVec; ++e) {
+        const uint32_t c = min(e, n - 1u - col);
+        st.vec[k][e] = src[in.mode == kFull ? i + c : in.mode == kRowVec ? col + c : 0u];
+      }
+    }
+  }
+}
+template <int NS, int N>
+__device__ __forceinline__ RF<NS> place_elements(RF<NS> f, const EwProg& p, const Staged<N>& st) {
+#pragma unroll
+  for (int k = 0; k < 2; ++k)
+#pragma unroll
+    for (int v = 0; v < kVec; ++v) f.e[v][k] = st.vec[k][v];
+  return f;
 }
 
 // TM x TN: blocks of 32 x 32 per workgroup tile (1 x 1, 2 x 1 or 2 x 2); the eight waves are NB =
@@ -620,11 +655,15 @@ __device__ __forceinline__ float small_colsum(const float (&bv)[kSmallG][4]) {
 template <int TM, int TN, bool AV, bool BV, bool CS>
 __device__ __forceinline__ void small_tile32(const GemmArgs& a) {
   constexpr uint32_t NB = TM * TN, KW = kSmallWaves / NB;      // blocks, k shares inside the workgroup
+  static_assert(!CS || NB == 1, "column sums ride with tiles of 32 x 32");
+  constexpr int G = NB == 1 ? 2 : kSmallG;                     // groups of 8 k in flight (and as many being multiplied)
   constexpr uint32_t kQuads = NB * 256u, QT = (kQuads + kSmallThreads - 1u) / kSmallThreads;   // quads of the tile, per thread
   __shared__ __attribute__((aligned(16))) float Cs[kSmallWaves * 32 * kSmallStride];
   __shared__ uint32_t is_last;
-  __shared__ float colp[CS ? kSmallThreads : 1], coltot[CS ? 32 * TN : 1];
+  __shared__ float colp[CS ? kSmallThreads : 1];
+  __shared__ __attribute__((aligned(16))) float coltot[CS ? 32 : 4];
   const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  constexpr uint32_t kColWave = kQuads / 64u % (uint32_t)kSmallWaves;
   const uint32_t block = wave % NB, kway = wave / NB, bm = block / TN, bn = block % TN;
   const SmallTile st = small_tile(a);
   const uint32_t tile = st.number, split = st.split, tile_m = st.row * (32u * TM), tile_n = st.col * (32u * TN), b0 = st.b0, b1 = st.b1;
@@ -647,7 +686,11 @@ __device__ __forceinline__ void small_tile32(const GemmArgs& a) {
   const ProgRegs pr = load_prog_regs(p);
   // column sums of B ride along in the first tile row (every column block exactly once)
   const bool cols_here = CS && tile_m == 0u;                    // (workgroup-uniform)
-  const bool cols_mine = cols_here && bm == 0u;                 // (wave-uniform)
+  // ... and the column program runs on a wave that has no quads of the tile
+  const bool col_wave = cols_here && wave == kColWave;
+  const uint32_t col_at = tile_n + (lane & 7u) * (uint32_t)kVec;   // (its first eight lanes)
+  const EwProg& cp = a.col_post;
+  const bool col_fast = CS && cp.fast && cp.full_vec_ok && cp.n_in <= 4u && cp.n_slots <= 8u && (a.n & 3u) == 0u;
   const ProgRegs cpr = CS ? load_prog_regs(a.col_post) : ProgRegs{0u, 0.0f};
   float csum = 0.0f;
   // (a tile over the edge: quads past it read the last row's or column's inputs and are not stored)
@@ -673,31 +716,39 @@ __device__ __forceinline__ void small_tile32(const GemmArgs& a) {
     }
   }
 #pragma clang diagnostic pop
+  // (an output whose rows are no whole vectors: the inputs element by element, but all at once and as early)
+  const bool loose = !fast && single_elements(p);
+  if (loose && has_quad) {
+#pragma unroll
+    for (uint32_t j = 0; j < QT; ++j)
+      fetch_elements(staged[j], p, qi[j] - qcol[j] + min(qcol[j], a.n - 1u) - (qrow[j] < a.m ? 0u : (uint32_t)((qrow[j] - (a.m - 1u)) * a.o_row)), min(qcol[j], a.n - 1u), a.n);
+  }
+  if (col_wave && col_fast) staged[0] = fetch_inputs_at<4, false, false>(cp, min(col_at, a.n - 4u), 0u, min(col_at, a.n - 4u));
   v16f acc0, acc1;
 #pragma unroll
   for (int r = 0; r < 16; ++r) acc0[r] = acc1[r] = 0.0f;
-  constexpr uint32_t kChunk = (uint32_t)kSmallG * 8u;
+  constexpr uint32_t kChunk = (uint32_t)G * 8u;
   const uint32_t nch = (k_end - k_begin + kChunk - 1u) / kChunk;   // (wave-uniform)
-  float a0[kSmallG][4], b0v[kSmallG][4], a1[kSmallG][4], b1v[kSmallG][4];
+  float a0[G][4], b0v[G][4], a1[G][4], b1v[G][4];
   const uint32_t kl = k_begin + 4u * h;   // this lane's first k
   if (nch > 0u) {
-    small_fetch<AV>(a0, ap, a.a.s_col, kl, k_end);
-    small_fetch<BV>(b0v, bp, a.b.s_row, kl, k_end);
+    small_fetch<AV, G>(a0, ap, a.a.s_col, kl, k_end);
+    small_fetch<BV, G>(b0v, bp, a.b.s_row, kl, k_end);
   }
   for (uint32_t c = 0; c < nch; c += 2u) {
     if (c + 1u < nch) {
-      small_fetch<AV>(a1, ap, a.a.s_col, kl + (c + 1u) * kChunk, k_end);
-      small_fetch<BV>(b1v, bp, a.b.s_row, kl + (c + 1u) * kChunk, k_end);
+      small_fetch<AV, G>(a1, ap, a.a.s_col, kl + (c + 1u) * kChunk, k_end);
+      small_fetch<BV, G>(b1v, bp, a.b.s_row, kl + (c + 1u) * kChunk, k_end);
     }
-    small_mma(acc0, acc1, a0, b0v);
-    if (cols_mine) csum += small_colsum(b0v);
+    small_mma<G>(acc0, acc1, a0, b0v);
+    if (cols_here) csum += small_colsum<G>(b0v);
     if (c + 2u < nch) {
-      small_fetch<AV>(a0, ap, a.a.s_col, kl + (c + 2u) * kChunk, k_end);
-      small_fetch<BV>(b0v, bp, a.b.s_row, kl + (c + 2u) * kChunk, k_end);
+      small_fetch<AV, G>(a0, ap, a.a.s_col, kl + (c + 2u) * kChunk, k_end);
+      small_fetch<BV, G>(b0v, bp, a.b.s_row, kl + (c + 2u) * kChunk, k_end);
     }
     if (c + 1u < nch) {
-      small_mma(acc0, acc1, a1, b1v);
-      if (cols_mine) csum += small_colsum(b1v);
+      small_mma<G>(acc0, acc1, a1, b1v);
+      if (cols_here) csum += small_colsum<G>(b1v);
     }
   }
   if (CS) colp[threadIdx.x] = csum;
@@ -717,33 +768,29 @@ __device__ __forceinline__ void small_tile32(const GemmArgs& a) {
       sum[j].x += t.x; sum[j].y += t.y; sum[j].z += t.z; sum[j].w += t.w;
     }
   }
-  if (cols_here) {
-    // column c of column block bn: the shares of k in order, lower half of the wave before the upper
-    // (deterministic); then the column program on quads of four columns
-    if (threadIdx.x < 32u * TN) {
-      const uint32_t cb = threadIdx.x >> 5, cx = threadIdx.x & 31u;
+  if (col_wave) {
+    // the shares of k in order, lower half of the wave before the upper (deterministic); then the column program on quads of
+    // four columns.  (One wave: its LDS accesses are in order.)
+    if (lane < 32u) {
       float t = 0.0f;
 #pragma unroll
       for (uint32_t w = 0; w < KW; ++w) {
-        const float* src = colp + (w * NB + cb) * 64u + cx;   // (wave = share * NB + block; block = bm * TN + bn with bm = 0)
-        t += src[0];
-        t += src[32];
+        t += colp[w * 64u + lane];
+        t += colp[w * 64u + 32u + lane];
       }
       if (a.col_red == kRedMean) t = t / (float)a.k;
-      coltot[threadIdx.x] = t;
+      coltot[lane] = t;
     }
-    __syncthreads();
-    const uint32_t cc = tile_n + threadIdx.x * (uint32_t)kVec;
-    if (threadIdx.x < 8u * TN && cc < a.n) {
-      const EwProg& cp = a.col_post;
-      const uint32_t nv = a.n - cc >= (uint32_t)kVec ? (uint32_t)kVec : a.n - cc;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    if (lane < 8u && col_at < a.n) {
+      const uint32_t nv = a.n - col_at >= (uint32_t)kVec ? (uint32_t)kVec : a.n - col_at;
       Quad q;
 #pragma unroll
-      for (int e = 0; e < kVec; ++e) q.v[e] = coltot[threadIdx.x * (uint32_t)kVec + (uint32_t)e];
-      RF<16> f = load_inputs<16, kMaxIn, false, false>(rf_zero<16>(), cp, 0, cc, nv);
+      for (int e = 0; e < kVec; ++e) q.v[e] = coltot[lane * (uint32_t)kVec + (uint32_t)e];
+      RF<16> f = col_fast ? place_inputs<16, 4, true, false, 0>(rf_zero<16>(), cp, staged[0], kVec) : load_inputs<16, kMaxIn, false, false>(rf_zero<16>(), cp, 0, col_at, nv);
       f = rf_set<16>(f, cp.anchor_slot, q);
       f = interp<16>(f, cpr, cp.n_code);
-      store_outputs<16, false, false>(f, cp, 0, cc, nv);
+      store_outputs<16, false, false>(f, cp, 0, col_at, nv);
     }
   }
   if (a.splits > 1u) {
@@ -781,7 +828,7 @@ __device__ __forceinline__ void small_tile32(const GemmArgs& a) {
       if (qrow[j] < a.m && qcol[j] < a.n) store_outputs<16, true, false, 0>(f, p, 0, qi[j], kVec);
     } else if (qrow[j] < a.m && qcol[j] < a.n) {
       const uint32_t nvalid = a.n - qcol[j] >= (uint32_t)kVec ? (uint32_t)kVec : a.n - qcol[j];
-      RF<16> f = load_inputs<16, kMaxIn, false, false>(rf_zero<16>(), p, 0, qi[j], nvalid);
+      RF<16> f = loose ? place_elements(rf_zero<16>(), p, staged[j]) : load_inputs<16, kMaxIn, false, false>(rf_zero<16>(), p, 0, qi[j], nvalid);
       f = rf_set<16>(f, p.anchor_slot, anchor);
       f = interp<16>(f, pr, n_code);
       store_outputs<16, false, false>(f, p, 0, qi[j], nvalid);
