@@ -21,6 +21,8 @@ typedef const char* (*lt_last_error_fn)(void* ctx);
 typedef int (*lt_assign_fn)(void* ctx, uint64_t dst, uint64_t src);
 typedef int (*lt_release_many_fn)(void* ctx, const uint64_t* ids, size_t n);
 typedef int (*lt_barrier_fn)(void* ctx, int blocking, void* info);
+typedef int (*lt_shape_fn)(void* ctx, uint64_t t, int* dtype, int* rank, int64_t* dims);
+typedef int (*lt_device_ptr_fn)(void* ctx, uint64_t t, void** dptr);
 
 static lt_op_fn p_op;
 static lt_scalar_fn p_scalar;
@@ -29,13 +31,18 @@ static lt_last_error_fn p_last_error;
 static lt_assign_fn p_assign;
 static lt_release_many_fn p_release_many;
 static lt_barrier_fn p_barrier;
+static lt_shape_fn p_shape;
+static lt_device_ptr_fn p_device_ptr;
 static PyObject* str_tid;
 static PyObject* str_dead;
 static PyObject* str_kept;
 static PyObject* rec_error;
-static PyObject* query_hook;   /* callable(tensor): fills in _dtype and _shape from the library */
+static PyObject* str_hv;
+static PyObject* dtype_names;  /* tuple of str, by the library's number */
 
-enum { kMaxIn = 8, kMaxOut = 4 };
+enum { kMaxIn = 8, kMaxOut = 4, kMaxRank = 6 /* LT_MAX_RANK */ };
+
+static PyObject* raise_status(void* ctx, int st);
 
 /* ---- the tensor handle -------------------------------------------------------------------
  * A unique tensor id plus what the binding knows about it.  Dropping the last reference tells the
@@ -123,14 +130,49 @@ static void tensor_dealloc(TensorObject* self) {
   Py_TYPE(self)->tp_free((PyObject*)self);
 }
 
-static int tensor_ask(TensorObject* self) {   /* 0: _dtype and _shape are known now */
-  if (!query_hook) {
-    PyErr_SetString(PyExc_RuntimeError, "_ltrec.set_query has not been called");
+/* the library's context behind a binding's Context (0 if it is closed); (void*)-1 and an error set on failure */
+static void* context_of(PyObject* owner) {
+  PyObject* hv = PyObject_GetAttr(owner, str_hv);
+  if (!hv) return (void*)-1;
+  void* ctx = (void*)(uintptr_t)PyLong_AsUnsignedLongLong(hv);
+  Py_DECREF(hv);
+  return PyErr_Occurred() ? (void*)-1 : ctx;
+}
+
+/* Asks the library for element type and shape.  (Through ctypes it took 1.5 us, more than recording four ops, and a step
+ * that hands its results over asks for every one of them.) */
+static int tensor_ask(TensorObject* self) {   /* 0: dtype and shape are known now */
+  if (!p_shape || !dtype_names) {
+    PyErr_SetString(PyExc_RuntimeError, "_ltrec.init has not been called");
     return -1;
   }
-  PyObject* r = PyObject_CallFunctionObjArgs(query_hook, (PyObject*)self, NULL);
-  if (!r) return -1;
-  Py_DECREF(r);
+  void* ctx = context_of(self->ctx);
+  if (ctx == (void*)-1) return -1;
+  int dt = 0, rank = 0;
+  int64_t dims[kMaxRank];
+  const int st = p_shape(ctx, self->tid, &dt, &rank, dims);
+  if (st != 0) {
+    raise_status(ctx, st);
+    return -1;
+  }
+  if (dt < 0 || dt >= PyTuple_GET_SIZE(dtype_names) || rank < 0 || rank > kMaxRank) {
+    PyErr_SetString(PyExc_RuntimeError, "lt_shape: unknown element type or rank");
+    return -1;
+  }
+  PyObject* shape = PyTuple_New(rank);
+  if (!shape) return -1;
+  for (int i = 0; i < rank; ++i) {
+    PyObject* d = PyLong_FromLongLong(dims[i]);
+    if (!d) {
+      Py_DECREF(shape);
+      return -1;
+    }
+    PyTuple_SET_ITEM(shape, i, d);
+  }
+  PyObject* name = PyTuple_GET_ITEM(dtype_names, dt);
+  Py_INCREF(name);
+  Py_SETREF(self->dtype, name);
+  Py_SETREF(self->shape, shape);
   return 0;
 }
 
@@ -214,8 +256,9 @@ static PyTypeObject TensorType = {
 };
 
 static PyObject* rec_init(PyObject* self, PyObject* args) {
-  unsigned long long a, b, c, d, e, f, g;
-  if (!PyArg_ParseTuple(args, "KKKKKKK", &a, &b, &c, &d, &e, &f, &g)) return NULL;
+  unsigned long long a, b, c, d, e, f, g, h, i;
+  PyObject* names;
+  if (!PyArg_ParseTuple(args, "KKKKKKKKKO!", &a, &b, &c, &d, &e, &f, &g, &h, &i, &PyTuple_Type, &names)) return NULL;
   p_op = (lt_op_fn)(uintptr_t)a;
   p_scalar = (lt_scalar_fn)(uintptr_t)b;
   p_release = (lt_release_fn)(uintptr_t)c;
@@ -223,6 +266,10 @@ static PyObject* rec_init(PyObject* self, PyObject* args) {
   p_assign = (lt_assign_fn)(uintptr_t)e;
   p_release_many = (lt_release_many_fn)(uintptr_t)f;
   p_barrier = (lt_barrier_fn)(uintptr_t)g;
+  p_shape = (lt_shape_fn)(uintptr_t)h;
+  p_device_ptr = (lt_device_ptr_fn)(uintptr_t)i;
+  Py_INCREF(names);
+  Py_XSETREF(dtype_names, names);
   Py_RETURN_NONE;
 }
 
@@ -234,12 +281,6 @@ static PyObject* rec_set_error(PyObject* self, PyObject* cls) {
   }
   Py_INCREF(cls);
   Py_XSETREF(rec_error, cls);
-  Py_RETURN_NONE;
-}
-
-static PyObject* rec_set_query(PyObject* self, PyObject* fn) {
-  Py_INCREF(fn);
-  Py_XSETREF(query_hook, fn);
   Py_RETURN_NONE;
 }
 
@@ -346,8 +387,6 @@ typedef struct {
   PyObject* keyword;   /* interned str or NULL */
 } PlainOpObject;
 
-static PyObject* str_hv;
-
 static PyObject* plainop_call(PyObject* callable, PyObject* const* args, size_t nargsf, PyObject* kwnames) {
   PlainOpObject* op = (PlainOpObject*)callable;
   const Py_ssize_t nargs = PyVectorcall_NARGS(nargsf);
@@ -451,7 +490,7 @@ static PyTypeObject PlainOpType = {
 /* assign(ctx: int, dst: Tensor, src: Tensor): lt_assign; what is known of src's type and shape
  * becomes what is known of dst's (unknown stays unknown: asked for on demand) */
 static PyObject* rec_assign(PyObject* self, PyObject* const* args, Py_ssize_t nargs) {
-  if (nargs != 3 || Py_TYPE(args[1]) != &TensorType || Py_TYPE(args[2]) != &TensorType) {
+  if (nargs != 3 || !PyObject_TypeCheck(args[1], &TensorType) || Py_TYPE(args[2]) != &TensorType) {
     PyErr_SetString(PyExc_TypeError, "assign(ctx, dst: Tensor, src: Tensor)");
     return NULL;
   }
@@ -511,6 +550,24 @@ static PyObject* rec_release_many(PyObject* self, PyObject* const* args, Py_ssiz
   Py_RETURN_NONE;
 }
 
+/* device_ptr(ctx: int, t: Tensor) -> int: lt_device_ptr */
+static PyObject* rec_device_ptr(PyObject* self, PyObject* const* args, Py_ssize_t nargs) {
+  if (nargs != 2 || !PyObject_TypeCheck(args[1], &TensorType)) {
+    PyErr_SetString(PyExc_TypeError, "device_ptr(ctx, tensor)");
+    return NULL;
+  }
+  if (!p_device_ptr) {
+    PyErr_SetString(PyExc_RuntimeError, "_ltrec.init has not been called");
+    return NULL;
+  }
+  void* ctx = (void*)(uintptr_t)PyLong_AsUnsignedLongLong(args[0]);
+  if (PyErr_Occurred()) return NULL;
+  void* p = NULL;
+  const int st = p_device_ptr(ctx, ((TensorObject*)args[1])->tid, &p);
+  if (st != 0) return raise_status(ctx, st);
+  return PyLong_FromUnsignedLongLong((unsigned long long)(uintptr_t)p);
+}
+
 /* barrier(ctx: int, dead: list of int, blocking: int, info_addr: int): hands the dropped tensors over
  * (lt_release_many, the list is emptied), then lt_barrier into the lt_barrier_info at info_addr.  The
  * interpreter lock is released while the barrier runs (a blocking one waits for the device). */
@@ -537,12 +594,12 @@ static PyObject* rec_barrier(PyObject* self, PyObject* const* args, Py_ssize_t n
 }
 
 static PyMethodDef methods[] = {
-    {"init", rec_init, METH_VARARGS, "init(lt_op, lt_scalar, lt_release, lt_last_error, lt_assign, lt_release_many, lt_barrier): addresses of the entry points"},
+    {"init", rec_init, METH_VARARGS, "init(lt_op, lt_scalar, lt_release, lt_last_error, lt_assign, lt_release_many, lt_barrier, lt_shape, lt_device_ptr, names): addresses of the entry points, names of the element types"},
     {"set_error", rec_set_error, METH_O, "set_error(cls): the exception class raised as cls(status, message)"},
-    {"set_query", rec_set_query, METH_O, "set_query(fn): fn(tensor) fills in tensor._dtype and tensor._shape"},
     {"op", (PyCFunction)(void (*)(void))rec_op, METH_FASTCALL, "record one op; returns its result tensor(s)"},
     {"assign", (PyCFunction)(void (*)(void))rec_assign, METH_FASTCALL, "record dst <- src"},
     {"release_many", (PyCFunction)(void (*)(void))rec_release_many, METH_FASTCALL, "release the listed tensor ids and empty the list"},
+    {"device_ptr", (PyCFunction)(void (*)(void))rec_device_ptr, METH_FASTCALL, "device address of a materialised tensor"},
     {"barrier", (PyCFunction)(void (*)(void))rec_barrier, METH_FASTCALL, "release the listed tensor ids, then lt_barrier"},
     {NULL, NULL, 0, NULL}};
 
@@ -559,7 +616,7 @@ PyMODINIT_FUNC PyInit__ltrec(void) {
   if (!str_tid || !str_dead || !str_kept || !str_hv || !rec_error) return NULL;
   Py_INCREF(rec_error);   /* one reference is the module attribute's, one stays with rec_error */
   if (PyModule_AddObject(m, "Error", rec_error) < 0) return NULL;
-  if (PyModule_AddIntConstant(m, "API", 6) < 0) return NULL;   /* bumped when the binding's expectations change */
+  if (PyModule_AddIntConstant(m, "API", 7) < 0) return NULL;   /* bumped when the binding's expectations change */
   if (PyType_Ready(&TensorType) < 0) return NULL;
   Py_INCREF(&TensorType);
   if (PyModule_AddObject(m, "Tensor", (PyObject*)&TensorType) < 0) return NULL;

@@ -172,7 +172,8 @@ def load_library():
         raise ImportError("paper_2102_13267_amd/_ltrec extension is missing or stale: run python -m paper_2102_13267_amd.build")
     addr = lambda fn: C.cast(fn, C.c_void_p).value
     _ltrec.init(addr(lib.lt_op), addr(lib.lt_scalar), addr(lib.lt_release), addr(lib.lt_last_error), addr(lib.lt_assign),
-                addr(lib.lt_release_many), addr(lib.lt_barrier))
+                addr(lib.lt_release_many), addr(lib.lt_barrier), addr(lib.lt_shape), addr(lib.lt_device_ptr),
+                tuple(_DTYPE_NAMES[i] for i in range(len(_DTYPE_NAMES))))
     global _REC
     _REC = _ltrec
     _LIB = lib
@@ -190,7 +191,7 @@ _REC = None                   # the _ltrec extension (set by load_library)
 # library learns that it is no longer live (liveness matters when the trace is cut, not before: dead
 # ids are collected in Context._dead and handed over in one call -- see Context._flush).  Element
 # type and shape of an op's result are asked from the library only when somebody reads them.
-_LTREC_API = 6   # what this file expects of the extension (its `API` attribute)
+_LTREC_API = 7   # what this file expects of the extension (its `API` attribute)
 try:
     from . import _ltrec
     if getattr(_ltrec, "API", 0) != _LTREC_API:
@@ -201,15 +202,7 @@ except ImportError:   # not built yet, or built from older sources: load_library
     Tensor = None
 
 
-def _query(t):
-    dt, rank = C.c_int(), C.c_int()
-    dims = (C.c_int64 * MAX_RANK)()
-    t.ctx._check(t.ctx._lib.lt_shape(t.ctx._h, t.tid, C.byref(dt), C.byref(rank), dims))
-    t._dtype, t._shape = _DTYPE_NAMES[dt.value], tuple(dims[i] for i in range(rank.value))
-
-
 if _ltrec is not None:
-    _ltrec.set_query(_query)
     _ltrec.set_error(LtError)   # a failed call raises LtError(status, message) straight from C
     _rec_op = _ltrec.op
 
@@ -491,9 +484,7 @@ class Context:
         return out.reshape(t.shape)
 
     def device_ptr(self, t: Tensor) -> int:
-        p = C.c_void_p()
-        self._check(self._lib.lt_device_ptr(self._h, t.tid, C.byref(p)))
-        return p.value or 0
+        return _ltrec.device_ptr(self._hv, t)
 
     def _dump(self, fn, binary=False):
         self._flush()
