@@ -34,7 +34,7 @@ template <bool BF> struct ChainChunk {
     Raw r;
 #pragma unroll
     for (int e = 0; e < 4; ++e) r[e] = BF ? f32_to_bf16_pair(v[2 * e], v[2 * e + 1]) : __float_as_uint(v[e]);
-    *(Raw*)((char*)p + (size_t)i * (BF ? 2u : 4u)) = r;
+    store_through((char*)p + (size_t)i * (BF ? 2u : 4u), r);
   }
 };
 

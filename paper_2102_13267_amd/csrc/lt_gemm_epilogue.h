@@ -168,7 +168,7 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, const v16f (&acc)[MB
       float* dst = raw + (size_t)(row_flat0 + row) * a.n + col;
       const float4 t = *(const float4*)&Cs[r * kCStride + c];
       if (vec) {
-        *(float4*)dst = t;
+        store_through(dst, t);
       } else {
         dst[0] = t.x;
         if (col + 1 < a.n) dst[1] = t.y;
@@ -182,7 +182,7 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, const v16f (&acc)[MB
   // checks on inputs, no divisions (row and column are known).
   const bool fast = p.fast && p.full_vec_ok && (a.n & 3u) == 0u && p.n_in <= 4u && p.n_slots <= 8u;
   const uint32_t row_flat0 = (b0 * a.batch1 + b1) * a.m + tile_m;   // row number in the flattened [rows, n] output
-  if (n_code == 0u && p.n_in == 0u && p.n_out == 1u && !p.out[0].scalar && p.out[0].slot == p.anchor_slot) {
+  if (!a.chain.n && n_code == 0u && p.n_in == 0u && p.n_out == 1u && !p.out[0].scalar && p.out[0].slot == p.anchor_slot) {
     // the product itself is the only output: convert and store, nothing to interpret
     const EwOut& o = p.out[0];
     if (fast && tile_m + BM <= a.m && tile_n + BN <= a.n) {

@@ -547,22 +547,32 @@ __device__ __forceinline__ void store_elem(void* ptr, uint32_t dtype, uint64_t i
 }
 
 // NT: non-temporal store (the data is not read again by this kernel).
-template <bool F32 = false, bool NT = false>
+// Stores of 16 bytes a lane that go through to memory (sc1) instead of waiting in the die's L2 until the launch ends: what is
+// still there then is written back before the next launch may start, in its way and not under this one's work.  (Written in assembly: a
+// store of this scope is otherwise an atomic one, of at most eight bytes.  Two wait states: the compiler does not know that the
+// registers of the data are still being read and may overwrite them next.)
+typedef uint32_t Through4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void store_through(void* p, Through4 v) { asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" : : "v"(p), "v"(v) : "memory"); }
+__device__ __forceinline__ void store_through(void* p, const float4& v) {
+  store_through(p, Through4{__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z), __float_as_uint(v.w)});
+}
+
+// HOW: plain, past the caches (operands larger than they are), or through them (store_through; fp32)
+enum StoreHow { kPlain, kPast, kThrough };
+template <bool F32 = false, StoreHow HOW = kPlain>
 __device__ __forceinline__ void store_vec4(void* ptr, uint32_t dtype, uint64_t base, uint32_t lane, const Quad& q) {
   if (!F32 && dtype == kBF16) {
+    char* b = (char*)ptr + base * 2u;
     uint2 u;
     u.x = f32_to_bf16_pair(q.v[0], q.v[1]);
     u.y = f32_to_bf16_pair(q.v[2], q.v[3]);
-    char* b = (char*)ptr + base * 2u;
     *(uint2*)(b + (size_t)lane * 2u) = u;
   } else {
     char* b = (char*)ptr + base * 4u;
-    if (NT) {
-      const RawVec t = {q.v[0], q.v[1], q.v[2], q.v[3]};
-      __builtin_nontemporal_store(t, (RawVec*)(b + (size_t)lane * 4u));
-    } else {
-      *(float4*)(b + (size_t)lane * 4u) = make_float4(q.v[0], q.v[1], q.v[2], q.v[3]);
-    }
+    const RawVec t = {q.v[0], q.v[1], q.v[2], q.v[3]};
+    if (HOW == kPast) __builtin_nontemporal_store(t, (RawVec*)(b + (size_t)lane * 4u));
+    else if (HOW == kThrough) store_through(b + (size_t)lane * 4u, make_float4(q.v[0], q.v[1], q.v[2], q.v[3]));
+    else *(float4*)(b + (size_t)lane * 4u) = make_float4(q.v[0], q.v[1], q.v[2], q.v[3]);
   }
 }
 
@@ -579,7 +589,7 @@ __device__ __forceinline__ void store_vec4_any(void* ptr, uint32_t dtype, uint64
 
 // Store the outputs of the program for elements i .. i+nvalid-1, i = base + lane (flat,
 // contiguous outputs).
-template <int NS, bool FAST = false, bool F32 = false, int OFF = 0, bool NT = false>
+template <int NS, bool FAST = false, bool F32 = false, int OFF = 0, StoreHow HOW = kPlain>
 __device__ __forceinline__ void store_outputs(RF<NS> f, const EwProg& p, uint64_t base, uint32_t lane, uint32_t nvalid) {
   const uint32_t n_out = p.n_out;
   if (!FAST) {   // general path: one rolled copy (see load_inputs_general)
@@ -607,7 +617,7 @@ __device__ __forceinline__ void store_outputs(RF<NS> f, const EwProg& p, uint64_
       if (out.scalar) {
         if (base + lane == 0) store_elem<F32>(out.ptr, out.dtype, 0, q.v[0]);
       } else {
-        store_vec4<F32, NT>(out.ptr, out.dtype, base, lane, q);
+        store_vec4<F32, HOW>(out.ptr, out.dtype, base, lane, q);
       }
     }
   }

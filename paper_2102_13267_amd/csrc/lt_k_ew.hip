@@ -131,8 +131,8 @@ __global__ __launch_bounds__(kBlock) void lt_ew_stream_kernel(const EwStreamArgs
       }
       continue;
     }
-    store_outputs<16, true, true, 0, NT>(f, p, base0, lane, kVec);
-    store_outputs<16, true, true, 8, NT>(f, p, base1, lane, kVec);
+    store_outputs<16, true, true, 0, NT ? kPast : kThrough>(f, p, base0, lane, kVec);
+    store_outputs<16, true, true, 8, NT ? kPast : kThrough>(f, p, base1, lane, kVec);
   }
   args_touched(touched);
 }
@@ -311,7 +311,7 @@ __global__ __launch_bounds__(kBlock) void lt_split_post_kernel(const SplitPostAr
     RF<16> f = load_inputs<16, MAXIN, FAST, false>(rf_zero<16>(), p, base, lane, nvalid);
     f = rf_set<16>(f, p.anchor_slot, anchor);
     f = interp<16>(f, pr, n_code);
-    store_outputs<16, FAST, false>(f, p, base, lane, nvalid);
+    store_outputs<16, FAST, false, 0, kThrough>(f, p, base, lane, nvalid);
   }
   args_touched(touched);
 }
@@ -411,8 +411,8 @@ __global__ __launch_bounds__(kBlock) void lt_split_post_stream_kernel(const Spli
     q.v[0] = s1.x; q.v[1] = s1.y; q.v[2] = s1.z; q.v[3] = s1.w;
     f = rf_set<16>(f, p.anchor_slot + 8u, q);
     f = interp<16, 2>(f, pr, n_code);
-    store_outputs<16, true, false, 0>(f, p, t0 * kTile, lane, kVec);
-    store_outputs<16, true, false, 8>(f, p, t1 * kTile, lane, kVec);
+    store_outputs<16, true, false, 0, kThrough>(f, p, t0 * kTile, lane, kVec);
+    store_outputs<16, true, false, 8, kThrough>(f, p, t1 * kTile, lane, kVec);
   }
   args_touched(touched);
 }

@@ -261,19 +261,33 @@ __global__ __launch_bounds__(kBlock) void lt_all_reduce_kernel(const AllArgs a) 
           }
         }
       }
-#pragma unroll 1
-      for (uint32_t u = 0; u < (uint32_t)kTail; ++u) {
-        const uint32_t tile = t0 + u * gridDim.x * kBlock;
-        if (tile >= (uint32_t)nvec) break;
-        RF<NS> f = stream_place<NS, NN, kTail, BF>(rf_zero<NS>(), st, u);
-        f = interp<NS>(f, pro_regs, pro_n);
-        const Quad q = rf_get(f, pro.anchor_slot);
+      auto add = [&](uint32_t tile, const Quad& q) {
         const uint32_t own = (tile + threadIdx.x) * kVec, e = min(own, last);
 #pragma unroll
         for (int v = 0; v < kVec; ++v) {
           const float x = red_combine(a.red, acc, q.v[v]);
           acc = tile + threadIdx.x < (uint32_t)nvec && e + (uint32_t)v >= own ? x : acc;
         }
+      };
+      if (NN == 1 && lone != 0u) {   // (as above; 669,706 squares: 2.6 -> 1.95 us up to here)
+#pragma unroll
+        for (int u = 0; u < kTail; ++u) {
+          const uint32_t tile = t0 + (uint32_t)u * gridDim.x * kBlock;
+          if (tile >= (uint32_t)nvec) continue;
+          Quad q = stream_quad<NN, kTail, BF>(st, 0, u);
+#pragma unroll
+          for (int v = 0; v < kVec; ++v) q.v[v] = lone == kSquare ? q.v[v] * q.v[v] : fabsf(q.v[v]);
+          add(tile, q);
+        }
+        continue;
+      }
+#pragma unroll 1
+      for (uint32_t u = 0; u < (uint32_t)kTail; ++u) {
+        const uint32_t tile = t0 + u * gridDim.x * kBlock;
+        if (tile >= (uint32_t)nvec) break;
+        RF<NS> f = stream_place<NS, NN, kTail, BF>(rf_zero<NS>(), st, u);
+        f = interp<NS>(f, pro_regs, pro_n);
+        add(tile, rf_get(f, pro.anchor_slot));
       }
     }
   } else {
