@@ -1016,6 +1016,7 @@ lt_status lt_set_streams(lt_ctx* ctx, int n) {
   if (!ctx) return LT_ERR_ARG;
   if (n < 1 || n > kMaxStreams) return fail(ctx, LT_ERR_ARG, "lt_set_streams: between 1 and 4 streams");
   ctx->max_streams = n;
+  ctx->streams_asked = true;
   return LT_OK;
 }
 

@@ -303,8 +303,10 @@ static lt_status execute(lt_ctx* ctx, Plan* plan, const std::vector<BufRef>& par
   // plan (40 to 46) 561 / 535, 741 / 753, 320 / 367, two (26 to 30) 488 / 527, 372 / 393; 3 to 18 launches: feed-forward block
   // 512 rows 102 / 135, 4096 374 / 383, 16384 1178 / 1288, head of 16384 rows 683 / 745, norm of 131072 rows 408 / 425, attention 8 x
   // 1024 303 / 319, classifier 245 / 270.  Long launches are no reason either: at best, independent fp32 products and
-  // column sums of 8 x 16384 x 1024, 2400 / 2298.  (Where a plan of 30 launches and more gains is not a matter of their number alone.)
-  const bool multi = real && !prof && !use_static && ctx->max_streams > 1 && plan->n_streams > 1 && upfront && plan->launches.size() >= LT_SPREAD_LAUNCHES;
+  // column sums of 8 x 16384 x 1024, 2400 / 2298.  (Where a plan of 24 launches and more
+  // gains is not a matter of their number: Plan::spread_pays, unless the caller has asked for streams.)
+  const bool multi = real && !prof && !use_static && ctx->max_streams > 1 && plan->n_streams > 1 && upfront && plan->launches.size() >= LT_SPREAD_LAUNCHES &&
+                     (ctx->streams_asked || plan->spread_pays);
   ctx->last_launches.clear();
   if (prof) {
     while (ctx->events.size() < 2 * plan->launches.size()) {

@@ -185,6 +185,7 @@ struct Plan {
   std::vector<RootBind> roots;
   uint64_t bytes_planned = 0, flops_planned = 0;
   int n_streams = 1;                 // streams the schedule uses (1: everything on the caller's stream)
+  bool spread_pays = false;          // the time the schedule's edges cost the host is less than what it gains (estimated)
   size_t temp_bytes = 0;             // arena bytes when no temporary is reused inside the step
   std::vector<hipEvent_t> events;    // one per launch with `record` set (created on first use)
   GraphSlots graphs;                 // lt_set_graphs
@@ -280,6 +281,7 @@ struct lt_ctx {
   hipStream_t side[lt::kMaxStreams - 1] = {};
   hipEvent_t fork_event = nullptr, join_event[lt::kMaxStreams - 1] = {};
   int max_streams = lt::kMaxStreams;   // lt_set_streams
+  bool streams_asked = false;          // it has been called
   bool graphs = false;                 // lt_set_graphs: steps with unchanged addresses run as one HIP graph
   hipStream_t graph_stream = nullptr;  // the stream that graph captures are made on (created on first use)
   bool fusion = true;                  // lt_set_fusion: off = one region per recorded op

@@ -1,0 +1,31 @@
+"""GPU (-m gpu): a context that was never told how many streams to use decides by the plan whether it spreads; results are bit-identical
+to one stream and to four, whatever it decides (few edges and long launches, many edges and short ones)."""
+import numpy as np
+import pytest
+
+from test_gpu_parity import _stream_case, rng
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("rows,cols", [(64, 256), (1024, 512), (8192, 1024)])
+def test_default_streams_do_not_change_results(rows, cols):
+    from paper_2102_13267_amd import Context
+    g = rng(rows + cols)
+    data = [g.standard_normal(s).astype(np.float32) * f for s, f in (((rows, cols), 1.0), ((cols, cols // 2), 0.03), ((cols, cols), 0.03), ((rows, cols), 1.0))]
+    results = []
+    for n_streams in (None, 1, 4):
+        c = Context(device=0, workspace_bytes=2 << 30)
+        if n_streams:
+            c.set_streams(n_streams)
+        steps = []
+        for _ in range(2):
+            outs = _stream_case(c, *data)
+            c.barrier(False)
+            steps.append([c.fetch(t).copy() for t in outs])
+        results.append(steps)
+        c.close()
+    for other in results[1:]:
+        for a_step, b_step in zip(results[0], other):
+            for a, b in zip(a_step, b_step):
+                assert np.array_equal(a, b)
