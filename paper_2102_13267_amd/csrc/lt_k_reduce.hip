@@ -238,7 +238,7 @@ __global__ __launch_bounds__(kBlock) void lt_all_reduce_kernel(const AllArgs a) 
       }
     }
     // The rest, kTail tiles per workgroup and round.
-    constexpr int kTail = 4;
+    constexpr int kTail = NN == 1 ? 8 : 4;
     const uint32_t last = (uint32_t)(n - kVec);   // (n >= 4, and every index fits 32 bits)
     for (uint32_t t0 = (uint32_t)(trips * per_trip) + blockIdx.x * kBlock; t0 < (uint32_t)nvec; t0 += (uint32_t)kTail * gridDim.x * kBlock) {
       Stream<NN, kTail, BF> st;
