@@ -407,7 +407,7 @@ __global__ __launch_bounds__(kGemmThreads * KS, BM == 64 ? 2 : 1) void lt_gemm_k
     auto pipeline = [&](auto sum) __attribute__((always_inline)) {
       constexpr int kSum = (int)decltype(sum)::value;
       Frags f0, f1;
-  #pragma unroll
+#pragma unroll
       for (int g = 0; g < BK / 8; ++g) {
         read_a(f0, 0, g);
         read_b(f0, 0, g);
