@@ -222,7 +222,8 @@ template <typename T, int BM, int BN> struct Smem {
 // walk their slices side by side.
 // CS: column sums of B ride along (GemmArgs::col_sum; AKC and BKC false).  The workgroups of the first tile row take them from
 // the B fragments that they multiply anyway, half of each slice by either wave row.  A slice's values are added pairwise before
-// they join one of four running sums (4096 rows of N(0, 1): 0.98e-7 from 64 bits, 1.34e-7 in a launch of their own).
+// they join a running sum: one of four, which join the total every 32 slices, or in the loop of unaligned rows one, which joins it every
+// eight.  However many rows: the total keeps what its additions lose (ColTotal).
 template <typename T, int BM, int BN, bool AKC, bool BKC, bool AL, int KS, bool CS>
 __global__ __launch_bounds__(kGemmThreads * KS, BM == 64 ? 2 : 1) void lt_gemm_kernel(const GemmArgs a) {
   static_assert(!CS || (!AKC && !BKC), "a weight gradient");
@@ -260,14 +261,14 @@ __global__ __launch_bounds__(kGemmThreads * KS, BM == 64 ? 2 : 1) void lt_gemm_k
         for (int r = 0; r < 16; ++r) accs[c][i][j][r] = 0.0f;
 
   const bool summing = CS && tile_m == 0u;
-  float csum[4][NB], ctot[NB];
+  float csum[4][NB];
+  ColTotal ctot[NB];
 #pragma unroll
-  for (int j = 0; j < NB; ++j) ctot[j] = csum[0][j] = csum[1][j] = csum[2][j] = csum[3][j] = 0.0f;
-  // (the running sums join the total every 32 slices: 8192 rows 1.32e-7 -> 1.05e-7 from 64 bits, 1.25e-7 in a launch of their own)
+  for (int j = 0; j < NB; ++j) csum[0][j] = csum[1][j] = csum[2][j] = csum[3][j] = 0.0f;
   auto join_columns = [&]() __attribute__((always_inline)) {
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
-      ctot[j] += (csum[0][j] + csum[1][j]) + (csum[2][j] + csum[3][j]);
+      ctot[j].add((csum[0][j] + csum[1][j]) + (csum[2][j] + csum[3][j]));
       csum[0][j] = csum[1][j] = csum[2][j] = csum[3][j] = 0.0f;
     }
   };
@@ -459,8 +460,14 @@ __global__ __launch_bounds__(kGemmThreads * KS, BM == 64 ? 2 : 1) void lt_gemm_k
         if (summing) add_columns(Bs(j & 1u));
       }
     };
+    // (a loop inside a loop: 8192 rows, 1030 x 1032, 312 us, with a branch in each step 316; 307 in one chain, 312 with the sums in a
+    // launch of their own)
+    for (uint32_t j = 0; j < both;) {
+      const uint32_t to = CS ? min(j + 8u, both) : both;
 #pragma unroll 1
-    for (uint32_t j = 0; j < both; ++j) step(j, true);
+      for (; j < to; ++j) step(j, true);
+      if (summing) join_columns();
+    }
     if (KS > 1 && both < n) step(both, half == 0u);   // (the first half's odd one)
   }
   // the rest of k: every access checked, one slice at a time, by the first half
@@ -495,7 +502,7 @@ __global__ __launch_bounds__(kGemmThreads * KS, BM == 64 ? 2 : 1) void lt_gemm_k
     // (read behind the epilogue's barriers)
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
-      float t = ctot[j];
+      float t = ctot[j].value();
       t += __shfl_xor(t, 32);
       if (lane < 32u) col_lds[(half * 2u + wave_m) * BN + wave_n * (BN / 2) + j * 32u + lane] = t;
     }

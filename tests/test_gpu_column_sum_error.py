@@ -1,0 +1,48 @@
+"""GPU (-m gpu): column sums that ride with a weight gradient are no further from 64 bits than in a launch of their own, over long columns,
+rows aligned and not, unsplit, split and in halves.  Root mean square over the columns, of which a thousand fix it to a few per
+cent: hence 1.1."""
+import numpy as np
+import pytest
+
+from test_gpu_parity import ctx  # noqa: F401  (a fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+def error(ctx, rows, m, n, mean, dt, ride):  # noqa: F811
+    """Distance of the sums from 64 bits; the contraction's kernel."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(rows + n)
+    dy = torch.randn(rows, n, device="cuda", generator=gen).add_(mean).to(torch.float32 if dt == "f32" else torch.bfloat16)
+    x = torch.zeros(rows, m, device="cuda", dtype=dy.dtype)
+    exact = torch.zeros(n, dtype=torch.float64, device="cuda")
+    for part in dy.split(8192):
+        exact += part.double().sum(0)
+    D, zero = ctx.tensor(dy, dtype=dt), ctx.tensor(torch.zeros(n, device="cuda"))
+    dw = ctx.matmul(ctx.tensor(x, dtype=dt), D, trans_a=True) if ride else None
+    db = ctx.sum(D, axis=0)
+    if dt == "bf16":                 # (the sum itself is of 32 bits; what is stored would be rounded to 16)
+        db = ctx.add(ctx.cast(db, "f32"), zero)
+    ctx.set_profiling(True)
+    ctx.barrier()
+    names = [r["kernel"] for r in ctx.last_launches()]
+    ctx.set_profiling(False)
+    assert any("sums" in k for k in names) == ride, names
+    got = ctx.fetch(db).astype(np.float64)
+    del dw
+    exact = exact.cpu().numpy()
+    return np.linalg.norm(got - exact) / np.linalg.norm(exact), names[0]
+
+
+def closer(ctx, rows, m, n, mean, dt):  # noqa: F811
+    (own, _), (riding, name) = error(ctx, rows, m, n, mean, dt, False), error(ctx, rows, m, n, mean, dt, True)
+    assert riding <= 1.1 * own, (riding, own)
+    return name
+
+
+@pytest.mark.parametrize("rows,m,n,aligned", [(4096, 1030, 1030, False), (8192, 1030, 1030, False), (8209, 1030, 1030, False), (8192, 1030, 2052, False),
+                                              (4096, 1030, 4100, False), (65536, 1030, 1030, False), (8192, 1024, 1024, True), (65536, 1024, 1024, True),
+                                              (65536, 2048, 4096, True)])
+@pytest.mark.parametrize("mean", [0.0, 1.0])
+def test_long_columns_in_fp32(ctx, rows, m, n, aligned, mean):  # noqa: F811
+    assert closer(ctx, rows, m, n, mean, "f32").split(",")[4].startswith("true" if aligned else "false")
