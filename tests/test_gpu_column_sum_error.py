@@ -46,3 +46,29 @@ def closer(ctx, rows, m, n, mean, dt):  # noqa: F811
 @pytest.mark.parametrize("mean", [0.0, 1.0])
 def test_long_columns_in_fp32(ctx, rows, m, n, aligned, mean):  # noqa: F811
     assert closer(ctx, rows, m, n, mean, "f32").split(",")[4].startswith("true" if aligned else "false")
+
+
+@pytest.mark.parametrize("rows,m,n,kernel", [(65536, 2048, 2048, "true,2>"), (65536, 4096, 4096, "true,1>"), (65536, 2050, 4098, "false,1>"), (8192, 1030, 1032, "false,2>"),
+                                             (16384, 1024, 1024, "true,2>"), (70, 1030, 2052, "false,1>")])
+@pytest.mark.parametrize("mean", [0.0, 1.0])
+def test_long_columns_in_bf16(ctx, rows, m, n, kernel, mean):  # noqa: F811
+    assert closer(ctx, rows, m, n, mean, "bf16").endswith(kernel)
+
+
+@pytest.mark.parametrize("dt,unit", [("f32", 2.0 ** -149), ("bf16", 2.0 ** -133)])
+@pytest.mark.parametrize("n", [2048, 2052])
+def test_subnormal_columns(ctx, dt, unit, n):  # noqa: F811
+    """Sums that stay subnormal and sums that become normal: both exact."""
+    dy = np.zeros((512, n), np.float32)
+    dy[:, 3] = 3 * unit
+    dy[[7, 300], 5] = unit, 2 * unit
+    dy[::2, 9], dy[1::2, 9] = 5 * unit, -4 * unit
+    x, D = ctx.tensor(np.zeros((512, 2048), np.float32), dtype=dt), ctx.tensor(dy, dtype=dt)
+    dw, db = ctx.matmul(x, D, trans_a=True), ctx.sum(D, axis=0)
+    ctx.set_profiling(True)
+    ctx.barrier()
+    names = [r["kernel"] for r in ctx.last_launches()]
+    ctx.set_profiling(False)
+    assert "sums" in names[0], names
+    got = ctx.fetch(db).astype(np.float64)
+    assert got[3] == 1536 * unit and got[5] == 3 * unit and got[9] == 256 * unit and got[0] == 0
