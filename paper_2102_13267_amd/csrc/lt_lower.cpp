@@ -1480,6 +1480,14 @@ struct Lowering {
       for (const PtrPatch* pp : of[i])
         same_b = same_b || (pp->offset == offsetof(ltk::GemmArgs, b) + offsetof(ltk::GemmOperand, ptr) && pp->storage == summed.second && pp->byte_offset == summed.byte_offset);
       if (!same_b) continue;
+      // (The first tile row's workgroups take a tenth longer, and where a product's are there at most a few times over, so does the
+      // product.  bf16, whole and aligned, unsplit, no halves, us, riding / in a launch of their own: 16384 x 4096 x 4096 662 / 662, 16384 x
+      // 16384 x 1024 595 / 608, 32768 x 1024 x 8192 640 / 655, 32768 x 2048 x 4096 605 / 614; 20000 x 4096 x 4096 857 / 851, 24576 1071 /
+      // 1053, 32768 1462 / 1399, 65536 x 1024 x 8192 1400 / 1368, but 8192 x 8192 x 8192 1350 / 1359.  fp32, halves and split ones gain at
+      // all sizes tried, unaligned rows twice over.)
+      if (ga->in_dtype == ltk::kBF16 && ga->splits == 1u && ga->halves == 1u && ga->m % 8u == 0u && ga->n % 8u == 0u &&
+          (double)ga->m * ga->n * ga->k > (double)(1ull << 38))
+        continue;
       if (ga->splits == 1u) {
         if (!alone || post.prog.n_slots > 16u) return false;
         ga->col_post = post.prog;

@@ -67,3 +67,10 @@ def test_sums_whose_parameter_is_read_in_between_are_not_early():
     writer = [i for i, l in enumerate(sched) if "p3" in l["writes"] or any(w.startswith("p") for w in l["writes"])]
     readers = [i for i, l in enumerate(sched) if set(sched[writer[-1]]["writes"]) & set(l["reads"])]
     assert max(readers) <= writer[-1]
+
+
+@pytest.mark.parametrize("rows,cols,rides", [(16384, (4096, 4096), True), (16392, (4096, 4096), False), (65536, (1024, 8192), False),
+                                             (65536, (2048, 2048), True), (16392, (4100, 4100), True)])
+def test_longest_bf16_products(rows, cols, rides):
+    """Beyond 2^38 multiply-adds an unsplit product in whole tiles, whose workgroups are no halves, is slower with the sums than without."""
+    assert kinds(schedule(gradients(rows=rows, cols=cols))) == ["MM"] + ([] if rides else ["COL"])

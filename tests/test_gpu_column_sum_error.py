@@ -48,7 +48,7 @@ def test_long_columns_in_fp32(ctx, rows, m, n, aligned, mean):  # noqa: F811
     assert closer(ctx, rows, m, n, mean, "f32").split(",")[4].startswith("true" if aligned else "false")
 
 
-@pytest.mark.parametrize("rows,m,n,kernel", [(65536, 2048, 2048, "true,2>"), (65536, 4096, 4096, "true,1>"), (65536, 2050, 4098, "false,1>"), (8192, 1030, 1032, "false,2>"),
+@pytest.mark.parametrize("rows,m,n,kernel", [(65536, 2048, 2048, "true,2>"), (32768, 2048, 4096, "true,1>"), (65536, 2050, 4098, "false,1>"), (8192, 1030, 1032, "false,2>"),
                                              (16384, 1024, 1024, "true,2>"), (70, 1030, 2052, "false,1>")])
 @pytest.mark.parametrize("mean", [0.0, 1.0])
 def test_long_columns_in_bf16(ctx, rows, m, n, kernel, mean):  # noqa: F811
