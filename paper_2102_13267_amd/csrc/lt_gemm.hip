@@ -622,8 +622,7 @@ __device__ __forceinline__ void small_mma(v16f& acc0, v16f& acc1, const float (&
 }
 
 template <int G>
-__device__ __forceinline__ float small_colsum(const float (&bv)[G][4]) {
-  float s = 0.0f;
+__device__ __forceinline__ float small_colsum(float s, const float (&bv)[G][4]) {
 #pragma unroll
   for (int g = 0; g < G; ++g) s += (bv[g][0] + bv[g][1]) + (bv[g][2] + bv[g][3]);
   return s;
@@ -756,15 +755,18 @@ __device__ __forceinline__ void small_tile32(const GemmArgs& a) {
       small_fetch<BV, G>(b1v, bp, a.b.s_row, kl + (c + 1u) * kChunk, k_end);
     }
     small_mma<G>(acc0, acc1, a0, b0v);
-    if (cols_here) csum += small_colsum<G>(b0v);
+    // (a wave's column sum: four groups, two chunks, at a time, which then join its running sum: with a chunk at a time
+    // 1000 rows of N(0, 1) were 1.04e-7 from 64 bits instead of 0.92e-7)
+    float four = cols_here ? small_colsum<G>(0.0f, b0v) : 0.0f;
     if (c + 2u < nch) {
       small_fetch<AV, G>(a0, ap, a.a.s_col, kl + (c + 2u) * kChunk, k_end);
       small_fetch<BV, G>(b0v, bp, a.b.s_row, kl + (c + 2u) * kChunk, k_end);
     }
     if (c + 1u < nch) {
       small_mma<G>(acc0, acc1, a1, b1v);
-      if (cols_here) csum += small_colsum<G>(b1v);
+      if (cols_here) four = small_colsum<G>(four, b1v);
     }
+    csum += four;
   }
   if (CS) colp[threadIdx.x] = csum;
   float* mine = Cs + wave * (32u * kSmallStride);   // (wave = kway * NB + block)

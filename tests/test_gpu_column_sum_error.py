@@ -72,3 +72,38 @@ def test_subnormal_columns(ctx, dt, unit, n):  # noqa: F811
     assert "sums" in names[0], names
     got = ctx.fetch(db).astype(np.float64)
     assert got[3] == 1536 * unit and got[5] == 3 * unit and got[9] == 256 * unit and got[0] == 0
+
+
+def small_sums(dy):
+    """The order of a small product's riding sums: eight shares of k, each half of a wave every other four rows of its share; four groups
+    of those at a time, then one after the other; the shares in order, the lower half before the upper."""
+    rows, n = dy.shape
+    per = -(-(-(-rows // 8)) // 8)
+    padded = np.zeros((8 * per * 8, n), np.float32)
+    padded[:rows] = dy
+    v = padded.reshape(8, per, 2, 4, n)
+    group = (v[:, :, :, 0] + v[:, :, :, 1]) + (v[:, :, :, 2] + v[:, :, :, 3])
+    share = np.zeros((8, 2, n), np.float32)
+    for first in range(0, per, 4):
+        four = np.zeros((8, 2, n), np.float32)
+        for g in range(first, min(first + 4, per)):
+            four = four + group[:, g]
+        share = share + four
+    total = np.zeros(n, np.float32)
+    for w in range(8):
+        total = total + share[w, 0] + share[w, 1]
+    return total
+
+
+@pytest.mark.parametrize("rows,m,n", [(1000, 100, 100), (1024, 300, 333), (700, 250, 40), (40, 64, 10), (129, 512, 784)])
+def test_small_products_add_up_in_fours(ctx, rows, m, n):  # noqa: F811
+    """Bit for bit: with running sums joined group by group, or two by two, a thousand rows are an eighth further from 64 bits."""
+    dy = np.random.default_rng(rows).standard_normal((rows, n), dtype=np.float32)
+    D = ctx.tensor(dy)
+    dw, db = ctx.matmul(ctx.tensor(np.ones((rows, m), np.float32)), D, trans_a=True), ctx.sum(D, axis=0)
+    ctx.set_profiling(True)
+    ctx.barrier()
+    names = [r["kernel"] for r in ctx.last_launches()]
+    ctx.set_profiling(False)
+    assert len(names) == 1 and "small" in names[0], names
+    assert np.array_equal(ctx.fetch(db), small_sums(dy))
