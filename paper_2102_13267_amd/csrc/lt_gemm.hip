@@ -525,7 +525,7 @@ __global__ __launch_bounds__(kGemmThreads * KS, BM == 64 ? 2 : 1) void lt_gemm_k
 // of its four MFMAs is free as long as both operands agree, so a lane takes four CONSECUTIVE k
 // (4 h .. 4 h + 3): one 16-byte load where k is the operand's contiguous dimension, four 4-byte
 // loads that neighbouring lanes coalesce where it is not.  No LDS staging and no barrier in the
-// loop; kSmallG groups (32 k) are in flight per wave while the previous ones are multiplied.  The
+// loop; two groups (16 k) or kSmallG (32 k) are in flight per wave while as many are multiplied.  The
 // partial tiles of the waves meet in LDS, are added in a fixed order, and the post program runs on
 // the sum: one launch.  (A tile may also be two blocks of 32 x 32: then two times four waves.)
 // A long k over very few tiles (a batch of 8 rows against a 2048 x 2048 weight: 64 tiles) would
@@ -670,7 +670,12 @@ template <int TM, int TN, bool AV, bool BV, bool CS>
 __device__ __forceinline__ void small_tile32(const GemmArgs& a) {
   constexpr uint32_t NB = TM * TN, KW = kSmallWaves / NB;      // blocks, k shares inside the workgroup
   static_assert(!CS || NB == 1, "column sums ride with tiles of 32 x 32");
-  constexpr int G = NB == 1 ? 2 : kSmallG;                     // groups of 8 k in flight (and as many being multiplied)
+  // Groups of 8 k in flight, and as many being multiplied.  Two, where a wave's share of k is often no more (nothing is fetched past
+  // it) and loads of single values keep a wave busy; four where B's rows are read along k, 16 bytes a lane, so that a chunk is a whole
+  // cache line of each.  us, two / four: weight gradients 128: 784 x 512 7.2 / 8.7, 300: 512 x 512 7.0 / 8.3; k of no whole vectors
+  // 32 x 2047 x 1000 11.1 / 12.6, B transposed 12.5 / 15.3; B transposed, whole vectors, 32 x 2048 x 2048 11.6 / 11.0, 8 x 4096 x 4096 24.7 /
+  // 23.3, 32 x 4096 x 4096 28.3 / 26.4.
+  constexpr int G = NB == 1 && (CS || !BV) ? 2 : kSmallG;
   constexpr uint32_t kQuads = NB * 256u, QT = (kQuads + kSmallThreads - 1u) / kSmallThreads;   // quads of the tile, per thread
   __shared__ __attribute__((aligned(16))) float Cs[kSmallWaves * 32 * kSmallStride];
   __shared__ uint32_t is_last;
