@@ -314,13 +314,21 @@ lt_status lt_last_launches(lt_ctx* ctx, lt_launch_record* out, int cap, int* n);
  * returns, so the caller sees the ordering of a single stream.  n = 1 keeps every launch on the
  * caller's stream, and so does a plan of fewer than LT_SPREAD_LAUNCHES launches, in which the events
  * between streams cost more than they gain (lt_dump_schedule shows the streams that n = 4 would
- * use in a longer plan).  Until this is called, so does a longer plan whose events are estimated to cost more than they gain.  A plan whose temporaries do not fit the workspace without being recycled
+ * use in a longer plan).  Until this is called, so does a longer plan whose events are estimated to cost
+ * more than they gain.  A plan whose temporaries do not fit the workspace without being recycled
  * inside the step also runs on one stream.  Barriers that record per-launch timings
  * (lt_set_profiling) run on one stream so that the timings are those of the kernels alone.
  * Errors: LT_ERR_ARG (n out of range).
  */
 #define LT_SPREAD_LAUNCHES 24
 lt_status lt_set_streams(lt_ctx* ctx, int n);
+
+/*
+ * How many streams the last barrier's plan is for under the present lt_set_streams setting (1 to 4; 0
+ * before the first barrier): its schedule's streams, or 1 where it is kept on the caller's stream for being
+ * short, or because its events are estimated to cost more than they gain.
+ */
+lt_status lt_plan_streams(lt_ctx* ctx, int* n);
 
 /*
  * Ops without a lowering (section 4.5: every tensor op must give a correct program, if a slower

@@ -1020,6 +1020,12 @@ lt_status lt_set_streams(lt_ctx* ctx, int n) {
   return LT_OK;
 }
 
+lt_status lt_plan_streams(lt_ctx* ctx, int* n) {
+  if (!ctx || !n) return LT_ERR_ARG;
+  *n = !ctx->last_plan ? 0 : spreads(ctx, ctx->last_plan) ? ctx->last_plan->n_streams : 1;
+  return LT_OK;
+}
+
 lt_status lt_set_fusion(lt_ctx* ctx, int on) {
   if (!ctx) return LT_ERR_ARG;
   if (ctx->fusion == (on != 0)) return LT_OK;

@@ -305,8 +305,7 @@ static lt_status execute(lt_ctx* ctx, Plan* plan, const std::vector<BufRef>& par
   // 1024 303 / 319, classifier 245 / 270.  Long launches are no reason either: at best, independent fp32 products and
   // column sums of 8 x 16384 x 1024, 2400 / 2298.  (Where a plan of 24 launches and more
   // gains is not a matter of their number: Plan::spread_pays, unless the caller has asked for streams.)
-  const bool multi = real && !prof && !use_static && ctx->max_streams > 1 && plan->n_streams > 1 && upfront && plan->launches.size() >= LT_SPREAD_LAUNCHES &&
-                     (ctx->streams_asked || plan->spread_pays);
+  const bool multi = real && !prof && !use_static && upfront && spreads(ctx, plan);
   ctx->last_launches.clear();
   if (prof) {
     while (ctx->events.size() < 2 * plan->launches.size()) {

@@ -326,8 +326,9 @@ uint64_t fnv1a64(const uint8_t* p, size_t n);
 
 // lowering (lt_lower.cpp): returns nullptr and sets ctx->err / *status on failure.  spare: see Plan
 std::unique_ptr<Plan> lower(lt_ctx* ctx, const Cut& cut, lt_status* status, bool spare = false);
-// stream schedule of a lowered plan (lt_schedule.cpp)
+// stream schedule of a lowered plan (lt_schedule.cpp), and whether the context uses it
 void schedule_streams(Plan* plan);
+bool spreads(const lt_ctx* ctx, const Plan* plan);
 // 32 x 32 tiles of a one-launch small contraction whose workgroups share tiles (they exchange partial
 // tiles through the reduction scratch and take tickets); 0 for every other launch
 uint64_t gemm_shared_tiles(const Launch& l);

@@ -183,7 +183,8 @@ void schedule_streams(Plan* plan) {
   // 9), 12 x 200 x 256 409 / 514 (405, 9), 32 x 256 x 256 479 / 618 (515, 27), 4 x 128 x 512 389 / 546 (405, 9), 8 x 200 x 512 424 / 567
   // (470, 26), 16 x 256 x 512 529 / 613 (618, 27), 32 x 256 x 512 643 / 681 (840, 26), 2 x 256 x 1024 527 / 615 (592, 21), 4 x 256 x 1024 592 /
   // 627 (688, 21); 1 x 100 x 1024 444 / 391 (454, 4), 8 x 256 x 1024 716 / 703 (913, 25), 16 x 256 x 1024 805 / 746 (1265, 20), 32 x 256 x 1024
-  // 1233 / 1146 (2128, 22).  The line below has all of the first nine on one side and the last four on the other.
+  // 1233 / 1146 (2128, 22).  The line below has the first nine on one side and the last four on the other; of 1 x 64 x 1024, 415 / 424, it says that it
+  // pays.  (Nothing but such steps has been measured; 8 x 256 x 1024 is 9 us above the line.)
   double total = 0.0;
   size_t edges = 0;
   for (const Launch& l : plan->launches) {
@@ -191,6 +192,10 @@ void schedule_streams(Plan* plan) {
     edges += l.waits.size();
   }
   plan->spread_pays = total >= 300.0 + 24.0 * (double)edges;
+}
+
+bool spreads(const lt_ctx* ctx, const Plan* plan) {
+  return ctx->max_streams > 1 && plan->n_streams > 1 && plan->launches.size() >= LT_SPREAD_LAUNCHES && (ctx->streams_asked || plan->spread_pays);
 }
 
 }  // namespace lt

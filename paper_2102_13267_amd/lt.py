@@ -149,6 +149,7 @@ def load_library():
         "lt_release_many": [P, C.POINTER(C.c_uint64), C.c_size_t],
         "lt_set_profiling": [P, i32],
         "lt_set_streams": [P, i32],
+        "lt_plan_streams": [P, C.POINTER(i32)],
         "lt_set_fusion": [P, i32],
         "lt_set_graphs": [P, i32],
         "lt_set_quick_lookup": [P, i32],
@@ -517,6 +518,12 @@ class Context:
 
     def set_streams(self, n: int) -> None:
         self._check(self._lib.lt_set_streams(self._h, int(n)))
+
+    def plan_streams(self) -> int:
+        """How many streams the last barrier's plan is for under the present setting."""
+        n = C.c_int()
+        self._check(self._lib.lt_plan_streams(self._h, C.byref(n)))
+        return n.value
 
     # ---- ops without a lowering (lt_set_fallback) ----------------------------------------------------
     def set_fallback(self, fn):

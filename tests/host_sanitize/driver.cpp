@@ -208,6 +208,8 @@ int main() {
   CHECK(lt_set_fusion(ctx, 1) == LT_OK);
   (void)f1;
   CHECK(lt_barrier_static(ctx, 1, &info) == LT_OK);
+  int on_streams = 0;
+  CHECK(lt_plan_streams(ctx, nullptr) == LT_ERR_ARG && lt_plan_streams(ctx, &on_streams) == LT_OK && on_streams == 1);
   CHECK(lt_set_streams(ctx, 9) == LT_ERR_ARG && lt_set_streams(ctx, 1) == LT_OK && lt_set_profiling(ctx, 1) == LT_OK);
   lt_launch_record recs[4];
   int nrec = 0;

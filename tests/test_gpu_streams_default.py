@@ -8,8 +8,10 @@ from test_gpu_parity import _stream_case, rng
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("rows,cols", [(64, 256), (1024, 512), (8192, 1024)])
-def test_default_streams_do_not_change_results(rows, cols):
+@pytest.mark.parametrize("rows,cols,schedule,default", [(64, 256, 1, 1), (1024, 512, 1, 1),              # nothing leaves the caller's stream
+                                                        (2048, 1024, 4, 1), (16384, 256, 4, 1),          # declined
+                                                        (8192, 1024, 4, 4)])                             # spread
+def test_default_streams_do_not_change_results(rows, cols, schedule, default):
     from paper_2102_13267_amd import Context
     g = rng(rows + cols)
     data = [g.standard_normal(s).astype(np.float32) * f for s, f in (((rows, cols), 1.0), ((cols, cols // 2), 0.03), ((cols, cols), 0.03), ((rows, cols), 1.0))]
@@ -23,6 +25,7 @@ def test_default_streams_do_not_change_results(rows, cols):
             outs = _stream_case(c, *data)
             c.barrier(False)
             steps.append([c.fetch(t).copy() for t in outs])
+        assert c.plan_streams() == {None: default, 1: 1, 4: schedule}[n_streams]
         results.append(steps)
         c.close()
     for other in results[1:]:
