@@ -490,7 +490,7 @@ static PyTypeObject PlainOpType = {
 /* assign(ctx: int, dst: Tensor, src: Tensor): lt_assign; what is known of src's type and shape
  * becomes what is known of dst's (unknown stays unknown: asked for on demand) */
 static PyObject* rec_assign(PyObject* self, PyObject* const* args, Py_ssize_t nargs) {
-  if (nargs != 3 || !PyObject_TypeCheck(args[1], &TensorType) || Py_TYPE(args[2]) != &TensorType) {
+  if (nargs != 3 || Py_TYPE(args[1]) != &TensorType || Py_TYPE(args[2]) != &TensorType) {
     PyErr_SetString(PyExc_TypeError, "assign(ctx, dst: Tensor, src: Tensor)");
     return NULL;
   }
@@ -550,9 +550,9 @@ static PyObject* rec_release_many(PyObject* self, PyObject* const* args, Py_ssiz
   Py_RETURN_NONE;
 }
 
-/* device_ptr(ctx: int, t: Tensor) -> int: lt_device_ptr */
+/* device_ptr(ctx: int, t) -> int: lt_device_ptr of a Tensor, or of anything with a `tid` */
 static PyObject* rec_device_ptr(PyObject* self, PyObject* const* args, Py_ssize_t nargs) {
-  if (nargs != 2 || !PyObject_TypeCheck(args[1], &TensorType)) {
+  if (nargs != 2) {
     PyErr_SetString(PyExc_TypeError, "device_ptr(ctx, tensor)");
     return NULL;
   }
@@ -562,8 +562,18 @@ static PyObject* rec_device_ptr(PyObject* self, PyObject* const* args, Py_ssize_
   }
   void* ctx = (void*)(uintptr_t)PyLong_AsUnsignedLongLong(args[0]);
   if (PyErr_Occurred()) return NULL;
+  uint64_t tid;
+  if (Py_TYPE(args[1]) == &TensorType) {
+    tid = ((TensorObject*)args[1])->tid;
+  } else {
+    PyObject* id = PyObject_GetAttr(args[1], str_tid);
+    if (!id) return NULL;
+    tid = PyLong_AsUnsignedLongLong(id);
+    Py_DECREF(id);
+    if (PyErr_Occurred()) return NULL;
+  }
   void* p = NULL;
-  const int st = p_device_ptr(ctx, ((TensorObject*)args[1])->tid, &p);
+  const int st = p_device_ptr(ctx, tid, &p);
   if (st != 0) return raise_status(ctx, st);
   return PyLong_FromUnsignedLongLong((unsigned long long)(uintptr_t)p);
 }
