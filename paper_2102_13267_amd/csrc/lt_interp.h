@@ -546,18 +546,20 @@ __device__ __forceinline__ void store_elem(void* ptr, uint32_t dtype, uint64_t i
   else ((float*)ptr)[idx] = v;
 }
 
-// NT: non-temporal store (the data is not read again by this kernel).
 // Stores of 16 bytes a lane that go through to memory (sc1) instead of waiting in the die's L2 until the launch ends: what is
 // still there then is written back before the next launch may start, in its way and not under this one's work.  (Written in assembly: a
 // store of this scope is otherwise an atomic one, of at most eight bytes.  Two wait states: the compiler does not know that the
 // registers of the data are still being read and may overwrite them next.)
+// For results that nobody reads before the launch ends.  The compiler does not count these stores as outstanding either, so its
+// waits, those of a release among them, may pass them by: a ticket or flag behind one needs an s_waitcnt vmcnt(0) of its own (all_published).
 typedef uint32_t Through4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void store_through(void* p, Through4 v) { asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" : : "v"(p), "v"(v) : "memory"); }
 __device__ __forceinline__ void store_through(void* p, const float4& v) {
   store_through(p, Through4{__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z), __float_as_uint(v.w)});
 }
 
-// HOW: plain, past the caches (operands larger than they are), or through them (store_through; fp32)
+// HOW whole vectors of fp32 are stored: plain, past the caches (operands larger than they are), or through them (store_through).
+// bf16 vectors, eight bytes a lane, and what the general path of store_outputs stores (rests, single elements) are plain either way.
 enum StoreHow { kPlain, kPast, kThrough };
 template <bool F32 = false, StoreHow HOW = kPlain>
 __device__ __forceinline__ void store_vec4(void* ptr, uint32_t dtype, uint64_t base, uint32_t lane, const Quad& q) {

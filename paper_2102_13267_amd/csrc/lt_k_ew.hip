@@ -311,7 +311,7 @@ __global__ __launch_bounds__(kBlock) void lt_split_post_kernel(const SplitPostAr
     RF<16> f = load_inputs<16, MAXIN, FAST, false>(rf_zero<16>(), p, base, lane, nvalid);
     f = rf_set<16>(f, p.anchor_slot, anchor);
     f = interp<16>(f, pr, n_code);
-    store_outputs<16, FAST, false, 0, kThrough>(f, p, base, lane, nvalid);
+    store_outputs<16, FAST, false, 0, FAST ? kThrough : kPlain>(f, p, base, lane, nvalid);
   }
   args_touched(touched);
 }
