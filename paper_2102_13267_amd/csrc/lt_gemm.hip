@@ -11,8 +11,8 @@
 // stages, so that the loop holds nothing but LDS reads, MFMAs and one barrier per slice: the matrix
 // cores bound it (fp32 MFMA 157 TFLOP/s; the vendor library reaches 141 to 154).  Measured against
 // staging the same tiles through registers (transposing stores, the same four slices ahead):
-// [1024, 2048] x [2048, 2048] with bias and GELU 90.5 -> 70 us (122 TFLOP/s), a head's three products of
-// 2048 x 1024 x 1000, ragged, 67 / 62 / 75 -> 44 / 42 / 45.  A tile over the operand's edge takes the same
+// [1024, 2048] x [2048, 2048] with bias and GELU 90.5 -> 70 us, a head's three products of 2048 x 1024 x 1000, ragged, 67 / 62 / 75 -> 44 /
+// 42 / 45; with reads and copies put between the MFMAs by hand (below) 64.5 (133 TFLOP/s) and 37 / 36 / 34, in a row.  A tile over the operand's edge takes the same
 // path; what is left of k behind the last whole slice is one checked slice; rows that are not
 // 16-byte aligned go through registers.  A long k over few tiles is split over workgroups (partial
 // products to a workspace, summed by a second launch).

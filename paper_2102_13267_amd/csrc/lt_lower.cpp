@@ -1265,7 +1265,8 @@ struct Lowering {
       Launch l = make_launch(L_ALL, k, args);
       // (4096 elements to a workgroup, in the middle 8192: the workgroups' tickets meet on one address, 2.4 us for 164 of them.  Clipping
       // and Adam, us, 4096 / 8192: 300,000 14.3 / 15.1, 669,706 16.7 / 16.7, 1,048,576 18.0 / 16.9, 1,500,000 20.6 / 19.0, 2,359,972
-      // 26.8 / 25.3, 4,000,000 (512 workgroups either way) 34.5 / 35.0)
+      // 26.8 / 25.3; 3,145,732 (512 / 384 workgroups) 30.9 / 30.5, 3,600,000 32.4 / 32.3, 4,000,000 (512 / 489) 34.3 / 34.8, from 4,194,304 on 512
+      // either way: the upper line could lie anywhere in between.  The sum alone: 3,145,732 12.0 / 11.0, 3,600,000 12.1 / 11.5, 4,000,000 12.3 / 12.1.)
       const uint64_t per_wg = args.count > (3u << 18) && args.count <= (3u << 20) ? 8192 : 4096;
       l.grid_x = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((args.count + per_wg - 1) / per_wg, 256 * 2));
       l.bytes = pro.bytes + post.bytes;
