@@ -1263,11 +1263,19 @@ struct Lowering {
       args.red = red;
       args.count = (uint64_t)count(in_shape);
       Launch l = make_launch(L_ALL, k, args);
-      // (4096 elements to a workgroup, in the middle 8192: the workgroups' tickets meet on one address, 2.4 us for 164 of them.  Clipping
-      // and Adam, us, 4096 / 8192: 300,000 14.3 / 15.1, 669,706 16.7 / 16.7, 1,048,576 18.0 / 16.9, 1,500,000 20.6 / 19.0, 2,359,972
-      // 26.8 / 25.3; 3,145,732 (512 / 384 workgroups) 30.9 / 30.5, 3,600,000 32.4 / 32.3, 4,000,000 (512 / 489) 34.3 / 34.8, from 4,194,304 on 512
-      // either way: the upper line could lie anywhere in between.  The sum alone: 3,145,732 12.0 / 11.0, 3,600,000 12.1 / 11.5, 4,000,000 12.3 / 12.1.)
-      const uint64_t per_wg = args.count > (3u << 18) && args.count <= (3u << 20) ? 8192 : 4096;
+      // 4096 elements to a workgroup, but in the middle 8192 where nothing is interpreted -- one whole tensor, as it is or its squares or
+      // magnitudes: there the workgroups' tickets, which meet on one address, are what takes long (2.4 us for 164 of them).  us, 4096 / 8192:
+      // fp32 sums 790,000 7.9 / 7.9, 1,500,000 10.1 / 9.0, 2,360,000 12.0 / 10.5, maxima 8.4 / 8.7, 10.7 / 9.9, 12.5 / 11.2 (1,000,000 9.0 / 9.0), squares
+      // 7.9 / 7.7, 9.9 / 8.6, 11.7 / 10.0; clipping and Adam 669,706 16.7 / 16.7, 1,048,576 18.0 / 16.9, 2,359,972 26.8 / 25.3, 3,145,732 (512 / 384
+      // workgroups) 30.9 / 30.5, 3,600,000 32.4 / 32.3, 4,000,000 (512 / 489) 34.3 / 34.8, from 4,194,304 on 512 either way: the upper line could lie
+      // anywhere in between.  Interpreted prologues need the waves: x * y 790,000 8.9 / 9.3, in bf16 9.5 / 10.7, a chain of six operations
+      // 13.3 / 18.9, three tensors 14.7 / 21.8, bf16 of odd length 11.6 / 14.5, with a chain 17.3 / 26.1.
+      const ltk::EwProg& q = pro.prog;
+      const bool whole = q.n_in == 1u && q.in[0].mode == ltk::kFull && q.in[0].fetch == ltk::kFetchVec4 && (q.in[0].dtype == ltk::kF32 || q.n % 4u == 0u);
+      const bool lone = q.n_code == 1u && ((q.code[0] & 0xffu) == ltk::kSquare || (q.code[0] & 0xffu) == ltk::kAbs);
+      const bool sum = red == ltk::kRedSum || red == ltk::kRedMean;
+      const uint64_t from = !whole || (q.n_code != 0u && !lone) ? ~0ull : lone || sum ? 3u << 18 : 1u << 20;
+      const uint64_t per_wg = args.count > from && args.count <= (3u << 20) ? 8192 : 4096;
       l.grid_x = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((args.count + per_wg - 1) / per_wg, 256 * 2));
       l.bytes = pro.bytes + post.bytes;
       if (split_fin) {
