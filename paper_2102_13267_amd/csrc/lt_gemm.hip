@@ -525,7 +525,7 @@ __global__ __launch_bounds__(kGemmThreads * KS, BM == 64 ? 2 : 1) void lt_gemm_k
 // of its four MFMAs is free as long as both operands agree, so a lane takes four CONSECUTIVE k
 // (4 h .. 4 h + 3): one 16-byte load where k is the operand's contiguous dimension, four 4-byte
 // loads that neighbouring lanes coalesce where it is not.  No LDS staging and no barrier in the
-// loop; two groups (16 k) or kSmallG (32 k) are in flight per wave while as many are multiplied.  The
+// loop; two groups (16 k) or kSmallG (32 k) are in flight per wave while as many are multiplied (launch_small).  The
 // partial tiles of the waves meet in LDS, are added in a fixed order, and the post program runs on
 // the sum: one launch.  (A tile may also be two blocks of 32 x 32: then two times four waves.)
 // A long k over very few tiles (a batch of 8 rows against a 2048 x 2048 weight: 64 tiles) would
@@ -666,16 +666,13 @@ __device__ __forceinline__ RF<NS> place_elements(RF<NS> f, const EwProg& p, cons
 // every group of four is a whole, 16-byte aligned vector (the launcher checks the pointer, the
 // strides and k % 4).  CS: the column sums of B ride along (GemmArgs::col_sum); a variant of its own, because the
 // second program costs 40 registers that the plain product does not have to carry.
-template <int TM, int TN, bool AV, bool BV, bool CS>
+// FOUR: four groups of k in flight, not two (launch_small).
+template <int TM, int TN, bool AV, bool BV, bool CS, bool FOUR>
 __device__ __forceinline__ void small_tile32(const GemmArgs& a) {
   constexpr uint32_t NB = TM * TN, KW = kSmallWaves / NB;      // blocks, k shares inside the workgroup
   static_assert(!CS || NB == 1, "column sums ride with tiles of 32 x 32");
-  // Groups of 8 k in flight, and as many being multiplied.  Two, where a wave's share of k is often no more (nothing is fetched past
-  // it) and loads of single values keep a wave busy; four where B's rows are read along k, 16 bytes a lane, so that a chunk is a whole
-  // cache line of each.  us, two / four: weight gradients 128: 784 x 512 7.2 / 8.7, 300: 512 x 512 7.0 / 8.3; k of no whole vectors
-  // 32 x 2047 x 1000 11.1 / 12.6, B transposed 12.5 / 15.3; B transposed, whole vectors, 32 x 2048 x 2048 11.6 / 11.0, 8 x 4096 x 4096 24.7 /
-  // 23.3, 32 x 4096 x 4096 28.3 / 26.4.
-  constexpr int G = NB == 1 && (CS || !BV) ? 2 : kSmallG;
+  static_assert(!CS || !FOUR, "two chunks to a column sum's four groups");
+  constexpr int G = NB > 1 || FOUR ? kSmallG : 2;              // groups of 8 k in flight, and as many being multiplied
   constexpr uint32_t kQuads = NB * 256u, QT = (kQuads + kSmallThreads - 1u) / kSmallThreads;   // quads of the tile, per thread
   __shared__ __attribute__((aligned(16))) float Cs[kSmallWaves * 32 * kSmallStride];
   __shared__ uint32_t is_last;
@@ -1034,22 +1031,25 @@ __device__ __forceinline__ void small_tile16(const GemmArgs& a) {
 }
 
 // TM x TN: the workgroup's tile in units of 16 (2 x 2, 4 x 2, 1 x 1, 1 x 4).
-template <int TM, int TN, bool AV, bool BV, bool CS>
+template <int TM, int TN, bool AV, bool BV, bool CS, bool FOUR>
 __global__ __launch_bounds__(kSmallThreads) void lt_gemm_small_kernel(const GemmArgs a) {
   const uint32_t t = touch_args<GemmArgs>();
   if constexpr (TM == 1) small_tile16<AV, TN == 4 ? 2 : BV ? 1 : 0>(a);
-  else small_tile32<TM / 2, TN / 2, AV, BV, CS>(a);
+  else small_tile32<TM / 2, TN / 2, AV, BV, CS, FOUR>(a);
   args_touched(t);
 }
 
+// four: groups of k in flight in tiles of 32 x 32 (those of other sizes come in one version)
 template <int TM, int TN, bool CS>
-static void launch_small_tile(const GemmArgs& a, bool av, bool bv, dim3 grid, uint32_t threads, hipStream_t s) {
+static void launch_small_tile(const GemmArgs& a, bool av, bool bv, bool four, dim3 grid, uint32_t threads, hipStream_t s) {
   const dim3 block(threads);
+  constexpr bool one = TM != 2 || TN != 2;
   if (TN == 4) bv = false;   // (columns contiguous, four at a time)
-  if (av && bv) LT_LAUNCH((lt_gemm_small_kernel<TM, TN, true, true && TN != 4, CS>), grid, block, s, a);
-  else if (av) LT_LAUNCH((lt_gemm_small_kernel<TM, TN, true, false, CS>), grid, block, s, a);
-  else if (bv) LT_LAUNCH((lt_gemm_small_kernel<TM, TN, false, true && TN != 4, CS>), grid, block, s, a);
-  else LT_LAUNCH((lt_gemm_small_kernel<TM, TN, false, false, CS>), grid, block, s, a);
+  if (av && bv) LT_LAUNCH((lt_gemm_small_kernel<TM, TN, true, true && TN != 4, CS, !CS>), grid, block, s, a);
+  else if (av) LT_LAUNCH((lt_gemm_small_kernel<TM, TN, true, false, CS, one>), grid, block, s, a);
+  else if (bv) LT_LAUNCH((lt_gemm_small_kernel<TM, TN, false, true && TN != 4, CS, !CS>), grid, block, s, a);
+  else if (four && !CS) LT_LAUNCH((lt_gemm_small_kernel<TM, TN, false, false, CS, !CS>), grid, block, s, a);
+  else LT_LAUNCH((lt_gemm_small_kernel<TM, TN, false, false, CS, one>), grid, block, s, a);
   char name[64];
   snprintf(name, sizeof(name), "lt_gemm_small_kernel<%d, %d, %s, %s, %s>", TM, TN, av ? "true" : "false", bv ? "true" : "false", CS ? "true" : "false");
   note_kernel(name);
@@ -1074,9 +1074,17 @@ static hipError_t launch_small(const GemmArgs& args, hipStream_t s) {
   };
   const bool av = a.a.s_col == 1 && (a.k % 4u) == 0u && aligned(a.a, a.a.s_row), bv = a.b.s_row == 1 && (a.k % 4u) == 0u && aligned(a.b, a.b.s_col);
   const dim3 grid(a.tiles_n * a.splits, a.tiles_m, a.batch0 * a.batch1);
-  if (t22 && a.col_sum) launch_small_tile<2, 2, true>(a, av, bv, grid, kSmallThreads, s);
-  else if (t22) launch_small_tile<2, 2, false>(a, av, bv, grid, kSmallThreads, s);
-  else if (t42) launch_small_tile<4, 2, false>(a, av, bv, grid, kSmallThreads, s);
+  // Two groups of k in flight or four, in tiles of 32 x 32.  Four where B's rows are read along k, 16 bytes a lane, so that a chunk is
+  // a whole cache line of each; and in unshared products with both operands read across k, where a wave's share fills chunks of four
+  // as well as chunks of two (nothing is fetched past it).  us, two / four: B transposed, whole vectors, 32 x 2048 x 2048 11.6 / 11.0, 8 x 4096 x
+  // 4096 24.3 / 23.1, 32 x 4096 x 4096 27.5 / 26.3; across, with an input of the output's size, 512: 256 x 100 8.4 / 8.0, 200: 512 x 512 7.0 / 6.5, but 128: 784 x 512 7.2 / 8.7,
+  // 300: 512 x 512 7.0 / 8.3, shared 8000: 30 x 30 12.8 / 13.2; k of no whole vectors, single values, 32 x 2047 x 1000 11.1 / 12.6, B transposed
+  // 12.5 / 15.3.
+  const uint32_t per = ((a.k + 7u) / 8u + (uint32_t)kSmallWaves - 1u) / (uint32_t)kSmallWaves;   // (groups of a wave, unshared)
+  const bool four = a.splits == 1u && a.a.s_col != 1 && a.b.s_row != 1 && (per + 3u) / 4u * 2u == (per + 1u) / 2u;
+  if (t22 && a.col_sum) launch_small_tile<2, 2, true>(a, av, bv, false, grid, kSmallThreads, s);
+  else if (t22) launch_small_tile<2, 2, false>(a, av, bv, four, grid, kSmallThreads, s);
+  else if (t42) launch_small_tile<4, 2, false>(a, av, bv, true, grid, kSmallThreads, s);
   else {
     // a wave per group of 16 k that a workgroup has to do: at most eight, and the four that a tile of 64
     // columns needs for its epilogue
@@ -1084,9 +1092,9 @@ static hipError_t launch_small(const GemmArgs& args, hipStream_t s) {
     const uint32_t waves = std::max(std::min(groups, (uint32_t)kSmallWaves), t14 ? 4u : 1u);
     if (t14) {
       if (a.b.s_col != 1 || a.n < 4u || a.n % 4u != 0u) return hipErrorInvalidValue;   // (four columns at a time)
-      launch_small_tile<1, 4, false>(a, av, false, grid, 64u * waves, s);
+      launch_small_tile<1, 4, false>(a, av, false, true, grid, 64u * waves, s);
     } else {
-      launch_small_tile<1, 1, false>(a, av, bv, grid, 64u * waves, s);
+      launch_small_tile<1, 1, false>(a, av, bv, true, grid, 64u * waves, s);
     }
   }
   return hipGetLastError();
