@@ -178,20 +178,30 @@ void schedule_streams(Plan* plan) {
     }
   }
   // Whether all this pays.  An edge is an event recorded and an event waited for, 10 to 20 us of the host's time once a few
-  // launches are in flight, and what a launch gains by running next to another is a part of its own time.  Transformer layer
-  // steps in bf16 (batch x sequence x width), us on one stream / on four, estimated time and edges waited for: 8 x 64 x 512 383 / 501 (405,
-  // 9), 12 x 200 x 256 409 / 514 (405, 9), 32 x 256 x 256 479 / 618 (515, 27), 4 x 128 x 512 389 / 546 (405, 9), 8 x 200 x 512 424 / 567
-  // (470, 26), 16 x 256 x 512 529 / 613 (618, 27), 32 x 256 x 512 643 / 681 (840, 26), 2 x 256 x 1024 527 / 615 (592, 21), 4 x 256 x 1024 592 /
-  // 627 (688, 21); 1 x 100 x 1024 444 / 391 (454, 4), 8 x 256 x 1024 716 / 703 (913, 25), 16 x 256 x 1024 805 / 746 (1265, 20), 32 x 256 x 1024
-  // 1233 / 1146 (2128, 22).  The line below has the first nine on one side and the last four on the other; of 1 x 64 x 1024, 415 / 424, it says that it
-  // pays.  (Nothing but such steps has been measured; 8 x 256 x 1024 is 9 us above the line.)
-  double total = 0.0;
+  // launches are in flight: so launches have to be long enough for the host to get ahead of them (with an edge to ten launches or
+  // fewer, hardly longer than alone), and what could be gained by running next to each other has to be more than the edges take.  us on one stream / on four (estimated us a launch, gain an edge):
+  //   layer steps in bf16, batch x sequence x width: 8 x 64 x 512 377 / 556 (9.2, 11), 12 x 200 x 256 404 / 529 (9.2, 8), 1 x 64 x 1024 410 / 488 (9.4, 9), 1 x
+  //   100 x 1024 443 / 463 (9.5, 29), 1 x 200 x 1024 487 / 460 (9.8, 31), 2 x 128 x 1024 471 / 463 (10.1, 32), 2 x 256 x 1024 527 / 634 (11.4, 15), 32 x 256 x
+  //   256 463 / 620 (11.7, 9), 4 x 256 x 1024 586 / 674 (13.8, 14), 16 x 256 x 512 509 / 639 (14.0, 11), 8 x 256 x 1024 699 / 741 (18.3, 16), 32 x 256 x 512
+  //   622 / 679 (20.0, 15); 16 x 256 x 1024 792 / 737 (31.6, 24), 32 x 256 x 1024 1227 / 1145 (53.2, 34);
+  //   four feed-forward blocks, rows x width: 512 x 512 297 / 324 (9.6, 21), 2048 x 512 440 / 444 (13.6, 31), 2048 x 1024 698 / 669 (40, 44), 4096 x 1024
+  //   1066 / 1134 (94, 159), in fp32 512 x 512 400 / 395 (19, 26), 2048 x 512 1055 / 1011 (42, 88);
+  //   fp32 products and column sums, rows x width: 8192 x 256 434 / 371 (13, 14), 4096 x 512 392 / 368 (15, 16), 2048 x 1024 445 / 378 (18, 21), 3000 x 1024
+  //   583 / 448 (22, 27), 4096 x 1024 736 / 588 (25, 31), 16384 x 256 728 / 408 (17, 24);
+  //   random programs: 200 / 220 (9.2, 67), 381 / 295 (9.3, 21), 213 / 228 (10.7, 183), 223 / 301 (11.0, 36); 473 / 365 (12.8, 34), 363 / 334 (13.3, 32), 288 /
+  //   287 (13.6, 28), 420 / 392 (14.2, 58), 482 / 348 (15.5, 68), 360 / 332 (16.1, 51), 424 / 372 (16.4, 24), 362 / 310 (20.2, 60), 641 / 492 (23.2, 82),
+  //   590 / 522 (28.4, 183).
+  // (What the line keeps on one stream although it would gain: sums of 8192 x 256 and 4096 x 512, one random program; the other way round it errs
+  // on four blocks of 4096 x 1024, by 6 %.  8 x 256 x 1024, 1 x 100 x 1024 and the third random program are better on either, depending on the process.)
+  double total = 0.0;   // (estimated as for the schedule, but for fp32 products at 100 TFLOP/s)
   size_t edges = 0;
   for (const Launch& l : plan->launches) {
     total += estimate_us(l);
+    if (l.kind == L_GEMM && ((const ltk::GemmArgs*)l.args.data())->in_dtype == ltk::kF32) total += (double)l.flops * (1.0 / 1.0e8 - 1.0 / 4.0e8);
     edges += l.waits.size();
   }
-  plan->spread_pays = total >= 300.0 + 24.0 * (double)edges;
+  const double gain = total - *std::max_element(finish.begin(), finish.end());
+  plan->spread_pays = total >= (10u * edges <= n ? 9.4 : 12.0) * (double)n && gain >= 20.0 * (double)edges;
 }
 
 bool spreads(const lt_ctx* ctx, const Plan* plan) {

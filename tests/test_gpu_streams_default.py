@@ -9,8 +9,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("rows,cols,schedule,default", [(64, 256, 1, 1), (1024, 512, 1, 1),              # nothing leaves the caller's stream
-                                                        (2048, 1024, 4, 1), (16384, 256, 4, 1),          # declined
-                                                        (8192, 1024, 4, 4)])                             # spread
+                                                        (4096, 512, 4, 1), (8192, 256, 4, 1),            # declined
+                                                        (2048, 1024, 4, 4), (8192, 1024, 4, 4)])         # spread
 def test_default_streams_do_not_change_results(rows, cols, schedule, default):
     from paper_2102_13267_amd import Context
     g = rng(rows + cols)

@@ -20,7 +20,7 @@ def layer_step(ctx, batch, seq, d):
 
 
 @pytest.mark.parametrize("size,pays", [((4, 128, 512), False), ((32, 256, 256), False), ((32, 256, 512), False), ((4, 256, 1024), False),
-                                       ((1, 100, 1024), True), ((8, 256, 1024), True), ((32, 256, 1024), True)])
+                                       ((1, 64, 1024), False), ((1, 100, 1024), True), ((2, 128, 1024), True), ((16, 256, 1024), True), ((32, 256, 1024), True)])
 def test_layer_steps(size, pays):
     ctx = Context()
     assert ctx.plan_streams() == 0
@@ -43,4 +43,25 @@ def test_short_plans_do_not_spread():
     keep = [ctx.sum(ctx.mul(x, float(i + 2)), axis=0) for i in range(4)]
     ctx.barrier()
     assert ctx.plan_streams() == 1
+    del keep
+
+
+def products_and_sums(ctx, rows, cols):
+    """fp32 products next to column sums, three times over."""
+    new = lambda *shape: ctx.tensor(np.zeros(shape, np.float32))   # noqa: E731
+    x, w, w2, out = new(rows, cols), new(cols, cols // 2), new(cols, cols), []
+    for i in range(3):
+        xi = ctx.mul(x, 1.0 + 0.5 * i)
+        s = ctx.sum(ctx.square(xi), axis=0)
+        out += [ctx.matmul(xi, w), s, ctx.add(ctx.matmul(xi, w2), s)] + [ctx.sum(ctx.mul(xi, float(k + 2)), axis=0) for k in range(5)]
+    ctx.barrier()
+    return out
+
+
+@pytest.mark.parametrize("rows,cols,pays", [(1024, 512, False), (3000, 1024, True), (4096, 1024, True), (8192, 1024, True)])
+def test_fp32_products_and_column_sums(rows, cols, pays):
+    ctx = Context()
+    keep = products_and_sums(ctx, rows, cols)
+    assert len(ctx.dump_schedule().splitlines()) >= 24
+    assert (ctx.plan_streams() > 1) == pays
     del keep
