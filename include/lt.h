@@ -312,10 +312,10 @@ lt_status lt_last_launches(lt_ctx* ctx, lt_launch_record* out, int cap, int* n);
  * sequence) run on up to n - 1 side streams of the library's own next to the caller's stream;
  * every barrier forks them from the caller's stream and joins them into it again before it
  * returns, so the caller sees the ordering of a single stream.  n = 1 keeps every launch on the
- * caller's stream, and so does a plan of fewer than LT_SPREAD_LAUNCHES launches, in which the events
- * between streams cost more than they gain (lt_dump_schedule shows the streams that n = 4 would
- * use in a longer plan).  Until this is called, so does a longer plan whose events are estimated to cost
- * more than they gain.  A plan whose temporaries do not fit the workspace without being recycled
+ * caller's stream, and so does a plan of fewer than LT_SPREAD_LAUNCHES launches (column sums that a
+ * contraction takes along count as launches), in which the events between streams cost more than
+ * they gain (lt_dump_schedule shows the streams that n = 4 would use in a longer plan).  Until this
+ * is called, so does a longer plan whose events are estimated to cost more than they gain.  A plan whose temporaries do not fit the workspace without being recycled
  * inside the step also runs on one stream.  Barriers that record per-launch timings
  * (lt_set_profiling) run on one stream so that the timings are those of the kernels alone.
  * Errors: LT_ERR_ARG (n out of range).

@@ -185,6 +185,7 @@ struct Plan {
   std::vector<RootBind> roots;
   uint64_t bytes_planned = 0, flops_planned = 0;
   int n_streams = 1;                 // streams the schedule uses (1: everything on the caller's stream)
+  uint32_t riding = 0;               // column sums without a launch of their own: a contraction takes them along
   bool spread_pays = false;          // the schedule gains more than its edges cost (estimated)
   size_t temp_bytes = 0;             // arena bytes when no temporary is reused inside the step
   std::vector<hipEvent_t> events;    // one per launch with `record` set (created on first use)

@@ -1516,6 +1516,7 @@ struct Lowering {
       ga->col_sum = 1u;
       ga->col_red = red;
       plan->merged = true;
+      plan->riding += ga->splits == 1u;
       return ga->splits == 1u;
     }
     return false;

@@ -65,3 +65,17 @@ def test_fp32_products_and_column_sums(rows, cols, pays):
     assert len(ctx.dump_schedule().splitlines()) >= 24
     assert (ctx.plan_streams() > 1) == pays
     del keep
+
+
+@pytest.mark.parametrize("products,spread", [(11, False), (12, True)])
+def test_riding_sums_count_as_launches(products, spread):
+    ctx = Context()
+    ctx.set_streams(4)
+    x, keep = ctx.tensor(np.zeros((1024, 1024), np.float32)), []
+    for _ in range(products):
+        dy = ctx.tensor(np.zeros((1024, 2048), np.float32))
+        keep += [ctx.matmul(x, dy, trans_a=True), ctx.sum(dy, axis=0)]
+    ctx.barrier()
+    assert len(ctx.dump_schedule().splitlines()) == products
+    assert (ctx.plan_streams() > 1) == spread
+    del keep
