@@ -107,3 +107,24 @@ def test_small_products_add_up_in_fours(ctx, rows, m, n):  # noqa: F811
     ctx.set_profiling(False)
     assert len(names) == 1 and "small" in names[0], names
     assert np.array_equal(ctx.fetch(db), small_sums(dy))
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("rows,m,n", [(8192, 1030, 1032), (8192, 1024, 2048), (5001, 1030, 4100)])
+def test_infinite_totals_stay(ctx, dt, rows, m, n):  # noqa: F811
+    """What a total keeps of its additions' losses is nothing once it is infinite; largest values next to each other do not overflow it."""
+    dy = np.ones((rows, n), np.float32)
+    dy[70, 3], dy[rows - 2, 4], dy[100, 5], dy[rows - 1, 5], dy[9, 6] = np.inf, -np.inf, np.inf, -np.inf, np.nan
+    big = np.float32(2.0 ** 127)
+    dy[:, 7] = 0.0
+    dy[5, 7], dy[6, 7], dy[4000, 7] = big, -big, big
+    x, D = ctx.tensor(np.zeros((rows, m), np.float32), dtype=dt), ctx.tensor(dy, dtype=dt)
+    dw, db = ctx.matmul(x, D, trans_a=True), ctx.sum(D, axis=0)
+    ctx.set_profiling(True)
+    ctx.barrier()
+    names = [r["kernel"] for r in ctx.last_launches()]
+    ctx.set_profiling(False)
+    assert "sums" in names[0], names
+    got = ctx.fetch(db).astype(np.float64)
+    assert got[3] == np.inf and got[4] == -np.inf and np.isnan(got[5]) and np.isnan(got[6]) and got[7] == float(big)
+    assert abs(got[0] - rows) <= (0 if dt == "f32" else 2 ** -8 * rows)
